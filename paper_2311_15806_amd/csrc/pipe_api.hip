@@ -213,6 +213,8 @@ static void free_expansion(pipe_expansion* e) {
     if (t.src_dev) (void)hipFree(t.src_dev);
     if (t.cnt_dev) (void)hipFree(t.cnt_dev);
   }
+  for (auto& t : e->tile_bins)
+    if (t.bins_dev) (void)hipFree(t.bins_dev);
   for (auto& rt : e->res_tables) {
     if (rt.subs_dev) (void)hipFree(rt.subs_dev);
     if (rt.epi_dev) (void)hipFree(rt.epi_dev);
@@ -659,6 +661,101 @@ const PassTables* pipe_get_tables(const pipe_expansion* ce, const GemmArgs& a, i
   return &e->tables.back();
 }
 
+const TileBins* pipe_get_bins(const pipe_expansion* ce, const GemmArgs& a, int* rc_out) {
+  pipe_expansion* e = const_cast<pipe_expansion*>(ce);
+  const int n_rb = e->n_rb, gated = a.act == PIPE_ACT_SILU_GATED ? 1 : 0;
+  const bool joined = a.M == 1 || a.reduce;
+  const int M = joined ? 1 : a.M;
+  unsigned long long nib = 0;
+  int lo[PIPE_MAX_K] = {0}, hi[PIPE_MAX_K] = {e->K - 1};
+  if (!joined)
+    for (int m = 0; m < M; ++m) {
+      lo[m] = a.member_lo[m];
+      hi[m] = a.member_hi[m];
+      for (int k = lo[m]; k <= hi[m]; ++k) nib |= (unsigned long long)m << (4 * k);
+    }
+  for (const TileBins& t : e->tile_bins)
+    if (t.gated == gated && t.M == M && t.member_nib == nib) return &t;
+  *rc_out = PIPE_OK;
+  if (gated && n_rb % 2 != 0) { *rc_out = PIPE_ESHAPE; return nullptr; }
+  if (pipe_capturing()) { *rc_out = PIPE_ENOTREADY; return nullptr; }
+
+  TileBins t;
+  t.member_nib = nib; t.M = M; t.gated = gated;
+  std::vector<TileBin> bins;
+  const int n_units = gated ? n_rb / 2 : n_rb;   // row blocks, or (gate, up) pairs
+  struct Item { int pos, spos, rb, up, end; };
+  for (int m = 0; m < M; ++m) {
+    // a unit's items: its orders of this member, ascending; a row block without any still ends (its sum is zero)
+    auto items_of = [&](int u) {
+      std::vector<Item> it;
+      for (int half = 0; half < (gated ? 2 : 1); ++half) {
+        const size_t first = it.size();
+        for (int k = lo[m]; k <= hi[m]; ++k) {
+          const int pos = e->pos_of[(size_t)k * n_rb + u + half * n_units];
+          if (pos >= 0) it.push_back({pos, pos, u, half, 0});
+        }
+        if (it.size() == first) it.push_back({-1, e->zero_pos, u, half, 0});
+        it.back().end = 1;
+      }
+      return it;
+    };
+    std::vector<std::vector<Item>> items(n_units);
+    std::vector<int> of_size[5];
+    for (int u = 0; u < n_units; ++u) {
+      items[u] = items_of(u);
+      if (items[u].size() > 4) { *rc_out = PIPE_EINVAL; return nullptr; }
+      of_size[items[u].size()].push_back(u);
+    }
+    // Bins of 4 items from units of equal kind in channel order (neighbouring waves then store neighbouring channels):
+    // 4; 3 + 1; 2 + 2; 1 + 1 + 1 + 1, and what is left over together.
+    size_t at[5] = {0, 0, 0, 0, 0};
+    auto left = [&](int s) { return of_size[s].size() - at[s]; };
+    auto put = [&](std::initializer_list<int> sizes) {
+      TileBin b;
+      int n = 0, first_pos = -1, ends = 0, ups = 0;
+      for (int q = 0; q < 4; ++q) { b.pos[q] = -1; b.spos[q] = e->zero_pos; b.rb[q] = -1; }
+      for (int s : sizes) {
+        for (const Item& it : items[of_size[s][at[s]++]]) {
+          b.pos[n] = it.pos; b.spos[n] = it.spos; b.rb[n] = it.rb;
+          if (it.pos >= 0 && first_pos < 0) first_pos = it.pos;
+          ends |= it.end << n;
+          ups |= it.up << n;
+          ++n;
+        }
+      }
+      // items without codes read a live one's (or the all-zero position); their scale is zero or they end nothing
+      for (int q = 0; q < 4; ++q)
+        if (b.pos[q] < 0) b.pos[q] = first_pos >= 0 ? first_pos : e->zero_pos;
+      b.info[0] = m; b.info[1] = ends; b.info[2] = ups; b.info[3] = first_pos >= 0 ? 1 : 0;
+      bins.push_back(b);
+    };
+    while (left(4)) put({4});
+    while (left(3)) { if (left(1)) put({3, 1}); else put({3}); }
+    while (left(2) >= 2) put({2, 2});
+    while (left(2)) { if (left(1) >= 2) put({2, 1, 1}); else if (left(1)) put({2, 1}); else put({2}); }
+    while (left(1)) { if (left(1) >= 4) put({1, 1, 1, 1}); else if (left(1) >= 2) put({1, 1}); else put({1}); }
+    while (bins.size() % 4 != 0) {   // a member's last tile: waves without items
+      TileBin b;
+      for (int q = 0; q < 4; ++q) { b.pos[q] = e->zero_pos; b.spos[q] = e->zero_pos; b.rb[q] = -1; }
+      b.info[0] = m; b.info[1] = 0; b.info[2] = 0; b.info[3] = 0;
+      bins.push_back(b);
+    }
+  }
+  t.n_ct = (int)(bins.size() / 4);
+  auto fail = [&](hipError_t he, const char* what) {
+    pipe_note_hip_error(he, what);
+    if (t.bins_dev) (void)hipFree(t.bins_dev);
+    *rc_out = PIPE_EDEVICE;
+    return (const TileBins*)nullptr;
+  };
+  hipError_t he;
+  if ((he = hipMalloc(&t.bins_dev, bins.size() * sizeof(TileBin))) != hipSuccess) return fail(he, "hipMalloc(bins)");
+  if ((he = hipMemcpy(t.bins_dev, bins.data(), bins.size() * sizeof(TileBin), hipMemcpyHostToDevice)) != hipSuccess) return fail(he, "hipMemcpy(bins)");
+  e->tile_bins.push_back(t);
+  return &e->tile_bins.back();
+}
+
 // ------------------------------------------------------------------ forward
 static bool use_stream_kernel(const pipe_expansion* e, int T, bool acc_out = false) {
   if (g_kernel_choice == 1) return false;
@@ -687,15 +784,23 @@ static int get_act_buffers(int T, int in_pad, bool small, ActBuffers* b) {
   return PIPE_OK;
 }
 
-// The tile schedule the tiled kernel will need, fetched before anything is launched (so a failure
-// leaves no reduction slot raised).
+// The tile schedules the tiled kernels will need, fetched before anything is launched (so a failure leaves no reduction
+// slot raised).  kind as in PassTables.  A grouping that was used or prepared once may be captured in any form: members
+// summed, with one input or their own, or kept apart.
 static int ensure_tables(const pipe_expansion* e, int M, const int* lo, const int* hi, int kind) {
   GemmArgs a{};
   a.e = e;
   a.M = M;
   for (int m = 0; m < M; ++m) { a.member_lo[m] = lo[m]; a.member_hi[m] = hi[m]; }
+  a.act = kind == 1 ? PIPE_ACT_SILU_GATED : PIPE_ACT_NONE;
   int rc = PIPE_OK;
-  return pipe_get_tables(e, a, kind, &rc) != nullptr ? PIPE_OK : rc;
+  if (kind == 2) return pipe_get_tables(e, a, kind, &rc) != nullptr ? PIPE_OK : rc;
+  for (int form = 0; form < (kind == 0 && M > 1 ? 3 : 1); ++form) {
+    a.reduce = form > 0;
+    a.qx_mstride = form == 2;
+    if (pipe_bins_apply(a) ? pipe_get_bins(e, a, &rc) == nullptr : pipe_get_tables(e, a, kind, &rc) == nullptr) return rc;
+  }
+  return PIPE_OK;
 }
 
 // An error after the max|x| reduction was launched: the slot is raised and the contraction kernel
@@ -779,7 +884,7 @@ static int run_gemm(const GemmArgs& a0, bool small, hipStream_t st) {
   bool timed = false;
   int rc = timing_events(&a.ev_start, &a.ev_stop, &timed);
   if (rc) return rc;
-  rc = small ? launch_gemm_stream(a, st) : launch_gemm_tiled(a, st);
+  rc = small ? launch_gemm_stream(a, st) : pipe_bins_apply(a) ? launch_gemm_bins(a, st) : launch_gemm_tiled(a, st);
   if (timed && rc == PIPE_OK) g_events_used += 2;
   return rc;
 }
@@ -932,7 +1037,7 @@ extern "C" int pipe_forward_noalloc(const pipe_expansion* e, const float* x_dev,
   a.bias = bias_dev; a.reduce = reduce_members ? 1 : 0; a.y = y_dev; a.zero_after = b.amax;
   if (fused) { a.x_f32 = x_dev; a.s_static = s_x; }
   fill_members(a, Mm, lo, hi);
-  rc = small ? launch_gemm_stream(a, st) : launch_gemm_tiled(a, st);   // no timing events: creating one allocates
+  rc = small ? launch_gemm_stream(a, st) : pipe_bins_apply(a) ? launch_gemm_bins(a, st) : launch_gemm_tiled(a, st);   // no timing events: creating one allocates
   return rc == PIPE_OK ? rc : fail_after_reduction(rc, b, st);
 }
 

@@ -21,11 +21,9 @@
 // resident on one XCD share a few weight strips and activation strips in its L2.
 #include <type_traits>
 
-#include "pipe_internal.h"
+#include "pipe_tile.h"
 
 namespace {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr int S = 4;       // 64-k steps per LDS stage (256 k)
 constexpr int FRAG = 64;   // uint4 per fragment
@@ -59,8 +57,7 @@ struct TiledParams {
   long long res_mstride;
   int res_members, res_pre_act;
   int hidden;                     // MODE_GATED: H; the layer's rows are gate [0,H) and up [H,2H), y is [M,T,H]
-  int n_st_t;                     // super-tiles along tokens
-  int st_c_log2;                  // a super-tile is 2^st_c_log2 column tiles x 64 / 2^st_c_log2 token tiles
+  TileOrder order;
   // CONV (implicit GEMM: the expansion's k runs tap-major, channel-minor): the activation stage gathers
   // each 64-channel chunk of a tap straight from the channels-last codes of the input tensor
   const int8_t* cq8;              // Q(x) [N, H, W, C]
@@ -69,14 +66,10 @@ struct TiledParams {
   int cC, cH, cW, ckh, ckw, cstride, cpad, cHo, cWo;
 };
 
-__device__ __forceinline__ float gelu_erf(float a) {
-  return 0.5f * a * (1.f + erff(a * 0.70710678118654752440f));
-}
-
 template <int BITS>
 struct WRegs {
   static constexpr int N = BITS == 2 ? 1 : (BITS == 4 ? 2 : 4);   // uint4 per row block per stage
-  uint4 v[N];
+  v4u v[N];
 };
 
 // Hand-issued LDS reads: N fragments (16 bytes per lane each) at byte offsets BASE + b*STRIDE
@@ -113,39 +106,10 @@ __device__ __forceinline__ void lds_wait(v4i (&x)[N]) {
 
 template <int BITS>
 __device__ __forceinline__ v4i widen(const WRegs<BITS>& w, int j) {
-  if (BITS == 8) {
-    const uint4 a = w.v[j & (WRegs<BITS>::N - 1)];
-    return v4i{(int)a.x, (int)a.y, (int)a.z, (int)a.w};
-  } else if (BITS == 4) {
-    const uint4 q = w.v[(j >> 1) & (WRegs<BITS>::N - 1)];
-    const uint32_t a = (j & 1) ? q.z : q.x, b = (j & 1) ? q.w : q.y;
-    return v4i{(int)(a & 0x0F0F0F0Fu), (int)((a >> 4) & 0x0F0F0F0Fu), (int)(b & 0x0F0F0F0Fu), (int)((b >> 4) & 0x0F0F0F0Fu)};
-  } else {
-    const uint4 q = w.v[0];
-    const uint32_t a = j == 0 ? q.x : (j == 1 ? q.y : (j == 2 ? q.z : q.w));
-    return v4i{(int)(a & 0x03030303u), (int)((a >> 2) & 0x03030303u), (int)((a >> 4) & 0x03030303u), (int)((a >> 6) & 0x03030303u)};
-  }
-}
-
-// A load known to hit global memory.  Pointers rebuilt from integers are "generic" to the
-// compiler, which would emit FLAT loads: those also count as LDS operations (every wait on the
-// LDS fragment reads would then wait for the weight prefetch as well) and are ordered against
-// the LDS-direct loads.
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 gload16(const void* p) {
-  typedef const __attribute__((address_space(1))) v4u* gptr;
-  const v4u v = *(gptr)(unsigned long long)p;
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-// Loads of schedule tables at wave-uniform addresses through the constant address space: the
-// compiler then uses scalar loads (the tables are written once, by the host, when the expansion
-// is built; no kernel ever stores to them), which cost no vector registers and no vector wait.
-template <class T>
-__device__ __forceinline__ T cload(const T* base, size_t idx) {
-  typedef const __attribute__((address_space(4))) T* cptr;
-  return ((cptr)(unsigned long long)base)[idx];
+  if (BITS == 8) return (v4i)w.v[j & (WRegs<BITS>::N - 1)];
+  const v4u q = w.v[BITS == 4 ? (j >> 1) & (WRegs<BITS>::N - 1) : 0];
+  if (BITS == 4) return (j & 1) ? widen4(q.z, q.w) : widen4(q.x, q.y);
+  return widen2(j == 0 ? q.x : (j == 1 ? q.y : (j == 2 ? q.z : q.w)));
 }
 
 // MODE_CHAIN: activation chosen at run time (none, ReLU, GELU) and a skip tensor added before or
@@ -174,19 +138,11 @@ __global__ __launch_bounds__(256, MINW) void gemm_tiled_kernel(const TiledParams
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
 
-  // ---- (column tile, token tile) from blockIdx: super-tiles of 64 tiles, one per XCD at a time ----
   if (p.zero_big != nullptr)
     for (int i = blockIdx.x * 256 + threadIdx.x; i < p.zero_big_n; i += gridDim.x * 256) p.zero_big[i] = 0u;
   int ct, tt;
   {
-    const int i = blockIdx.x;
-    const int xcd = i & 7, j = i >> 3;
-    const int sidx = (j >> 6) * 8 + xcd, local = j & 63;
-    const int sc = sidx / p.n_st_t, st = sidx - sc * p.n_st_t;
-    const int tl2 = 6 - p.st_c_log2;
-    ct = (sc << p.st_c_log2) + (local >> tl2);
-    tt = (st << tl2) + (local & ((1 << tl2) - 1));
-    if (ct >= p.n_ct || tt >= p.n_tt) return;
+    if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
   }
   if (blockIdx.x == 0 && (int)threadIdx.x < p.zero_n && p.zero_after != nullptr) p.zero_after[threadIdx.x] = 0u;
   const int t0 = tt * (16 * MTB);
@@ -578,16 +534,8 @@ template <int BITS, int MTB, int NRW, int MINW>
 int launch_cfg(TiledParams& p, bool acc_out, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   p.n_tt = ceil_div(p.T, 16 * MTB);
   p.n_ct = ceil_div(p.n_ct * NRB_TILE, 4 * NRW);   // column tiles of this variant's width
-  // Super-tiles are dealt to the 8 XCDs in turn, column-tile rows (heaviest first) outermost.  With
-  // 8 token super-tiles per row every XCD gets a share of every row; with 4 (e.g. 2048 tokens)
-  // the even rows would all land on XCDs 0-3 and the odd rows on 4-7, the heavier half finishing
-  // last: then 16 x 4 super-tiles restore 8 per row.
-  p.st_c_log2 = 3;
-  if (ceil_div(p.n_tt, 8) % 8 != 0 && ceil_div(p.n_tt, 4) % 8 == 0) p.st_c_log2 = 4;
-  p.n_st_t = ceil_div(p.n_tt, 64 >> p.st_c_log2);
-  const int n_st_c = ceil_div(p.n_ct, 1 << p.st_c_log2);
-  // super-tile sidx runs on XCD sidx % 8 as blocks xcd + 8*(64*(sidx/8) + local), local = 0..63
-  const dim3 grid((unsigned)(ceil_div(p.n_st_t * n_st_c, 8) * 8 * 64));
+  p.order = tile_order(p.n_ct, p.n_tt);
+  const dim3 grid((unsigned)p.order.blocks());
   if (p.cq8 != nullptr) {
     // implicit-GEMM convolution: plain epilogue or the integer export
     if (p.res != nullptr || p.act != 0) return PIPE_EINVAL;

@@ -1,0 +1,487 @@
+// Single-pass tiled contraction kernel of the expanded layer (App. B, Eq. (define_dre)), for layers whose members hold
+// at most 4 orders:
+//   y[t,o] = sum_m ( s_x,m * sum_{k in member m} s_k[o] * acc_k[t,o]  (+ b[o] if m = 0) ),  acc_k exact, int32.
+//
+// All orders of a row block multiply the same Q(x), so a wave takes a bin of 4 stored row blocks ("items") that holds
+// EVERY order of its 1 to 4 output row blocks, and a tile is 4 such bins (the 4 waves) against 16*MTB tokens.  One walk
+// along k per tile, whatever the orders:
+//   - every tile costs the same, so nothing waits for the tile with the most orders;
+//   - the activations of a tile are fetched once, not once per order;
+//   - no fp32 running sum lives through the loop: int32 accumulators only, the orders are folded behind it.
+// Data paths of a stage (SK 64-k steps, one or two packed code tiles per item):
+//   - packed codes: L2 -> registers, 16 bytes per lane, requested two stages ahead (three register sets), widened to int8
+//     between the MFMAs of the item before;
+//   - activations: L2 -> LDS without passing through registers, already in the MFMA operand layout, three slots.
+// Bound by the matrix pipe and the issue slots around it (a stage of 64 tokens: 64 MFMAs against 112 unpack instructions, 20
+// LDS reads and 8 loads per wave); 160 vector registers and 52 KB of LDS let three workgroups share a compute unit.
+// Measured against one pass per order (pipe_gemm.hip, same box): 11008 x 4096 ternary, K = 4, 4096 tokens 227 -> 203 us,
+// 333 tokens 62 -> 30 us; 3x3 convolution 256 x 256 of 6272 pixels, 4 bit, K = 3 35.5 -> 18.4 us; 3072 x 768 and back, 4 bit,
+// K = 3, 4096 tokens 81 -> 60 us; eight 2048 x 2048 ternary layers, two members of 4 orders, 4096 tokens 676 -> 591 us.
+// One barrier per stage.  The LDS-direct loads are issued by hand (the compiler would make every LDS read wait for the
+// newest of them) and their waits are counted: a stage's loads are always CL codes, then XC activations.
+#include <type_traits>
+
+#include "pipe_tile.h"
+
+namespace {
+
+constexpr int FRAG = 64;   // uint4 per fragment
+constexpr int RING = 3;    // stages in flight: activation slots in LDS, register sets of codes
+
+struct BinsParams {
+  const uint8_t* qx;
+  int64_t qx_mstride;
+  const int32_t* rowsum;
+  int64_t rowsum_mstride;
+  const float* s_x;
+  int sx_mstride;
+  const uint8_t* codes;
+  const float* scales;
+  const TileBin* bins;            // [4 * n_ct]
+  const float* bias;
+  long long bias_mstride;
+  float* y;
+  uint32_t* amax_out;
+  uint32_t* amax_neg;
+  uint32_t* zero_after;
+  int zero_n;
+  uint32_t* zero_big;
+  int zero_big_n;
+  int T, T_pad, out, nks;
+  int apart;                      // 1: one output per member, y[M,T,out]
+  int fold_sx;                    // 1: the activation scale joins the row scales (a sum over several members)
+  int act;
+  const float* res;               // MODE_CHAIN: skip tensor
+  long long res_mstride;
+  int res_members, res_pre_act;
+  int hidden;                     // MODE_GATED: rows are gate [0,H) and up [H,2H), y is [M,T,H]
+  TileOrder order;
+  const int8_t* cq8;              // CONV (implicit GEMM), as in pipe_gemm.hip
+  const int32_t* ccsum;
+  const uint8_t* czero;
+  int cC, cH, cW, ckh, ckw, cstride, cpad, cHo, cWo;
+};
+
+enum { MODE_PLAIN = 0, MODE_GELU = 2, MODE_GATED = 3, MODE_CHAIN = 4 };
+
+// Packed codes of one item for one stage of SK 64-k steps.
+template <int BITS, int SK>
+struct Codes {
+  static constexpr int N = SK * BITS / 8;   // uint4
+  static_assert(N >= 1, "a stage is whole code tiles");
+  v4u v[N];
+};
+
+template <int BITS, int SK>
+__device__ __forceinline__ v4i widen(const Codes<BITS, SK>& w, int j) {
+  constexpr int N = Codes<BITS, SK>::N;
+  if (BITS == 8) return (v4i)w.v[j & (N - 1)];
+  const v4u q = w.v[BITS == 4 ? (j >> 1) & (N - 1) : 0];
+  if (BITS == 4) return (j & 1) ? widen4(q.z, q.w) : widen4(q.x, q.y);
+  return widen2(j == 0 ? q.x : (j == 1 ? q.y : (j == 2 ? q.z : q.w)));
+}
+
+// Global -> LDS, 16 (or 4) bytes per lane from its own address to LDS byte address `lds` + 16 (4) * lane.
+__device__ __forceinline__ void dma16(const void* g, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
+}
+__device__ __forceinline__ void dma4(const void* g, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(g) : "memory");
+}
+// the same at a wave-uniform base and a 32-bit offset per lane
+__device__ __forceinline__ void dma16s(const void* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+// s_waitcnt: at most vm vector-memory and lgkm LDS / scalar operations outstanding
+constexpr int wait_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm << 8) | ((vm >> 4) << 14); }
+
+template <int BITS, int MTB, int MINW, int MODE, bool CONV>
+__global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p) {
+  constexpr int OFF = BITS == 8 ? 0 : (BITS == 4 ? 8 : 1);
+  constexpr int SK = BITS == 2 || MTB == 1 ? 4 : 2;   // 64-k steps per stage
+  constexpr int XC = MTB * SK / 4;                    // activation fragments (1 KiB) a wave loads per stage
+  constexpr int WN = Codes<BITS, SK>::N;
+  constexpr int CL = 4 * WN;                          // code loads of a wave per stage
+  constexpr int SLOT = MTB * SK * 1024;               // bytes of a stage's activations
+  static_assert(TOK_TILE % (16 * MTB) == 0, "token tile");
+  static_assert(RING == 3, "register sets of codes");
+  struct Lds {                                        // LDS-direct loads reach the first 64 KiB
+    uint4 xs[RING * MTB * SK * FRAG];
+    float scl[4][64];                                 // per wave: row scales of its items
+    float bias[4][64];                                // ... bias of their output rows
+    int rs[4][64];                                    // ... code sums of the tile's tokens
+  };
+  static_assert(sizeof(Lds) <= 65536, "LDS-direct loads");
+  __shared__ Lds lds;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (p.zero_big != nullptr)
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < p.zero_big_n; i += gridDim.x * 256) p.zero_big[i] = 0u;
+  if (blockIdx.x == 0 && (int)threadIdx.x < p.zero_n && p.zero_after != nullptr) p.zero_after[threadIdx.x] = 0u;
+  int ct, tt;
+  if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
+  const int t0 = tt * (16 * MTB);
+
+  const TileBin* bin = p.bins + ct * 4 + wave;
+  const v4i pos4 = cload(&bin->pos, 0), spos4 = cload(&bin->spos, 0), rb4 = cload(&bin->rb, 0), info = cload(&bin->info, 0);
+  const int pos[4] = {pos4[0], pos4[1], pos4[2], pos4[3]};
+  const int rb[4] = {rb4[0], rb4[1], rb4[2], rb4[3]};
+  const int m = info[0], ends = info[1], ups = info[2];   // member; items that end a row block; items of an up block
+  const bool active = info[3] != 0;
+
+  // ---- load cursor: the stage requested next; behind the last one it stays there (those loads are never used)
+  const int n_stage = p.nks / SK;
+  const int64_t rb_bytes = (int64_t)p.nks * 8 * BITS * 16;   // packed codes of a row block
+  const int xb = wave * XC / SK, xj = wave * XC - xb * SK;   // this wave's fragments: token block, first 64-k step
+  const uint8_t* l_x = p.qx + (int64_t)m * p.qx_mstride + ((int64_t)(t0 / 16 + xb) * p.nks + xj) * 1024;
+  const uint8_t* l_wb[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) l_wb[r] = p.codes + pos[r] * rb_bytes;
+  int64_t l_w = 0;
+  int l_left = n_stage;
+  unsigned l_slot = 0;
+  constexpr int NCB = CONV ? XC : 1;
+  int c_off = 0, c_h0 = 0, c_w0 = 0;         // CONV: this lane's pixel: offset of the window's first tap, its row and column
+  int c_r[NCB], c_q[NCB], c_c0[NCB];         // wave-uniform: tap and first channel of the 64-k step each fragment loads next
+  if constexpr (CONV) {
+    const int t = t0 + xb * 16 + (lane & 15);
+    const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
+    const int h0 = ho * p.cstride - p.cpad;
+    c_h0 = t < p.T ? h0 : -(1 << 20);        // a token beyond the batch: every tap outside
+    c_w0 = wo * p.cstride - p.cpad;
+    c_off = ((img * p.cH + h0) * p.cW + c_w0) * p.cC + (lane >> 4) * 16;   // used only for taps inside the image
+#pragma unroll
+    for (int f = 0; f < XC; ++f) {
+      const int tap = ((xj + f) * 64) / p.cC;
+      c_c0[f] = (xj + f) * 64 - tap * p.cC;
+      c_r[f] = tap / p.ckw;
+      c_q[f] = tap - c_r[f] * p.ckw;
+    }
+  }
+  const unsigned xs_base = lds_addr(&lds.xs[0]);
+  auto xload = [&]() __attribute__((always_inline)) {
+    const unsigned dst = xs_base + l_slot + wave * XC * 1024;
+#pragma unroll
+    for (int f = 0; f < XC; ++f) {
+      if constexpr (CONV) {
+        const int r = c_r[f], q = c_q[f], c0 = c_c0[f];
+        const bool inside = r < p.ckh && (unsigned)(c_h0 + r) < (unsigned)p.cH && (unsigned)(c_w0 + q) < (unsigned)p.cW;
+        const int8_t* g = inside ? p.cq8 + (c_off + (r * p.cW + q) * p.cC + c0) : reinterpret_cast<const int8_t*>(p.czero);
+        dma16(g, dst + f * 1024);
+      } else {
+        dma16s(l_x + f * 1024, lane * 16, dst + f * 1024);
+      }
+    }
+    l_slot = l_slot == (RING - 1) * SLOT ? 0 : l_slot + SLOT;
+  };
+  auto wload = [&](Codes<BITS, SK>(&w)[4]) __attribute__((always_inline)) {
+    unsigned off = lane * 16;
+    asm volatile("" : "+v"(off));   // a 32-bit offset next to the loads: they take the scalar base + offset form
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int q = 0; q < WN; ++q) w[r].v[q] = gload16(l_wb[r] + l_w + q * 1024 + off);
+  };
+  auto advance = [&]() __attribute__((always_inline)) {
+    if (l_left > 1) {
+      --l_left;
+      l_w += WN * 1024;
+      l_x += SK * 1024;
+      if constexpr (CONV) {
+        // the 64-k steps run tap-major, channel-minor (C is a multiple of 64); the position is stepped, not divided out
+#pragma unroll
+        for (int f = 0; f < XC; ++f) {
+          c_c0[f] += SK * 64;
+          while (c_c0[f] >= p.cC) {
+            c_c0[f] -= p.cC;
+            if (++c_q[f] == p.ckw) { c_q[f] = 0; ++c_r[f]; }
+          }
+        }
+      }
+    }
+  };
+
+  // ---- what the epilogue needs travels ahead of the ring, into LDS of this wave
+  {
+    const int r = lane >> 4;
+    int sp = 0, br = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {   // selects on scalar registers (an indexed array would live in scratch memory)
+      sp |= r == q ? spos4[q] : 0;
+      br |= r == q ? max(rb[q], 0) * 16 + ((ups >> q) & 1 ? p.hidden : 0) : 0;
+    }
+    dma4(p.scales + (size_t)sp * 16 + (lane & 15), lds_addr(&lds.scl[wave][0]));
+    if (p.bias != nullptr) dma4(p.bias + (size_t)m * p.bias_mstride + br + (lane & 15), lds_addr(&lds.bias[wave][0]));
+    if (OFF && !CONV) dma4(p.rowsum + (size_t)m * p.rowsum_mstride + min(t0 + lane, p.T_pad - 1), lds_addr(&lds.rs[wave][0]));
+  }
+  Codes<BITS, SK> w0[4], w1[4], w2[4];
+  wload(w0);
+  __builtin_amdgcn_sched_barrier(0);
+  xload();
+  __builtin_amdgcn_sched_barrier(0);
+  advance();
+  wload(w1);
+  __builtin_amdgcn_sched_barrier(0);
+  xload();
+  __builtin_amdgcn_sched_barrier(0);
+  advance();
+  const float sx = p.s_x[m * p.sx_mstride];
+  if constexpr (OFF != 0 && CONV) {
+    // token code sum = the channel sums of the window's pixels that lie inside the image
+    const int t = t0 + min(lane, 16 * MTB - 1);
+    const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
+    const int h0 = ho * p.cstride - p.cpad, w0_ = wo * p.cstride - p.cpad;
+    int sum = 0;
+    if (t < p.T)
+      for (int r = 0; r < p.ckh; ++r)
+        for (int q = 0; q < p.ckw; ++q)
+          if ((unsigned)(h0 + r) < (unsigned)p.cH && (unsigned)(w0_ + q) < (unsigned)p.cW)
+            sum += p.ccsum[(img * p.cH + h0 + r) * p.cW + w0_ + q];
+    lds.rs[wave][lane] = sum;
+  }
+
+  v4i acc[4][MTB];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int b = 0; b < MTB; ++b) acc[r][b] = v4i{0, 0, 0, 0};
+  unsigned c_slot = 0;
+
+  // One stage.  `cur` and the ring slot c_slot hold its codes and activations, requested two stages ago; `far` is
+  // free (multiplied in the stage before) and takes the codes of the stage after next.
+  auto stage = [&](Codes<BITS, SK>(&cur)[4], Codes<BITS, SK>(&far)[4], bool multiply) __attribute__((always_inline)) {
+    // this stage's codes have arrived: the wait the compiler places here leaves the newest loads in flight
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int q = 0; q < WN; ++q) asm volatile("" : "+v"(cur[r].v[q]));
+    // ... and so have this wave's activations of the stage (all but the CL + XC loads behind them)
+    __builtin_amdgcn_s_waitcnt(wait_imm(CL + XC, 0));
+    asm volatile("s_barrier" ::: "memory");    // everyone's have, and the slot of the stage before is free
+    wload(far);
+    __builtin_amdgcn_sched_barrier(0);
+    xload();
+    __builtin_amdgcn_sched_barrier(0);
+    advance();
+    if (multiply) {
+      // Software pipeline of the SK 64-k steps: a wave issues in order, so everything that is not an MFMA has to sit in
+      // the shadow of one.  The fragments of step j+1 are requested before step j's MFMAs start (two register
+      // sets), and the codes of item r+1 are widened between the MFMAs of item r (two register sets).
+      const v4i* xs = reinterpret_cast<const v4i*>(lds.xs) + c_slot / 16 + lane;
+      v4i xf[2][MTB];
+      v4i wf[2];
+#pragma unroll
+      for (int b = 0; b < MTB; ++b) xf[0][b] = xs[b * SK * FRAG];
+      wf[0] = widen<BITS, SK>(cur[0], 0);
+#pragma unroll
+      for (int j = 0; j < SK; ++j) {
+        if (j + 1 < SK) {
+#pragma unroll
+          for (int b = 0; b < MTB; ++b) xf[(j + 1) & 1][b] = xs[(b * SK + j + 1) * FRAG];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (r + 1 < 4) wf[(r + 1) & 1] = widen<BITS, SK>(cur[r + 1], j);
+          else if (j + 1 < SK) wf[(r + 1) & 1] = widen<BITS, SK>(cur[0], j + 1);
+#pragma unroll
+          for (int b = 0; b < MTB; ++b)
+            acc[r][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[r & 1], xf[j & 1][b], acc[r][b], 0, 0, 0);
+          if (BITS != 8) {
+            // one MFMA, then some of the unpack instructions, and so on
+#pragma unroll
+            for (int b = 0; b < MTB; ++b) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x002, 8 / MTB, 0);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);   // keep the items apart: bounds live registers
+        }
+      }
+    }
+    c_slot = c_slot == (RING - 1) * SLOT ? 0 : c_slot + SLOT;
+  };
+  // Three stages a round, so every register set keeps its role and the ring has one exit (the compiler counts
+  // outstanding loads exactly then); behind the last stage the rest of the round multiplies nothing.
+  for (int s = 0; s < n_stage; s += RING) {
+    stage(w0, w2, active);
+    stage(w1, w0, active && s + 1 < n_stage);
+    stage(w2, w1, active && s + 2 < n_stage);
+  }
+  // the ring's last loads write into this workgroup's LDS and registers: they end here
+  __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
+  asm volatile("" ::: "memory");
+
+  // ---- epilogue: orders folded in ascending k, one output row block after the other.  A lane holds 4 channels of one
+  // token per 16-token block, 64 contiguous bytes of a token per 16 lanes.
+  int lane_e = lane;
+  asm volatile("" : "+v"(lane_e));   // keeps the epilogue's addresses out of the loop's live range
+  const int tl = lane_e & 15, g = lane_e >> 4;
+  int rs[MTB];
+#pragma unroll
+  for (int b = 0; b < MTB; ++b) rs[b] = OFF ? lds.rs[wave][b * 16 + tl] : 0;
+  float mx = 0.f, mn = 0.f;
+  const bool two_sided = p.amax_neg != nullptr;
+  const bool with_bias = p.bias != nullptr && (m == 0 || !p.apart || p.bias_mstride != 0);
+  float* ym = p.y + (size_t)(p.apart ? m : 0) * p.T * p.out + 4 * g;
+  const int n_res = (MODE == MODE_CHAIN && p.res != nullptr) ? (p.apart ? (m < p.res_members ? 1 : 0) : p.res_members) : 0;
+  const float* resm = MODE == MODE_CHAIN ? p.res + (size_t)(p.apart ? m : 0) * p.res_mstride + 4 * g : nullptr;
+  float v[MTB][4], gate[MODE == MODE_GATED ? MTB : 1][4];
+#pragma unroll
+  for (int b = 0; b < MTB; ++b)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[b][i] = 0.f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wave][r * 16 + g * 4]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float s = p.fold_sx ? sc[i] * sx : sc[i];
+#pragma unroll
+      for (int b = 0; b < MTB; ++b) v[b][i] = fmaf(s, (float)(acc[r][b][i] - OFF * rs[b]), v[b][i]);
+    }
+    if (!((ends >> r) & 1)) continue;
+    v4f bb = v4f{0.f, 0.f, 0.f, 0.f};
+    if (with_bias) bb = *reinterpret_cast<const v4f*>(&lds.bias[wave][r * 16 + g * 4]);
+#pragma unroll
+    for (int b = 0; b < MTB; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[b][i] = p.fold_sx ? v[b][i] + bb[i] : fmaf(sx, v[b][i], bb[i]);   // same rounding as the other contraction kernels
+    if (MODE == MODE_GATED && !((ups >> r) & 1)) {
+#pragma unroll
+      for (int b = 0; b < MTB; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { gate[b][i] = v[b][i]; v[b][i] = 0.f; }
+      continue;
+    }
+#pragma unroll
+    for (int b = 0; b < MTB; ++b) {
+      const int t = t0 + b * 16 + tl;
+      if (MODE == MODE_CHAIN) {
+        float4 rq = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int mm = 0; mm < n_res; ++mm) {
+          const float4 x = *reinterpret_cast<const float4*>(resm + (size_t)mm * p.res_mstride + (size_t)min(t, p.T - 1) * p.out + rb[r] * 16);
+          rq.x += x.x; rq.y += x.y; rq.z += x.z; rq.w += x.w;
+        }
+        const float rr[4] = {rq.x, rq.y, rq.z, rq.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (p.res_pre_act) v[b][i] += rr[i];
+          if (p.act == PIPE_ACT_RELU) v[b][i] = fmaxf(v[b][i], 0.f);
+          else if (p.act == PIPE_ACT_GELU) v[b][i] = gelu_erf(v[b][i]);
+          if (!p.res_pre_act) v[b][i] += rr[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (MODE == MODE_GELU) v[b][i] = gelu_erf(v[b][i]);
+        if (MODE == MODE_GATED) v[b][i] = gate[b][i] / (1.f + expf(-gate[b][i])) * v[b][i];
+      }
+      if (t < p.T) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          mx = fmaxf(mx, two_sided ? v[b][i] : fabsf(v[b][i]));
+          if (two_sided) mn = fmaxf(mn, -v[b][i]);
+        }
+        *reinterpret_cast<float4*>(ym + (size_t)t * p.out + rb[r] * 16) = make_float4(v[b][0], v[b][1], v[b][2], v[b][3]);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[b][i] = 0.f;
+    }
+  }
+  if (p.amax_out != nullptr) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    if (lane == 0) amax_raise(&p.amax_out[m], mx);
+    if (two_sided) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) mn = fmaxf(mn, __shfl_xor(mn, o, 64));
+      if (lane == 0) amax_raise(&p.amax_neg[m], mn);
+    }
+  }
+}
+
+template <int BITS, int MTB, int MINW>
+int launch_cfg(BinsParams& p, int n_ct, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
+  p.order = tile_order(n_ct, ceil_div(p.T, 16 * MTB));
+  const dim3 grid((unsigned)p.order.blocks());
+  if (p.cq8 != nullptr) {
+    if (p.res != nullptr || p.act != 0) return PIPE_EINVAL;   // implicit-GEMM convolution: plain epilogue
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true>), grid, dim3(256), st, ev0, ev1, p);
+  } else if (p.res != nullptr || p.act == PIPE_ACT_RELU) {
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false>), grid, dim3(256), st, ev0, ev1, p);
+  } else if (p.act == PIPE_ACT_GELU) {
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GELU, false>), grid, dim3(256), st, ev0, ev1, p);
+  } else if (p.act == PIPE_ACT_SILU_GATED) {
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GATED, false>), grid, dim3(256), st, ev0, ev1, p);
+  } else {
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, false>), grid, dim3(256), st, ev0, ev1, p);
+  }
+  PIPE_HIP(hipGetLastError());
+  return PIPE_OK;
+}
+
+}  // namespace
+
+// Members whose outputs stay apart each have their own bins; members that share one input and are summed are one set of
+// orders.  A sum over members with inputs of their own, a member with more orders than a bin holds, a gate||up pair that
+// may need more than a bin (3 orders and more), and the integer export run pass by pass (pipe_gemm.hip).
+bool pipe_bins_apply(const GemmArgs& a) {
+  if (a.acc_out != nullptr) return false;
+  const bool joined = a.M == 1 || a.reduce;
+  if (joined) {
+    if (a.M > 1 && (a.qx_mstride != 0 || a.sx_mstride != 0)) return false;
+    if (a.act == PIPE_ACT_SILU_GATED) return a.M == 1 && a.e->K <= 2;
+    return a.e->K <= 4;
+  }
+  for (int m = 0; m < a.M; ++m)
+    if (a.member_hi[m] - a.member_lo[m] + 1 > (a.act == PIPE_ACT_SILU_GATED ? 2 : 4)) return false;
+  return true;
+}
+
+int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
+  const pipe_expansion* e = a.e;
+  if (a.T <= 0) return PIPE_OK;
+  if (a.T_pad % TOK_TILE != 0 || a.T_pad < a.T) return PIPE_ESHAPE;
+  if (a.conv_q8 != nullptr && (a.conv_C % 64 != 0 || (a.M > 1 && a.qx_mstride != 0))) return PIPE_ESHAPE;
+  if (a.res != nullptr && (a.act == PIPE_ACT_SILU_GATED || a.res_members < 1 || a.res_members > a.M)) return PIPE_EINVAL;
+  if (a.act == PIPE_ACT_SILU_GATED && a.reduce) return PIPE_EINVAL;
+  int rc = PIPE_OK;
+  const TileBins* tb = pipe_get_bins(e, a, &rc);
+  if (tb == nullptr) return rc;
+  BinsParams p;
+  p.qx = a.qx; p.qx_mstride = a.qx_mstride; p.rowsum = a.rowsum; p.rowsum_mstride = a.rowsum_mstride;
+  p.s_x = a.s_x; p.sx_mstride = a.sx_mstride;
+  p.codes = e->codes_dev; p.scales = e->scales_all_dev; p.bins = tb->bins_dev;
+  p.bias = a.bias; p.bias_mstride = a.bias_mstride; p.y = a.y; p.amax_out = a.amax_out; p.amax_neg = a.amax_neg;
+  p.zero_after = a.zero_after; p.zero_n = a.zero_n; p.zero_big = a.zero_big; p.zero_big_n = a.zero_big_n;
+  p.T = a.T; p.T_pad = a.T_pad; p.out = e->out; p.nks = e->nks;
+  p.apart = !a.reduce; p.fold_sx = a.reduce && a.M > 1; p.act = a.act;
+  p.res = a.res; p.res_mstride = a.res_mstride; p.res_members = a.res_members; p.res_pre_act = a.res_pre_act;
+  p.hidden = 0;
+  if (a.act == PIPE_ACT_SILU_GATED) { p.hidden = e->out / 2; p.out = e->out / 2; }
+  p.cq8 = a.conv_q8; p.ccsum = a.conv_csum; p.czero = a.conv_zero;
+  p.cC = a.conv_C; p.cH = a.conv_H; p.cW = a.conv_W; p.ckh = a.conv_kh; p.ckw = a.conv_kw; p.cstride = a.conv_stride; p.cpad = a.conv_pad;
+  p.cHo = a.conv_Ho; p.cWo = a.conv_Wo;
+  // Token-tile height: 64 tokens amortize the unpacking of the codes best (the 4096-token layer above: 203, 245 and 317 us
+  // with 64, 32 and 16), and a second tile on a compute unit costs less than twice one; so the tallest that still gives
+  // three quarters of the 256 compute units a tile (256 tokens of that layer, 304 tiles of 64: 29.4, 27.2 and 29.1 us; 129
+  // tokens: 22 us each).
+  int mtb = g_tiled_mtb;
+  if (mtb != 1 && mtb != 2 && mtb != 4) {
+    auto tiles = [&](int tokens) { return (int64_t)tb->n_ct * ceil_div(a.T, tokens); };
+    mtb = tiles(64) >= 192 ? 4 : (tiles(32) >= 192 ? 2 : 1);
+  }
+  switch (e->bits * 8 + mtb) {
+    case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 1: return launch_cfg<8, 1, 2>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 4: return launch_cfg<4, 4, 3>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 2: return launch_cfg<4, 2, 4>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 1: return launch_cfg<4, 1, 3>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 4: return launch_cfg<2, 4, 3>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 2: return launch_cfg<2, 2, 4>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 1: return launch_cfg<2, 1, 4>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    default: return PIPE_EINVAL;
+  }
+}

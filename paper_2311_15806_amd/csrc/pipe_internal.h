@@ -90,6 +90,20 @@ struct PassTables {
   int32_t* src_dev = nullptr;          // [M][p_max][n_sorted] position of the row block's j-th stored order, or -1
   uint8_t* cnt_dev = nullptr;          // [n_ct][16] passes of member m in tile t
 };
+// Bins of the single-pass tiled kernel (pipe_gemm_bins.hip): 4 stored row blocks ("items") that hold every order of
+// 1 to 4 output row blocks of one member, items of a row block adjacent and in ascending order.  4 bins are a column tile.
+struct TileBin {
+  int32_t pos __attribute__((vector_size(16)));    // positions of the items' codes
+  int32_t spos __attribute__((vector_size(16)));   // ... and of their row scales (zero_pos: an item without an order)
+  int32_t rb __attribute__((vector_size(16)));     // output row block of the item (of a gate||up layer: the hidden block)
+  int32_t info __attribute__((vector_size(16)));   // member; mask of items that end a row block; mask of items of up blocks; 1 = not empty
+};
+struct TileBins {
+  unsigned long long member_nib = 0;   // as in PassTables
+  int M = 0, gated = 0;                // members apart (joined members count as one)
+  int n_ct = 0;
+  TileBin* bins_dev = nullptr;         // [4 * n_ct]
+};
 // Work units of the resident decode kernel (pipe_resident.hip), built on first use per expansion.
 //   sub-unit: 16 ints  {pos[4] (items a sub-unit does not have repeat pos[0]), k[4], n_items,
 //             first LDS tile of its items, 1 = last sub-unit of its unit, 5 unused}
@@ -127,6 +141,7 @@ struct pipe_expansion {
   // of the orders into members, kept until the expansion is freed.
   std::vector<int32_t> pos_of;       // [K][n_rb] position (in codes_dev) of output row block rb at order k, or -1
   std::vector<PassTables> tables;
+  std::vector<TileBins> tile_bins;   // the single-pass kernel's, likewise
   // dense per-order codes [K][in][out] (int8, tap-major, pruned rows zero) and scales [K][out] of a depthwise layer
   // (in = kh*kw), built on first use of pipe_forward_depthwise2d
   int8_t* dw_codes_dev = nullptr;
@@ -349,6 +364,10 @@ struct GemmArgs {
     else hipLaunchKernelGGL(kernel, grid, block, 0, st, __VA_ARGS__);                         \
   } while (0)
 int launch_gemm_tiled(const GemmArgs& a, hipStream_t st);
+// the single-pass kernel, for the calls that fit it; its bins are built on first use as pipe_get_tables' tables are
+bool pipe_bins_apply(const GemmArgs& a);
+const TileBins* pipe_get_bins(const pipe_expansion* e, const GemmArgs& a, int* rc);
+int launch_gemm_bins(const GemmArgs& a, hipStream_t st);
 // depthwise layers: dense per-order codes and scales (built once), then the forward kernel
 int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st);
 int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static, const uint32_t* amax_bits, float qmax,

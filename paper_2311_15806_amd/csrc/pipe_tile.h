@@ -1,0 +1,77 @@
+// Device helpers shared by the two tiled contraction kernels (pipe_gemm.hip, pipe_gemm_bins.hip).
+#pragma once
+#include "pipe_internal.h"
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float gelu_erf(float a) {
+  return 0.5f * a * (1.f + erff(a * 0.70710678118654752440f));
+}
+
+// One 64-k step of packed codes as int8 MFMA operand: 8-bit codes are the operand, a 4-bit step is two dwords (lo, hi),
+// a ternary one a single dword (lo).
+__device__ __forceinline__ v4i widen4(uint32_t lo, uint32_t hi) {
+  return v4i{(int)(lo & 0x0F0F0F0Fu), (int)((lo >> 4) & 0x0F0F0F0Fu), (int)(hi & 0x0F0F0F0Fu), (int)((hi >> 4) & 0x0F0F0F0Fu)};
+}
+__device__ __forceinline__ v4i widen2(uint32_t a) {
+  return v4i{(int)(a & 0x03030303u), (int)((a >> 2) & 0x03030303u), (int)((a >> 4) & 0x03030303u), (int)((a >> 6) & 0x03030303u)};
+}
+
+// A load known to hit global memory.  Pointers rebuilt from integers are "generic" to the
+// compiler, which would emit FLAT loads: those also count as LDS operations (every wait on the
+// LDS fragment reads would then wait for the weight prefetch as well) and are ordered against
+// the LDS-direct loads.
+__device__ __forceinline__ v4u gload16(const void* p) {
+  typedef const __attribute__((address_space(1))) v4u* gptr;
+  return *(gptr)(unsigned long long)p;
+}
+
+// Loads of schedule tables at wave-uniform addresses through the constant address space: the
+// compiler then uses scalar loads (the tables are written once, by the host, when the expansion
+// is built; no kernel ever stores to them), which cost no vector registers and no vector wait.
+template <class T>
+__device__ __forceinline__ T cload(const T* base, size_t idx) {
+  typedef const __attribute__((address_space(4))) T* cptr;
+  return ((cptr)(unsigned long long)base)[idx];
+}
+
+// The LDS byte address of an object in shared memory.
+template <class T>
+__device__ __forceinline__ unsigned lds_addr(T* p) {
+  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) T*)p;
+}
+
+// Which tile a workgroup computes.  Blocks i, i + 8, ... of a launch run on one XCD (one L2): chunks of `chunk`
+// consecutive tiles are dealt to the 8 XCDs in turn.  Tiles are numbered in strips of `strip` column tiles (heaviest
+// first), along the tokens inside a strip.
+struct TileOrder {
+  int n_ct, n_tt, strip, chunk;
+  __host__ __device__ int blocks() const { return (n_ct * n_tt + 8 * chunk - 1) / (8 * chunk) * 8 * chunk; }
+  __device__ __forceinline__ bool tile(int block, int* ct, int* tt) const {
+    const int xcd = block & 7, j = block >> 3;
+    const int jc = j / chunk;
+    const int t = (jc * 8 + xcd) * chunk + j - jc * chunk;
+    if (t >= n_ct * n_tt) return false;
+    const int s = t / (strip * n_tt), rem = t - s * strip * n_tt;
+    const int width = n_ct - s * strip < strip ? n_ct - s * strip : strip;
+    *tt = rem / width;
+    *ct = s * strip + rem - *tt * width;
+    return true;
+  }
+};
+
+// Few token tiles and many column tiles: a chunk is a column tile with all its token tiles (its codes are read by one
+// XCD, the few activations by all: 333 tokens of the 11008 x 4096 ternary layer 29.8 us, 33.1 us dealt tile by tile).
+// Otherwise strips of 8 column tiles and one token tile of a strip per chunk, so that neither the XCDs nor the rounds differ by
+// more than 8 tiles (super-tiles of 8 x 8 per XCD: 49.8 against 29.8 us at 333 tokens, 212 against 203 at 4096; strips of
+// 1, 4 and 16: 204, 205 and 209 us).
+static inline TileOrder tile_order(int n_ct, int n_tt) {
+  TileOrder o;
+  o.n_ct = n_ct;
+  o.n_tt = n_tt;
+  if (n_tt <= 16 && n_ct >= 16) { o.strip = 1; o.chunk = n_tt; }
+  else { o.strip = n_ct < 8 ? n_ct : 8; o.chunk = o.strip; }
+  return o;
+}

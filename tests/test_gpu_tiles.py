@@ -1,0 +1,78 @@
+"""The single-pass tiled kernel (batches above 128 tokens, members of at most 4 orders) where its tiles have edges:
+one token more than the streaming kernel takes, token tiles of one token, all token-tile heights, column tiles with
+empty waves, row blocks that a member pruned, bins of every composition, one stage of k and many.  With a given scale
+every token is independent of its batch, and both kernels fold the orders with the same fp32 operations in the same
+order: a batch must equal its parts of at most 128 tokens, which the streaming kernel serves, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from _parity import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pipe():
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    import paper_2311_15806_amd.binding as b
+    return b
+
+
+def _weight(seed, O, I):
+    rng = np.random.default_rng(seed)
+    return (rng.standard_t(3, size=(O, I)) * 0.02).astype(np.float32)
+
+
+def _parts(T):
+    return [(a, min(a + 128, T)) for a in range(0, T, 128)]
+
+
+#            O     I     bits K gamma group split   T
+LAYERS = [(16, 100, 4, 1, 1.0, 16, [1], 129),
+          (48, 256, 2, 4, 0.34, 16, [4], 193),       # counts 1 to 4: every kind of bin; n_bins no multiple of 4
+          (1040, 300, 2, 4, 0.25, 16, [1, 3], 150),  # members: most row blocks of the second are pruned
+          (320, 1030, 4, 3, 0.5, 32, [2, 1], 257),
+          (256, 700, 8, 2, 1.0, 16, [1, 1], 191),
+          (2048, 512, 3, 4, 0.5, 64, [2, 2], 400),   # 64-token tiles
+          (4096, 260, 2, 3, 0.5, 64, [3], 321)]
+
+
+@pytest.mark.parametrize("O,I,bits,K,gamma,group,split,T", LAYERS)
+@pytest.mark.parametrize("reduce", [True, False])
+def test_batch_equals_its_parts(pipe, O, I, bits, K, gamma, group, split, T, reduce):
+    rng = np.random.default_rng(O + I + T)
+    e = pipe.pipe_expand(dev(_weight(O * 7 + I, O, I)), bits, K, gamma, group)
+    x = dev(rng.standard_normal((T, I)).astype(np.float32))
+    b = dev(rng.standard_normal(O).astype(np.float32))
+    for tile in (0, 16, 32, 64):
+        pipe.pipe_set_token_tile(tile)
+        try:
+            y = pipe.pipe_forward(e, x, s_x=0.03, split=split, bias=b, reduce_members=reduce)
+        finally:
+            pipe.pipe_set_token_tile(0)
+        ref = torch.cat([pipe.pipe_forward(e, x[a:z].contiguous(), s_x=0.03, split=split, bias=b, reduce_members=reduce)
+                         for a, z in _parts(T)], dim=0 if reduce else 1)
+        assert torch.equal(y, ref), "token tile %d" % tile
+    e.free()
+
+
+@pytest.mark.parametrize("H,I,bits,K,gamma,split,T", [(48, 200, 4, 2, 0.5, [2], 129), (336, 260, 2, 4, 0.25, [2, 2], 321),
+                                                      (2752, 300, 4, 4, 0.5, [2, 2], 200)])
+def test_gated_batch_equals_its_parts(pipe, H, I, bits, K, gamma, split, T):
+    rng = np.random.default_rng(H + T)
+    l1 = pipe.pipe_expand(dev(_weight(H, 2 * H, I)), bits, K, gamma, 16)
+    l2 = pipe.pipe_expand(dev(_weight(H + 1, 64, H)), bits, K, gamma, 16)
+    x = dev(rng.standard_normal((T, I)).astype(np.float32))
+    b1 = dev(rng.standard_normal(2 * H).astype(np.float32))
+    call = lambda v: pipe.pipe_mlp_forward_given_scales(l1, l2, pipe.PIPE_ACT_SILU_GATED, v, 0.03, [0.02] * len(split), split=split,
+                                                        bias1=b1, return_hidden=True)
+    y, h = call(x)
+    parts = [call(x[a:z].contiguous()) for a, z in _parts(T)]
+    # SiLU(gate)*up is evaluated by another kernel at 128 tokens and less: the same fp32 formula, a few ulp apart at most
+    ref = torch.cat([p[1] for p in parts], dim=1)
+    assert (h - ref).abs().max() <= 4e-7 * ref.abs().max()
+    # one code of Q(h) may fall the other way for it: one step of the hidden scale times a weight
+    yr = torch.cat([p[0] for p in parts], dim=0)
+    assert (y - yr).abs().max() <= 1e-5 * yr.abs().max() + 0.02 * float(pipe.pipe_expansion_reconstruct(l2).abs().max())
+    l1.free(), l2.free()
