@@ -209,9 +209,7 @@ static void free_expansion(pipe_expansion* e) {
     if (o.pos_dev) (void)hipFree(o.pos_dev);
   }
   for (auto& t : e->tables) {
-    if (t.rb_out_dev) (void)hipFree(t.rb_out_dev);
-    if (t.src_dev) (void)hipFree(t.src_dev);
-    if (t.cnt_dev) (void)hipFree(t.cnt_dev);
+    if (t.rb_out_dev) (void)hipFree(t.rb_out_dev);   // the block of all three
   }
   for (auto& t : e->tile_bins)
     if (t.bins_dev) (void)hipFree(t.bins_dev);
@@ -642,21 +640,24 @@ const PassTables* pipe_get_tables(const pipe_expansion* ce, const GemmArgs& a, i
       }
     }
   }
-  auto fail = [&](hipError_t he, const char* what) {
-    pipe_note_hip_error(he, what);
-    if (t.rb_out_dev) (void)hipFree(t.rb_out_dev);
-    if (t.src_dev) (void)hipFree(t.src_dev);
-    if (t.cnt_dev) (void)hipFree(t.cnt_dev);
+  // one block: the three tables one behind the other
+  const size_t at_src = (size_t)round_up64((int64_t)rb_out.size() * 4, 256), at_cnt = at_src + (size_t)round_up64((int64_t)src.size() * 4, 256);
+  std::vector<uint8_t> block(at_cnt + cnts.size());
+  std::memcpy(block.data(), rb_out.data(), rb_out.size() * 4);
+  std::memcpy(block.data() + at_src, src.data(), src.size() * 4);
+  std::memcpy(block.data() + at_cnt, cnts.data(), cnts.size());
+  uint8_t* dev = nullptr;
+  hipError_t he = hipMalloc(&dev, block.size());
+  if (he == hipSuccess) he = hipMemcpy(dev, block.data(), block.size(), hipMemcpyHostToDevice);
+  if (he != hipSuccess) {
+    pipe_note_hip_error(he, "pass tables");
+    if (dev) (void)hipFree(dev);
     *rc_out = PIPE_EDEVICE;
-    return (const PassTables*)nullptr;
-  };
-  hipError_t he;
-  if ((he = hipMalloc(&t.rb_out_dev, rb_out.size() * 4)) != hipSuccess) return fail(he, "hipMalloc(rb_out)");
-  if ((he = hipMalloc(&t.src_dev, src.size() * 4)) != hipSuccess) return fail(he, "hipMalloc(src)");
-  if ((he = hipMalloc(&t.cnt_dev, cnts.size())) != hipSuccess) return fail(he, "hipMalloc(cnt)");
-  if ((he = hipMemcpy(t.rb_out_dev, rb_out.data(), rb_out.size() * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail(he, "hipMemcpy(rb_out)");
-  if ((he = hipMemcpy(t.src_dev, src.data(), src.size() * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail(he, "hipMemcpy(src)");
-  if ((he = hipMemcpy(t.cnt_dev, cnts.data(), cnts.size(), hipMemcpyHostToDevice)) != hipSuccess) return fail(he, "hipMemcpy(cnt)");
+    return nullptr;
+  }
+  t.rb_out_dev = reinterpret_cast<int32_t*>(dev);
+  t.src_dev = reinterpret_cast<int32_t*>(dev + at_src);
+  t.cnt_dev = dev + at_cnt;
   e->tables.push_back(t);
   return &e->tables.back();
 }
@@ -766,21 +767,27 @@ static bool use_stream_kernel(const pipe_expansion* e, int T, bool acc_out = fal
 struct ActBuffers {
   uint8_t* qx;
   int32_t* rowsum;
-  uint32_t* amax;        // max|x| bit pattern: zero on entry, cleared again by the contraction kernel
+  uint32_t* amax;        // control words: from 16 on the hidden tensors' max and range slots (zero on entry, cleared by the
+                         // contraction kernel that follows their last reader), zero-point offsets
+  uint32_t* part;        // parts of the input's max reduction, PIPE_MAX_PARTS (and as many for the negative side)
   float* scale;          // [PIPE_MAX_K] scales
   int T_pad;
 };
+
+static MaxOf input_max(const ActBuffers& b, int64_t n) { return MaxOf{b.part, max_parts(n)}; }
+static MaxOf input_neg_max(const ActBuffers& b, int64_t n) { return MaxOf{b.part + PIPE_MAX_PARTS, max_parts(n)}; }
 
 static int get_act_buffers(int T, int in_pad, bool small, ActBuffers* b) {
   b->T_pad = (int)round_up64(T, small ? 16 : TOK_TILE);
   b->qx = (uint8_t*)pipe_ws_get(WS_QX, (size_t)b->T_pad * in_pad);
   b->rowsum = (int32_t*)pipe_ws_get(WS_ROWSUM, (size_t)b->T_pad * 4);
   const bool fresh = t_ws == nullptr || t_ws->slot[WS_SCAL].ptr == nullptr;
-  uint8_t* sc = (uint8_t*)pipe_ws_get(WS_SCAL, 4096);
+  uint8_t* sc = (uint8_t*)pipe_ws_get(WS_SCAL, 4096 + 2 * PIPE_MAX_PARTS * 4);
   if (!b->qx || !b->rowsum || !sc) return pipe_ws_error();
   if (fresh) PIPE_HIP(hipMemset(sc, 0, 4096));   // never under capture: a fresh block is refused there
   b->amax = (uint32_t*)sc;
   b->scale = (float*)(sc + 1024);
+  b->part = (uint32_t*)(sc + 4096);
   return PIPE_OK;
 }
 
@@ -801,13 +808,6 @@ static int ensure_tables(const pipe_expansion* e, int M, const int* lo, const in
     if (pipe_bins_apply(a) ? pipe_get_bins(e, a, &rc) == nullptr : pipe_get_tables(e, a, kind, &rc) == nullptr) return rc;
   }
   return PIPE_OK;
-}
-
-// An error after the max|x| reduction was launched: the slot is raised and the contraction kernel
-// that would clear it will not run.  Clears it so that the next dynamic scale starts from zero.
-static int fail_after_reduction(int rc, const ActBuffers& b, hipStream_t st) {
-  (void)launch_zero_u32(b.amax, 1, st);
-  return rc;
 }
 
 // ------------------------------------------------------------------ kernel timing
@@ -853,15 +853,13 @@ static int quantize_input(const float* x_dev, int T, int in, int in_pad, float s
                           int8_t* qx_rowmajor, float* scale_out, hipStream_t st) {
   if (small && T <= PIPE_QUANT1_MAX_T)
     return launch_quantize_small(x_dev, 0, 1, T, in, in_pad, s_x, nullptr, b.qx, 0, b.rowsum, qx_rowmajor, scale_out, st);
-  // The reduction slot is zero on entry (workspace allocation, then every contraction kernel
-  // clears it again); the reduction kernel also clears the code sums, so a dynamic scale costs
-  // two launches and no memset.
+  // The reduction kernel also clears the code sums, so a dynamic scale costs two launches and no memset.
   const bool dynamic = !(s_x > 0.f);
   if (dynamic) {
-    int rc = launch_absmax(x_dev, (int64_t)T * in, b.amax, b.rowsum, b.T_pad, st);
+    int rc = launch_absmax(x_dev, (int64_t)T * in, b.part, b.rowsum, b.T_pad, st);
     if (rc) return rc;
   }
-  return launch_quantize_act(x_dev, T, in, in_pad, b.T_pad, s_x, b.amax, b.qx, b.rowsum, dynamic, qx_rowmajor, scale_out, st);
+  return launch_quantize_act(x_dev, T, in, in_pad, b.T_pad, s_x, input_max(b, (int64_t)T * in), b.qx, b.rowsum, dynamic, qx_rowmajor, scale_out, st);
 }
 
 // While timing is on: the pair of events the next contraction launch records its begin and end into.
@@ -920,11 +918,11 @@ extern "C" int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, 
   GemmArgs a{};
   a.e = e; a.T = T; a.T_pad = b.T_pad; a.qx = b.qx; a.qx_mstride = 0; a.rowsum = b.rowsum; a.rowsum_mstride = 0;
   a.s_x = b.scale; a.sx_mstride = 0; a.bias = bias_dev; a.reduce = reduce_members ? 1 : 0; a.act = 0;
-  a.y = y_dev; a.acc_out = nullptr; a.amax_out = nullptr; a.zero_after = b.amax;
+  a.y = y_dev; a.acc_out = nullptr; a.amax_out = nullptr;
   if (fused) { a.x_f32 = x_dev; a.s_static = s_x; }
   fill_members(a, Mm, lo, hi);
   rc = run_gemm(a, small, st);
-  return rc == PIPE_OK ? rc : fail_after_reduction(rc, b, st);
+  return rc;
 }
 
 extern "C" int pipe_prepare(const pipe_expansion* e, const int* split, int M, int T_max, void* stream) {
@@ -958,14 +956,14 @@ extern "C" int pipe_forward_acc(const pipe_expansion* e, const float* x_dev, int
   rc = quantize_input(x_dev, T, e->in, e->in_pad, s_x, b, small, qx_dev, b.scale, st);
   if (rc) return rc;
   if (s_x_out_dev) PIPE_HIP(hipMemcpyAsync(s_x_out_dev, b.scale, sizeof(float), hipMemcpyDeviceToDevice, st));
-  if (!acc_dev) return launch_zero_u32(b.amax, 1, st);   // no contraction kernel follows to clear it
+  if (!acc_dev) return PIPE_OK;
   PIPE_HIP(hipMemsetAsync(acc_dev, 0, (size_t)e->K * T * e->out * sizeof(int32_t), st));
   GemmArgs a{};
   a.e = e; a.T = T; a.T_pad = b.T_pad; a.qx = b.qx; a.rowsum = b.rowsum;
-  a.s_x = b.scale; a.reduce = 1; a.acc_out = acc_dev; a.zero_after = b.amax;
+  a.s_x = b.scale; a.reduce = 1; a.acc_out = acc_dev;
   fill_members(a, 1, &lo, &hi);
   rc = run_gemm(a, small, st);
-  return rc == PIPE_OK ? rc : fail_after_reduction(rc, b, st);
+  return rc;
 }
 
 // ------------------------------------------------------------------ the entry point that allocates nothing
@@ -1016,6 +1014,8 @@ extern "C" int pipe_forward_noalloc(const pipe_expansion* e, const float* x_dev,
   if ((rc = noalloc_scratch(&base)) != PIPE_OK) return rc;
   b.amax = reinterpret_cast<uint32_t*>(base);
   b.scale = reinterpret_cast<float*>(base + 1024);
+  b.part = reinterpret_cast<uint32_t*>(base + 2048);
+  static_assert(2048 + PIPE_MAX_PARTS * 4 <= NOALLOC_SCAL_BYTES, "parts of the max reduction");
   b.rowsum = reinterpret_cast<int32_t*>(base + NOALLOC_SCAL_BYTES);
   b.qx = base + NOALLOC_SCAL_BYTES + NOALLOC_ROWSUM_BYTES;
   struct Guard {   // schedules are looked up, never built, inside this call
@@ -1025,20 +1025,16 @@ extern "C" int pipe_forward_noalloc(const pipe_expansion* e, const float* x_dev,
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   const bool fused = fuse_decode_quant(e, T, x_dev, small, y_dev, (size_t)(reduce_members ? 1 : Mm) * T * e->out);
   if (!fused) {
-    // The array keeps what the last call left: the max|x| slot has to start at zero (a call that
-    // failed after its reduction, or that overlapped another one, may have left it raised).
-    const bool uses_slot = !(s_x > 0.f) && !(small && T <= PIPE_QUANT1_MAX_T);
-    if (uses_slot && (rc = launch_zero_u32(b.amax, 1, st)) != PIPE_OK) return rc;
     rc = quantize_input(x_dev, T, e->in, e->in_pad, s_x, b, small, nullptr, b.scale, st);
     if (rc) return rc;
   }
   GemmArgs a{};
   a.e = e; a.T = T; a.T_pad = b.T_pad; a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;
-  a.bias = bias_dev; a.reduce = reduce_members ? 1 : 0; a.y = y_dev; a.zero_after = b.amax;
+  a.bias = bias_dev; a.reduce = reduce_members ? 1 : 0; a.y = y_dev;
   if (fused) { a.x_f32 = x_dev; a.s_static = s_x; }
   fill_members(a, Mm, lo, hi);
   rc = small ? launch_gemm_stream(a, st) : pipe_bins_apply(a) ? launch_gemm_bins(a, st) : launch_gemm_tiled(a, st);   // no timing events: creating one allocates
-  return rc == PIPE_OK ? rc : fail_after_reduction(rc, b, st);
+  return rc;
 }
 
 // ------------------------------------------------------------------ asymmetric activation codes
@@ -1103,17 +1099,19 @@ static int asym_prepare(const pipe_expansion* ce, hipStream_t st) {
 }
 
 // quantizes x with asymmetric codes into the activation buffers; dz (= 2^(a-1) - z) and the scale stay on the device
+// (C != nullptr: and the effective bias to e->asym_bias_dev)
 static int asym_quantize(const pipe_expansion* e, const float* x_dev, int T, const ActBuffers& b, uint8_t* qx_u8,
-                         uint32_t** slots_out, int32_t** dz_out, hipStream_t st) {
+                         int32_t** dz_out, hipStream_t st, const float* bias = nullptr, const float* C = nullptr) {
   const int act_bits = (int)std::lround(std::log2((double)g_act_qmax_host + 1.0)) + 1;
   // |Q(x) - z| <= 2^a - 1: the exact accumulator must fit 32 bits
   if ((int64_t)((1 << act_bits) - 1) * ((1 << (e->qbits - 1)) - 1) * e->in >= ((int64_t)1 << 31)) return PIPE_ESHAPE;
-  uint32_t* slots = b.amax + 64;              // two range slots, zero between calls
   int32_t* dz = reinterpret_cast<int32_t*>(b.amax + 66);
-  int rc = launch_minmax(x_dev, (int64_t)T * e->in, slots, st);
+  const int64_t n = (int64_t)T * e->in;
+  int rc = launch_minmax(x_dev, n, b.part, b.part + PIPE_MAX_PARTS, b.rowsum, b.T_pad, st);
   if (rc) return rc;
-  rc = launch_quantize_asym(x_dev, T, e->in, e->in_pad, b.T_pad, slots, slots + 1, act_bits, b.qx, b.rowsum, qx_u8, b.scale, dz, st);
-  *slots_out = slots; *dz_out = dz;
+  rc = launch_quantize_asym(x_dev, T, e->in, e->in_pad, b.T_pad, input_max(b, n), input_neg_max(b, n), act_bits, b.qx, b.rowsum, true, qx_u8, b.scale, dz, st,
+                            bias, C, e->asym_bias_dev, e->out);
+  *dz_out = dz;
   return rc;
 }
 
@@ -1135,16 +1133,13 @@ extern "C" int pipe_forward_asymmetric(const pipe_expansion* e, const float* x_d
   rc = get_act_buffers(T, e->in_pad, small, &b);
   if (rc) return rc;
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
-  uint32_t* slots = nullptr;
   int32_t* dz = nullptr;
-  rc = asym_quantize(e, x_dev, T, b, nullptr, &slots, &dz, st);
-  if (rc) return rc;
-  rc = launch_asym_bias(bias_dev, e->asym_C_dev, b.scale, dz, e->asym_bias_dev, e->out, slots, st);
+  rc = asym_quantize(e, x_dev, T, b, nullptr, &dz, st, bias_dev, e->asym_C_dev);
   if (rc) return rc;
   GemmArgs a{};
   a.e = e; a.T = T; a.T_pad = b.T_pad; a.qx = b.qx; a.qx_mstride = 0; a.rowsum = b.rowsum; a.rowsum_mstride = 0;
   a.s_x = b.scale; a.sx_mstride = 0; a.bias = e->asym_bias_dev; a.reduce = 1; a.act = 0;
-  a.y = y_dev; a.acc_out = nullptr; a.amax_out = nullptr; a.zero_after = b.amax;
+  a.y = y_dev; a.acc_out = nullptr; a.amax_out = nullptr;
   fill_members(a, Mm, lo, hi);
   return run_gemm(a, small, st);
 }
@@ -1179,18 +1174,18 @@ extern "C" int pipe_forward_conv2d_asymmetric(const pipe_expansion* e, const flo
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   int8_t* q8 = (int8_t*)pipe_ws_get(WS_Q8X, (size_t)N * C * H * W);   // the input's codes, in its own layout
   if (!q8) return pipe_ws_error();
-  uint32_t* slots = b.amax + 64;
   int32_t* dz = reinterpret_cast<int32_t*>(b.amax + 66);
-  rc = launch_minmax(x_dev, (int64_t)N * C * H * W, slots, st);
+  const int64_t n_in = (int64_t)N * C * H * W;
+  rc = launch_minmax(x_dev, n_in, b.part, b.part + PIPE_MAX_PARTS, nullptr, 0, st);
   if (rc) return rc;
-  rc = launch_quantize_im2col_asym(x_dev, N, C, H, W, kh, kw, stride, pad, nhwc, Ho, Wo, e->in_pad, b.T_pad, slots, slots + 1,
+  rc = launch_quantize_im2col_asym(x_dev, N, C, H, W, kh, kw, stride, pad, nhwc, Ho, Wo, e->in_pad, b.T_pad, input_max(b, n_in), input_neg_max(b, n_in),
                                    act_bits, q8, b.qx, b.rowsum, b.scale, dz, st);
   if (rc) return rc;
-  rc = launch_asym_bias(bias_dev, e->asym_C_dev, b.scale, dz, e->asym_bias_dev, e->out, slots, st);
+  rc = launch_asym_bias(bias_dev, e->asym_C_dev, b.scale, dz, e->asym_bias_dev, e->out, st);
   if (rc) return rc;
   GemmArgs a{};
   a.e = e; a.T = T; a.T_pad = b.T_pad; a.qx = b.qx; a.rowsum = b.rowsum;
-  a.s_x = b.scale; a.bias = e->asym_bias_dev; a.reduce = 1; a.y = y_dev; a.zero_after = b.amax;
+  a.s_x = b.scale; a.bias = e->asym_bias_dev; a.reduce = 1; a.y = y_dev;
   fill_members(a, Mm, lo, hi);
   return run_gemm(a, small, st);
 }
@@ -1211,16 +1206,13 @@ extern "C" int pipe_forward_acc_asymmetric(const pipe_expansion* e, const float*
   if (rc) return rc;
   int klo = 0, khi = e->K - 1;
   if (!small && (rc = ensure_tables(e, 1, &klo, &khi, 2)) != PIPE_OK) return rc;
-  uint32_t* slots = nullptr;
   int32_t* dz = nullptr;
-  rc = asym_quantize(e, x_dev, T, b, qx_dev, &slots, &dz, st);
-  if (rc) return rc;
-  rc = launch_asym_bias(nullptr, e->asym_C_dev, b.scale, dz, e->asym_bias_dev, e->out, slots, st);   // clears the range slots
+  rc = asym_quantize(e, x_dev, T, b, qx_dev, &dz, st);
   if (rc) return rc;
   PIPE_HIP(hipMemsetAsync(acc_dev, 0, (size_t)e->K * T * e->out * sizeof(int32_t), st));
   GemmArgs a{};
   a.e = e; a.T = T; a.T_pad = b.T_pad; a.qx = b.qx; a.rowsum = b.rowsum;
-  a.s_x = b.scale; a.reduce = 1; a.acc_out = acc_dev; a.zero_after = b.amax;
+  a.s_x = b.scale; a.reduce = 1; a.acc_out = acc_dev;
   fill_members(a, 1, &klo, &khi);
   rc = run_gemm(a, small, st);
   if (rc) return rc;
@@ -1279,13 +1271,13 @@ static int conv2d_impl(const pipe_expansion* e, const float* x_dev, int N, int C
     if (!q8 || !csum) return pipe_ws_error();
     int klo = 0, khi = e->K - 1;
     if ((rc = export_acc ? ensure_tables(e, 1, &klo, &khi, 2) : ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
-    if (!(s_x > 0.f)) rc = launch_absmax(x_dev, (int64_t)n_in, b.amax, csum, N * H * W, st);
+    if (!(s_x > 0.f)) rc = launch_absmax(x_dev, (int64_t)n_in, b.part, csum, N * H * W, st);
     else rc = launch_zero_u32(reinterpret_cast<uint32_t*>(csum), N * H * W, st);
     if (rc) return rc;
-    rc = launch_quantize_nhwc_sums(x_dev, N, C, H * W, nhwc, s_x, b.amax, q8, csum, b.scale, st);
-    if (rc) return fail_after_reduction(rc, b, st);
+    rc = launch_quantize_nhwc_sums(x_dev, N, C, H * W, nhwc, s_x, input_max(b, (int64_t)n_in), q8, csum, b.scale, st);
+    if (rc) return rc;
     GemmArgs a{};
-    a.e = e; a.T = T; a.T_pad = (int)round_up64(T, TOK_TILE); a.s_x = b.scale; a.zero_after = b.amax;
+    a.e = e; a.T = T; a.T_pad = (int)round_up64(T, TOK_TILE); a.s_x = b.scale;
     a.conv_q8 = q8; a.conv_csum = csum; a.conv_zero = e->conv_zero_dev;
     a.conv_C = C; a.conv_H = H; a.conv_W = W; a.conv_kh = kh; a.conv_kw = kw; a.conv_stride = stride; a.conv_pad = pad;
     a.conv_Ho = Ho; a.conv_Wo = Wo;
@@ -1294,7 +1286,7 @@ static int conv2d_impl(const pipe_expansion* e, const float* x_dev, int N, int C
         if (qx_dev) {
           // the codes in the input's own layout
           if (nhwc) PIPE_HIP(hipMemcpyAsync(qx_dev, q8, n_in, hipMemcpyDeviceToDevice, st));
-          else if ((rc = launch_quantize_elem(x_dev, (int64_t)n_in, s_x, b.amax, qx_dev, nullptr, st)) != PIPE_OK) return fail_after_reduction(rc, b, st);
+          else if ((rc = launch_quantize_elem(x_dev, (int64_t)n_in, s_x, input_max(b, (int64_t)n_in), qx_dev, nullptr, st)) != PIPE_OK) return rc;
         }
         if (s_x_out_dev) PIPE_HIP(hipMemcpyAsync(s_x_out_dev, b.scale, sizeof(float), hipMemcpyDeviceToDevice, st));
         PIPE_HIP(hipMemsetAsync(acc_dev, 0, (size_t)e->K * T * e->out * sizeof(int32_t), st));
@@ -1306,7 +1298,7 @@ static int conv2d_impl(const pipe_expansion* e, const float* x_dev, int N, int C
       fill_members(a, Mm, lo, hi);
     }
     rc = run_gemm(a, false, st);
-    return rc == PIPE_OK ? rc : fail_after_reduction(rc, b, st);
+    return rc;
   }
   const bool small = use_stream_kernel(e, T, export_acc);
   ActBuffers b;
@@ -1319,15 +1311,15 @@ static int conv2d_impl(const pipe_expansion* e, const float* x_dev, int N, int C
     if (!small && (rc = export_acc ? ensure_tables(e, 1, &klo, &khi, 2) : ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   }
   if (!(s_x > 0.f)) {
-    rc = launch_absmax(x_dev, (int64_t)n_in, b.amax, nullptr, 0, st);
+    rc = launch_absmax(x_dev, (int64_t)n_in, b.part, nullptr, 0, st);
     if (rc) return rc;
   }
   rc = launch_quantize_im2col(x_dev, N, C, H, W, kh, kw, stride, pad, nhwc, Ho, Wo, e->in_pad, b.T_pad, s_x,
-                              b.amax, q8, b.qx, b.rowsum, b.scale, st);
+                              input_max(b, (int64_t)n_in), q8, b.qx, b.rowsum, b.scale, st);
   if (rc) return rc;
   GemmArgs a{};
   a.e = e; a.T = T; a.T_pad = b.T_pad; a.qx = b.qx; a.rowsum = b.rowsum;
-  a.s_x = b.scale; a.zero_after = b.amax;
+  a.s_x = b.scale;
   if (export_acc) {
     if (pipe_dry_run()) return PIPE_OK;
     if (qx_dev) PIPE_HIP(hipMemcpyAsync(qx_dev, q8, n_in, hipMemcpyDeviceToDevice, st));
@@ -1341,7 +1333,7 @@ static int conv2d_impl(const pipe_expansion* e, const float* x_dev, int N, int C
     fill_members(a, Mm, lo, hi);
   }
   rc = run_gemm(a, small, st);
-  return rc == PIPE_OK ? rc : fail_after_reduction(rc, b, st);
+  return rc;
 }
 
 extern "C" int pipe_forward_conv2d(const pipe_expansion* e, const float* x_dev, int N, int C, int H,
@@ -1386,17 +1378,16 @@ extern "C" int pipe_forward_depthwise2d(const pipe_expansion* e, const float* x_
   int8_t* q8 = (int8_t*)pipe_ws_get(WS_Q8X, (size_t)n);
   if (!q8) return pipe_ws_error();
   if (!(s_x > 0.f)) {
-    rc = launch_absmax(x_dev, n, b.amax, nullptr, 0, st);
+    rc = launch_absmax(x_dev, n, b.part, nullptr, 0, st);
     if (rc) return rc;
   }
   // the codes of the input, channels last whatever the input's layout
-  if (nhwc) rc = launch_quantize_elem(x_dev, n, s_x, b.amax, q8, b.scale, st);
-  else rc = launch_quantize_to_nhwc(x_dev, N, C, H * W, s_x, b.amax, g_act_qmax_host, q8, b.scale, st);
+  if (nhwc) rc = launch_quantize_elem(x_dev, n, s_x, input_max(b, n), q8, b.scale, st);
+  else rc = launch_quantize_to_nhwc(x_dev, N, C, H * W, s_x, input_max(b, n), g_act_qmax_host, q8, b.scale, st);
   if (rc) return rc;
   rc = launch_depthwise(e, q8, b.scale, N, C, H, W, kh, kw, stride, pad, Ho, Wo, Mm, lo, hi, bias_dev,
                         reduce_members ? 1 : 0, y_dev, st);
-  if (rc) return rc;
-  return launch_zero_u32(b.amax, 1, st);   // no contraction kernel follows to clear the max slot
+  return rc;
 }
 
 // ------------------------------------------------------------------ resident decode launch
@@ -1570,14 +1561,14 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
   // layer 1: every member reads the same Q(x); outputs stay separate
   GemmArgs a{};
   a.e = l1; a.T = T; a.T_pad = T_pad; a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;
-  a.bias = bias1_dev; a.reduce = 0; a.zero_after = b.amax;
+  a.bias = bias1_dev; a.reduce = 0;
   a.zero_big = reinterpret_cast<uint32_t*>(rowsum_h); a.zero_big_n = Mm * T_pad;   // the code sums of Q(h) start at zero
   if (fused) { a.x_f32 = x_dev; a.s_static = s_x; }
   fill_members(a, Mm, lo, hi);
   if (act == PIPE_ACT_GELU) {
     a.act = PIPE_ACT_GELU; a.y = h; a.amax_out = amax_h;
     rc = run_gemm(a, small, st);
-    if (rc) return fail_after_reduction(rc, b, st);
+    if (rc) return rc;
   } else if (paired) {
     a.act = PIPE_ACT_SILU_GATED; a.y = h; a.amax_out = amax_h;
     rc = run_gemm(a, small, st);
@@ -1598,7 +1589,7 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
         rc = launch_quantize_small(h + (size_t)m * T * H, 0, 1, T, H, l2->in_pad, s_h_host[m], nullptr, qh + (size_t)m * T_pad * l2->in_pad, 0,
                                    rowsum_h + (size_t)m * T_pad, nullptr, scale_h + m, st);
       else
-        rc = launch_quantize_act(h + (size_t)m * T * H, T, H, l2->in_pad, T_pad, s_h_host[m], nullptr, qh + (size_t)m * T_pad * l2->in_pad,
+        rc = launch_quantize_act(h + (size_t)m * T * H, T, H, l2->in_pad, T_pad, s_h_host[m], MaxOf{nullptr, 1}, qh + (size_t)m * T_pad * l2->in_pad,
                                  rowsum_h + (size_t)m * T_pad, true, nullptr, scale_h + m, st);
       if (rc) return rc;
     }
@@ -1669,9 +1660,8 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
     if ((rc = ensure_tables(l2, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   }
   if (pipe_dry_run()) return PIPE_OK;
-  // slots as in pipe_chain_forward_asymmetric: the input's range and offset, the members' ranges (positive parts
+  // slots as in pipe_chain_forward_asymmetric: the input's offset, the members' ranges (positive parts
   // [0, 16), negative parts [16, 32)), offsets and scales
-  uint32_t* slots_x = b.amax + 64;
   int32_t* dz_x = reinterpret_cast<int32_t*>(b.amax + 66);
   uint32_t* rng = b.amax + 128;
   int32_t* dz_h = reinterpret_cast<int32_t*>(b.amax + 128 + 4 * PIPE_MAX_K);
@@ -1682,15 +1672,13 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
   }
   t_ws->range_h_dirty = true;
 
-  rc = launch_minmax(x_dev, (int64_t)T * l1->in, slots_x, st);
+  const int64_t n_x = (int64_t)T * l1->in;
+  rc = launch_minmax(x_dev, n_x, b.part, b.part + PIPE_MAX_PARTS, b.rowsum, T_pad, st);
   if (rc) return rc;
-  rc = launch_quantize_asym(x_dev, T, l1->in, l1->in_pad, T_pad, slots_x, slots_x + 1, act_bits, b.qx, b.rowsum, nullptr, b.scale, dz_x, st);
+  rc = launch_quantize_asym(x_dev, T, l1->in, l1->in_pad, T_pad, input_max(b, n_x), input_neg_max(b, n_x), act_bits, b.qx, b.rowsum, true, nullptr, b.scale, dz_x, st);
   if (rc == PIPE_OK)
-    rc = launch_asym_bias_members(bias1_dev, l1->asym_P_dev, b.scale, 0, dz_x, 0, Mm, lo, hi, 0, bias_m, l1->out, slots_x, 2, st);
-  if (rc) {
-    (void)launch_zero_u32(slots_x, 2, st);
-    return rc;
-  }
+    rc = launch_asym_bias_members(bias1_dev, l1->asym_P_dev, b.scale, 0, dz_x, 0, Mm, lo, hi, 0, bias_m, l1->out, nullptr, 0, st);
+  if (rc) return rc;
   // layer 1: every member reads the same codes; its own offset vector; outputs stay separate
   GemmArgs a{};
   a.e = l1; a.T = T; a.T_pad = T_pad; a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;
@@ -1708,8 +1696,8 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
     if (rc) return rc;
   }
   for (int m = 0; m < Mm; ++m) {
-    rc = launch_quantize_asym(h + (size_t)m * T * H, T, H, l2->in_pad, T_pad, rng + m, rng + PIPE_MAX_K + m, act_bits,
-                              qh + (size_t)m * T_pad * l2->in_pad, rowsum_h + (size_t)m * T_pad, nullptr, scale_h + m, dz_h + m, st);
+    rc = launch_quantize_asym(h + (size_t)m * T * H, T, H, l2->in_pad, T_pad, MaxOf{rng + m, 1}, MaxOf{rng + PIPE_MAX_K + m, 1}, act_bits,
+                              qh + (size_t)m * T_pad * l2->in_pad, rowsum_h + (size_t)m * T_pad, false, nullptr, scale_h + m, dz_h + m, st);
     if (rc) return rc;
   }
   rc = launch_asym_bias_members(bias2_dev, l2->asym_P_dev, scale_h, 1, dz_h, 1, Mm, lo, hi, 1, bias_m, l2->out, nullptr, 0, st);
@@ -1913,16 +1901,16 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
       // every member reads the same Q(x)
       if (conv) {
         if (!(s_x > 0.f)) {
-          rc = launch_absmax(x_dev, Tin[0] * Cin[0], b.amax, nullptr, 0, st);
+          rc = launch_absmax(x_dev, Tin[0] * Cin[0], b.part, nullptr, 0, st);
           if (rc) return rc;
         }
         rc = launch_quantize_im2col(x_dev, N, Cin[0], Hin[0], Win[0], ly.kh, ly.kw, ly.stride, ly.pad, 1, Hin[1], Win[1],
-                                    e->in_pad, T_pad, s_x, b.amax, q8, b.qx, b.rowsum, b.scale, st);
+                                    e->in_pad, T_pad, s_x, input_max(b, Tin[0] * Cin[0]), q8, b.qx, b.rowsum, b.scale, st);
       } else {
         rc = quantize_input(x_dev, T, e->in, e->in_pad, s_x, b, small[0], nullptr, b.scale, st);
       }
       if (rc) return rc;
-      a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale; a.zero_after = b.amax;
+      a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;
     } else {
       // each member quantizes its own tensor with its own scale
       const float* src = act[l - 1];
@@ -1934,7 +1922,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
       if (conv) {
         for (int m = 0; m < Mm; ++m) {
           rc = launch_quantize_im2col(src + (size_t)m * Tin[l] * Cin[l], N, Cin[l], Hin[l], Win[l], ly.kh, ly.kw, ly.stride,
-                                      ly.pad, 1, Hin[l + 1], Win[l + 1], e->in_pad, T_pad, s_given ? s_given[m] : 0.f, amax_in + m, q8,
+                                      ly.pad, 1, Hin[l + 1], Win[l + 1], e->in_pad, T_pad, s_given ? s_given[m] : 0.f, MaxOf{amax_in + m, 1}, q8,
                                       qh + (size_t)m * q_ms, rs_in + (size_t)m * T_pad_max, scale_h + m, st);
           if (rc) return rc;
         }
@@ -1945,7 +1933,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
             rc = launch_quantize_small(src + (size_t)m * T * in, 0, 1, T, in, e->in_pad, s_given[m], nullptr, qh + (size_t)m * q_ms, 0,
                                        rs_in + (size_t)m * T_pad_max, nullptr, scale_h + m, st);
           else
-            rc = launch_quantize_act(src + (size_t)m * T * in, T, in, e->in_pad, T_pad, s_given[m], nullptr, qh + (size_t)m * q_ms,
+            rc = launch_quantize_act(src + (size_t)m * T * in, T, in, e->in_pad, T_pad, s_given[m], MaxOf{nullptr, 1}, qh + (size_t)m * q_ms,
                                      rs_in + (size_t)m * T_pad_max, true, nullptr, scale_h + m, st);
           if (rc) return rc;
         }
@@ -1957,7 +1945,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
         if (rc) return rc;
       } else {
         for (int m = 0; m < Mm; ++m) {
-          rc = launch_quantize_act(src + (size_t)m * T * in, T, in, e->in_pad, T_pad, 0.f, amax_in + m, qh + (size_t)m * q_ms,
+          rc = launch_quantize_act(src + (size_t)m * T * in, T, in, e->in_pad, T_pad, 0.f, MaxOf{amax_in + m, 1}, qh + (size_t)m * q_ms,
                                    rs_in + (size_t)m * T_pad_max, true, nullptr, scale_h + m, st);
           if (rc) return rc;
         }
@@ -2090,10 +2078,9 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
   for (int l = 0; l < L; ++l)
     if (!small[l] && (rc = ensure_tables(layers[l].e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   if (pipe_dry_run()) return PIPE_OK;
-  // the input's range slots and zero-point offset, then per member and set the hidden tensors' ranges
+  // the input's zero-point offset, then per member and set the hidden tensors' ranges
   // (positive parts [0, 16), negative parts [16, 32) of a set; layer l's epilogue raises set l & 1, the
   // quantizers of layer l+1 read it and layer l+1's contraction clears it), offsets and scales
-  uint32_t* slots_x = b.amax + 64;
   int32_t* dz_x = reinterpret_cast<int32_t*>(b.amax + 66);
   uint32_t* rng[2] = {b.amax + 128, b.amax + 128 + 2 * PIPE_MAX_K};
   int32_t* dz_h = reinterpret_cast<int32_t*>(b.amax + 128 + 4 * PIPE_MAX_K);
@@ -2112,21 +2099,19 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
     GemmArgs a{};
     a.e = e; a.T = T; a.T_pad = T_pad;
     if (l == 0) {
-      rc = launch_minmax(x_dev, Tin[0] * Cin[0], slots_x, st);
+      const int64_t n_x = Tin[0] * Cin[0];
+      rc = launch_minmax(x_dev, n_x, b.part, b.part + PIPE_MAX_PARTS, b.rowsum, T_pad, st);
       if (rc) return rc;
       if (conv)
         rc = launch_quantize_im2col_asym(x_dev, N, Cin[0], Hin[0], Win[0], ly.kh, ly.kw, ly.stride, ly.pad, 1, Hin[1], Win[1], e->in_pad,
-                                         T_pad, slots_x, slots_x + 1, act_bits, q8, b.qx, b.rowsum, b.scale, dz_x, st);
+                                         T_pad, input_max(b, n_x), input_neg_max(b, n_x), act_bits, q8, b.qx, b.rowsum, b.scale, dz_x, st);
       else
-        rc = launch_quantize_asym(x_dev, T, e->in, e->in_pad, T_pad, slots_x, slots_x + 1, act_bits, b.qx, b.rowsum, nullptr,
-                                  b.scale, dz_x, st);
+        rc = launch_quantize_asym(x_dev, T, e->in, e->in_pad, T_pad, input_max(b, n_x), input_neg_max(b, n_x), act_bits, b.qx, b.rowsum, true,
+                                  nullptr, b.scale, dz_x, st);
       if (rc == PIPE_OK)
         rc = launch_asym_bias_members(ly.bias_dev, e->asym_P_dev, b.scale, 0, dz_x, 0, Mm, lo, hi, last_layer ? 1 : 0, bias_m,
-                                      e->out, slots_x, 2, st);
-      if (rc) {
-        (void)launch_zero_u32(slots_x, 2, st);   // the raised range slots: the kernel that clears them did not run
-        return rc;
-      }
+                                      e->out, nullptr, 0, st);
+      if (rc) return rc;
       a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;
       a.zero_after = nullptr; a.zero_n = 0;
     } else {
@@ -2137,11 +2122,11 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
         const float* src_m = src + (size_t)m * Tin[l] * Cin[l];
         if (conv)
           rc = launch_quantize_im2col_asym(src_m, N, Cin[l], Hin[l], Win[l], ly.kh, ly.kw, ly.stride, ly.pad, 1, Hin[l + 1], Win[l + 1],
-                                           e->in_pad, T_pad, r_in + m, r_in + PIPE_MAX_K + m, act_bits, q8, qh + (size_t)m * q_ms,
+                                           e->in_pad, T_pad, MaxOf{r_in + m, 1}, MaxOf{r_in + PIPE_MAX_K + m, 1}, act_bits, q8, qh + (size_t)m * q_ms,
                                            rowsum_h + (size_t)m * T_pad_max, scale_h + m, dz_h + m, st);
         else
-          rc = launch_quantize_asym(src_m, T, e->in, e->in_pad, T_pad, r_in + m, r_in + PIPE_MAX_K + m, act_bits,
-                                    qh + (size_t)m * q_ms, rowsum_h + (size_t)m * T_pad_max, nullptr, scale_h + m, dz_h + m, st);
+          rc = launch_quantize_asym(src_m, T, e->in, e->in_pad, T_pad, MaxOf{r_in + m, 1}, MaxOf{r_in + PIPE_MAX_K + m, 1}, act_bits,
+                                    qh + (size_t)m * q_ms, rowsum_h + (size_t)m * T_pad_max, false, nullptr, scale_h + m, dz_h + m, st);
         if (rc) return rc;
       }
       rc = launch_asym_bias_members(ly.bias_dev, e->asym_P_dev, scale_h, 1, dz_h, 1, Mm, lo, hi, last_layer ? 1 : 0, bias_m, e->out,

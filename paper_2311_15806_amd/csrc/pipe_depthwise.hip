@@ -28,10 +28,20 @@ __global__ void dense_order_kernel(const int8_t* __restrict__ rows_codes, const 
 // fp32 [N,C,H,W] -> int8 codes [N,H,W,C]: 32 channels x 32 pixels per workgroup through LDS, so
 // that reads run along the pixels and writes along the channels
 __global__ __launch_bounds__(256) void quantize_to_nhwc_kernel(const float* __restrict__ x, int C, int HW, float s_static,
-                                                               const uint32_t* __restrict__ amax_bits, float qmax,
+                                                               MaxOf amax, float qmax,
                                                                int8_t* __restrict__ q8, float* __restrict__ scale_out) {
   __shared__ int8_t tile[32][33];
-  const float s = s_static > 0.f ? s_static : __fdiv_rn(__uint_as_float(*amax_bits), qmax);
+  __shared__ float smax[4];
+  float s = s_static;
+  if (!(s_static > 0.f)) {
+    float m = 0.f;
+    for (int i = threadIdx.x; i < amax.n; i += 256) m = fmaxf(m, __uint_as_float(amax.p[i]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = m;
+    __syncthreads();
+    s = __fdiv_rn(fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3])), qmax);
+  }
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && scale_out) *scale_out = s;
   const int n = blockIdx.z, c0 = blockIdx.y * 32, p0 = blockIdx.x * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
@@ -159,10 +169,10 @@ int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st) {
   return PIPE_OK;
 }
 
-int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static, const uint32_t* amax_bits, float qmax,
+int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static, MaxOf amax, float qmax,
                             int8_t* q8, float* scale_out, hipStream_t st) {
   PIPE_KLAUNCH(quantize_to_nhwc_kernel, dim3(ceil_div(HW, 32), ceil_div(C, 32), N), dim3(256), 0, st, x, C, HW, s_static,
-                     amax_bits, qmax, q8, scale_out);
+                     amax, qmax, q8, scale_out);
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
 }

@@ -221,6 +221,15 @@ bool pipe_capturing();
   } while (0)
 enum { WS_QX = 0, WS_ROWSUM, WS_SCAL, WS_Y1, WS_H, WS_QH, WS_ROWSUM_H, WS_RESID, WS_ENERGY, WS_MISC, WS_Q8X, WS_CHAIN, WS_DIAG, WS_DIAG_CODES, WS_DIAG_DENSE, WS_RES, WS_RES_Q, WS_CSUM, WS_ABIAS, WS_SLOTS };
 
+// A maximum as the bit patterns of its parts (device): one word for a slot that a contraction kernel's epilogue raised,
+// max_parts(n) for the reduction of an n-element input.
+struct MaxOf {
+  const uint32_t* p;
+  int n;
+};
+constexpr int PIPE_MAX_PARTS = 512;
+int max_parts(int64_t n);
+
 // ------------------------------------------------------------------ expand kernels (pipe_expand.hip)
 int launch_row_energy(const float* E, int out, int in, double* row_energy, hipStream_t st);
 int launch_group_select(const double* row_energy, int n_groups, int group, int n_keep,
@@ -228,7 +237,7 @@ int launch_group_select(const double* row_energy, int n_groups, int group, int n
 // W [out, C*kh*kw] with rows flattened [C, kh, kw] -> rows flattened [kh, kw, C] (tap-major)
 int launch_permute_conv_weight(const float* W, int out, int C, int taps, float* W_out, hipStream_t st);
 // channels-last int8 codes of a convolution input and the per-pixel sums of their channels (zero on entry)
-int launch_quantize_nhwc_sums(const float* x, int N, int C, int HW, int nhwc, float s_static, const uint32_t* amax_bits,
+int launch_quantize_nhwc_sums(const float* x, int N, int C, int HW, int nhwc, float s_static, MaxOf amax,
                               int8_t* q8, int32_t* csum, float* scale_out, hipStream_t st);
 int launch_fold_batchnorm(const float* W, const float* b, const float* gamma, const float* beta, const float* mean,
                           const float* var, float eps, int out, int in, float* W_out, float* b_out, hipStream_t st);
@@ -252,20 +261,20 @@ int launch_gather_row_blocks(const uint8_t* codes_k, const float* scales_k, cons
                              int64_t rb_bytes, uint8_t* codes_all, float* scales_all, hipStream_t st);
 
 // ------------------------------------------------------------------ activation kernels (pipe_quant.hip)
-// amax_bits: device uint32 holding the bit pattern of max|x| (must be zeroed first).
 int launch_zero_u32(uint32_t* p, int n, hipStream_t st);
 // asymmetric activation codes: range slots {max(x,0), max(-x,0)}; unsigned a-bit codes stored minus 2^(a-1) in the
 // fragment layout with their token sums, scale and 2^(a-1) - z to device memory; the token-free correction as a bias
-int launch_minmax(const float* x, int64_t n, uint32_t* slots, hipStream_t st);
-int launch_quantize_asym(const float* x, int T, int in, int in_pad, int T_pad, const uint32_t* hi_slot, const uint32_t* nlo_slot, int act_bits,
-                         uint8_t* qx_frag, int32_t* rowsum, uint8_t* qx_rowmajor, float* scale_out, int32_t* dz_out,
-                         hipStream_t st);
+int launch_minmax(const float* x, int64_t n, uint32_t* hi_part, uint32_t* nlo_part, int32_t* zero_me, int n_zero, hipStream_t st);
+int launch_quantize_asym(const float* x, int T, int in, int in_pad, int T_pad, MaxOf hi_max, MaxOf nlo_max, int act_bits,
+                         uint8_t* qx_frag, int32_t* rowsum, bool rowsum_is_zero, uint8_t* qx_rowmajor, float* scale_out,
+                         int32_t* dz_out, hipStream_t st, const float* bias = nullptr, const float* C = nullptr,
+                         float* bias_eff = nullptr, int n_out = 0);
 int launch_quantize_im2col_asym(const float* x, int N, int C, int H, int W, int kh, int kw, int stride, int pad, int nhwc,
-                                int Ho, int Wo, int in_pad, int T_pad, const uint32_t* hi_slot, const uint32_t* nlo_slot,
+                                int Ho, int Wo, int in_pad, int T_pad, MaxOf hi_max, MaxOf nlo_max,
                                 int act_bits, int8_t* q8_scratch, uint8_t* qx_frag, int32_t* rowsum, float* scale_out,
                                 int32_t* dz_out, hipStream_t st);
 int launch_asym_bias(const float* bias, const float* C, const float* scale, const int32_t* dz, float* out, int n,
-                     uint32_t* slots, hipStream_t st);
+                     hipStream_t st);
 int launch_asym_acc_fix(int32_t* acc, const int32_t* wsum, const int32_t* dz, int K, int T, int out, hipStream_t st);
 // member chains with asymmetric codes: per-member offset vectors [M][n] (reduce = 0; the bias joins member 0) or their
 // sum plus the bias [n] (reduce = 1) from P[k][o] = s_k[o] * sum_i q_k[o,i]; clears n_clear words at `clear`
@@ -278,12 +287,12 @@ int launch_asym_bias_members(const float* bias, const float* P, const float* sca
                              int n_clear, hipStream_t st);
 int launch_row_code_sums(const int8_t* codes, int rows, int in, int group, const int32_t* gids, int32_t* wsum, hipStream_t st);
 // launch_absmax also zeroes n_zero ints at zero_me (the code sums of the quantizer that follows).
-int launch_absmax(const float* x, int64_t n, uint32_t* amax_bits, int32_t* zero_me, int n_zero, hipStream_t st);
+int launch_absmax(const float* x, int64_t n, uint32_t* part, int32_t* zero_me, int n_zero, hipStream_t st);
 // Quantize x [T, in] into the fragment layout (padded region written as zero), row sums and
-// optionally row-major int8.  scale: if s_static > 0 use it, else amax/127 from amax_bits.
+// optionally row-major int8.  scale: if s_static > 0 use it, else amax/127.
 // Writes the scale used to *scale_out (device).
 int launch_quantize_act(const float* x, int T, int in, int in_pad, int T_pad, float s_static,
-                        const uint32_t* amax_bits, uint8_t* qx_frag, int32_t* rowsum, bool rowsum_is_zero,
+                        MaxOf amax, uint8_t* qx_frag, int32_t* rowsum, bool rowsum_is_zero,
                         int8_t* qx_rowmajor, float* scale_out, hipStream_t st);
 // Decode-sized batches (T <= 16, T_pad == 16): max|x|, scale, codes and code sums in ONE launch,
 // one workgroup per member (x, qx_frag, rowsum [16 per member], scale_out [M] with member strides).
@@ -294,7 +303,7 @@ int launch_quantize_members(const float* x, int64_t x_mstride, int M, int T, int
                             bool rowsum_is_zero, float* scale_out, hipStream_t st);
 int set_act_qmax(float qmax);   // largest activation code of all quantizers from now on (synchronous copy to the device)
 // every element quantized once, in the input's own layout (scale from s_static or the max slot)
-int launch_quantize_elem(const float* x, int64_t n, float s_static, const uint32_t* amax_bits, int8_t* q8,
+int launch_quantize_elem(const float* x, int64_t n, float s_static, MaxOf amax, int8_t* q8,
                          float* scale_out, hipStream_t st);
 int launch_quantize_small(const float* x, int64_t x_mstride, int M, int T, int in, int in_pad, float s_static,
                           const uint32_t* amax_bits, uint8_t* qx_frag, int64_t qx_mstride, int32_t* rowsum,
@@ -302,7 +311,7 @@ int launch_quantize_small(const float* x, int64_t x_mstride, int M, int T, int i
 // Same for the virtual im2col matrix of a convolution.
 int launch_quantize_im2col(const float* x, int N, int C, int H, int W, int kh, int kw, int stride,
                            int pad, int nhwc, int Ho, int Wo, int in_pad, int T_pad,
-                           float s_static, const uint32_t* amax_bits, int8_t* q8_scratch, uint8_t* qx_frag,
+                           float s_static, MaxOf amax, int8_t* q8_scratch, uint8_t* qx_frag,
                            int32_t* rowsum, float* scale_out, hipStream_t st);
 // Hidden activation of the MLP call: h = act(y1) element-wise, plus per-member max|h| (or, with amax_neg, the
 // positive and negative parts of its range apart).
@@ -370,7 +379,7 @@ const TileBins* pipe_get_bins(const pipe_expansion* e, const GemmArgs& a, int* r
 int launch_gemm_bins(const GemmArgs& a, hipStream_t st);
 // depthwise layers: dense per-order codes and scales (built once), then the forward kernel
 int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st);
-int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static, const uint32_t* amax_bits, float qmax,
+int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static, MaxOf amax, float qmax,
                             int8_t* q8, float* scale_out, hipStream_t st);   // fp32 [N,C,H,W] -> int8 codes [N,H,W,C]
 int launch_depthwise(const pipe_expansion* e, const int8_t* q8, const float* s_x, int N, int C, int H, int W, int kh, int kw,
                      int stride, int pad, int Ho, int Wo, int M, const int* lo, const int* hi,
