@@ -220,6 +220,7 @@ static void free_expansion(pipe_expansion* e) {
   if (e->conv_zero_dev) (void)hipFree(e->conv_zero_dev);
   if (e->dw_codes_dev) (void)hipFree(e->dw_codes_dev);
   if (e->dw_scales_dev) (void)hipFree(e->dw_scales_dev);
+  if (e->dw_cols_dev) (void)hipFree(e->dw_cols_dev);
   if (e->bins_dev) (void)hipFree(e->bins_dev);
   if (e->codes_dev) (void)hipFree(e->codes_dev);
   if (e->scales_all_dev) (void)hipFree(e->scales_all_dev);
@@ -1375,12 +1376,18 @@ extern "C" int pipe_forward_depthwise2d(const pipe_expansion* e, const float* x_
   rc = get_act_buffers(16, IN_PAD, true, &b);   // only the scale and max slots are used
   if (rc) return rc;
   const int64_t n = (int64_t)N * C * H * W;
-  int8_t* q8 = (int8_t*)pipe_ws_get(WS_Q8X, (size_t)n);
-  if (!q8) return pipe_ws_error();
+  // (the fused kernel reads x while others already write y: an output that overlaps the input keeps the two-step path)
+  const uintptr_t x0 = reinterpret_cast<uintptr_t>(x_dev), y0 = reinterpret_cast<uintptr_t>(y_dev);
+  const bool fused = pipe_depthwise_fused(e, kh, kw, stride, Mm, N, Ho, Wo) &&
+                     (x0 + (size_t)n * sizeof(float) <= y0 || y0 + (size_t)N * Ho * Wo * C * sizeof(float) <= x0);
+  int8_t* q8 = fused ? nullptr : (int8_t*)pipe_ws_get(WS_Q8X, (size_t)n);
+  if (!fused && !q8) return pipe_ws_error();
   if (!(s_x > 0.f)) {
     rc = launch_absmax(x_dev, n, b.part, nullptr, 0, st);
     if (rc) return rc;
   }
+  if (fused)
+    return launch_depthwise_fused(e, x_dev, s_x, input_max(b, n), g_act_qmax_host, N, C, H, W, stride, pad, nhwc, Ho, Wo, bias_dev, y_dev, st);
   // the codes of the input, channels last whatever the input's layout
   if (nhwc) rc = launch_quantize_elem(x_dev, n, s_x, input_max(b, n), q8, b.scale, st);
   else rc = launch_quantize_to_nhwc(x_dev, N, C, H * W, s_x, input_max(b, n), g_act_qmax_host, q8, b.scale, st);

@@ -146,6 +146,7 @@ struct pipe_expansion {
   // (in = kh*kw), built on first use of pipe_forward_depthwise2d
   int8_t* dw_codes_dev = nullptr;
   float* dw_scales_dev = nullptr;
+  uint32_t* dw_cols_dev = nullptr;   // 3 x 3: [K][3][C], the vertical taps of a window column packed in a dword
   // Stored row blocks of all orders in schedule order, bin after bin of the weight-streaming kernel, which
   // addresses its codes from its block index alone: bins of 4 lie without gaps, fullest first (a bin's first
   // position follows from bin_thr), wider bins own positions [b*bin_cap, (b+1)*bin_cap) with zeros in the unused
@@ -384,6 +385,10 @@ int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static
 int launch_depthwise(const pipe_expansion* e, const int8_t* q8, const float* s_x, int N, int C, int H, int W, int kh, int kw,
                      int stride, int pad, int Ho, int Wo, int M, const int* lo, const int* hi,
                      const float* bias, int reduce, float* y, hipStream_t st);   // q8 channels last
+// 3 x 3, stride 1 or 2, one member of at most 4 orders: quantizer and layer in one launch, from the fp32 input
+bool pipe_depthwise_fused(const pipe_expansion* e, int kh, int kw, int stride, int M, int N, int Ho, int Wo);
+int launch_depthwise_fused(const pipe_expansion* e, const float* x, float s_static, MaxOf amax, float qmax, int N, int C, int H, int W,
+                           int stride, int pad, int nhwc, int Ho, int Wo, const float* bias, float* y, hipStream_t st);
 extern float g_act_qmax_host;   // the activation quantizer's largest code (host copy of the device constant)
 int launch_gemm_stream(const GemmArgs& a, hipStream_t st);
 // ---- resident decode kernel (pipe_resident.hip)

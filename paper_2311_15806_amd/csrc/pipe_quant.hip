@@ -4,31 +4,18 @@
 //
 // Q(x) = clamp(rint(x / s_x), -127, 127) with an IEEE fp32 division and round-half-to-even;
 // this file is compiled with floating-point contraction off.
-#include "pipe_internal.h"
+#include "pipe_codes.h"
 
 #include <algorithm>
 #include <type_traits>
 
 namespace {
 
-constexpr int BLK = 256;
+constexpr int BLK = CODES_BLK;
 
 __global__ void zero_u32_kernel(uint32_t* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
-}
-
-__device__ __forceinline__ float block_max(float v) {
-  __shared__ float sm[BLK / 64];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = sm[0];
-#pragma unroll
-  for (int i = 1; i < BLK / 64; ++i) r = fmaxf(r, sm[i]);
-  __syncthreads();
-  return r;
 }
 
 // max|x| over n elements, one value per workgroup (the quantizer that follows takes the maximum of them: a slot that all
@@ -70,40 +57,10 @@ __global__ __launch_bounds__(BLK) void absmax_kernel(const float* __restrict__ x
 // still travel as bytes).  Set by pipe_set_activation_bits through set_act_qmax below.
 __constant__ float c_act_qmax = 127.f;
 
-// The value of a max reduction: the largest of its parts.  Called by all threads of a workgroup.
-__device__ __forceinline__ float max_of(const MaxOf& a) {
-  if (a.n == 1) return __uint_as_float(a.p[0]);
-  float m = 0.f;
-  for (int i = threadIdx.x; i < a.n; i += BLK) m = fmaxf(m, __uint_as_float(a.p[i]));
-  return block_max(m);
-}
-
 __device__ __forceinline__ float act_scale(float s_static, const MaxOf& amax) {
   if (s_static > 0.f) return s_static;
   return __fdiv_rn(max_of(amax), c_act_qmax);
 }
-
-// Correctly rounded quotients by one divisor.  The compiler's IEEE division is about 11 instructions per element; with
-// y = RN(1/s) at hand, Markstein's two corrections q' = RN(q + RN(v - s q) y) of a first guess give RN(v/s) in five (P.
-// Markstein, "Computation of elementary functions on the IBM RISC System/6000 processor", 1990: exact remainder, and a
-// correctly rounded result from a faithful q).  The remainder is exact while nothing underflows, hence the range of
-// s (quotients below 1/4 in magnitude may be inexact: they round to code 0 either way).  v is bounded by 1024 s first, far
-// beyond the largest code, so that no quotient or remainder is infinite; NaN becomes the lower bound, and thus the smallest
-// code, which is what the clamp of the codes makes of a NaN quotient.
-struct Divisor {
-  float s, y, bound;
-  bool fast;
-  __device__ __forceinline__ explicit Divisor(float s_)
-      : s(s_), y(__fdiv_rn(1.f, s_)), bound(1024.f * s_), fast(s_ > 1e-27f && s_ < 1e27f) {}
-  template <bool FAST>
-  __device__ __forceinline__ float quotient(float v) const {
-    if (!FAST) return __fdiv_rn(v, s);
-    v = __builtin_amdgcn_fmed3f(v, -bound, bound);
-    float q = __fmul_rn(v, y);
-    q = __fmaf_rn(__fmaf_rn(-q, s, v), y, q);
-    return __fmaf_rn(__fmaf_rn(-q, s, v), y, q);
-  }
-};
 
 // Q(x), symmetric: code = clamp(rint(x / s), -qmax, qmax)
 struct SymCodes {
@@ -128,11 +85,6 @@ __device__ __forceinline__ int quant1(float v, float s) {
   float q = rintf(__fdiv_rn(v, s));
   q = fminf(fmaxf(q, -c_act_qmax), c_act_qmax);
   return (int)q;
-}
-
-__device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
-  return (uint32_t)(uint8_t)a | ((uint32_t)(uint8_t)b << 8) | ((uint32_t)(uint8_t)c << 16) |
-         ((uint32_t)(uint8_t)d << 24);
 }
 
 // One block: token block blockIdx.x (16 tokens), a range of 16-wide k-chunks given by

@@ -76,3 +76,32 @@ def test_gated_batch_equals_its_parts(pipe, H, I, bits, K, gamma, split, T):
     yr = torch.cat([p[0] for p in parts], dim=0)
     assert (y - yr).abs().max() <= 1e-5 * yr.abs().max() + 0.02 * float(pipe.pipe_expansion_reconstruct(l2).abs().max())
     l1.free(), l2.free()
+
+
+#            N  C    H   W   stride pad bits K
+DEPTHWISE = [(2, 16, 1, 1, 1, 1, 8, 1), (3, 80, 7, 7, 1, 1, 4, 2), (1, 64, 13, 36, 1, 0, 2, 4), (2, 144, 28, 28, 2, 1, 4, 3),
+             (1, 32, 9, 70, 2, 2, 3, 4), (1, 208, 6, 33, 1, 2, 4, 3)]
+
+
+@pytest.mark.parametrize("N,C,H,W,stride,pad,bits,K", DEPTHWISE)
+def test_fused_depthwise_at_its_tile_edges(pipe, N, C, H, W, stride, pad, bits, K):
+    """Partial channel groups, row bands and column tiles, windows wholly in the padding, all three ways the input is read."""
+    from oracle import pipe_oracle as po
+    rng = np.random.default_rng(C + W)
+    Wt = rng.standard_normal((C, 9)).astype(np.float32)
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    b = rng.standard_normal(C).astype(np.float32)
+    e = pipe.pipe_expand(dev(Wt), bits, K, 0.5, 16)
+    ora = po.expand(Wt, bits, K, 0.5, 16)
+    for s_x in (0.0, 0.02):
+        ref = po.forward_depthwise2d(ora, x, 3, 3, stride, pad, s_x=s_x if s_x > 0 else None, bias=b)["y"]
+        y = pipe.pipe_forward_depthwise2d(e, dev(x), 3, 3, stride, pad, s_x=s_x, bias=dev(b))
+        # exact integer sums, at most K + 1 rounded fp32 operations of terms no larger than the layer's largest output
+        assert np.abs(y.cpu().numpy() - ref).max() <= (K + 1) * 1.2e-7 * 4 * np.abs(ref).max()
+        yl = pipe.pipe_forward_depthwise2d(e, dev(x.transpose(0, 2, 3, 1)), 3, 3, stride, pad, nhwc=True, s_x=s_x, bias=dev(b))
+        assert torch.equal(y, yl)
+        buf = torch.empty(x.size + 1, dtype=torch.float32, device="cuda")   # not 16-byte aligned: element by element
+        xs = buf[1:].view(N, C, H, W)
+        xs.copy_(dev(x))
+        assert torch.equal(y, pipe.pipe_forward_depthwise2d(e, xs, 3, 3, stride, pad, s_x=s_x, bias=dev(b)))
+    e.free()
