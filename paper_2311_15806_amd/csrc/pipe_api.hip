@@ -838,7 +838,7 @@ extern "C" int pipe_timing_read(double* total_ms, int* launches) {
 
 // Activation quantization of a [T, in] input into the buffers of `b`; small batches take the
 // single-launch path.
-// A single token: the streaming kernel quantizes it itself, one launch instead of two
+// Few tokens: the streaming kernel quantizes them itself, one launch instead of two
 // (the kernel reads x while other workgroups already write results, so an output buffer that
 // overlaps x -- legal on the two-launch path, whose quantizer has consumed x by then -- keeps that path)
 static bool fuse_decode_quant(const pipe_expansion* e, int T, const float* x_dev, bool small,
@@ -846,7 +846,7 @@ static bool fuse_decode_quant(const pipe_expansion* e, int T, const float* x_dev
   const uintptr_t x0 = reinterpret_cast<uintptr_t>(x_dev), x1 = x0 + (size_t)T * e->in * sizeof(float);
   const uintptr_t o0 = reinterpret_cast<uintptr_t>(out_dev), o1 = o0 + out_floats * sizeof(float);
   const bool apart = x1 <= o0 || o1 <= x0;
-  return small && g_decode_fusion && T <= PIPE_FUSED_QUANT_MAX_T && e->in_pad <= PIPE_FUSED_QUANT_MAX_IN &&
+  return small && g_decode_fusion && T <= 16 && T * e->in_pad <= (T == 1 ? PIPE_FUSED_QUANT_MAX_1 : PIPE_FUSED_QUANT_MAX) &&
          e->in % 4 == 0 && (x0 & 15) == 0 && e->bin_cap == 4 && apart;
 }
 

@@ -56,7 +56,7 @@ struct StreamParams {
   int n_bins;
   int thr0, thr1, thr2;    // bins of 4, fullest first: how many hold 4, at least 3, at least 2 items
   int zero_pos;            // an all-zero position (codes and scales): read for the items a bin does not have
-  const float* x_f32;      // QFUSE: the fp32 input [T, in] (T <= 4), quantized by every workgroup itself
+  const float* x_f32;      // QFUSE: the fp32 input [T, in], quantized by every workgroup itself
   float s_static;          // QFUSE: given activation scale, or <= 0 for max|x| / act_qmax
   float act_qmax;          // QFUSE: largest activation code
   int in;                  // QFUSE: in_features (multiple of 4)
@@ -97,15 +97,15 @@ __device__ __forceinline__ void unpack_step(const uint4& w, int j, v4i& o) {
 // orders), or 2 / 4 (one input per ensemble member, at most XM members).
 // XMASK: the batch does not fill its last 16-token block; the activation loads of that block are
 // issued for the lanes of real tokens only.
-// QFUSE (a single token, one activation tensor): there is no quantizer launch; every
+// QFUSE (few tokens of few features, one activation tensor): there is no quantizer launch; every
 // workgroup reduces max|x| over the few-KiB input itself, quantizes it into LDS with the same
 // arithmetic as the quantizer kernels (IEEE division, round half to even) while its first codes are
 // on their way, and builds its activation fragments from there.
-constexpr int QF_T = 1, QF_IN = 8192;
+constexpr int QF_T = 16, QF_IN = 8192;   // tokens; codes of all tokens
 template <int BITS, int NW, int XM, bool ACC_OUT, bool XMASK, bool QFUSE = false>
 __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)) <= 4) ? 4 : 2) void gemm_stream_kernel(const StreamParams p) {
   static_assert(!QFUSE || (XM == 1 && !ACC_OUT), "the fused quantizer serves one shared input");
-  __shared__ __attribute__((aligned(16))) uint8_t s_qx[QFUSE ? QF_T * QF_IN : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t s_qx[QFUSE ? QF_IN : 16];
   __shared__ float s_red[NW];
   __shared__ int s_rs[QF_T];
   constexpr int OFF = BITS == 8 ? 0 : (BITS == 4 ? 8 : 1);
@@ -117,6 +117,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   __shared__ int part[NW][R][256];   // each wave's partial tiles
   __shared__ int s_last;
 
+  if (QFUSE) request_arguments<sizeof(StreamParams)>();
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_tiles = (p.nks * 64) / KSUP;
@@ -247,8 +248,14 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       const int a = q1(v.x), b = q1(v.y), c = q1(v.z), d = q1(v.w);
       *reinterpret_cast<uint32_t*>(&s_qx[(size_t)tq * in_pad_q + k]) =
           (uint32_t)(uint8_t)a | ((uint32_t)(uint8_t)b << 8) | ((uint32_t)(uint8_t)c << 16) | ((uint32_t)(uint8_t)d << 24);
-      const int sum4 = a + b + c + d;
-      if (sum4 != 0) atomicAdd(&s_rs[tq], sum4);
+      int sum4 = a + b + c + d;
+      if (in % 256 == 0) {   // a wave's 64 quads lie in one row
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum4 += __shfl_xor(sum4, o, 64);
+        if (lane == 0) atomicAdd(&s_rs[tq], sum4);
+      } else if (sum4 != 0) {
+        atomicAdd(&s_rs[tq], sum4);
+      }
     }
     // codes beyond in_features are zero
     const int pad4 = (in_pad_q - in) >> 2;
@@ -667,7 +674,7 @@ int launch_nw(const StreamParams& p, int n_bins, int xm, bool acc_out, const Gem
   const dim3 grid((unsigned)((n_bins + 7) / 8 * 8 * p.ksplit * p.n_tb)), blk(NW * 64);
   if (p.x_f32 != nullptr) {
     // no quantizer launch: the contraction quantizes its few tokens itself
-    if (xm != 1 || acc_out || p.T > QF_T || p.nks * 64 > QF_IN || p.in % 4 != 0 || p.n_tb != 1) return PIPE_EINVAL;
+    if (xm != 1 || acc_out || p.T > QF_T || p.T * p.nks * 64 > QF_IN || p.in % 4 != 0 || p.n_tb != 1) return PIPE_EINVAL;
     PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true>), grid, blk, st, a.ev_start, a.ev_stop, p);
     PIPE_HIP(hipGetLastError());
     return PIPE_OK;

@@ -43,8 +43,10 @@ static inline int64_t round_up64(int64_t a, int64_t b) { return (a + b - 1) / b 
 // in ascending order k).
 constexpr int STREAM_BIN_CAP = 16;
 constexpr int PIPE_STREAM_MAX_T = 128;   // the weight-streaming kernel serves up to this many tokens
-constexpr int PIPE_FUSED_QUANT_MAX_T = 1;     // the streaming kernel quantizes a single token itself (no quantizer launch); every workgroup repeats the work, which costs more than the launch it saves from 2 tokens on
-constexpr int PIPE_FUSED_QUANT_MAX_IN = 8192; // ... for layers of at most this many (padded) input features
+// The streaming kernel quantizes small batches itself (one launch instead of two): every workgroup repeats the work, which
+// pays up to 4096 codes (16 tokens of 256 features 12.8 -> 10.4 us a call; 2 tokens of 4096: 14.8 us against 14.6) and
+// for a single token up to 8192.
+constexpr int PIPE_FUSED_QUANT_MAX = 4096, PIPE_FUSED_QUANT_MAX_1 = 8192;
 constexpr int PIPE_QUANT1_MAX_T = 64;    // the one-launch quantizer (every token's workgroup scans the whole input for the maximum) up to this many
 constexpr int PIPE_MAX_SPLIT = 8;   // workgroups per bin of the weight-streaming kernel, at most
 struct StreamBin {
@@ -179,6 +181,21 @@ struct pipe_expansion {
 // to a 23-us kernel), so a wave first reads the slot -- a device-coherent load, not serialized --
 // and sends the atomic only if it would raise the value: a handful per launch instead of one per wave.
 #if defined(__HIPCC__)
+// Requests every 64-byte line of the kernel's arguments at once.  An eagerly launched kernel's arguments lie in host memory
+// (the runtime's default): each line's first use costs a trip there, one after the other, and some are first used in
+// the epilogue (a token of the 11008 x 4096 ternary layer 13.1 -> 12.7 us a call).  Only for kernels that need nearly all of
+// them at once: a two-layer MLP at 35 tokens, whose launches use few of the lines, lost 5 of 30 us to the trips.
+template <int BYTES>
+__device__ __forceinline__ void request_arguments() {
+  typedef const __attribute__((address_space(4))) int* cptr;
+  const cptr k = (cptr)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int N = (BYTES + 63) / 64;
+  int v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = k[i * 16];
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" ::"s"(v[i]));
+}
 __device__ __forceinline__ void amax_raise(uint32_t* slot, float mx) {
   const uint32_t bits = __float_as_uint(mx);
   if (bits == 0u) return;
@@ -333,7 +350,7 @@ struct GemmArgs {
   int M;                 // members
   int member_lo[PIPE_MAX_K];  // 0-based first order of member m
   int member_hi[PIPE_MAX_K];  // 0-based last order (inclusive)
-  const float* x_f32;    // streaming kernel, at most 4 tokens: the fp32 input [T, in] when the contraction quantizes it
+  const float* x_f32;    // streaming kernel, few tokens: the fp32 input [T, in] when the contraction quantizes it
                          // itself (then qx, rowsum and s_x are not read), else nullptr
   float s_static;        // with x_f32: the given activation scale, or <= 0 for the dynamic one
   const float* bias;     // or nullptr

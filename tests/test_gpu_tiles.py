@@ -105,3 +105,19 @@ def test_fused_depthwise_at_its_tile_edges(pipe, N, C, H, W, stride, pad, bits, 
         xs.copy_(dev(x))
         assert torch.equal(y, pipe.pipe_forward_depthwise2d(e, xs, 3, 3, stride, pad, s_x=s_x, bias=dev(b)))
     e.free()
+
+
+@pytest.mark.parametrize("T,I,bits,s_x", [(16, 256, 8, 0.0), (15, 200, 4, 0.0), (5, 768, 2, 0.02), (2, 1020, 4, 0.0), (1, 4096, 2, 0.0),
+                                          (1, 8192, 4, 0.0), (16, 4, 8, 0.0), (4, 1024, 3, 0.0)])
+def test_quantizing_in_the_streaming_kernel_changes_nothing(pipe, T, I, bits, s_x):
+    """Few codes: one launch instead of two, bit for bit (rows whose quads fill a wave and rows that do not)."""
+    e = pipe.pipe_expand(dev(_weight(T * I, 112, I)), bits, 2, 1.0, 16)
+    x = dev(np.random.default_rng(I + T).standard_normal((T, I)).astype(np.float32))
+    y = pipe.pipe_forward(e, x, s_x=s_x)
+    pipe.pipe_set_decode_fusion(False)
+    try:
+        ref = pipe.pipe_forward(e, x, s_x=s_x)
+    finally:
+        pipe.pipe_set_decode_fusion(True)
+    assert torch.equal(y, ref)
+    e.free()
