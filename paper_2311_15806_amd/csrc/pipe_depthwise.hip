@@ -210,22 +210,34 @@ __global__ __launch_bounds__(BLK) void depthwise3_kernel(const Dw3Params p) {
   auto row_ok = [&](int j, int i) { return (unsigned)(ri0 + 4 * j + i) < (unsigned)p.H; };
   float sx = p.s_static;
   if (p.vec) {
-    const int g0 = max(ci0, 0) & ~3, ng = (min(ci0 + cols, p.W) - g0 + 3) >> 2;   // groups of 4 columns inside the image
-    const int per_c = ND * ng, units = nc * per_c;
+    // A unit is 4 rows x 4 neighbours in memory order, 16-byte loads: channels first, 4 columns of one channel; channels last,
+    // 4 channels of one column.  Unit -> (channel or channel quad cc, row quad j, column quad or column g).
+    const int g0 = p.nhwc ? max(ci0, 0) : max(ci0, 0) & ~3;
+    const int span = min(ci0 + cols, p.W) - g0;                     // columns inside the image
+    const int ng = p.nhwc ? span : (span + 3) >> 2, ncc = p.nhwc ? (nc + 3) >> 2 : nc;
+    const int units = max(ncc * ND * ng, 0);
+    auto split = [&](int u, int& cc, int& j, int& g) __attribute__((always_inline)) {
+      if (p.nhwc) { cc = u % ncc; const int r = u / ncc; j = r % ND; g = r / ND; }
+      else { g = u % ng; const int r = u / ng; j = r % ND; cc = r / ND; }
+    };
+    const ptrdiff_t row_step = p.nhwc ? (ptrdiff_t)p.W * p.C : p.W;
     float4 a[4], b[4];
     auto ld = [&](int u, float4(&v)[4]) {
       if (u >= units) return;
-      const int cc = u / per_c, r = u - cc * per_c, j = r / ng, g = r - j * ng;
-      const float* src = p.x + (((size_t)n * p.C + c0 + cc) * p.H + ri0 + 4 * j) * p.W + g0 + 4 * g;
+      int cc, j, g;
+      split(u, cc, j, g);
+      const int h = ri0 + 4 * j;
+      const float* src = p.nhwc ? p.x + (((ptrdiff_t)n * p.H + h) * p.W + g0 + g) * p.C + c0 + 4 * cc
+                                : p.x + (((ptrdiff_t)n * p.C + c0 + cc) * p.H + h) * p.W + g0 + 4 * g;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] = row_ok(j, i) ? *reinterpret_cast<const float4*>(src + (ptrdiff_t)i * p.W) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = 0; i < 4; ++i) v[i] = row_ok(j, i) ? *reinterpret_cast<const float4*>(src + i * row_step) : make_float4(0.f, 0.f, 0.f, 0.f);
     };
     int u = threadIdx.x;
     ld(u, a);
     ld(u + BLK, b);
     request_weights();
     // the columns outside the image (at most the padding on either side)
-    const int left = max(0, -ci0), right = max(0, ci0 + cols - p.W);
+    const int left = min(cols, max(0, -ci0)), right = min(cols, max(0, ci0 + cols - p.W));
     for (int i = threadIdx.x; i < (left + right) * ND * 64; i += BLK) {
       const int col = i / (ND * 64), rem = i - col * ND * 64;
       tile[((col < left ? col : cols - right + col - left) * ND + (rem >> 6)) * PITCH + (rem & 63)] = 0u;
@@ -238,15 +250,18 @@ __global__ __launch_bounds__(BLK) void depthwise3_kernel(const Dw3Params p) {
       };
       auto st = [&](int u, const float4(&v)[4]) {
         if (u >= units) return;
-        const int cc = u / per_c, r = u - cc * per_c, j = r / ng, g = r - j * ng;
-        const int col = g0 + 4 * g - ci0;
+        int cc, j, g;
+        split(u, cc, j, g);
         const uint32_t q[4] = {pack4(code(v[0].x), code(v[1].x), code(v[2].x), code(v[3].x)),
                                pack4(code(v[0].y), code(v[1].y), code(v[2].y), code(v[3].y)),
                                pack4(code(v[0].z), code(v[1].z), code(v[2].z), code(v[3].z)),
                                pack4(code(v[0].w), code(v[1].w), code(v[2].w), code(v[3].w))};
+        const int col = g0 - ci0 + (p.nhwc ? g : 4 * g);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if ((unsigned)(col + e) < (unsigned)cols) tile[((col + e) * ND + j) * PITCH + cc] = sx > 0.f ? q[e] : 0u;
+        for (int e = 0; e < 4; ++e) {
+          if (p.nhwc) tile[(col * ND + j) * PITCH + 4 * cc + e] = sx > 0.f ? q[e] : 0u;   // nc is a multiple of 16
+          else if ((unsigned)(col + e) < (unsigned)cols) tile[((col + e) * ND + j) * PITCH + cc] = sx > 0.f ? q[e] : 0u;
+        }
       };
       while (u < units) {
         st(u, a);
@@ -415,6 +430,6 @@ int launch_depthwise_fused(const pipe_expansion* e, const float* x, float s_stat
   p.x = x; p.amax = amax; p.s_static = s_static; p.qmax = qmax;
   p.codes = e->dw_cols_dev; p.scales = e->dw_scales_dev; p.bias = bias; p.y = y;
   p.N = N; p.C = C; p.H = H; p.W = W; p.Ho = Ho; p.Wo = Wo; p.pad = pad; p.nhwc = nhwc;
-  p.vec = !nhwc && W % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 1 : 0;
+  p.vec = (nhwc || W % 4 == 0) && (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 1 : 0;   // (C is a multiple of 16)
   return stride == 1 ? launch_depthwise3<1>(p, e->K, st) : launch_depthwise3<2>(p, e->K, st);
 }

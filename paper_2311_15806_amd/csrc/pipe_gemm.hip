@@ -534,7 +534,7 @@ template <int BITS, int MTB, int NRW, int MINW>
 int launch_cfg(TiledParams& p, bool acc_out, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   p.n_tt = ceil_div(p.T, 16 * MTB);
   p.n_ct = ceil_div(p.n_ct * NRB_TILE, 4 * NRW);   // column tiles of this variant's width
-  p.order = tile_order(p.n_ct, p.n_tt);
+  p.order = tile_order(p.n_ct, p.n_tt, true);
   const dim3 grid((unsigned)p.order.blocks());
   if (p.cq8 != nullptr) {
     // implicit-GEMM convolution: plain epilogue or the integer export

@@ -326,6 +326,18 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   float* ym = p.y + (size_t)(p.apart ? m : 0) * p.T * p.out + 4 * g;
   const int n_res = (MODE == MODE_CHAIN && p.res != nullptr) ? (p.apart ? (m < p.res_members ? 1 : 0) : p.res_members) : 0;
   const float* resm = MODE == MODE_CHAIN ? p.res + (size_t)(p.apart ? m : 0) * p.res_mstride + 4 * g : nullptr;
+  // the skip tensor of every row block, requested together (the loop's registers are free)
+  float4 rq[MODE == MODE_CHAIN ? 4 : 1][MODE == MODE_CHAIN ? MTB : 1];
+  if (MODE == MODE_CHAIN) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int b = 0; b < MTB; ++b) {
+        rq[r][b] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (n_res > 0 && ((ends >> r) & 1))
+          rq[r][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(t0 + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
+      }
+  }
   float v[MTB][4], gate[MODE == MODE_GATED ? MTB : 1][4];
 #pragma unroll
   for (int b = 0; b < MTB; ++b)
@@ -358,12 +370,12 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
     for (int b = 0; b < MTB; ++b) {
       const int t = t0 + b * 16 + tl;
       if (MODE == MODE_CHAIN) {
-        float4 rq = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int mm = 0; mm < n_res; ++mm) {
+        float4 rs4 = rq[r][b];
+        for (int mm = 1; mm < n_res; ++mm) {   // a sum over several members, each with a skip tensor of its own
           const float4 x = *reinterpret_cast<const float4*>(resm + (size_t)mm * p.res_mstride + (size_t)min(t, p.T - 1) * p.out + rb[r] * 16);
-          rq.x += x.x; rq.y += x.y; rq.z += x.z; rq.w += x.w;
+          rs4.x += x.x; rs4.y += x.y; rs4.z += x.z; rs4.w += x.w;
         }
-        const float rr[4] = {rq.x, rq.y, rq.z, rq.w};
+        const float rr[4] = {rs4.x, rs4.y, rs4.z, rs4.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           if (p.res_pre_act) v[b][i] += rr[i];
@@ -403,7 +415,7 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
 
 template <int BITS, int MTB, int MINW>
 int launch_cfg(BinsParams& p, int n_ct, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
-  p.order = tile_order(n_ct, ceil_div(p.T, 16 * MTB));
+  p.order = tile_order(n_ct, ceil_div(p.T, 16 * MTB), false);
   const dim3 grid((unsigned)p.order.blocks());
   if (p.cq8 != nullptr) {
     if (p.res != nullptr || p.act != 0) return PIPE_EINVAL;   // implicit-GEMM convolution: plain epilogue
