@@ -44,8 +44,7 @@ extern "C" const char* pipe_strerror(int code) {
 // less than the live one.
 struct WsSet {
   PipeWorkspace slot[WS_SLOTS];
-  bool amax_h_dirty = false;   // the members' max|h| slots hold a value no kernel will clear
-  bool range_h_dirty = false;  // the same for the members' range slots of the asymmetric chain
+  bool slots_dirty = false;    // the members' max|h| or range slots hold a value no kernel will clear
 };
 static std::mutex g_ws_mu;
 static std::map<std::pair<int, hipStream_t>, WsSet*> g_ws_sets;
@@ -768,8 +767,9 @@ static bool use_stream_kernel(const pipe_expansion* e, int T, bool acc_out = fal
 struct ActBuffers {
   uint8_t* qx;
   int32_t* rowsum;
-  uint32_t* amax;        // control words: from 16 on the hidden tensors' max and range slots (zero on entry, cleared by the
-                         // contraction kernel that follows their last reader), zero-point offsets
+  uint32_t* amax;        // control words: zero-point offsets
+  uint32_t* slots;       // the hidden tensors' max and range slots, two sets of 2 * PIPE_MAX_K (zero on entry, cleared by the
+                         // contraction kernel that follows their last reader); not part of a call without allocations
   uint32_t* part;        // parts of the input's max reduction, PIPE_MAX_PARTS (and as many for the negative side)
   float* scale;          // [PIPE_MAX_K] scales
   int T_pad;
@@ -788,6 +788,8 @@ static int get_act_buffers(int T, int in_pad, bool small, ActBuffers* b) {
   if (fresh) PIPE_HIP(hipMemset(sc, 0, 4096));   // never under capture: a fresh block is refused there
   b->amax = (uint32_t*)sc;
   b->scale = (float*)(sc + 1024);
+  b->slots = (uint32_t*)(sc + 2048);
+  static_assert(4 * PIPE_MAX_K <= PIPE_SLOT_WORDS && PIPE_SLOT_LINES * PIPE_SLOT_WORDS * 4 <= 2048, "slots");
   b->part = (uint32_t*)(sc + 4096);
   return PIPE_OK;
 }
@@ -1521,7 +1523,7 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
   uint8_t* qh = (uint8_t*)pipe_ws_get(WS_QH, (size_t)Mm * T_pad * l2->in_pad);
   int32_t* rowsum_h = (int32_t*)pipe_ws_get(WS_ROWSUM_H, (size_t)Mm * T_pad * 4);
   if (!h || !qh || !rowsum_h) return pipe_ws_error();
-  uint32_t* amax_h = b.amax + 16;
+  uint32_t* amax_h = b.slots;
   float* scale_h = b.scale + 16;
   {
     // decode-sized batches: both layers in one resident launch
@@ -1559,11 +1561,11 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
   // The members' max|h| slots are zero on entry: cleared when the workspace is allocated and,
   // after each use, by the layer-2 kernel that follows their last reader.  A call that failed
   // between the two leaves them dirty; then they are cleared by a launch of their own.
-  if (t_ws->amax_h_dirty) {
-    rc = launch_zero_u32(amax_h, 2 * PIPE_MAX_K, st);
+  if (t_ws->slots_dirty) {
+    rc = launch_zero_u32(b.slots, PIPE_SLOT_LINES * PIPE_SLOT_WORDS, st);
     if (rc) return rc;
   }
-  t_ws->amax_h_dirty = true;
+  t_ws->slots_dirty = true;
 
   // layer 1: every member reads the same Q(x); outputs stay separate
   GemmArgs a{};
@@ -1619,7 +1621,7 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
   a2.zero_after = amax_h; a2.zero_n = Mm;
   fill_members(a2, Mm, lo, hi);
   rc = run_gemm(a2, small, st);
-  if (rc == PIPE_OK) t_ws->amax_h_dirty = false;
+  if (rc == PIPE_OK) t_ws->slots_dirty = false;
   return rc;
 }
 
@@ -1670,14 +1672,14 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
   // slots as in pipe_chain_forward_asymmetric: the input's offset, the members' ranges (positive parts
   // [0, 16), negative parts [16, 32)), offsets and scales
   int32_t* dz_x = reinterpret_cast<int32_t*>(b.amax + 66);
-  uint32_t* rng = b.amax + 128;
+  uint32_t* rng = b.slots;
   int32_t* dz_h = reinterpret_cast<int32_t*>(b.amax + 128 + 4 * PIPE_MAX_K);
   float* scale_h = b.scale + 16;
-  if (t_ws->range_h_dirty) {
-    rc = launch_zero_u32(rng, 4 * PIPE_MAX_K, st);
+  if (t_ws->slots_dirty) {
+    rc = launch_zero_u32(b.slots, PIPE_SLOT_LINES * PIPE_SLOT_WORDS, st);
     if (rc) return rc;
   }
-  t_ws->range_h_dirty = true;
+  t_ws->slots_dirty = true;
 
   const int64_t n_x = (int64_t)T * l1->in;
   rc = launch_minmax(x_dev, n_x, b.part, b.part + PIPE_MAX_PARTS, b.rowsum, T_pad, st);
@@ -1703,7 +1705,7 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
     if (rc) return rc;
   }
   for (int m = 0; m < Mm; ++m) {
-    rc = launch_quantize_asym(h + (size_t)m * T * H, T, H, l2->in_pad, T_pad, MaxOf{rng + m, 1}, MaxOf{rng + PIPE_MAX_K + m, 1}, act_bits,
+    rc = launch_quantize_asym(h + (size_t)m * T * H, T, H, l2->in_pad, T_pad, MaxOf{rng + m, 0}, MaxOf{rng + PIPE_MAX_K + m, 0}, act_bits,
                               qh + (size_t)m * T_pad * l2->in_pad, rowsum_h + (size_t)m * T_pad, false, nullptr, scale_h + m, dz_h + m, st);
     if (rc) return rc;
   }
@@ -1716,7 +1718,7 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
   a2.zero_after = rng; a2.zero_n = 2 * PIPE_MAX_K;
   fill_members(a2, Mm, lo, hi);
   rc = run_gemm(a2, small, st);
-  if (rc == PIPE_OK) t_ws->range_h_dirty = false;
+  if (rc == PIPE_OK) t_ws->slots_dirty = false;
   return rc;
 }
 
@@ -1861,7 +1863,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
   int32_t* rs_buf[2] = {rowsum_h, rowsum_h ? rowsum_h + (size_t)Mm * T_pad_max : nullptr};
   // max|tensor| per member, two sets used in turn: layer l writes set l & 1 in its epilogue, the
   // quantizer of layer l+1 reads it, and the contraction of layer l+1 clears it again
-  uint32_t* amax_set[2] = {b.amax + 16, b.amax + 16 + PIPE_MAX_K};
+  uint32_t* amax_set[2] = {b.slots, b.slots + 2 * PIPE_MAX_K};
   float* scale_h = b.scale + 16;
   {
     // decode-sized batches of fully-connected layers: the whole chain in one resident launch
@@ -1891,11 +1893,11 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
   for (int l = 0; l < L; ++l)
     if (!small[l] && (rc = ensure_tables(layers[l].e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   if (pipe_dry_run()) return PIPE_OK;
-  if (t_ws->amax_h_dirty) {
-    rc = launch_zero_u32(amax_set[0], 2 * PIPE_MAX_K, st);
+  if (t_ws->slots_dirty) {
+    rc = launch_zero_u32(b.slots, PIPE_SLOT_LINES * PIPE_SLOT_WORDS, st);
     if (rc) return rc;
   }
-  t_ws->amax_h_dirty = true;
+  t_ws->slots_dirty = true;
 
   for (int l = 0; l < L; ++l) {
     const pipe_chain_layer& ly = layers[l];
@@ -1929,7 +1931,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
       if (conv) {
         for (int m = 0; m < Mm; ++m) {
           rc = launch_quantize_im2col(src + (size_t)m * Tin[l] * Cin[l], N, Cin[l], Hin[l], Win[l], ly.kh, ly.kw, ly.stride,
-                                      ly.pad, 1, Hin[l + 1], Win[l + 1], e->in_pad, T_pad, s_given ? s_given[m] : 0.f, MaxOf{amax_in + m, 1}, q8,
+                                      ly.pad, 1, Hin[l + 1], Win[l + 1], e->in_pad, T_pad, s_given ? s_given[m] : 0.f, MaxOf{amax_in + m, 0}, q8,
                                       qh + (size_t)m * q_ms, rs_in + (size_t)m * T_pad_max, scale_h + m, st);
           if (rc) return rc;
         }
@@ -1952,7 +1954,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
         if (rc) return rc;
       } else {
         for (int m = 0; m < Mm; ++m) {
-          rc = launch_quantize_act(src + (size_t)m * T * in, T, in, e->in_pad, T_pad, 0.f, MaxOf{amax_in + m, 1}, qh + (size_t)m * q_ms,
+          rc = launch_quantize_act(src + (size_t)m * T * in, T, in, e->in_pad, T_pad, 0.f, MaxOf{amax_in + m, 0}, qh + (size_t)m * q_ms,
                                    rs_in + (size_t)m * T_pad_max, true, nullptr, scale_h + m, st);
           if (rc) return rc;
         }
@@ -1982,7 +1984,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
     if (rc) return rc;
   }
   // the last layer cleared the set it read; the other set was cleared one layer earlier
-  t_ws->amax_h_dirty = false;
+  t_ws->slots_dirty = false;
   return PIPE_OK;
 }
 
@@ -2089,14 +2091,14 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
   // (positive parts [0, 16), negative parts [16, 32) of a set; layer l's epilogue raises set l & 1, the
   // quantizers of layer l+1 read it and layer l+1's contraction clears it), offsets and scales
   int32_t* dz_x = reinterpret_cast<int32_t*>(b.amax + 66);
-  uint32_t* rng[2] = {b.amax + 128, b.amax + 128 + 2 * PIPE_MAX_K};
+  uint32_t* rng[2] = {b.slots, b.slots + 2 * PIPE_MAX_K};
   int32_t* dz_h = reinterpret_cast<int32_t*>(b.amax + 128 + 4 * PIPE_MAX_K);
   float* scale_h = b.scale + 16;
-  if (t_ws->range_h_dirty) {
-    rc = launch_zero_u32(rng[0], 4 * PIPE_MAX_K, st);
+  if (t_ws->slots_dirty) {
+    rc = launch_zero_u32(b.slots, PIPE_SLOT_LINES * PIPE_SLOT_WORDS, st);
     if (rc) return rc;
   }
-  t_ws->range_h_dirty = true;
+  t_ws->slots_dirty = true;
 
   for (int l = 0; l < L; ++l) {
     const pipe_chain_layer& ly = layers[l];
@@ -2129,10 +2131,10 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
         const float* src_m = src + (size_t)m * Tin[l] * Cin[l];
         if (conv)
           rc = launch_quantize_im2col_asym(src_m, N, Cin[l], Hin[l], Win[l], ly.kh, ly.kw, ly.stride, ly.pad, 1, Hin[l + 1], Win[l + 1],
-                                           e->in_pad, T_pad, MaxOf{r_in + m, 1}, MaxOf{r_in + PIPE_MAX_K + m, 1}, act_bits, q8, qh + (size_t)m * q_ms,
+                                           e->in_pad, T_pad, MaxOf{r_in + m, 0}, MaxOf{r_in + PIPE_MAX_K + m, 0}, act_bits, q8, qh + (size_t)m * q_ms,
                                            rowsum_h + (size_t)m * T_pad_max, scale_h + m, dz_h + m, st);
         else
-          rc = launch_quantize_asym(src_m, T, e->in, e->in_pad, T_pad, MaxOf{r_in + m, 1}, MaxOf{r_in + PIPE_MAX_K + m, 1}, act_bits,
+          rc = launch_quantize_asym(src_m, T, e->in, e->in_pad, T_pad, MaxOf{r_in + m, 0}, MaxOf{r_in + PIPE_MAX_K + m, 0}, act_bits,
                                     qh + (size_t)m * q_ms, rowsum_h + (size_t)m * T_pad_max, false, nullptr, scale_h + m, dz_h + m, st);
         if (rc) return rc;
       }
@@ -2162,7 +2164,7 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
     rc = run_gemm(a, small[l], st);
     if (rc) return rc;
   }
-  t_ws->range_h_dirty = false;
+  t_ws->slots_dirty = false;
   return PIPE_OK;
 }
 

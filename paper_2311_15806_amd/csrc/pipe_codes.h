@@ -19,8 +19,17 @@ __device__ __forceinline__ float block_max(float v) {
   return r;
 }
 
+// The value of a slot, by a whole wave
+__device__ __forceinline__ float slot_max(const uint32_t* slot) {
+  float m = __uint_as_float(slot[(threadIdx.x & (PIPE_SLOT_LINES - 1)) * PIPE_SLOT_WORDS]);
+#pragma unroll
+  for (int o = PIPE_SLOT_LINES / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  return m;
+}
+
 // The value of a max reduction: the largest of its parts.  Called by all threads of a workgroup.
 __device__ __forceinline__ float max_of(const MaxOf& a) {
+  if (a.n == 0) return slot_max(a.p);
   if (a.n == 1) return __uint_as_float(a.p[0]);
   float m = 0.f;
   for (int i = threadIdx.x; i < a.n; i += CODES_BLK) m = fmaxf(m, __uint_as_float(a.p[i]));

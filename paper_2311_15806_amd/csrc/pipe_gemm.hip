@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256, MINW) void gemm_tiled_kernel(const TiledParams
   {
     if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
   }
-  if (blockIdx.x == 0 && (int)threadIdx.x < p.zero_n && p.zero_after != nullptr) p.zero_after[threadIdx.x] = 0u;
+  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<256>(p.zero_after, p.zero_n);
   const int t0 = tt * (16 * MTB);
   // LDS byte address of this lane's 16 bytes inside fragment 0 of buffer 0
   const unsigned xs_lane = (unsigned)(uintptr_t)(__attribute__((address_space(3))) uint4*)&Xs[0][0] + lane * 16;
@@ -520,11 +520,11 @@ __global__ __launch_bounds__(256, MINW) void gemm_tiled_kernel(const TiledParams
     if (p.amax_out != nullptr) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-      if (lane == 0) amax_raise(&p.amax_out[m], mx);
+      if (lane == 0) slot_raise(&p.amax_out[m], mx);
       if (two_sided) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) mn = fmaxf(mn, __shfl_xor(mn, o, 64));
-        if (lane == 0) amax_raise(&p.amax_neg[m], mn);
+        if (lane == 0) slot_raise(&p.amax_neg[m], mn);
       }
     }
   }  // members

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (p.zero_big != nullptr)
     for (int i = blockIdx.x * 256 + threadIdx.x; i < p.zero_big_n; i += gridDim.x * 256) p.zero_big[i] = 0u;
-  if (blockIdx.x == 0 && (int)threadIdx.x < p.zero_n && p.zero_after != nullptr) p.zero_after[threadIdx.x] = 0u;
+  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<256>(p.zero_after, p.zero_n);
   int ct, tt;
   if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
   const int t0 = tt * (16 * MTB);
@@ -322,6 +322,9 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   for (int b = 0; b < MTB; ++b) rs[b] = OFF ? lds.rs[wave][b * 16 + tl] : 0;
   float mx = 0.f, mn = 0.f;
   const bool two_sided = p.amax_neg != nullptr;
+  // the slots as they are now, read while the orders are folded
+  const uint32_t seen = p.amax_out != nullptr ? slot_seen(&p.amax_out[m]) : 0u;
+  const uint32_t seen_neg = two_sided ? slot_seen(&p.amax_neg[m]) : 0u;
   const bool with_bias = p.bias != nullptr && (m == 0 || !p.apart || p.bias_mstride != 0);
   float* ym = p.y + (size_t)(p.apart ? m : 0) * p.T * p.out + 4 * g;
   const int n_res = (MODE == MODE_CHAIN && p.res != nullptr) ? (p.apart ? (m < p.res_members ? 1 : 0) : p.res_members) : 0;
@@ -404,11 +407,11 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   if (p.amax_out != nullptr) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-    if (lane == 0) amax_raise(&p.amax_out[m], mx);
+    if (lane == 0) slot_raise(&p.amax_out[m], seen, mx);
     if (two_sided) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) mn = fmaxf(mn, __shfl_xor(mn, o, 64));
-      if (lane == 0) amax_raise(&p.amax_neg[m], mn);
+      if (lane == 0) slot_raise(&p.amax_neg[m], seen_neg, mn);
     }
   }
 }

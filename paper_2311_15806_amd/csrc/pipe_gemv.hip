@@ -121,7 +121,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_tiles = (p.nks * 64) / KSUP;
-  if (blockIdx.x == 0 && (int)threadIdx.x < p.zero_n && p.zero_after != nullptr) p.zero_after[threadIdx.x] = 0u;
+  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<NW * 64>(p.zero_after, p.zero_n);
   if (p.zero_big != nullptr)
     for (int i = blockIdx.x * (NW * 64) + threadIdx.x; i < p.zero_big_n; i += gridDim.x * (NW * 64)) p.zero_big[i] = 0u;
 
@@ -407,12 +407,12 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
         float mx = tg < p.T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
 #pragma unroll
         for (int s = 32; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-        if (lane == 0) amax_raise(&p.amax_out[m], mx);
+        if (lane == 0) slot_raise(&p.amax_out[m], mx);
         if (two_sided) {
           float mn = tg < p.T ? fmaxf(-v, 0.f) : 0.f;
 #pragma unroll
           for (int s = 32; s > 0; s >>= 1) mn = fmaxf(mn, __shfl_xor(mn, s, 64));
-          if (lane == 0) amax_raise(&p.amax_neg[m], mn);
+          if (lane == 0) slot_raise(&p.amax_neg[m], mn);
         }
       }
       if (tg < p.T) p.y[((size_t)(p.reduce ? 0 : m) * p.T + tg) * p.out + col] = v;
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_tiles = (p.nks * 64) / KSUP;
-  if (blockIdx.x == 0 && (int)threadIdx.x < p.zero_n && p.zero_after != nullptr) p.zero_after[threadIdx.x] = 0u;
+  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<NW * 64>(p.zero_after, p.zero_n);
   if (p.zero_big != nullptr)
     for (int i = blockIdx.x * (NW * 64) + threadIdx.x; i < p.zero_big_n; i += gridDim.x * (NW * 64)) p.zero_big[i] = 0u;
 
@@ -637,12 +637,12 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
         float mx = tg < p.T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
 #pragma unroll
         for (int s = 32; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-        if (lane == 0) amax_raise(&p.amax_out[m], mx);
+        if (lane == 0) slot_raise(&p.amax_out[m], mx);
         if (two_sided) {
           float mn = tg < p.T ? fmaxf(-v, 0.f) : 0.f;
 #pragma unroll
           for (int s = 32; s > 0; s >>= 1) mn = fmaxf(mn, __shfl_xor(mn, s, 64));
-          if (lane == 0) amax_raise(&p.amax_neg[m], mn);
+          if (lane == 0) slot_raise(&p.amax_neg[m], mn);
         }
       }
       if (tg < p.T) p.y[((size_t)(p.reduce ? 0 : m) * p.T + tg) * p.out + col] = v;

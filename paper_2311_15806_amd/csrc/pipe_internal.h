@@ -176,10 +176,14 @@ struct pipe_expansion {
   uint8_t* conv_zero_dev = nullptr;   // 256 zero bytes
 };
 
-// max|.| reduction slot (fp32 bit pattern of a non-negative value).  Atomics of many waves on
-// one address are served one after another (about 10 ns each, measured: 4096 of them added 40 us
-// to a 23-us kernel), so a wave first reads the slot -- a device-coherent load, not serialized --
-// and sends the atomic only if it would raise the value: a handful per launch instead of one per wave.
+// Slots of the max|.| reductions in the epilogues (fp32 bit patterns of non-negative values): PIPE_SLOT_LINES lines of
+// PIPE_SLOT_WORDS words, each with all the slots of a call; a workgroup raises the line of its XCD, the value is the largest
+// of the lines.  Accesses of many waves to one line are served one after another (atomics about 10 ns each: 4096 of them
+// added 40 us to a 23-us kernel), so a wave first reads the slot and sends the atomic only if it would raise the value.  Those
+// device-coherent reads queue up as well where thousands of waves end within a few microseconds: with one line the
+// hidden layers of the eight 2048 x 2048 ternary layers, two members, 4096 tokens cost 775 us together, with eight 682.
+constexpr int PIPE_SLOT_LINES = 8;
+constexpr int PIPE_SLOT_WORDS = 64;   // 256 bytes: the lines lie on different channels
 #if defined(__HIPCC__)
 // Requests every 64-byte line of the kernel's arguments at once.  An eagerly launched kernel's arguments lie in host memory
 // (the runtime's default): each line's first use costs a trip there, one after the other, and some are first used in
@@ -196,11 +200,24 @@ __device__ __forceinline__ void request_arguments() {
 #pragma unroll
   for (int i = 0; i < N; ++i) asm volatile("" ::"s"(v[i]));
 }
-__device__ __forceinline__ void amax_raise(uint32_t* slot, float mx) {
-  const uint32_t bits = __float_as_uint(mx);
-  if (bits == 0u) return;
-  if (__hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= bits) return;
-  atomicMax(slot, bits);
+__device__ __forceinline__ uint32_t* slot_line(uint32_t* slot) {
+  return slot + (blockIdx.x & (PIPE_SLOT_LINES - 1)) * PIPE_SLOT_WORDS;
+}
+// `seen`: the slot as read at any time since it was cleared (it only grows)
+__device__ __forceinline__ uint32_t slot_seen(uint32_t* slot) {
+  return __hip_atomic_load(slot_line(slot), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void slot_raise(uint32_t* slot, uint32_t seen, float mx) {
+  if (__float_as_uint(mx) > seen) atomicMax(slot_line(slot), __float_as_uint(mx));
+}
+__device__ __forceinline__ void slot_raise(uint32_t* slot, float mx) {
+  if (__float_as_uint(mx) != 0u) slot_raise(slot, slot_seen(slot), mx);
+}
+// the first n slots of every line, by one workgroup of NT threads
+template <int NT>
+__device__ __forceinline__ void slots_clear(uint32_t* slots, int n) {
+  for (int i = threadIdx.x; i < PIPE_SLOT_LINES * PIPE_SLOT_WORDS; i += NT)
+    if ((i & (PIPE_SLOT_WORDS - 1)) < n) slots[i] = 0u;
 }
 #endif
 
@@ -239,8 +256,8 @@ bool pipe_capturing();
   } while (0)
 enum { WS_QX = 0, WS_ROWSUM, WS_SCAL, WS_Y1, WS_H, WS_QH, WS_ROWSUM_H, WS_RESID, WS_ENERGY, WS_MISC, WS_Q8X, WS_CHAIN, WS_DIAG, WS_DIAG_CODES, WS_DIAG_DENSE, WS_RES, WS_RES_Q, WS_CSUM, WS_ABIAS, WS_SLOTS };
 
-// A maximum as the bit patterns of its parts (device): one word for a slot that a contraction kernel's epilogue raised,
-// max_parts(n) for the reduction of an n-element input.
+// A maximum as the bit patterns of its parts (device): max_parts(n) words for the reduction of an n-element input, and n = 0
+// for a slot that a contraction kernel's epilogue raised.
 struct MaxOf {
   const uint32_t* p;
   int n;
@@ -366,10 +383,10 @@ struct GemmArgs {
   int res_pre_act = 1;          // 1: act(z + res); 0: act(z) + res
   float* y;
   int32_t* acc_out;      // debug: [K,T,out] or nullptr (then y may be nullptr)
-  uint32_t* amax_out;    // per member max|output| bit pattern (or nullptr)
+  uint32_t* amax_out;    // per member the slot of max|output| (or nullptr)
   uint32_t* amax_neg = nullptr;   // if set: amax_out[m] receives max(output, 0) and amax_neg[m] max(-output, 0), the
                                   // range the asymmetric quantizer of the next layer needs
-  uint32_t* zero_after;  // words the kernel clears (the max|x| slots this call consumed), or nullptr
+  uint32_t* zero_after;  // the first of zero_n slots the kernel clears (the max|x| slots this call consumed), or nullptr
   int zero_n = 1;        // how many (at most 64)
   uint32_t* zero_big = nullptr;   // a buffer the kernel clears as well (the code sums the next layer's quantizer
   int zero_big_n = 0;             // adds into: nobody reads them while this kernel runs), any length

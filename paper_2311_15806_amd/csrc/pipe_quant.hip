@@ -252,7 +252,7 @@ __global__ __launch_bounds__(SBLK) void quantize_small_kernel(const float* __res
   float s = s_static;
   if (!(s_static > 0.f) && amax_bits != nullptr) {
     // the producer of x already reduced max|x| of member m
-    s = __fdiv_rn(__uint_as_float(amax_bits[m]), c_act_qmax);
+    s = __fdiv_rn(slot_max(&amax_bits[m]), c_act_qmax);
   } else if (!(s_static > 0.f)) {
     float mx = 0.f;
     const int64_t cnt = (int64_t)T * in;
@@ -457,10 +457,10 @@ __global__ __launch_bounds__(BLK) void mlp_act_kernel(const float* __restrict__ 
     }
   }
   mx = block_max(mx);
-  if (threadIdx.x == 0) amax_raise(&amax_bits[m], mx);
+  if (threadIdx.x == 0) slot_raise(&amax_bits[m], mx);
   if (two_sided) {
     mn = block_max(mn);
-    if (threadIdx.x == 0) amax_raise(&amax_neg[m], mn);
+    if (threadIdx.x == 0) slot_raise(&amax_neg[m], mn);
   }
 }
 
@@ -753,7 +753,7 @@ int launch_quantize_members(const float* x, int64_t x_mstride, int M, int T, int
     if (rc) return rc;
   }
   dim3 grid(T_pad / 16, ksplit_for(T_pad * M, in_pad), M);
-  PIPE_KLAUNCH(quantize_act_kernel, grid, dim3(BLK), 0, st, x, x_mstride, T, in, in_pad, 0.f, MaxOf{amax_bits, 1},
+  PIPE_KLAUNCH(quantize_act_kernel, grid, dim3(BLK), 0, st, x, x_mstride, T, in, in_pad, 0.f, MaxOf{amax_bits, 0},
                      qx_frag, qx_mstride, rowsum, T_pad, (int8_t*)nullptr, scale_out);
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
