@@ -1403,7 +1403,7 @@ extern "C" int pipe_forward_depthwise2d(const pipe_expansion* e, const float* x_
 // Scratch of the resident kernel in the stream's workspace: flag words, tagged maxima, the epoch the
 // last launch ended with and the status word (all zero when allocated; the kernels keep them
 // consistent afterwards), and one code buffer per layer.
-constexpr size_t RES_FLAGS_BYTES = 4096, RES_TAG_BYTES = 1024 * 2 * 8, RES_CTRL_BYTES = RES_FLAGS_BYTES + RES_TAG_BYTES + 256;
+constexpr size_t RES_FLAGS_BYTES = PIPE_RES_FLAGS * 4, RES_TAG_BYTES = PIPE_RES_FLAGS * 2 * 8, RES_CTRL_BYTES = RES_FLAGS_BYTES + RES_TAG_BYTES + 256;
 
 struct ResidentLayerSpec {
   const pipe_expansion* e;

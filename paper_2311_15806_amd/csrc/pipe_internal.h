@@ -113,6 +113,8 @@ struct TileBins {
 //             items 0-3 the gate block's orders (slot 0), 4-7 the up block's (slot 1), order -1 = absent,
 //             out_rb = {hidden block, gate row block, up row block}
 constexpr int PIPE_RES_MAX_LAYERS = 16;
+constexpr int PIPE_RES_MAX_G = 1024;      // workgroups of the resident kernel
+constexpr int PIPE_RES_FLAGS = 2048;      // its flag words: workgroups times copies
 constexpr int PIPE_RES_MAX_M = 2;
 constexpr int PIPE_RES_MAX_ITEMS = 8;
 constexpr int PIPE_RES_DESC_INTS = 4096;   // LDS copy of one workgroup's unit descriptors, all layers
