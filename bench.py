@@ -311,7 +311,7 @@ def main():
     if mfma_bound:
         roofline = dict(bound="mfma", achieved=head["kernel_eff_tops"], peak=INT8_MFMA_PEAK_TOPS, unit="TOP/s",
                         frac=(head["kernel_eff_tops"] or 0) / INT8_MFMA_PEAK_TOPS, traffic=None,
-                        kernel="gemm_tiled_kernel", kernel_ms=head["kernel_ms_per_step"],
+                        kernel="gemm_bins_kernel", kernel_ms=head["kernel_ms_per_step"],
                         step_achieved=head["eff_tops"], step_frac=head["eff_tops"] / INT8_MFMA_PEAK_TOPS)
     else:
         roofline = dict(bound="hbm", achieved=head["kernel_gbs"], peak=HBM_PEAK_GBS, unit="GB/s",

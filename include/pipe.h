@@ -485,10 +485,11 @@ int pipe_set_token_tile(int tokens);
 int pipe_set_stream_split(int workgroups_per_bin);
 
 /* A single token (pipe_forward, and layer 1 of pipe_mlp_forward, on a layer of at
- * most 8192 input features, a multiple of 4, 16-byte aligned input): by default the weight-streaming kernel quantizes the
+ * most 8192 input features, a multiple of 4, 16-byte aligned input) and up to 16 tokens of at most 4096 codes together:
+ * by default the weight-streaming kernel quantizes the
  * input itself -- every workgroup reduces max|x| and rounds the few KiB of activations
  * with the quantizer's own arithmetic -- so the step is one launch instead of two.
- * (From two tokens on the repeated work costs more than the launch it saves.)
+ * (Beyond that the repeated work costs more than the launch it saves.)
  * An output buffer that overlaps the input keeps the two-launch path.  0 switches
  * this off (tuning and tests), 1 on (default).  Results do not depend on the
  * setting.  Returns PIPE_EINVAL for other values.                                    */

@@ -1419,7 +1419,7 @@ struct ResidentLayerSpec {
 static bool resident_eligible(const pipe_expansion* const* es, int L, int T, int M, const float* x_dev, bool given_scales = false) {
   if (!g_decode_resident || g_kernel_choice == 1) return false;
   // automatic: where it measured faster (short chains of few tokens only when no maxima are exchanged)
-  if (g_decode_resident == 1 && L < 3 && T <= 8 && !given_scales) return false;   // (gated MLP, 8 tokens: 60.0 against 65.2 us; 16 tokens: 68.4 against 66.5)
+  if (g_decode_resident == 1 && L < 3 && T <= 8 && !given_scales) return false;   // (per layer against resident: gated MLP 4096 x 11008, 8 tokens 60.2 and 58.1 us, 16 tokens 66.7 and 60.9; GELU MLP 768 x 3072, one token 17.1 and 21.3, 9 tokens 22.2 and 21.6)
   if (T < 1 || T > 16 || M > PIPE_RES_MAX_M || L > PIPE_RES_MAX_LAYERS) return false;
   if (es[0]->in % 4 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 15) != 0) return false;
   for (int l = 0; l < L; ++l)
@@ -1686,7 +1686,7 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
   if (rc) return rc;
   rc = launch_quantize_asym(x_dev, T, l1->in, l1->in_pad, T_pad, input_max(b, n_x), input_neg_max(b, n_x), act_bits, b.qx, b.rowsum, true, nullptr, b.scale, dz_x, st);
   if (rc == PIPE_OK)
-    rc = launch_asym_bias_members(bias1_dev, l1->asym_P_dev, b.scale, 0, dz_x, 0, Mm, lo, hi, 0, bias_m, l1->out, nullptr, 0, st);
+    rc = launch_asym_bias_members(bias1_dev, l1->asym_P_dev, b.scale, 0, dz_x, 0, Mm, lo, hi, 0, bias_m, l1->out, st);
   if (rc) return rc;
   // layer 1: every member reads the same codes; its own offset vector; outputs stay separate
   GemmArgs a{};
@@ -1709,7 +1709,7 @@ extern "C" int pipe_mlp_forward_asymmetric(const pipe_expansion* l1, const pipe_
                               qh + (size_t)m * T_pad * l2->in_pad, rowsum_h + (size_t)m * T_pad, false, nullptr, scale_h + m, dz_h + m, st);
     if (rc) return rc;
   }
-  rc = launch_asym_bias_members(bias2_dev, l2->asym_P_dev, scale_h, 1, dz_h, 1, Mm, lo, hi, 1, bias_m, l2->out, nullptr, 0, st);
+  rc = launch_asym_bias_members(bias2_dev, l2->asym_P_dev, scale_h, 1, dz_h, 1, Mm, lo, hi, 1, bias_m, l2->out, st);
   if (rc) return rc;
   GemmArgs a2{};
   a2.e = l2; a2.T = T; a2.T_pad = T_pad; a2.qx = qh; a2.qx_mstride = (int64_t)T_pad * l2->in_pad;
@@ -2119,7 +2119,7 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
                                   nullptr, b.scale, dz_x, st);
       if (rc == PIPE_OK)
         rc = launch_asym_bias_members(ly.bias_dev, e->asym_P_dev, b.scale, 0, dz_x, 0, Mm, lo, hi, last_layer ? 1 : 0, bias_m,
-                                      e->out, nullptr, 0, st);
+                                      e->out, st);
       if (rc) return rc;
       a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;
       a.zero_after = nullptr; a.zero_n = 0;
@@ -2139,7 +2139,7 @@ static int chain_forward_asym_grid(const pipe_chain_layer* layers, int L, const 
         if (rc) return rc;
       }
       rc = launch_asym_bias_members(ly.bias_dev, e->asym_P_dev, scale_h, 1, dz_h, 1, Mm, lo, hi, last_layer ? 1 : 0, bias_m, e->out,
-                                    nullptr, 0, st);
+                                    st);
       if (rc) return rc;
       a.qx = qh; a.qx_mstride = q_ms;
       a.rowsum = rowsum_h; a.rowsum_mstride = T_pad_max;

@@ -1,4 +1,6 @@
-// Tiled int8-MFMA kernel of the expanded layer (App. B, Eq. (define_dre)):
+// Tiled int8-MFMA kernel of the expanded layer (App. B, Eq. (define_dre)), one pass over k per order, for what the
+// single-pass kernel (pipe_gemm_bins.hip) does not take: sums over members with inputs of their own, members of more than 4
+// orders, gate||up pairs of more than 2, and the integer export:
 //   y[t,o] = sum_m ( s_x,m * sum_{k in member m} s_k[o] * acc_k[t,o]  (+ b[o] if m = 0) )
 //   acc_k[t,o] = sum_i Qx[t,i] * q_k[o,i]          (exact, int32)
 //
@@ -16,9 +18,8 @@
 // skipped (no load, no MFMA).  Per order the int32 accumulators (minus offset * token code
 // sum, exact) are folded into an fp32 running sum with the row-wise scale; activation scale,
 // bias, optional GELU and the member sum are applied once in the epilogue.
-// Workgroups are mapped to (column tile, token tile) in super-tiles of 64 tiles per XCD (8 x 8, or
-// 16 x 4 when that deals every XCD a share of every column-tile row) so that the 64 workgroups
-// resident on one XCD share a few weight strips and activation strips in its L2.
+// Workgroups are mapped to (column tile, token tile) so that those resident on one XCD share a few weight strips and
+// activation strips in its L2 (TileOrder).
 #include <type_traits>
 
 #include "pipe_tile.h"

@@ -320,8 +320,7 @@ struct MemberRanges {
   int lo[PIPE_MAX_K], hi[PIPE_MAX_K];
 };
 int launch_asym_bias_members(const float* bias, const float* P, const float* scale, int scale_stride, const int32_t* dz,
-                             int dz_stride, int M, const int* lo, const int* hi, int reduce, float* outv, int n, uint32_t* clear,
-                             int n_clear, hipStream_t st);
+                             int dz_stride, int M, const int* lo, const int* hi, int reduce, float* outv, int n, hipStream_t st);
 int launch_row_code_sums(const int8_t* codes, int rows, int in, int group, const int32_t* gids, int32_t* wsum, hipStream_t st);
 // launch_absmax also zeroes n_zero ints at zero_me (the code sums of the quantizer that follows).
 int launch_absmax(const float* x, int64_t n, uint32_t* part, int32_t* zero_me, int n_zero, hipStream_t st);

@@ -597,9 +597,8 @@ __global__ void asym_bias_kernel(const float* __restrict__ bias, const float* __
 // bias joins the first member.  reduce: one vector, the members' sum (ascending m) plus the bias.
 __global__ void asym_bias_members_kernel(const float* __restrict__ bias, const float* __restrict__ P, const float* __restrict__ scale,
                                          int scale_stride, const int32_t* __restrict__ dz, int dz_stride, MemberRanges mr,
-                                         int reduce, float* __restrict__ outv, int n, uint32_t* __restrict__ clear, int n_clear) {
+                                         int reduce, float* __restrict__ outv, int n) {
   const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o < n_clear) clear[o] = 0u;
   if (o >= n) return;
   float tot = bias != nullptr ? bias[o] : 0.f;
   for (int m = 0; m < mr.M; ++m) {
@@ -862,13 +861,12 @@ int launch_asym_bias(const float* bias, const float* C, const float* scale, cons
 }
 
 int launch_asym_bias_members(const float* bias, const float* P, const float* scale, int scale_stride, const int32_t* dz,
-                             int dz_stride, int M, const int* lo, const int* hi, int reduce, float* outv, int n, uint32_t* clear,
-                             int n_clear, hipStream_t st) {
+                             int dz_stride, int M, const int* lo, const int* hi, int reduce, float* outv, int n, hipStream_t st) {
   MemberRanges mr{};
   mr.M = M;
   for (int m = 0; m < M; ++m) { mr.lo[m] = lo[m]; mr.hi[m] = hi[m]; }
-  PIPE_KLAUNCH(asym_bias_members_kernel, dim3((std::max(n, n_clear) + 255) / 256), dim3(256), 0, st, bias, P, scale, scale_stride,
-               dz, dz_stride, mr, reduce, outv, n, clear, n_clear);
+  PIPE_KLAUNCH(asym_bias_members_kernel, dim3((n + 255) / 256), dim3(256), 0, st, bias, P, scale, scale_stride,
+               dz, dz_stride, mr, reduce, outv, n);
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
 }
