@@ -121,3 +121,29 @@ def test_quantizing_in_the_streaming_kernel_changes_nothing(pipe, T, I, bits, s_
         pipe.pipe_set_decode_fusion(True)
     assert torch.equal(y, ref)
     e.free()
+
+
+@pytest.mark.parametrize("T", [9, 100, 700])
+def test_hidden_maximum_wherever_it_lies(pipe, T):
+    """The hidden tensor's largest value in the first, a middle and the last tokens and channels (another workgroup and line of its
+    slot each time): the scale is that of the tensor, and the next call finds the slots cleared, also one of the other quantizer."""
+    I, H = 256, 1040
+    rng = np.random.default_rng(T)
+    W1 = _weight(T + 1, H, I)
+    l1, l2 = pipe.pipe_expand(dev(W1), 4, 4, 0.5, 16), pipe.pipe_expand(dev(_weight(T + 2, 64, H)), 4, 4, 0.5, 16)
+    x0 = rng.standard_normal((T, I)).astype(np.float32)
+    split, act = [2, 2], pipe.PIPE_ACT_GELU
+    asym = lambda: pipe.pipe_mlp_forward_asymmetric(l1, l2, act, dev(x0), split=split)
+    pipe.pipe_set_decode_resident(0)
+    try:
+        before = asym()
+        for t, c in ((0, 0), (T // 2, 517), (T - 1, H - 1), (T // 3, 300), (T - 1, 16)):
+            x = x0.copy()
+            x[t] = 4 * W1[c] / np.abs(W1[c]).max()      # the row of W1 it meets answers loudest or nearly so
+            y, h = pipe.pipe_mlp_forward(l1, l2, act, dev(x), s_x=0.05, split=split, return_hidden=True)
+            sh = [float(np.float32(h[m].abs().max().item()) / np.float32(127)) for m in range(2)]
+            assert torch.equal(y, pipe.pipe_mlp_forward_given_scales(l1, l2, act, dev(x), 0.05, sh, split=split))
+            assert torch.equal(before, asym())
+    finally:
+        pipe.pipe_set_decode_resident(1)
+    l1.free(), l2.free()
