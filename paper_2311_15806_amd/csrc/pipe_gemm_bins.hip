@@ -16,7 +16,8 @@
 // LDS reads and 8 loads per wave); 160 vector registers and 52 KB of LDS let three workgroups share a compute unit.
 // Measured against one pass per order (pipe_gemm.hip, same box): 11008 x 4096 ternary, K = 4, 4096 tokens 227 -> 203 us,
 // 333 tokens 62 -> 30 us; 3x3 convolution 256 x 256 of 6272 pixels, 4 bit, K = 3 35.5 -> 18.4 us; 3072 x 768 and back, 4 bit,
-// K = 3, 4096 tokens 81 -> 60 us; eight 2048 x 2048 ternary layers, two members of 4 orders, 4096 tokens 676 -> 591 us.
+// K = 3, 4096 tokens 81 -> 60 us; eight 2048 x 2048 ternary layers, two members of 4 orders, 4096 tokens 676 -> 591 us
+// (550 with the hidden maxima in eight lines).
 // One barrier per stage.  The LDS-direct loads are issued by hand (the compiler would make every LDS read wait for the
 // newest of them) and their waits are counted: a stage's loads are always CL codes, then XC activations.
 #include <type_traits>
