@@ -18,6 +18,12 @@ static thread_local std::string g_last_hip_error;
 
 void pipe_note_hip_error(hipError_t e, const char* what) {
   g_last_hip_error = std::string(hipGetErrorString(e)) + " in " + what;
+  (void)hipGetLastError();   // reported: a later launch's check must not find it again
+}
+
+bool pipe_hip_ok(hipError_t e, const char* what) {
+  if (e != hipSuccess) pipe_note_hip_error(e, what);
+  return e == hipSuccess;
 }
 
 extern "C" const char* pipe_last_device_error(void) { return g_last_hip_error.c_str(); }
@@ -494,7 +500,7 @@ extern "C" int pipe_expand_conv2d(const float* W_dev, int out, int C, int kh, in
   (void)hipFree(Wp);
   if (rc != PIPE_OK) return rc;
   e->conv_C = C; e->conv_kh = kh; e->conv_kw = kw;
-  if (hipMalloc(&e->conv_zero_dev, 256) != hipSuccess || hipMemset(e->conv_zero_dev, 0, 256) != hipSuccess) {
+  if (!pipe_hip_ok(hipMalloc(&e->conv_zero_dev, 256), "hipMalloc(zeros)") || !pipe_hip_ok(hipMemset(e->conv_zero_dev, 0, 256), "hipMemset(zeros)")) {
     free_expansion(e);
     return PIPE_ENOMEM;
   }
@@ -1058,7 +1064,7 @@ static int asym_prepare(const pipe_expansion* ce, hipStream_t st) {
   int8_t* tmp = nullptr;
   size_t max_rows = 0;
   for (auto& o : e->orders) max_rows = std::max(max_rows, (size_t)o.n_kept * e->group);
-  if (rc == PIPE_OK && hipMalloc(&tmp, max_rows * (size_t)e->in) != hipSuccess) rc = PIPE_ENOMEM;
+  if (rc == PIPE_OK && !pipe_hip_ok(hipMalloc(&tmp, max_rows * (size_t)e->in), "hipMalloc(codes)")) rc = PIPE_ENOMEM;
   for (int k = 0; k < e->K && rc == PIPE_OK; ++k) {
     const PipeOrder& o = e->orders[k];
     const int rows = o.n_kept * e->group;
@@ -1067,9 +1073,9 @@ static int asym_prepare(const pipe_expansion* ce, hipStream_t st) {
   }
   std::vector<int32_t> hw((size_t)e->K * out);
   std::vector<float> all((size_t)e->n_pos * 16), hC(out, 0.f), hP((size_t)e->K * out, 0.f);
-  if (rc == PIPE_OK && (hipStreamSynchronize(st) != hipSuccess ||
-                        hipMemcpy(hw.data(), wsum, hw.size() * sizeof(int32_t), hipMemcpyDeviceToHost) != hipSuccess ||
-                        hipMemcpy(all.data(), e->scales_all_dev, all.size() * sizeof(float), hipMemcpyDeviceToHost) != hipSuccess))
+  if (rc == PIPE_OK && (!pipe_hip_ok(hipStreamSynchronize(st), "code sums") ||
+                        !pipe_hip_ok(hipMemcpy(hw.data(), wsum, hw.size() * sizeof(int32_t), hipMemcpyDeviceToHost), "code sums") ||
+                        !pipe_hip_ok(hipMemcpy(all.data(), e->scales_all_dev, all.size() * sizeof(float), hipMemcpyDeviceToHost), "code sums")))
     rc = PIPE_EDEVICE;
   if (tmp) (void)hipFree(tmp);
   if (rc == PIPE_OK) {
@@ -1084,10 +1090,11 @@ static int asym_prepare(const pipe_expansion* ce, hipStream_t st) {
           hC[ch] += pk;
         }
     }
-    if (hipMalloc(&C, out * sizeof(float)) != hipSuccess || hipMalloc(&be, out * sizeof(float)) != hipSuccess ||
-        hipMalloc(&P, hP.size() * sizeof(float)) != hipSuccess ||
-        hipMemcpy(C, hC.data(), out * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(P, hP.data(), hP.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess)
+    const char* what = "sums of the codes";
+    if (!pipe_hip_ok(hipMalloc(&C, out * sizeof(float)), what) || !pipe_hip_ok(hipMalloc(&be, out * sizeof(float)), what) ||
+        !pipe_hip_ok(hipMalloc(&P, hP.size() * sizeof(float)), what) ||
+        !pipe_hip_ok(hipMemcpy(C, hC.data(), out * sizeof(float), hipMemcpyHostToDevice), what) ||
+        !pipe_hip_ok(hipMemcpy(P, hP.data(), hP.size() * sizeof(float), hipMemcpyHostToDevice), what))
       rc = PIPE_EDEVICE;
   }
   if (rc != PIPE_OK) {

@@ -225,6 +225,7 @@ __device__ __forceinline__ void slots_clear(uint32_t* slots, int n) {
 
 // ------------------------------------------------------------------ error plumbing
 void pipe_note_hip_error(hipError_t e, const char* what);
+bool pipe_hip_ok(hipError_t e, const char* what);   // notes an error; true if there is none
 #define PIPE_HIP(call)                                   \
   do {                                                   \
     hipError_t _e = (call);                              \

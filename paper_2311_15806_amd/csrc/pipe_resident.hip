@@ -877,9 +877,9 @@ int pipe_resident_tables(const pipe_expansion* ce, int kind, int G, ResidentTabl
   }
   int32_t *sd = nullptr, *ed = nullptr;
   PIPE_HIP(hipMalloc(&sd, subs.size() * 4));
-  if (hipMalloc(&ed, epi.size() * 4) != hipSuccess) { (void)hipFree(sd); return PIPE_ENOMEM; }
-  if (hipMemcpy(sd, subs.data(), subs.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(ed, epi.data(), epi.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
+  if (!pipe_hip_ok(hipMalloc(&ed, epi.size() * 4), "hipMalloc(units)")) { (void)hipFree(sd); return PIPE_ENOMEM; }
+  if (!pipe_hip_ok(hipMemcpy(sd, subs.data(), subs.size() * 4, hipMemcpyHostToDevice), "hipMemcpy(units)") ||
+      !pipe_hip_ok(hipMemcpy(ed, epi.data(), epi.size() * 4, hipMemcpyHostToDevice), "hipMemcpy(units)")) {
     (void)hipFree(sd); (void)hipFree(ed);
     return PIPE_EDEVICE;
   }
