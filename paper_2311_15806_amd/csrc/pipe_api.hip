@@ -50,6 +50,7 @@ extern "C" const char* pipe_strerror(int code) {
 // less than the live one.
 struct WsSet {
   PipeWorkspace slot[WS_SLOTS];
+  bool words_cleared = false;  // the control words (WS_SCAL) were set to zero
   bool slots_dirty = false;    // the members' max|h| or range slots hold a value no kernel will clear
 };
 static std::mutex g_ws_mu;
@@ -788,10 +789,13 @@ static int get_act_buffers(int T, int in_pad, bool small, ActBuffers* b) {
   b->T_pad = (int)round_up64(T, small ? 16 : TOK_TILE);
   b->qx = (uint8_t*)pipe_ws_get(WS_QX, (size_t)b->T_pad * in_pad);
   b->rowsum = (int32_t*)pipe_ws_get(WS_ROWSUM, (size_t)b->T_pad * 4);
-  const bool fresh = t_ws == nullptr || t_ws->slot[WS_SCAL].ptr == nullptr;
   uint8_t* sc = (uint8_t*)pipe_ws_get(WS_SCAL, 4096 + 2 * PIPE_MAX_PARTS * 4);
   if (!b->qx || !b->rowsum || !sc) return pipe_ws_error();
-  if (fresh) PIPE_HIP(hipMemset(sc, 0, 4096));   // never under capture: a fresh block is refused there
+  if (!t_ws->words_cleared) {
+    if (pipe_capturing()) return PIPE_ENOTREADY;
+    PIPE_HIP(hipMemset(sc, 0, 4096));
+    t_ws->words_cleared = true;
+  }
   b->amax = (uint32_t*)sc;
   b->scale = (float*)(sc + 1024);
   b->slots = (uint32_t*)(sc + 2048);

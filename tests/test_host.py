@@ -28,7 +28,18 @@ def failed_allocation_is_reported_once(rt):
     assert _linear(rt, e, 200) == 0
 
 
-@pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once"])
+def control_words_start_at_zero(rt):
+    """The stream's control words (among them the slots that kernels only ever raise) are cleared when they are allocated, also
+    by a call that then fails for want of another buffer."""
+    e = rt.expand(64, 64, 4, 2, 1.0, 16)
+    rt.host.host_fail(1)
+    assert _linear(rt, e, 200) == ENOMEM
+    rt.host.host_fail(0)
+    assert _linear(rt, e, 200) == 0
+    assert rt.names().count("hipMemset") == 1
+
+
+@pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
