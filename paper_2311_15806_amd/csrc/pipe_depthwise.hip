@@ -362,13 +362,11 @@ int launch_depthwise3(Dw3Params& p, int K, hipStream_t st) {
 
 }  // namespace
 
-int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st) {
-  if (e->dw_codes_dev != nullptr) return PIPE_OK;
+// Fills the tables of a depthwise layer, which the caller allocated
+static int build_tables(const pipe_expansion* e, int8_t* codes, float* scales, uint32_t* cols, hipStream_t st) {
   const size_t n_codes = (size_t)e->K * e->out * e->in;
-  PIPE_HIP(hipMalloc(&e->dw_codes_dev, n_codes));
-  PIPE_HIP(hipMalloc(&e->dw_scales_dev, (size_t)e->K * e->out * sizeof(float)));
-  PIPE_HIP(hipMemsetAsync(e->dw_codes_dev, 0, n_codes, st));
-  PIPE_HIP(hipMemsetAsync(e->dw_scales_dev, 0, (size_t)e->K * e->out * sizeof(float), st));
+  PIPE_HIP(hipMemsetAsync(codes, 0, n_codes, st));
+  PIPE_HIP(hipMemsetAsync(scales, 0, (size_t)e->K * e->out * sizeof(float), st));
   for (int k = 0; k < e->K; ++k) {
     const PipeOrder& o = e->orders[k];
     const int rows = o.n_kept * e->group;
@@ -378,15 +376,37 @@ int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st) {
     int rc = launch_unpack_codes(e->codes_dev, o.pos_dev, e->bits, rows, e->in, e->in_pad, tmp, st);
     if (rc) return rc;
     PIPE_KLAUNCH(dense_order_kernel, dim3(rows), dim3(64), 0, st, tmp, e->scales_all_dev, o.pos_dev, o.gids_dev,
-                       e->group, e->in, e->out, e->dw_codes_dev + (size_t)k * e->out * e->in, e->dw_scales_dev + (size_t)k * e->out);
+                       e->group, e->in, e->out, codes + (size_t)k * e->out * e->in, scales + (size_t)k * e->out);
     PIPE_HIP(hipGetLastError());
   }
-  if (e->in == 9) {
-    PIPE_HIP(hipMalloc(&e->dw_cols_dev, (size_t)e->K * 3 * e->out * sizeof(uint32_t)));
-    PIPE_KLAUNCH(pack_columns_kernel, dim3(ceil_div(e->K * 3 * e->out, 256)), dim3(256), 0, st, e->dw_codes_dev, e->K, e->out, e->dw_cols_dev);
+  if (cols != nullptr) {
+    PIPE_KLAUNCH(pack_columns_kernel, dim3(ceil_div(e->K * 3 * e->out, 256)), dim3(256), 0, st, codes, e->K, e->out, cols);
     PIPE_HIP(hipGetLastError());
   }
   PIPE_HIP(hipStreamSynchronize(st));   // the scratch rows are reused by other calls
+  return PIPE_OK;
+}
+
+// The expansion holds all of a layer's tables or none: a call that fails on the way leaves nothing for the next to find.
+int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st) {
+  if (e->dw_codes_dev != nullptr) return PIPE_OK;
+  if (pipe_capturing()) return PIPE_ENOTREADY;   // allocates and synchronizes: run the call once outside capture
+  int8_t* codes = nullptr;
+  float* scales = nullptr;
+  uint32_t* cols = nullptr;
+  const char* what = "hipMalloc(depthwise tables)";
+  int rc = pipe_hip_ok(hipMalloc(&codes, (size_t)e->K * e->out * e->in), what) &&
+           pipe_hip_ok(hipMalloc(&scales, (size_t)e->K * e->out * sizeof(float)), what) &&
+           (e->in != 9 || pipe_hip_ok(hipMalloc(&cols, (size_t)e->K * 3 * e->out * sizeof(uint32_t)), what)) ? PIPE_OK : PIPE_ENOMEM;
+  if (rc == PIPE_OK) rc = build_tables(e, codes, scales, cols, st);
+  if (rc != PIPE_OK) {
+    (void)hipStreamSynchronize(st);   // what was launched has ended
+    if (codes) (void)hipFree(codes);
+    if (scales) (void)hipFree(scales);
+    if (cols) (void)hipFree(cols);
+    return rc;
+  }
+  e->dw_codes_dev = codes; e->dw_scales_dev = scales; e->dw_cols_dev = cols;
   return PIPE_OK;
 }
 
@@ -421,7 +441,7 @@ int launch_depthwise(const pipe_expansion* e, const int8_t* q8, const float* s_x
 bool pipe_depthwise_fused(const pipe_expansion* e, int kh, int kw, int stride, int M, int N, int Ho, int Wo) {
   // (the grid: image x row band x column tile, at least 3 output rows a band, 16 columns a tile)
   const int64_t tiles = (int64_t)N * ceil_div(Ho, 3) * ceil_div(Wo, 16);
-  return kh == 3 && kw == 3 && (stride == 1 || stride == 2) && M == 1 && e->K <= 4 && tiles < ((int64_t)1 << 31) && e->out <= 64 * 65535;
+  return e->dw_cols_dev != nullptr && kh == 3 && kw == 3 && (stride == 1 || stride == 2) && M == 1 && e->K <= 4 && tiles < ((int64_t)1 << 31) && e->out <= 64 * 65535;
 }
 
 int launch_depthwise_fused(const pipe_expansion* e, const float* x, float s_static, MaxOf amax, float qmax, int N, int C, int H, int W,

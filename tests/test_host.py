@@ -39,7 +39,50 @@ def control_words_start_at_zero(rt):
     assert rt.names().count("hipMemset") == 1
 
 
-@pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero"])
+def _depthwise(rt, e, N=2, Ch=32, H=6, W=6, k=3, nhwc=0, x=1 << 40, y=1 << 44):
+    rt.lib.pipe_forward_depthwise2d.argtypes = ([C.c_void_p] * 2 + [C.c_int] * 9 + [C.c_float, C.c_void_p, C.c_int, C.c_void_p, C.c_int] +
+                                                [C.c_void_p] * 2)
+    return rt.lib.pipe_forward_depthwise2d(e, x, N, Ch, H, W, k, k, 1, k // 2, nhwc, 0.0, None, 0, None, 1, y, None)
+
+
+def failed_preparation_starts_over(rt):
+    """Whichever allocation of the preparation fails, the call after it builds every table before the layer reads them."""
+    for k in (3, 5):
+        whole = ["dense_order_kernel"] * 2 + (["pack_columns_kernel"] if k == 3 else [])
+        nth, failures = 1, 0
+        while True:
+            e = rt.expand(32, k * k, 4, 2, 1.0, 16)
+            rt.host.host_fail(nth)
+            rc = _depthwise(rt, e, k=k)
+            rt.host.host_fail(0)
+            names = rt.names()
+            if rc == 0:
+                break
+            failures += 1
+            assert not any("depthwise" in n for n in names)
+            assert _depthwise(rt, e, k=k) == 0
+            built = [w for n in rt.names() for w in ("dense_order_kernel", "pack_columns_kernel") if w in n]
+            assert built == whole, (k, nth, built)
+            assert _depthwise(rt, e, k=k) == 0
+            assert not any(w in n for n in rt.names() for w in whole)      # built once
+            nth += 1
+        assert failures >= (3 if k == 3 else 2)
+
+
+def capture_builds_nothing(rt):
+    """Under capture an unprepared layer is refused before anything is allocated; afterwards it is prepared as if never called."""
+    e = rt.expand(32, 9, 4, 2, 1.0, 16)
+    rt.host.host_capture(1)
+    rt.host.host_fail(0)
+    assert _depthwise(rt, e) == ENOTREADY
+    assert rt.host.host_mallocs() == 0 and rt.names() == []
+    rt.host.host_capture(0)
+    assert _depthwise(rt, e) == 0
+    assert sum("dense_order_kernel" in n for n in rt.names()) == 2
+
+
+@pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
+                                      "failed_preparation_starts_over", "capture_builds_nothing"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
