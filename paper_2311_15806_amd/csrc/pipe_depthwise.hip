@@ -4,6 +4,7 @@
 // on the vector ALUs: a thread owns one (pixel, channel), reads its window once and applies
 // every stored order of the channel to it.  Arithmetic as everywhere: exact integer sums,
 // fp32 sum over the orders of a member in ascending order, activation scale, bias.
+#include <algorithm>
 #include <type_traits>
 
 #include "pipe_codes.h"
@@ -25,42 +26,47 @@ __global__ void dense_order_kernel(const int8_t* __restrict__ rows_codes, const 
   if (threadIdx.x == 0) scales_k[o] = scales_all[(size_t)pos[r >> 4] * 16 + (r & 15)];
 }
 
-// fp32 [N,C,H,W] -> int8 codes [N,H,W,C]: 32 channels x 32 pixels per workgroup through LDS, so
-// that reads run along the pixels and writes along the channels
-__global__ __launch_bounds__(256) void quantize_to_nhwc_kernel(const float* __restrict__ x, int C, int HW, float s_static,
+// fp32 [N,C,H,W] -> int8 codes [N,H,W,C]: 32 channels x 32 pixels at a time through LDS, so that reads run along the pixels
+// and writes along the channels.  A workgroup takes the same tile of one image after another, the next one's values
+// requested ahead: it finds the scale once for all of them (32768 images of 32 x 2 x 2, the whole layer 49.3 -> 34.7 us).
+constexpr int NHWC_BLOCKS = 4096;
+__global__ __launch_bounds__(256) void quantize_to_nhwc_kernel(const float* __restrict__ x, int N, int C, int HW, float s_static,
                                                                MaxOf amax, float qmax,
                                                                int8_t* __restrict__ q8, float* __restrict__ scale_out) {
-  __shared__ int8_t tile[32][33];
-  __shared__ float smax[4];
-  float s = s_static;
-  if (!(s_static > 0.f)) {
-    float m = 0.f;
-    for (int i = threadIdx.x; i < amax.n; i += 256) m = fmaxf(m, __uint_as_float(amax.p[i]));
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) smax[threadIdx.x >> 6] = m;
-    __syncthreads();
-    s = __fdiv_rn(fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3])), qmax);
-  }
-  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && scale_out) *scale_out = s;
-  const int n = blockIdx.z, c0 = blockIdx.y * 32, p0 = blockIdx.x * 32;
+  __shared__ int8_t tile[2][32][33];
+  const int c0 = blockIdx.y * 32, p0 = blockIdx.x * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
+  const float* src = x + (size_t)blockIdx.z * C * HW + (size_t)(c0 + ty) * HW + p0 + tx;
+  int8_t* dst = q8 + (size_t)blockIdx.z * C * HW + (size_t)(p0 + ty) * C + c0 + tx;
+  const size_t step = (size_t)gridDim.z * C * HW;
+  float xv[4];
+  auto load = [&]() {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int c = c0 + ty + 8 * j, pp = p0 + tx;
-    int v = 0;
-    if (c < C && pp < HW && s > 0.f) {
-      float q = rintf(__fdiv_rn(x[((size_t)n * C + c) * HW + pp], s));
-      q = fminf(fmaxf(q, -qmax), qmax);
-      v = (int)q;
-    }
-    tile[ty + 8 * j][tx] = (int8_t)v;
-  }
-  __syncthreads();
+    for (int j = 0; j < 4; ++j)
+      if (c0 + ty + 8 * j < C && p0 + tx < HW) xv[j] = src[(size_t)(8 * j) * HW];
+  };
+  load();
+  const float s = s_static > 0.f ? s_static : __fdiv_rn(max_of(amax), qmax);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && scale_out) *scale_out = s;
+  const Divisor d(s);
+  int buf = 0;
+  for (int left = (N - 1 - (int)blockIdx.z) / (int)gridDim.z; left >= 0; --left) {
+    auto put = [&](auto fast) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int pp = p0 + ty + 8 * j, c = c0 + tx;
-    if (c < C && pp < HW) q8[((size_t)n * HW + pp) * C + c] = tile[tx][ty + 8 * j];
+      for (int j = 0; j < 4; ++j)
+        if (c0 + ty + 8 * j < C && p0 + tx < HW)
+          tile[buf][ty + 8 * j][tx] = s > 0.f ? (int8_t)(int)fminf(fmaxf(rintf(d.quotient<decltype(fast)::value>(xv[j])), -qmax), qmax) : (int8_t)0;
+    };
+    if (d.fast) put(std::true_type{});
+    else put(std::false_type{});
+    src += step;
+    if (left > 0) load();
+    __syncthreads();   // (before anyone writes the other buffer again, everyone has read it and come here)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (c0 + tx < C && p0 + ty + 8 * j < HW) dst[(size_t)(8 * j) * C] = tile[buf][tx][ty + 8 * j];
+    dst += step;
+    buf ^= 1;
   }
 }
 
@@ -412,7 +418,9 @@ int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st) {
 
 int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static, MaxOf amax, float qmax,
                             int8_t* q8, float* scale_out, hipStream_t st) {
-  PIPE_KLAUNCH(quantize_to_nhwc_kernel, dim3(ceil_div(HW, 32), ceil_div(C, 32), N), dim3(256), 0, st, x, C, HW, s_static,
+  const int64_t tiles = (int64_t)ceil_div(HW, 32) * ceil_div(C, 32);
+  const int images = (int)std::min<int64_t>(N, std::max<int64_t>(1, std::min<int64_t>(NHWC_BLOCKS / tiles, 65535)));
+  PIPE_KLAUNCH(quantize_to_nhwc_kernel, dim3(ceil_div(HW, 32), ceil_div(C, 32), images), dim3(256), 0, st, x, N, C, HW, s_static,
                      amax, qmax, q8, scale_out);
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;

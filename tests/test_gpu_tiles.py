@@ -107,6 +107,20 @@ def test_fused_depthwise_at_its_tile_edges(pipe, N, C, H, W, stride, pad, bits, 
     e.free()
 
 
+@pytest.mark.parametrize("N,C,H,W", [(5000, 48, 3, 3), (70000, 16, 1, 1), (9, 80, 20, 33), (300, 32, 30, 41)])
+@pytest.mark.parametrize("s_x", [0.0, 0.02])
+def test_many_maps_channels_first(pipe, N, C, H, W, s_x):
+    """More tiles than the turning quantizer has workgroups, more images than a grid has rows, partial tiles: the layer on a
+    channels-first input equals the one on the same input channels last, which no tile turns."""
+    e = pipe.pipe_expand(dev(np.random.default_rng(C).standard_normal((C, 9)).astype(np.float32)), 4, 2, 0.5, 16)
+    x = torch.randn((N, H, W, C), generator=torch.Generator().manual_seed(N))
+    kw = dict(s_x=s_x, split=[1, 1], reduce_members=False)   # (two members: never the fused kernel)
+    last = pipe.pipe_forward_depthwise2d(e, x.cuda(), 3, 3, 1, 1, nhwc=True, **kw)
+    first = pipe.pipe_forward_depthwise2d(e, x.permute(0, 3, 1, 2).contiguous().cuda(), 3, 3, 1, 1, **kw)
+    assert torch.equal(first, last)
+    e.free()
+
+
 @pytest.mark.parametrize("T,I,bits,s_x", [(16, 256, 8, 0.0), (15, 200, 4, 0.0), (5, 768, 2, 0.02), (2, 1020, 4, 0.0), (1, 4096, 2, 0.0),
                                           (1, 8192, 4, 0.0), (16, 4, 8, 0.0), (4, 1024, 3, 0.0)])
 def test_quantizing_in_the_streaming_kernel_changes_nothing(pipe, T, I, bits, s_x):
