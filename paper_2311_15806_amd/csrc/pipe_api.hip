@@ -1391,7 +1391,7 @@ extern "C" int pipe_forward_depthwise2d(const pipe_expansion* e, const float* x_
   const int64_t n = (int64_t)N * C * H * W;
   // (the fused kernel reads x while others already write y: an output that overlaps the input keeps the two-step path)
   const uintptr_t x0 = reinterpret_cast<uintptr_t>(x_dev), y0 = reinterpret_cast<uintptr_t>(y_dev);
-  const bool fused = pipe_depthwise_fused(e, kh, kw, stride, Mm, N, Ho, Wo) &&
+  const bool fused = pipe_depthwise_fused(e, x_dev, kh, kw, stride, Mm, N, W, nhwc, Ho, Wo) &&
                      (x0 + (size_t)n * sizeof(float) <= y0 || y0 + (size_t)N * Ho * Wo * C * sizeof(float) <= x0);
   int8_t* q8 = fused ? nullptr : (int8_t*)pipe_ws_get(WS_Q8X, (size_t)n);
   if (!fused && !q8) return pipe_ws_error();

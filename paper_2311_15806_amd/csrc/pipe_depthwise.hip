@@ -179,11 +179,17 @@ struct Dw3Params {
   int bands, x_tiles;
 };
 
+// output rows and columns (at most) of a workgroup
+constexpr int dw3_rows(int stride) { return stride == 1 ? 6 : 3; }
+constexpr int dw3_columns(int stride) { return stride == 1 ? 32 : 16; }
+// the input can be read 16 bytes at a time (C is a multiple of 16)
+inline bool dw3_wide(const float* x, int W, int nhwc) { return (nhwc || W % 4 == 0) && (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
+
 template <int STRIDE, int K>
 __global__ __launch_bounds__(BLK) void depthwise3_kernel(const Dw3Params p) {
   constexpr int ND = 2, R = 4 * ND;                        // input rows held (16 rows: 25.8 us against 23.7 on the layer above)
-  constexpr int RB = STRIDE == 1 ? R - 2 : (R - 1) / 2;    // output rows
-  constexpr int XT = STRIDE == 1 ? 32 : 16;                // output columns, at most
+  constexpr int RB = dw3_rows(STRIDE), XT = dw3_columns(STRIDE);
+  static_assert((RB - 1) * STRIDE + 3 <= R, "rows held");
   constexpr int COLS = (XT - 1) * STRIDE + 3;
   constexpr int PITCH = 65;                                // dwords per (column, 4 rows): 64 channels, rotated over the banks
   __shared__ uint32_t tile[COLS * ND * PITCH];
@@ -352,9 +358,8 @@ __global__ __launch_bounds__(BLK) void depthwise3_kernel(const Dw3Params p) {
 
 template <int STRIDE>
 int launch_depthwise3(Dw3Params& p, int K, hipStream_t st) {
-  constexpr int RB = STRIDE == 1 ? 6 : 3, XT = STRIDE == 1 ? 32 : 16;   // as in the kernel
-  p.bands = ceil_div(p.Ho, RB);
-  p.x_tiles = ceil_div(p.Wo, XT);
+  p.bands = ceil_div(p.Ho, dw3_rows(STRIDE));
+  p.x_tiles = ceil_div(p.Wo, dw3_columns(STRIDE));
   const dim3 grid((unsigned)(p.N * p.bands * p.x_tiles), (unsigned)ceil_div(p.C, 64));
   switch (K) {
     case 1: PIPE_KLAUNCH((depthwise3_kernel<STRIDE, 1>), grid, dim3(BLK), 0, st, p); break;
@@ -446,10 +451,20 @@ int launch_depthwise(const pipe_expansion* e, const int8_t* q8, const float* s_x
   return PIPE_OK;
 }
 
-bool pipe_depthwise_fused(const pipe_expansion* e, int kh, int kw, int stride, int M, int N, int Ho, int Wo) {
-  // (the grid: image x row band x column tile, at least 3 output rows a band, 16 columns a tile)
-  const int64_t tiles = (int64_t)N * ceil_div(Ho, 3) * ceil_div(Wo, 16);
-  return e->dw_cols_dev != nullptr && kh == 3 && kw == 3 && (stride == 1 || stride == 2) && M == 1 && e->K <= 4 && tiles < ((int64_t)1 << 31) && e->out <= 64 * 65535;
+// A workgroup of the fused kernel costs nearly as much for a few outputs as for all it has room for (64 channels, 6 or 3 rows, 32
+// or 16 columns), while the two-step path runs through the pixels in full waves: many small images, or few channels of them, are
+// quicker in two steps.  The lines by outputs a workgroup, 2049 to 24000 workgroups, 16 to 960 channels, 4 bit, K = 3, fused time
+// over two-step time: channels last 0.44 to 1.04 from 1024 on (784 outputs of 32 x 7 x 7: up to 1.12, 256 of 64 x 2 x 2: 1.78);
+// channels first with 16-byte rows, which two steps have to turn, 0.45 to 0.96 from 576 on (512 of 16 x 8 x 8: 1.46); element by
+// element 0.63 to 0.96 from 1536 on (1045 of 16 x 14 x 14: 1.58).  Up to 2048 workgroups the chip is not full and the
+// launch that is saved decides (0.41 to 1.02).
+bool pipe_depthwise_fused(const pipe_expansion* e, const float* x, int kh, int kw, int stride, int M, int N, int W, int nhwc, int Ho, int Wo) {
+  if (e->dw_cols_dev == nullptr || kh != 3 || kw != 3 || (stride != 1 && stride != 2) || M != 1 || e->K > 4) return false;
+  const int C = e->out, groups = ceil_div(C, 64);
+  const int64_t images = (int64_t)N * ceil_div(Ho, dw3_rows(stride)) * ceil_div(Wo, dw3_columns(stride));   // grid x
+  if (images >= (int64_t)1 << 24 || groups > 65535) return false;   // a launch holds fewer than 2^32 threads along x
+  const int64_t enough = !dw3_wide(x, W, nhwc) ? 1536 : (nhwc ? 1024 : 576);
+  return images * groups <= 2048 || (int64_t)N * Ho * Wo * C >= enough * images * groups;
 }
 
 int launch_depthwise_fused(const pipe_expansion* e, const float* x, float s_static, MaxOf amax, float qmax, int N, int C, int H, int W,
@@ -458,6 +473,6 @@ int launch_depthwise_fused(const pipe_expansion* e, const float* x, float s_stat
   p.x = x; p.amax = amax; p.s_static = s_static; p.qmax = qmax;
   p.codes = e->dw_cols_dev; p.scales = e->dw_scales_dev; p.bias = bias; p.y = y;
   p.N = N; p.C = C; p.H = H; p.W = W; p.Ho = Ho; p.Wo = Wo; p.pad = pad; p.nhwc = nhwc;
-  p.vec = (nhwc || W % 4 == 0) && (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? 1 : 0;   // (C is a multiple of 16)
+  p.vec = dw3_wide(x, W, nhwc) ? 1 : 0;
   return stride == 1 ? launch_depthwise3<1>(p, e->K, st) : launch_depthwise3<2>(p, e->K, st);
 }

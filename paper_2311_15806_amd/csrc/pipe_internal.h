@@ -421,8 +421,9 @@ int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static
 int launch_depthwise(const pipe_expansion* e, const int8_t* q8, const float* s_x, int N, int C, int H, int W, int kh, int kw,
                      int stride, int pad, int Ho, int Wo, int M, const int* lo, const int* hi,
                      const float* bias, int reduce, float* y, hipStream_t st);   // q8 channels last
-// 3 x 3, stride 1 or 2, one member of at most 4 orders: quantizer and layer in one launch, from the fp32 input
-bool pipe_depthwise_fused(const pipe_expansion* e, int kh, int kw, int stride, int M, int N, int Ho, int Wo);
+// 3 x 3, stride 1 or 2, one member of at most 4 orders: quantizer and layer in one launch, from the fp32 input, where that is
+// the quicker way
+bool pipe_depthwise_fused(const pipe_expansion* e, const float* x, int kh, int kw, int stride, int M, int N, int W, int nhwc, int Ho, int Wo);
 int launch_depthwise_fused(const pipe_expansion* e, const float* x, float s_static, MaxOf amax, float qmax, int N, int C, int H, int W,
                            int stride, int pad, int nhwc, int Ho, int Wo, const float* bias, float* y, hipStream_t st);
 extern float g_act_qmax_host;   // the activation quantizer's largest code (host copy of the device constant)

@@ -81,8 +81,32 @@ def capture_builds_nothing(rt):
     assert sum("dense_order_kernel" in n for n in rt.names()) == 2
 
 
+def any_number_of_images_is_served(rt):
+    """Many small maps: more images than a launch of one workgroup each can hold, and numbers where two steps are quicker."""
+    e = {c: rt.expand(c, 9, 4, 2, 1.0, 16) for c in (16, 32, 64)}
+
+    def fused(C, N, H, nhwc, x=1 << 40):
+        assert _depthwise(rt, e[C], N=N, Ch=C, H=H, W=H, nhwc=nhwc, x=x) == 0, (C, N, H, nhwc)
+        names = rt.names()
+        one = any("depthwise3_kernel" in n for n in names)
+        assert one != any("depthwise_kernel" in n for n in names)
+        return one
+
+    assert not fused(16, 1 << 24, 1, 1)      # more workgroups than a launch can hold
+    assert not fused(16, 1 << 22, 7, 1)
+    assert not fused(16, 100000, 1, 0)       # (channels first: more images than a grid has rows)
+    assert not fused(64, 65536, 1, 1)        # few outputs a workgroup
+    assert not fused(16, 5349, 7, 0)
+    assert not fused(32, 14563, 3, 0)
+    assert fused(16, 100, 1, 1)              # few workgroups: one launch less
+    for nhwc in (0, 1):
+        assert fused(64, 512, 28, nhwc)
+        assert fused(32, 600, 28, nhwc, x=(1 << 40) + 4)
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
-                                      "failed_preparation_starts_over", "capture_builds_nothing"])
+                                      "failed_preparation_starts_over", "capture_builds_nothing",
+                                      "any_number_of_images_is_served"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
