@@ -485,7 +485,9 @@ int pipe_set_token_tile(int tokens);
 int pipe_set_stream_split(int workgroups_per_bin);
 
 /* A single token (pipe_forward, and layer 1 of pipe_mlp_forward, on a layer of at
- * most 8192 input features, a multiple of 4, 16-byte aligned input) and up to 16 tokens of at most 4096 codes together:
+ * most 8192 input features, a multiple of 4, 16-byte aligned input), and up to 16 tokens of at most 4096 codes together (a token
+ * counts its features rounded up to a multiple of 256) on a layer of at most 1024 workgroups (65536 stored
+ * rows, or fewer where row blocks do not fill them):
  * by default the weight-streaming kernel quantizes the
  * input itself -- every workgroup reduces max|x| and rounds the few KiB of activations
  * with the quantizer's own arithmetic -- so the step is one launch instead of two.

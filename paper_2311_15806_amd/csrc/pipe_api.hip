@@ -859,6 +859,7 @@ static bool fuse_decode_quant(const pipe_expansion* e, int T, const float* x_dev
   const uintptr_t o0 = reinterpret_cast<uintptr_t>(out_dev), o1 = o0 + out_floats * sizeof(float);
   const bool apart = x1 <= o0 || o1 <= x0;
   return small && g_decode_fusion && T <= 16 && T * e->in_pad <= (T == 1 ? PIPE_FUSED_QUANT_MAX_1 : PIPE_FUSED_QUANT_MAX) &&
+         (T == 1 || e->n_bins <= PIPE_FUSED_QUANT_BINS) &&
          e->in % 4 == 0 && (x0 & 15) == 0 && e->bin_cap == 4 && apart;
 }
 

@@ -81,6 +81,16 @@ def capture_builds_nothing(rt):
     assert sum("dense_order_kernel" in n for n in rt.names()) == 2
 
 
+def wide_layers_quantize_once(rt):
+    """Few tokens: the streaming kernel quantizes them itself unless too many of its workgroups would repeat the work."""
+    for rows, one_launch in ((65536, True), (65552, False)):     # 1024 and 1025 bins
+        e = rt.expand(rows, 64, 8, 1, 1.0, 16)
+        assert _linear(rt, e, 2) == 0
+        assert not any("quantize_small" in n for n in rt.names()) == one_launch
+        assert _linear(rt, e, 1) == 0                              # a single token: always
+        assert not any("quantize_small" in n for n in rt.names())
+
+
 def any_number_of_images_is_served(rt):
     """Many small maps: more images than a launch of one workgroup each can hold, and numbers where two steps are quicker."""
     e = {c: rt.expand(c, 9, 4, 2, 1.0, 16) for c in (16, 32, 64)}
@@ -106,7 +116,7 @@ def any_number_of_images_is_served(rt):
 
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
-                                      "any_number_of_images_is_served"])
+                                      "any_number_of_images_is_served", "wide_layers_quantize_once"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
