@@ -76,6 +76,19 @@ __device__ __forceinline__ T pick(const T (&a)[PIPE_MAX_K], int k) {
   return v;
 }
 
+// The sum over a wave whose lanes are all active, by data-parallel moves within the vector unit
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+__device__ __forceinline__ int wave_sum(int v) {
+  v = dpp_add<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8: the last lane of 16 holds their sum
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);   // row_bcast 15, 31: lane 63 holds the wave's
+  v = dpp_add<0x143, 0xc>(v);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
 __device__ __forceinline__ float gelu_erf(float a) {
   return 0.5f * a * (1.f + erff(a * 0.70710678118654752440f));
 }
@@ -242,20 +255,26 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       const float q = fminf(fmaxf(rintf(__fdiv_rn(v, s_act)), -p.act_qmax), p.act_qmax);
       return live_q ? (int)q : 0;
     };
+    int sum_1 = 0;   // a single token: one sum per wave at the end
     for (int i = threadIdx.x; i < n4; i += NW * 64) {
       const float4 v = x4[i];
       const int tq = (i * 4) / in, k = i * 4 - tq * in;   // in is a multiple of 4: one token per float4
       const int a = q1(v.x), b = q1(v.y), c = q1(v.z), d = q1(v.w);
       *reinterpret_cast<uint32_t*>(&s_qx[(size_t)tq * in_pad_q + k]) =
           (uint32_t)(uint8_t)a | ((uint32_t)(uint8_t)b << 8) | ((uint32_t)(uint8_t)c << 16) | ((uint32_t)(uint8_t)d << 24);
-      int sum4 = a + b + c + d;
-      if (in % 256 == 0) {   // a wave's 64 quads lie in one row
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum4 += __shfl_xor(sum4, o, 64);
-        if (lane == 0) atomicAdd(&s_rs[tq], sum4);
+      const int sum4 = a + b + c + d;
+      if (p.T == 1) {
+        sum_1 += sum4;
+      } else if (in % 256 == 0) {   // a wave's 64 quads lie in one row
+        const int sum = wave_sum(sum4);
+        if (lane == 0) atomicAdd(&s_rs[tq], sum);
       } else if (sum4 != 0) {
         atomicAdd(&s_rs[tq], sum4);
       }
+    }
+    if (p.T == 1) {
+      const int sum = wave_sum(sum_1);
+      if (lane == 0) atomicAdd(&s_rs[0], sum);
     }
     // codes beyond in_features are zero
     const int pad4 = (in_pad_q - in) >> 2;

@@ -122,7 +122,7 @@ def test_many_maps_channels_first(pipe, N, C, H, W, s_x):
 
 
 @pytest.mark.parametrize("T,I,bits,s_x", [(16, 256, 8, 0.0), (15, 200, 4, 0.0), (5, 768, 2, 0.02), (2, 1020, 4, 0.0), (1, 4096, 2, 0.0),
-                                          (1, 8192, 4, 0.0), (16, 4, 8, 0.0), (4, 1024, 3, 0.0)])
+                                          (1, 8192, 4, 0.0), (1, 68, 4, 0.0), (16, 4, 8, 0.0), (4, 1024, 3, 0.0)])
 def test_quantizing_in_the_streaming_kernel_changes_nothing(pipe, T, I, bits, s_x):
     """Few codes: one launch instead of two, bit for bit (rows whose quads fill a wave and rows that do not)."""
     e = pipe.pipe_expand(dev(_weight(T * I, 112, I)), bits, 2, 1.0, 16)
