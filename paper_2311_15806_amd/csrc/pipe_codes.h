@@ -4,7 +4,7 @@
 #pragma once
 #include "pipe_internal.h"
 
-constexpr int CODES_BLK = 256;   // workgroup size that block_max assumes
+constexpr int CODES_BLK = 256;   // workgroup size that block_max and max_of assume
 
 __device__ __forceinline__ float block_max(float v) {
   __shared__ float sm[CODES_BLK / 64];
@@ -38,12 +38,25 @@ __device__ __forceinline__ float wave_max(float v) {
 
 // The value of a slot, by a whole wave
 __device__ __forceinline__ float slot_max(const uint32_t* slot) {
-  return wave_max(__uint_as_float(slot[(threadIdx.x & (PIPE_SLOT_LINES - 1)) * PIPE_SLOT_WORDS]));
+  float m = __uint_as_float(slot[(threadIdx.x & (PIPE_SLOT_LINES - 1)) * PIPE_SLOT_WORDS]);
+#pragma unroll
+  for (int o = PIPE_SLOT_LINES / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  return m;
 }
 
-// The value of a max reduction: the largest of its parts.  Every wave finds it for itself, all parts requested together: no
-// barrier (128 images of 64 x 56 x 56, 1 x 1 convolution: 148 us with a reduction over the workgroup, 145 with this one).
+// The value of a max reduction: the largest of its parts.  Called by all threads of a workgroup.
 __device__ __forceinline__ float max_of(const MaxOf& a) {
+  if (a.n == 0) return slot_max(a.p);
+  if (a.n == 1) return __uint_as_float(a.p[0]);
+  float m = 0.f;
+  for (int i = threadIdx.x; i < a.n; i += CODES_BLK) m = fmaxf(m, __uint_as_float(a.p[i]));
+  return block_max(m);
+}
+
+// The same found by every wave for itself, all parts requested together, no barrier: for kernels of short workgroups that have
+// registers to spare (128 images of 64 x 56 x 56, 1 x 1 convolution: 148 us with the reduction over the workgroup, 145 with this one; the
+// linear layers' quantizer, with eight loads of x in flight, would drop from five waves per SIMD to four).
+__device__ __forceinline__ float max_of_by_wave(const MaxOf& a) {
   if (a.n == 0) return slot_max(a.p);
   if (a.n == 1) return __uint_as_float(a.p[0]);
   const int lane = threadIdx.x & 63;

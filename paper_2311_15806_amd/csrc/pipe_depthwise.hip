@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void quantize_to_nhwc_kernel(const float* __re
       if (c0 + ty + 8 * j < C && p0 + tx < HW) xv[j] = src[(size_t)(8 * j) * HW];
   };
   load();
-  const float s = s_static > 0.f ? s_static : __fdiv_rn(max_of(amax), qmax);
+  const float s = s_static > 0.f ? s_static : __fdiv_rn(max_of_by_wave(amax), qmax);
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && scale_out) *scale_out = s;
   const Divisor d(s);
   int buf = 0;

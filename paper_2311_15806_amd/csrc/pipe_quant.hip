@@ -658,7 +658,7 @@ __global__ __launch_bounds__(BLK) void quantize_nhwc_sums_kernel(const float* __
     const int c = nhwc ? c0 + tx : c0 + ty + 8 * j, pp = nhwc ? p0 + ty + 8 * j : p0 + tx;
     xv[j] = c < C && pp < HW ? x[nhwc ? ((size_t)n * HW + pp) * C + c : ((size_t)n * C + c) * HW + pp] : 0.f;
   }
-  const float s = act_scale(s_static, amax);
+  const float s = s_static > 0.f ? s_static : __fdiv_rn(max_of_by_wave(amax), c_act_qmax);
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && scale_out) *scale_out = s;
   const SymCodes cd(s);
   int qv[4];
