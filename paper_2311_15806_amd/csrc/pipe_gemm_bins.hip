@@ -5,14 +5,16 @@
 // All orders of a row block multiply the same Q(x), so a wave takes a bin of 4 stored row blocks ("items") that holds
 // EVERY order of its 1 to 4 output row blocks, and a tile is 4 such bins (the 4 waves) against 16*MTB tokens.  One walk
 // along k per tile, whatever the orders:
-//   - every tile costs the same, so nothing waits for the tile with the most orders;
+//   - tiles differ by a quarter at most, so nothing waits for the tile with the most orders: 4 items are multiplied where a bin
+//     of the tile has 4, 3 where none has more (a third of the work of dense layers of 3 orders: 11008 x 2048 ternary, 4096 tokens 266 ->
+//     235 us), and none at all where every bin holds row blocks that its member pruned, which only get their bias;
 //   - the activations of a tile are fetched once, not once per order;
 //   - no fp32 running sum lives through the loop: int32 accumulators only, the orders are folded behind it.
 // Data paths of a stage (SK 64-k steps, one or two packed code tiles per item):
 //   - packed codes: L2 -> registers, 16 bytes per lane, requested two stages ahead (three register sets), widened to int8
 //     between the MFMAs of the item before;
 //   - activations: L2 -> LDS without passing through registers, already in the MFMA operand layout, three slots.
-// Bound by the matrix pipe and the issue slots around it (a stage of 64 tokens: 64 MFMAs against 112 unpack instructions, 20
+// Bound by the matrix pipe and the issue slots around it (a ternary stage of 64 tokens: 64 MFMAs against 112 unpack instructions, 16
 // LDS reads and 8 loads per wave); 160 vector registers and 52 KB of LDS let three workgroups share a compute unit.
 // Measured against one pass per order (pipe_gemm.hip, same box): 11008 x 4096 ternary, K = 4, 4096 tokens 227 -> 203 us,
 // 333 tokens 62 -> 30 us; 3x3 convolution 256 x 256 of 6272 pixels, 4 bit, K = 3 35.5 -> 18.4 us; 3072 x 768 and back, 4 bit,
@@ -56,6 +58,7 @@ struct BinsParams {
   long long res_mstride;
   int res_members, res_pre_act;
   int hidden;                     // MODE_GATED: rows are gate [0,H) and up [H,2H), y is [M,T,H]
+  int three;                      // 1: tiles of 3 items walk with 3
   TileOrder order;
   const int8_t* cq8;              // CONV (implicit GEMM), as in pipe_gemm.hip
   const int32_t* ccsum;
@@ -102,7 +105,6 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   constexpr int SK = BITS == 2 || MTB == 1 ? 4 : 2;   // 64-k steps per stage
   constexpr int XC = MTB * SK / 4;                    // activation fragments (1 KiB) a wave loads per stage
   constexpr int WN = Codes<BITS, SK>::N;
-  constexpr int CL = 4 * WN;                          // code loads of a wave per stage
   constexpr int SLOT = MTB * SK * 1024;               // bytes of a stage's activations
   static_assert(TOK_TILE % (16 * MTB) == 0, "token tile");
   static_assert(RING == 3, "register sets of codes");
@@ -129,7 +131,8 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   const int pos[4] = {pos4[0], pos4[1], pos4[2], pos4[3]};
   const int rb[4] = {rb4[0], rb4[1], rb4[2], rb4[3]};
   const int m = info[0], ends = info[1], ups = info[2];   // member; items that end a row block; items of an up block
-  const bool active = info[3] != 0;
+  const bool active = info[3] & 1;
+  const int tile_items = info[3] >> 1;                    // items that any bin of the tile multiplies: 4, 3 or none
 
   // ---- load cursor: the stage requested next; behind the last one it stays there (those loads are never used)
   const int n_stage = p.nks / SK;
@@ -176,11 +179,12 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
     }
     l_slot = l_slot == (RING - 1) * SLOT ? 0 : l_slot + SLOT;
   };
-  auto wload = [&](Codes<BITS, SK>(&w)[4]) __attribute__((always_inline)) {
+  auto wload = [&](auto& w) __attribute__((always_inline)) {
+    constexpr int NI = (int)std::extent<std::remove_reference_t<decltype(w)>>::value;
     unsigned off = lane * 16;
     asm volatile("" : "+v"(off));   // a 32-bit offset next to the loads: they take the scalar base + offset form
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < NI; ++r)
 #pragma unroll
       for (int q = 0; q < WN; ++q) w[r].v[q] = gload16(l_wb[r] + l_w + q * 1024 + off);
   };
@@ -216,99 +220,114 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
     if (p.bias != nullptr) dma4(p.bias + (size_t)m * p.bias_mstride + br + (lane & 15), lds_addr(&lds.bias[wave][0]));
     if (OFF && !CONV) dma4(p.rowsum + (size_t)m * p.rowsum_mstride + min(t0 + lane, p.T_pad - 1), lds_addr(&lds.rs[wave][0]));
   }
-  Codes<BITS, SK> w0[4], w1[4], w2[4];
-  wload(w0);
-  __builtin_amdgcn_sched_barrier(0);
-  xload();
-  __builtin_amdgcn_sched_barrier(0);
-  advance();
-  wload(w1);
-  __builtin_amdgcn_sched_barrier(0);
-  xload();
-  __builtin_amdgcn_sched_barrier(0);
-  advance();
   const float sx = p.s_x[m * p.sx_mstride];
-  if constexpr (OFF != 0 && CONV) {
-    // token code sum = the channel sums of the window's pixels that lie inside the image
-    const int t = t0 + min(lane, 16 * MTB - 1);
-    const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
-    const int h0 = ho * p.cstride - p.cpad, w0_ = wo * p.cstride - p.cpad;
-    int sum = 0;
-    if (t < p.T)
-      for (int r = 0; r < p.ckh; ++r)
-        for (int q = 0; q < p.ckw; ++q)
-          if ((unsigned)(h0 + r) < (unsigned)p.cH && (unsigned)(w0_ + q) < (unsigned)p.cW)
-            sum += p.ccsum[(img * p.cH + h0 + r) * p.cW + w0_ + q];
-    lds.rs[wave][lane] = sum;
-  }
+  auto window_sums = [&]() __attribute__((always_inline)) {
+    if constexpr (OFF != 0 && CONV) {
+      // token code sum = the channel sums of the window's pixels that lie inside the image
+      const int t = t0 + min(lane, 16 * MTB - 1);
+      const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
+      const int h0 = ho * p.cstride - p.cpad, w0_ = wo * p.cstride - p.cpad;
+      int sum = 0;
+      if (t < p.T)
+        for (int r = 0; r < p.ckh; ++r)
+          for (int q = 0; q < p.ckw; ++q)
+            if ((unsigned)(h0 + r) < (unsigned)p.cH && (unsigned)(w0_ + q) < (unsigned)p.cW)
+              sum += p.ccsum[(img * p.cH + h0 + r) * p.cW + w0_ + q];
+      lds.rs[wave][lane] = sum;
+    }
+  };
 
   v4i acc[4][MTB];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int b = 0; b < MTB; ++b) acc[r][b] = v4i{0, 0, 0, 0};
-  unsigned c_slot = 0;
 
-  // One stage.  `cur` and the ring slot c_slot hold its codes and activations, requested two stages ago; `far` is
-  // free (multiplied in the stage before) and takes the codes of the stage after next.
-  auto stage = [&](Codes<BITS, SK>(&cur)[4], Codes<BITS, SK>(&far)[4], bool multiply) __attribute__((always_inline)) {
-    // this stage's codes have arrived: the wait the compiler places here leaves the newest loads in flight
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int q = 0; q < WN; ++q) asm volatile("" : "+v"(cur[r].v[q]));
-    // ... and so have this wave's activations of the stage (all but the CL + XC loads behind them)
-    __builtin_amdgcn_s_waitcnt(wait_imm(CL + XC, 0));
-    asm volatile("s_barrier" ::: "memory");    // everyone's have, and the slot of the stage before is free
-    wload(far);
+  // ---- the walk along k with the first NI items of every bin of the tile
+  auto walk = [&](auto ni) __attribute__((always_inline)) {
+    constexpr int NI = decltype(ni)::value;
+    constexpr int CL = NI * WN;                         // code loads of a wave per stage
+    Codes<BITS, SK> w0[NI], w1[NI], w2[NI];
+    wload(w0);
     __builtin_amdgcn_sched_barrier(0);
     xload();
     __builtin_amdgcn_sched_barrier(0);
     advance();
-    if (multiply) {
-      // Software pipeline of the SK 64-k steps: a wave issues in order, so everything that is not an MFMA has to sit in
-      // the shadow of one.  The fragments of step j+1 are requested before step j's MFMAs start (two register
-      // sets), and the codes of item r+1 are widened between the MFMAs of item r (two register sets).
-      const v4i* xs = reinterpret_cast<const v4i*>(lds.xs) + c_slot / 16 + lane;
-      v4i xf[2][MTB];
-      v4i wf[2];
+    wload(w1);
+    __builtin_amdgcn_sched_barrier(0);
+    xload();
+    __builtin_amdgcn_sched_barrier(0);
+    advance();
+    window_sums();
+    unsigned c_slot = 0;
+
+    // One stage.  `cur` and the ring slot c_slot hold its codes and activations, requested two stages ago; `far` is
+    // free (multiplied in the stage before) and takes the codes of the stage after next.
+    auto stage = [&](Codes<BITS, SK>(&cur)[NI], Codes<BITS, SK>(&far)[NI], bool multiply) __attribute__((always_inline)) {
+      // this stage's codes have arrived: the wait the compiler places here leaves the newest loads in flight
 #pragma unroll
-      for (int b = 0; b < MTB; ++b) xf[0][b] = xs[b * SK * FRAG];
-      wf[0] = widen<BITS, SK>(cur[0], 0);
+      for (int r = 0; r < NI; ++r)
 #pragma unroll
-      for (int j = 0; j < SK; ++j) {
-        if (j + 1 < SK) {
+        for (int q = 0; q < WN; ++q) asm volatile("" : "+v"(cur[r].v[q]));
+      // ... and so have this wave's activations of the stage (all but the CL + XC loads behind them)
+      __builtin_amdgcn_s_waitcnt(wait_imm(CL + XC, 0));
+      asm volatile("s_barrier" ::: "memory");    // everyone's have, and the slot of the stage before is free
+      wload(far);
+      __builtin_amdgcn_sched_barrier(0);
+      xload();
+      __builtin_amdgcn_sched_barrier(0);
+      advance();
+      if (multiply) {
+        // Software pipeline of the SK 64-k steps: a wave issues in order, so everything that is not an MFMA has to sit in
+        // the shadow of one.  The fragments of step j+1 are requested before step j's MFMAs start (two register
+        // sets), and the codes of item r+1 are widened between the MFMAs of item r (two register sets).
+        const v4i* xs = reinterpret_cast<const v4i*>(lds.xs) + c_slot / 16 + lane;
+        v4i xf[2][MTB];
+        v4i wf[2];
 #pragma unroll
-          for (int b = 0; b < MTB; ++b) xf[(j + 1) & 1][b] = xs[(b * SK + j + 1) * FRAG];
-        }
+        for (int b = 0; b < MTB; ++b) xf[0][b] = xs[b * SK * FRAG];
+        wf[0] = widen<BITS, SK>(cur[0], 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (r + 1 < 4) wf[(r + 1) & 1] = widen<BITS, SK>(cur[r + 1], j);
-          else if (j + 1 < SK) wf[(r + 1) & 1] = widen<BITS, SK>(cur[0], j + 1);
+        for (int j = 0; j < SK; ++j) {
+          if (j + 1 < SK) {
 #pragma unroll
-          for (int b = 0; b < MTB; ++b)
-            acc[r][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[r & 1], xf[j & 1][b], acc[r][b], 0, 0, 0);
-          if (BITS != 8) {
-            // one MFMA, then some of the unpack instructions, and so on
-#pragma unroll
-            for (int b = 0; b < MTB; ++b) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-              __builtin_amdgcn_sched_group_barrier(0x002, 8 / MTB, 0);
-            }
+            for (int b = 0; b < MTB; ++b) xf[(j + 1) & 1][b] = xs[(b * SK + j + 1) * FRAG];
           }
-          __builtin_amdgcn_sched_barrier(0);   // keep the items apart: bounds live registers
+#pragma unroll
+          for (int r = 0; r < NI; ++r) {
+            const int n = j * NI + r;   // item-steps so far: the register set of this one's codes
+            if (r + 1 < NI) wf[(n + 1) & 1] = widen<BITS, SK>(cur[r + 1], j);
+            else if (j + 1 < SK) wf[(n + 1) & 1] = widen<BITS, SK>(cur[0], j + 1);
+#pragma unroll
+            for (int b = 0; b < MTB; ++b)
+              acc[r][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[n & 1], xf[j & 1][b], acc[r][b], 0, 0, 0);
+            if (BITS != 8) {
+              // one MFMA, then some of the unpack instructions, and so on
+#pragma unroll
+              for (int b = 0; b < MTB; ++b) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 8 / MTB, 0);
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);   // keep the items apart: bounds live registers
+          }
         }
       }
+      c_slot = c_slot == (RING - 1) * SLOT ? 0 : c_slot + SLOT;
+    };
+    // Three stages a round, so every register set keeps its role and the ring has one exit (the compiler counts
+    // outstanding loads exactly then); behind the last stage the rest of the round multiplies nothing.
+    for (int s = 0; s < n_stage; s += RING) {
+      stage(w0, w2, active);
+      stage(w1, w0, active && s + 1 < n_stage);
+      stage(w2, w1, active && s + 2 < n_stage);
     }
-    c_slot = c_slot == (RING - 1) * SLOT ? 0 : c_slot + SLOT;
   };
-  // Three stages a round, so every register set keeps its role and the ring has one exit (the compiler counts
-  // outstanding loads exactly then); behind the last stage the rest of the round multiplies nothing.
-  for (int s = 0; s < n_stage; s += RING) {
-    stage(w0, w2, active);
-    stage(w1, w0, active && s + 1 < n_stage);
-    stage(w2, w1, active && s + 2 < n_stage);
-  }
+  // (64 tokens of the ternary convolution: a second loop would spill; chain layers: see launch_gemm_bins)
+  constexpr bool THREE = !(CONV && SK * MTB == 16) && MODE != MODE_CHAIN;
+  if (tile_items == 0) window_sums();
+  else if (THREE && tile_items == 3 && p.three) walk(std::integral_constant<int, THREE ? 3 : 4>{});
+  else walk(std::integral_constant<int, 4>{});
   // the ring's last loads write into this workgroup's LDS and registers: they end here
   __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
   asm volatile("" ::: "memory");
@@ -471,6 +490,12 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
   p.codes = e->codes_dev; p.scales = e->scales_all_dev; p.bins = tb->bins_dev;
   p.bias = a.bias; p.bias_mstride = a.bias_mstride; p.y = a.y; p.amax_out = a.amax_out; p.amax_neg = a.amax_neg;
   p.zero_after = a.zero_after; p.zero_n = a.zero_n; p.zero_big = a.zero_big; p.zero_big_n = a.zero_big_n;
+  // The shorter walk of tiles with 3 items pays wherever they are the rule, and for plain and gate||up layers also next to tiles of
+  // 4 (4096 x 4096 4 bit, K = 4, half the groups kept, 4096 tokens: 174.7 -> 161 us a call; gate||up 22016 x 4096, 2048 tokens, the
+  // MLP 665 -> 641).  GELU layers lose by the mixture (768 x 3072 and back, K = 3, half the groups kept, 4096 tokens 81.5 -> 82.6;
+  // all kept 104.8 -> 97.4), and the chains' layers by any (eight 2048 x 2048 ternary layers, two members of 4 orders, 2000 tokens 404 ->
+  // 439 us; five, K = 3, all kept, 1000 tokens 145 -> 155): they walk with 4.
+  p.three = a.act != PIPE_ACT_GELU || tb->n_four * 8 <= tb->n_three;
   p.T = a.T; p.T_pad = a.T_pad; p.out = e->out; p.nks = e->nks;
   p.apart = !a.reduce; p.fold_sx = a.reduce && a.M > 1; p.act = a.act;
   p.res = a.res; p.res_mstride = a.res_mstride; p.res_members = a.res_members; p.res_pre_act = a.res_pre_act;

@@ -58,7 +58,11 @@ int hipMalloc(void** p, size_t n) {
   return *p ? 0 : (last = 2);
 }
 int hipFree(void* p) { free(p); return 0; }
-int hipMemcpy(void* d, const void* s, size_t n, int k) { (void)k; memcpy(d, s, n); return 0; }
+int hipMemcpy(void* d, const void* s, size_t n, int k) {
+  memcpy(d, s, n);
+  if (k == 1 && on_launch) on_launch("hipMemcpy", (uint32_t)n, 1, 1, 1, &d);   /* to the device */
+  return 0;
+}
 int hipMemcpyAsync(void* d, const void* s, size_t n, int k, void* st) { (void)k; (void)st; memcpy(d, s, n); return 0; }
 int hipMemcpyToSymbol(const void* d, const void* s, size_t n, size_t o, int k) { (void)d; (void)s; (void)n; (void)o; (void)k; return 0; }
 int hipMemset(void* d, int v, size_t n) {
@@ -93,12 +97,16 @@ class Runtime:
         self.host.host_mallocs.restype = C.c_long
         self.lib = C.CDLL(LIB)
         self.launches = []
+        self.copied = []        # what was copied to the device synchronously (tables), in order
         self.kept = []          # what the next expansion's orders keep: lists of groups, order 2 first
         self._cb = C.CFUNCTYPE(None, C.c_char_p, *[C.c_uint32] * 4, C.POINTER(C.c_void_p))(self._launched)
         self.host.host_set(self._cb)
 
     def _launched(self, name, gx, gy, gz, block, args):
         name = name.decode()
+        if name == "hipMemcpy":
+            self.copied.append(C.string_at(args[0], gx))
+            return
         self.launches.append((name, (gx, gy, gz), block))
         if "group_compact_kernel" in name:      # the selection's last launch (flags, groups, kept groups): the test's choice
             gids = C.cast(args[2], C.POINTER(C.POINTER(C.c_int32)))[0]

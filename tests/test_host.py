@@ -91,6 +91,67 @@ def wide_layers_quantize_once(rt):
         assert not any("quantize_small" in n for n in rt.names())
 
 
+def single_pass_tables_hold_no_needless_items(rt):
+    """The bins of the single-pass kernel: every order of every row block once, adjacent and ascending; and the items that its tiles
+    multiply (four bins, each as many as the fullest) exceed the stored row blocks only where a pair or a row block of three
+    orders leaves no other choice -- not by the row blocks that a member pruned."""
+    import random
+    rng = random.Random(5)
+    #         rows  K  kept of the groups, split, gated, items multiplied per stored row block at most
+    for rows, K, part, split, gated, most in ((4096, 4, 4, [2, 2], 0, 1.01), (4096, 8, 8, [2, 2, 2, 2], 0, 1.01), (4096, 2, 4, [1, 1], 0, 1.01),
+                                              (4096, 3, 1, [3], 0, 1.01), (2048, 4, 2, [4], 0, 1.05), (4096, 8, 4, [3, 3, 2], 0, 1.01),
+                                              (4096, 4, 4, [2, 2], 1, 1.2), (4096, 8, 8, [2, 2, 2, 2], 1, 1.35), (48, 4, 3, [1, 3], 0, 9)):
+        n_rb = rows // 16
+        kept = [sorted(rng.sample(range(n_rb), n_rb // part)) if part > 1 else list(range(n_rb)) for _ in range(K - 1)]
+        e = rt.expand(rows, 64, 4, K, 1.0 / part, 16, kept=kept if part > 1 else ())
+        rt.copied.clear()
+        rt.lib.pipe_prepare.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p]
+        rt.lib.pipe_prepare_mlp.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_int, C.c_void_p]
+        arr = (C.c_int * len(split))(*split)
+        if gated:
+            l2 = rt.expand(64, rows // 2, 4, K, 1.0, 16)
+            rt.copied.clear()
+            assert rt.lib.pipe_prepare_mlp(e, l2, 2, arr, len(split), 200, None) == 0
+        else:
+            assert rt.lib.pipe_prepare(e, arr, len(split), 200, None) == 0
+        raw = (C.c_int32 * (len(rt.copied[0]) // 4)).from_buffer_copy(rt.copied[0])
+        bins = [raw[i:i + 16] for i in range(0, len(raw), 16)]          # pos, scale pos, row block, {member, ends, ups, live | items << 1}
+        orders_of = [[0] + [k + 1 for k in range(K - 1) if part == 1 or rb in kept[k]] for rb in range(n_rb)]
+        first = [sum(split[:m]) for m in range(len(split))]
+        seen, stored, multiplied = {}, 0, 0
+        assert len(bins) % 4 == 0
+        zero = max(p for b in bins for p in b[4:8])                      # the all-zero position is the last
+        for c in range(0, len(bins), 4):
+            tile = bins[c:c + 4]
+            items = tile[0][15] >> 1
+            assert items in (0, 3, 4) and all(b[15] >> 1 == items for b in tile)
+            multiplied += 4 * items
+            for b in tile:
+                scaled = [q for q in range(4) if b[4 + q] != zero]
+                assert (b[15] & 1) == (len(scaled) > 0) and all(q < items for q in scaled)
+                assert all(b[q] == b[4 + q] for q in scaled)             # an item's codes and scales
+                run = []
+                for q in range(4):
+                    if b[4 + q] != zero:
+                        run.append(b[4 + q])
+                    if (b[13] >> q) & 1:
+                        key = (b[12], b[8 + q], (b[14] >> q) & 1)
+                        assert key not in seen
+                        seen[key] = run
+                        stored += len(run)
+                        run = []
+                assert run == []
+        for m, size in enumerate(split):
+            for rb in range(n_rb):
+                u, up = (rb % (n_rb // 2), rb // (n_rb // 2)) if gated else (rb, 0)
+                want = [k for k in orders_of[rb] if first[m] <= k < first[m] + size]
+                got = seen.pop((m, u, up))
+                assert len(got) == len(want) == len(set(got)), (rows, m, rb)
+        assert seen == {}
+        assert stored == sum(len(o) for o in orders_of)
+        assert multiplied <= most * stored, (rows, K, part, split, gated, multiplied, stored)
+
+
 def any_number_of_images_is_served(rt):
     """Many small maps: more images than a launch of one workgroup each can hold, and numbers where two steps are quicker."""
     e = {c: rt.expand(c, 9, 4, 2, 1.0, 16) for c in (16, 32, 64)}
@@ -116,7 +177,8 @@ def any_number_of_images_is_served(rt):
 
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
-                                      "any_number_of_images_is_served", "wide_layers_quantize_once"])
+                                      "any_number_of_images_is_served", "wide_layers_quantize_once",
+                                      "single_pass_tables_hold_no_needless_items"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
