@@ -85,7 +85,8 @@ DEPTHWISE = [(2, 16, 1, 1, 1, 1, 8, 1), (3, 80, 7, 7, 1, 1, 4, 2), (1, 64, 13, 3
 
 @pytest.mark.parametrize("N,C,H,W,stride,pad,bits,K", DEPTHWISE)
 def test_fused_depthwise_at_its_tile_edges(pipe, N, C, H, W, stride, pad, bits, K):
-    """Partial channel groups, row bands and column tiles, windows wholly in the padding, all three ways the input is read."""
+    """Partial channel groups, row bands and column tiles, windows wholly in the padding, all four ways the input is read (16 bytes
+    at a time or element by element, channels first or last); an output that overlaps the input, which takes two steps."""
     from oracle import pipe_oracle as po
     rng = np.random.default_rng(C + W)
     Wt = rng.standard_normal((C, 9)).astype(np.float32)
@@ -104,6 +105,15 @@ def test_fused_depthwise_at_its_tile_edges(pipe, N, C, H, W, stride, pad, bits, 
         xs = buf[1:].view(N, C, H, W)
         xs.copy_(dev(x))
         assert torch.equal(y, pipe.pipe_forward_depthwise2d(e, xs, 3, 3, stride, pad, s_x=s_x, bias=dev(b)))
+        xs = buf[1:].view(N, H, W, C)
+        xs.copy_(dev(x.transpose(0, 2, 3, 1)))
+        assert torch.equal(y, pipe.pipe_forward_depthwise2d(e, xs, 3, 3, stride, pad, nhwc=True, s_x=s_x, bias=dev(b)))
+        both = torch.empty(max(x.size, y.numel()), dtype=torch.float32, device="cuda")
+        both[:x.size].view(N, H, W, C).copy_(dev(x.transpose(0, 2, 3, 1)))
+        bias = dev(b)
+        assert pipe._lib.pipe_forward_depthwise2d(e.handle, both.data_ptr(), N, C, H, W, 3, 3, stride, pad, 1, float(s_x), None, 0,
+                                                  bias.data_ptr(), 1, both.data_ptr(), pipe._stream()) == 0
+        assert torch.equal(y, both[:y.numel()].view_as(y))
     e.free()
 
 
