@@ -84,6 +84,17 @@ def parse():
     return ap.parse_args()
 
 
+def tiled_kernels(cfg):
+    """The contraction kernels of a workload's layers above 128 tokens: one pass where a member has at most 4 orders (a gate and its
+    up block 2), pass by pass otherwise and where members with inputs of their own are summed (the last layer of an ensemble)."""
+    M, K = len(cfg.split), cfg.layers[0].K
+    one_pass = max(cfg.split) <= (2 if cfg.kind == "mlp_gated" else 4)
+    if cfg.kind in ("linear", "conv2d"):
+        return "gemm_bins_kernel" if K <= 4 else "gemm_tiled_kernel"
+    names = ["gemm_bins_kernel" if one_pass else "gemm_tiled_kernel", "gemm_bins_kernel" if M == 1 and K <= 4 else "gemm_tiled_kernel"]
+    return " + ".join(dict.fromkeys(names))
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -311,7 +322,7 @@ def main():
     if mfma_bound:
         roofline = dict(bound="mfma", achieved=head["kernel_eff_tops"], peak=INT8_MFMA_PEAK_TOPS, unit="TOP/s",
                         frac=(head["kernel_eff_tops"] or 0) / INT8_MFMA_PEAK_TOPS, traffic=None,
-                        kernel="gemm_bins_kernel", kernel_ms=head["kernel_ms_per_step"],
+                        kernel=tiled_kernels(cfg), kernel_ms=head["kernel_ms_per_step"],
                         step_achieved=head["eff_tops"], step_frac=head["eff_tops"] / INT8_MFMA_PEAK_TOPS)
     else:
         roofline = dict(bound="hbm", achieved=head["kernel_gbs"], peak=HBM_PEAK_GBS, unit="GB/s",

@@ -1,8 +1,10 @@
 // Expanded depthwise convolution (App. H: a convolution whose filters see one input channel;
 // the separable blocks of MobileNet / EfficientNet).  Not a dense contraction: every output is
-// kh*kw multiply-adds per order, so the layer is bound by reading Q(x) and writing y, and runs
-// on the vector ALUs: a thread owns one (pixel, channel), reads its window once and applies
-// every stored order of the channel to it.  Arithmetic as everywhere: exact integer sums,
+// kh*kw multiply-adds per order, so the layer is bound by reading the input and writing y, and runs
+// on the vector ALUs.  Two ways: depthwise3_kernel (3 x 3, one member of at most 4 orders, images that fill its
+// workgroups) quantizes the fp32 input into LDS and multiplies a window column's three taps at once; everything else takes two launches,
+// codes channels last first, then depthwise_kernel, whose thread owns one pixel and 4 channels, reads its window once and
+// applies every stored order to it.  Arithmetic as everywhere: exact integer sums,
 // fp32 sum over the orders of a member in ascending order, activation scale, bias.
 #include <algorithm>
 #include <type_traits>

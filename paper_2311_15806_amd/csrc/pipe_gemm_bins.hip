@@ -507,7 +507,9 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
   // Token-tile height: 64 tokens amortize the unpacking of the codes best (the 4096-token layer above: 203, 245 and 317 us
   // with 64, 32 and 16), and a second tile on a compute unit costs less than twice one; so the tallest that still gives
   // three quarters of the 256 compute units a tile (256 tokens of that layer, 304 tiles of 64: 29.4, 27.2 and 29.1 us; 129
-  // tokens: 22 us each).
+  // tokens: 22 us each).  Around the line of 192 tiles the choice is within 7 % of the best height for the 3 x 3 convolution 256 x 256 4 bit,
+  // K = 3 (147 tiles of 64: 17.8 against 17.5 us; 196: 18.1 and 18.0) and for layers of 3072 x 768, 1024 x 1024 and 4096 x 4096 at 2, 4
+  // and 8 bits; far below it 16 tokens lose to 32 by up to a quarter at 8 bits (128 x 128 convolution of 4704 pixels, K = 2: 14.0 and 11.0 us).
   int mtb = g_tiled_mtb;
   if (mtb != 1 && mtb != 2 && mtb != 4) {
     auto tiles = [&](int tokens) { return (int64_t)tb->n_ct * ceil_div(a.T, tokens); };

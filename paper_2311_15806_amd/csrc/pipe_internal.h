@@ -183,14 +183,14 @@ struct pipe_expansion {
 // PIPE_SLOT_WORDS words, each with all the slots of a call; a workgroup raises the line of its XCD, the value is the largest
 // of the lines.  Accesses of many waves to one line are served one after another (atomics about 10 ns each: 4096 of them
 // added 40 us to a 23-us kernel), so a wave first reads the slot and sends the atomic only if it would raise the value.  Those
-// device-coherent reads queue up as well where thousands of waves end within a few microseconds: with one line the
-// hidden layers of the eight 2048 x 2048 ternary layers, two members, 4096 tokens cost 775 us together, with eight 682.
+// device-coherent reads queue up as well where thousands of waves end within a few microseconds: a whole pass
+// through the eight 2048 x 2048 ternary layers, two members, 4096 tokens took 777 us with one line and 698 with eight.
 constexpr int PIPE_SLOT_LINES = 8;
 constexpr int PIPE_SLOT_WORDS = 64;   // 256 bytes: the lines lie on different channels
 #if defined(__HIPCC__)
 // Requests every 64-byte line of the kernel's arguments at once.  An eagerly launched kernel's arguments lie in host memory
 // (the runtime's default): each line's first use costs a trip there, one after the other, and some are first used in
-// the epilogue (a token of the 11008 x 4096 ternary layer 13.1 -> 12.7 us a call).  Only for kernels that need nearly all of
+// the epilogue (one token into 11008 to 32000 channels: 0 to 6 % of a call, 2 % on average, no more than the spread on 11008 x 4096 ternary).  Only for kernels that need nearly all of
 // them at once: a two-layer MLP at 35 tokens, whose launches use few of the lines, lost 5 of 30 us to the trips.
 template <int BYTES>
 __device__ __forceinline__ void request_arguments() {
@@ -316,7 +316,7 @@ int launch_asym_bias(const float* bias, const float* C, const float* scale, cons
                      hipStream_t st);
 int launch_asym_acc_fix(int32_t* acc, const int32_t* wsum, const int32_t* dz, int K, int T, int out, hipStream_t st);
 // member chains with asymmetric codes: per-member offset vectors [M][n] (reduce = 0; the bias joins member 0) or their
-// sum plus the bias [n] (reduce = 1) from P[k][o] = s_k[o] * sum_i q_k[o,i]; clears n_clear words at `clear`
+// sum plus the bias [n] (reduce = 1) from P[k][o] = s_k[o] * sum_i q_k[o,i]
 struct MemberRanges {
   int M;
   int lo[PIPE_MAX_K], hi[PIPE_MAX_K];
@@ -462,4 +462,4 @@ extern int g_resident_spin_limit;    // polls of a grid-wide wait before a workg
 extern unsigned long long* g_resident_trace;   // profiling buffer of the resident kernel, or nullptr
 extern int g_tiled_mtb;       // token blocks per tile of the tiled kernel; 0 = automatic
 extern int g_stream_ksplit;   // workgroups per bin of the streaming kernel; 0 = automatic
-extern int g_decode_fusion;   // 1: batches of at most 4 tokens are quantized inside the streaming kernel
+extern int g_decode_fusion;   // 1: few tokens of few codes (PIPE_FUSED_QUANT_MAX and the lines beside it) are quantized inside the streaming kernel
