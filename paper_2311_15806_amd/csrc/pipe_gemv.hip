@@ -89,10 +89,6 @@ __device__ __forceinline__ int wave_sum(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
-__device__ __forceinline__ float gelu_erf(float a) {
-  return 0.5f * a * (1.f + erff(a * 0.70710678118654752440f));
-}
-
 template <int BITS>
 __device__ __forceinline__ void unpack_step(const uint4& w, int j, v4i& o) {
   if (BITS == 8) {

@@ -420,7 +420,6 @@ __global__ __launch_bounds__(BLK) void mlp_act_kernel(const float* __restrict__ 
   float* dst = h + (size_t)m * n;
   float mx = 0.f, mn = 0.f;
   const bool two_sided = amax_neg != nullptr;
-  auto gelu1 = [](float a) { return 0.5f * a * (1.f + erff(a * 0.70710678118654752440f)); };
   auto gate1 = [](float gte, float up) { return gte / (1.f + expf(-gte)) * up; };
   auto take = [&](float v) { mx = fmaxf(mx, two_sided ? v : fabsf(v)); mn = fmaxf(mn, -v); };
   if ((H & 3) == 0 && ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0) {
@@ -437,7 +436,7 @@ __global__ __launch_bounds__(BLK) void mlp_act_kernel(const float* __restrict__ 
         v = make_float4(gate1(g.x, u.x), gate1(g.y, u.y), gate1(g.z, u.z), gate1(g.w, u.w));
       } else {
         const float4 a = s4[i];
-        v = make_float4(gelu1(a.x), gelu1(a.y), gelu1(a.z), gelu1(a.w));
+        v = make_float4(gelu_erf(a.x), gelu_erf(a.y), gelu_erf(a.z), gelu_erf(a.w));
       }
       d4[i] = v;
       take(v.x); take(v.y); take(v.z); take(v.w);
@@ -450,7 +449,7 @@ __global__ __launch_bounds__(BLK) void mlp_act_kernel(const float* __restrict__ 
         const int c = (int)(i - t * H);
         v = gate1(src[t * O1 + c], src[t * O1 + H + c]);
       } else {
-        v = gelu1(src[i]);
+        v = gelu_erf(src[i]);
       }
       dst[i] = v;
       take(v);

@@ -81,10 +81,6 @@ struct ResParams {
 
 static_assert(sizeof(ResParams) <= 3584, "kernel arguments are limited to 4 KiB");
 
-__device__ __forceinline__ float gelu_erf_r(float a) {
-  return 0.5f * a * (1.f + erff(a * 0.70710678118654752440f));
-}
-
 template <int BITS>
 __device__ __forceinline__ void unpack_step_r(const uint4& w, int j, v4i& o) {
   if (BITS == 8) {
@@ -672,7 +668,7 @@ __global__ __launch_bounds__(RES_THREADS, 1) void chain_resident_kernel(const Re
               yacc = 0.f;
               const float rsum = rsv[o][e_reduce ? 0 : m];
               if (e_pre) v += rsum;
-              if (e_act == PIPE_ACT_GELU) v = gelu_erf_r(v);
+              if (e_act == PIPE_ACT_GELU) v = gelu_erf(v);
               else if (e_act == PIPE_ACT_RELU) v = fmaxf(v, 0.f);
               if (!e_pre) v += rsum;
               vout[o][e_reduce ? 0 : m] = v;

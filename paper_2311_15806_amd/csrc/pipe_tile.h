@@ -6,10 +6,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float gelu_erf(float a) {
-  return 0.5f * a * (1.f + erff(a * 0.70710678118654752440f));
-}
-
 // One 64-k step of packed codes as int8 MFMA operand: 8-bit codes are the operand, a 4-bit step is two dwords (lo, hi),
 // a ternary one a single dword (lo).
 __device__ __forceinline__ v4i widen4(uint32_t lo, uint32_t hi) {

@@ -171,3 +171,54 @@ def test_hidden_maximum_wherever_it_lies(pipe, T):
     finally:
         pipe.pipe_set_decode_resident(1)
     l1.free(), l2.free()
+
+
+#            O     I    bits K gamma split   T  act: three or four workgroups of 64-token tiles share a compute unit (256 of them assumed)
+OCCUPANCY = [(4096, 256, 2, 1, 1.0, [1], 4096, "plain"),     # 1024 tiles: one round of four
+             (4096, 64, 4, 1, 1.0, [1], 4095, "plain"),      # an odd number of stages, a ragged last tile
+             (4096, 320, 4, 1, 1.0, [1], 3072, "plain"),     # 768: one round of three
+             (4096, 200, 2, 2, 0.5, [1, 1], 3000, "plain"),  # members apart, pruned row blocks
+             (4112, 260, 4, 1, 1.0, [1], 4000, "gelu"), (4096, 260, 2, 1, 1.0, [1], 3100, "gelu"), (4128, 130, 4, 2, 0.5, [2], 4095, "gated")]
+
+
+@pytest.mark.parametrize("O,I,bits,K,gamma,split,T,act", OCCUPANCY)
+def test_workgroups_per_unit_change_nothing(pipe, O, I, bits, K, gamma, split, T, act):
+    """Many 64-token tiles, served by the variant with one register set of fragments or by the one with two: 32-token tiles (other
+    loops) give the same bits."""
+    rng = np.random.default_rng(O + T)
+    l1 = pipe.pipe_expand(dev(_weight(O + I, O, I)), bits, K, gamma, 16)
+    x = dev(rng.standard_normal((T, I)).astype(np.float32))
+    b = dev(rng.standard_normal(O).astype(np.float32))
+    if act == "plain":
+        call = lambda: pipe.pipe_forward(l1, x, s_x=0.03, split=split, bias=b, reduce_members=len(split) == 1)
+    else:
+        l2 = pipe.pipe_expand(dev(_weight(O, 16, O if act == "gelu" else O // 2)), bits, K, gamma, 16)
+        kind = pipe.PIPE_ACT_GELU if act == "gelu" else pipe.PIPE_ACT_SILU_GATED
+        call = lambda: pipe.pipe_mlp_forward(l1, l2, kind, x, s_x=0.03, split=split, bias1=b, return_hidden=True)[1]
+    got = {}
+    for tile in (0, 32, 64):
+        pipe.pipe_set_token_tile(tile)
+        try:
+            got[tile] = call()
+        finally:
+            pipe.pipe_set_token_tile(0)
+    assert torch.equal(got[0], got[32]) and torch.equal(got[64], got[32])
+    l1.free()
+
+
+@pytest.mark.parametrize("scale", [0.05, 1.0, 6.0])
+def test_gelu_values(pipe, scale):
+    """GELU of every size of argument, as the hidden tensor of an MLP whose first layer is an identity (codes of one order, their
+    scale a power of two): against 64 bits, within two roundings of the result's terms (a and a * erfc / 2, each at most |a|)."""
+    T, I = 200, 256
+    l1 = pipe.pipe_expand(dev(np.eye(I, dtype=np.float32) * np.float32(127)), 8, 1, 1.0, 16)   # weights 127 = code 127 x scale 1
+    l2 = pipe.pipe_expand(dev(_weight(1, 16, I)), 8, 1, 1.0, 16)
+    s = 2.0 ** np.round(np.log2(scale / 40)) / 127
+    codes = np.random.default_rng(7).integers(-127, 128, size=(T, I)).astype(np.float64)
+    x = dev((codes * np.float32(s)).astype(np.float32))
+    y, h = pipe.pipe_mlp_forward(l1, l2, pipe.PIPE_ACT_GELU, x, s_x=float(np.float32(s)), split=[1], return_hidden=True)
+    a = torch.from_numpy((codes * 127 * np.float64(np.float32(s))).astype(np.float32)).double()
+    ref = 0.5 * a * torch.special.erfc(-a / 2 ** 0.5)
+    err = (h.view(T, I).cpu().double() - ref).abs()
+    assert bool((err <= 2.0 ** -23 * a.abs() + 1e-14).all()), float((err / a.abs().clamp(min=1e-30)).max())
+    l1.free(), l2.free()
