@@ -10,18 +10,24 @@
 //     235 us), and none at all where every bin holds row blocks that its member pruned, which only get their bias;
 //   - the activations of a tile are fetched once, not once per order;
 //   - no fp32 running sum lives through the loop: int32 accumulators only, the orders are folded behind it.
-// Data paths of a stage (SK 64-k steps, one or two packed code tiles per item):
-//   - packed codes: L2 -> registers, 16 bytes per lane, requested two stages ahead (three register sets), widened to int8
-//     between the MFMAs of the item before;
-//   - activations: L2 -> LDS without passing through registers, already in the MFMA operand layout, three slots.
+// Data paths of a stage (SK 64-k steps, one or two packed code tiles per item), requested while the stage before is multiplied:
+//   - packed codes: L2 -> registers, 16 bytes per lane, two register sets, widened to int8 between the MFMAs of the item before;
+//   - activations: L2 -> LDS without passing through registers, already in the MFMA operand layout, two slots.
 // Bound by the matrix pipe and the issue slots around it (a ternary stage of 64 tokens: 64 MFMAs against 112 unpack instructions, 16
-// LDS reads and 8 loads per wave); 160 vector registers and 52 KB of LDS let three workgroups share a compute unit.
+// LDS reads and 8 loads per wave), and by what a workgroup does outside its loop (4.3 of 27.5 us of a 16-stage tile), which other
+// workgroups have to cover: 150 vector registers and 35 KB of LDS let three share a compute unit, and four where the fragments
+// have one register set (126 registers; see launch_cfg for which).  A third stage in flight costs the registers and a fifth more loads
+// (each tile then requests stages behind its last) and gains nothing (11008 x 4096 ternary, 4096 tokens 203 us against 198 with two
+// and 191 with two and four workgroups); a workgroup that walks several tiles loses (220 us: 768 fixed walks fill the chip worse than
+// the dispatcher does); tiles of 128 tokens, two workgroups, lose on ternary codes (214) and win a little on 4 bits (gate||up
+// 22016 x 4096, 2048 tokens 364 against 372).
 // Measured against one pass per order (pipe_gemm.hip, same box): 11008 x 4096 ternary, K = 4, 4096 tokens 227 -> 203 us,
 // 333 tokens 62 -> 30 us; 3x3 convolution 256 x 256 of 6272 pixels, 4 bit, K = 3 35.5 -> 18.4 us; 3072 x 768 and back, 4 bit,
 // K = 3, 4096 tokens 81 -> 60 us; eight 2048 x 2048 ternary layers, two members of 4 orders, 4096 tokens 676 -> 591 us
 // (550 with the hidden maxima in eight lines).
-// One barrier per stage.  The LDS-direct loads are issued by hand (the compiler would make every LDS read wait for the
-// newest of them) and their waits are counted: a stage's loads are always CL codes, then XC activations.
+// One barrier per stage.  The activations are loaded through a buffer resource: unlike global LDS-direct loads, which the compiler
+// counts as flat ones and waits for one and all, their waits are counted, and its range check serves tokens and taps outside.
+#include <algorithm>
 #include <type_traits>
 
 #include "pipe_tile.h"
@@ -29,7 +35,6 @@
 namespace {
 
 constexpr int FRAG = 64;   // uint4 per fragment
-constexpr int RING = 3;    // stages in flight: activation slots in LDS, register sets of codes
 
 struct BinsParams {
   const uint8_t* qx;
@@ -62,7 +67,7 @@ struct BinsParams {
   TileOrder order;
   const int8_t* cq8;              // CONV (implicit GEMM), as in pipe_gemm.hip
   const int32_t* ccsum;
-  const uint8_t* czero;
+  unsigned cbytes;
   int cC, cH, cW, ckh, ckw, cstride, cpad, cHo, cWo;
 };
 
@@ -85,16 +90,14 @@ __device__ __forceinline__ v4i widen(const Codes<BITS, SK>& w, int j) {
   return widen2(j == 0 ? q.x : (j == 1 ? q.y : (j == 2 ? q.z : q.w)));
 }
 
-// Global -> LDS, 16 (or 4) bytes per lane from its own address to LDS byte address `lds` + 16 (4) * lane.
-__device__ __forceinline__ void dma16(const void* g, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
+// Global -> LDS, 16 bytes per lane from base + lane's offset + scalar offset to dst + 16 * lane, both moved by OFFS.
+template <int OFFS>
+__device__ __forceinline__ void bload16(__amdgpu_buffer_rsrc_t base, v4i* dst, unsigned lane_off, unsigned off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(base, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, OFFS, 0);
 }
+// ... and 4 bytes per lane from its own address
 __device__ __forceinline__ void dma4(const void* g, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(g) : "memory");
-}
-// the same at a wave-uniform base and a 32-bit offset per lane
-__device__ __forceinline__ void dma16s(const void* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
 }
 // s_waitcnt: at most vm vector-memory and lgkm LDS / scalar operations outstanding
 constexpr int wait_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm << 8) | ((vm >> 4) << 14); }
@@ -105,46 +108,49 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   constexpr int SK = BITS == 2 || MTB == 1 ? 4 : 2;   // 64-k steps per stage
   constexpr int XC = MTB * SK / 4;                    // activation fragments (1 KiB) a wave loads per stage
   constexpr int WN = Codes<BITS, SK>::N;
-  constexpr int SLOT = MTB * SK * 1024;               // bytes of a stage's activations
-  static_assert(TOK_TILE % (16 * MTB) == 0, "token tile");
-  static_assert(RING == 3, "register sets of codes");
-  struct Lds {                                        // LDS-direct loads reach the first 64 KiB
-    uint4 xs[RING * MTB * SK * FRAG];
+  constexpr int XF = MTB == 4 && MINW == 4 ? 1 : 2;   // register sets of activation fragments
+  static_assert(MTB == 8 || TOK_TILE % (16 * MTB) == 0, "token tile");
+  constexpr int RSN = MTB > 4 ? 16 * MTB : 64;
+  struct Side {
     float scl[4][64];                                 // per wave: row scales of its items
     float bias[4][64];                                // ... bias of their output rows
-    int rs[4][64];                                    // ... code sums of the tile's tokens
+    int rs[4][RSN];                                   // ... code sums of the tile's tokens
   };
-  static_assert(sizeof(Lds) <= 65536, "LDS-direct loads");
-  __shared__ Lds lds;
+  // One array per slot: the compiler tells their LDS-direct loads and reads apart by the array, and so waits before a read
+  // for nothing but the slot's own loads.
+  __shared__ v4i xs0[MTB * SK * FRAG], xs1[MTB * SK * FRAG];
+  __shared__ Side lds;
+  static_assert(sizeof(Side) + 2 * MTB * SK * 1024 <= 65536, "LDS-direct loads reach the first 64 KiB");
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (p.zero_big != nullptr)
     for (int i = blockIdx.x * 256 + threadIdx.x; i < p.zero_big_n; i += gridDim.x * 256) p.zero_big[i] = 0u;
   if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<256>(p.zero_after, p.zero_n);
+
   int ct, tt;
   if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
   const int t0 = tt * (16 * MTB);
-
   const TileBin* bin = p.bins + ct * 4 + wave;
-  const v4i pos4 = cload(&bin->pos, 0), spos4 = cload(&bin->spos, 0), rb4 = cload(&bin->rb, 0), info = cload(&bin->info, 0);
-  const int pos[4] = {pos4[0], pos4[1], pos4[2], pos4[3]};
-  const int rb[4] = {rb4[0], rb4[1], rb4[2], rb4[3]};
+  const v4i pos = cload(&bin->pos, 0), spos = cload(&bin->spos, 0), rb = cload(&bin->rb, 0), info = cload(&bin->info, 0);
   const int m = info[0], ends = info[1], ups = info[2];   // member; items that end a row block; items of an up block
   const bool active = info[3] & 1;
   const int tile_items = info[3] >> 1;                    // items that any bin of the tile multiplies: 4, 3 or none
 
-  // ---- load cursor: the stage requested next; behind the last one it stays there (those loads are never used)
+  // ---- load cursor: the stage requested next
   const int n_stage = p.nks / SK;
   const int64_t rb_bytes = (int64_t)p.nks * 8 * BITS * 16;   // packed codes of a row block
   const int xb = wave * XC / SK, xj = wave * XC - xb * SK;   // this wave's fragments: token block, first 64-k step
-  const uint8_t* l_x = p.qx + (int64_t)m * p.qx_mstride + ((int64_t)(t0 / 16 + xb) * p.nks + xj) * 1024;
+  // activations come through a buffer resource of the tile's fragments (of the whole image, CONV): base in scalar registers, a
+  // lane's offset that does not change and the stage's offset in a scalar register
+  const __amdgpu_buffer_rsrc_t l_x = __builtin_amdgcn_make_buffer_rsrc(
+      CONV ? (void*)p.cq8 : (void*)(p.qx + (int64_t)m * p.qx_mstride + (int64_t)(t0 / 16) * p.nks * 1024), 0,
+      CONV ? p.cbytes : (unsigned)(min(MTB, (p.T_pad - t0) / 16) * p.nks * 1024), 0x00020000);
+  const unsigned l_xlane = (unsigned)(xb * p.nks + xj) * 1024 + lane * 16;
+  unsigned l_xoff = 0;
   const uint8_t* l_wb[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) l_wb[r] = p.codes + pos[r] * rb_bytes;
-  int64_t l_w = 0;
-  int l_left = n_stage;
-  unsigned l_slot = 0;
   constexpr int NCB = CONV ? XC : 1;
   int c_off = 0, c_h0 = 0, c_w0 = 0;         // CONV: this lane's pixel: offset of the window's first tap, its row and column
   int c_r[NCB], c_q[NCB], c_c0[NCB];         // wave-uniform: tap and first channel of the 64-k step each fragment loads next
@@ -163,77 +169,91 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
       c_q[f] = tap - c_r[f] * p.ckw;
     }
   }
-  const unsigned xs_base = lds_addr(&lds.xs[0]);
-  auto xload = [&]() __attribute__((always_inline)) {
-    const unsigned dst = xs_base + l_slot + wave * XC * 1024;
-#pragma unroll
-    for (int f = 0; f < XC; ++f) {
-      if constexpr (CONV) {
-        const int r = c_r[f], q = c_q[f], c0 = c_c0[f];
-        const bool inside = r < p.ckh && (unsigned)(c_h0 + r) < (unsigned)p.cH && (unsigned)(c_w0 + q) < (unsigned)p.cW;
-        const int8_t* g = inside ? p.cq8 + (c_off + (r * p.cW + q) * p.cC + c0) : reinterpret_cast<const int8_t*>(p.czero);
-        dma16(g, dst + f * 1024);
-      } else {
-        dma16s(l_x + f * 1024, lane * 16, dst + f * 1024);
-      }
-    }
-    l_slot = l_slot == (RING - 1) * SLOT ? 0 : l_slot + SLOT;
-  };
-  auto wload = [&](auto& w) __attribute__((always_inline)) {
+  // requests a stage: the items' codes, this wave's share of the activations
+  auto request = [&](auto& w, v4i* slot) __attribute__((always_inline)) {
     constexpr int NI = (int)std::extent<std::remove_reference_t<decltype(w)>>::value;
     unsigned off = lane * 16;
     asm volatile("" : "+v"(off));   // a 32-bit offset next to the loads: they take the scalar base + offset form
 #pragma unroll
-    for (int r = 0; r < NI; ++r)
+    for (int r = 0; r < NI; ++r) {
 #pragma unroll
-      for (int q = 0; q < WN; ++q) w[r].v[q] = gload16(l_wb[r] + l_w + q * 1024 + off);
-  };
-  auto advance = [&]() __attribute__((always_inline)) {
-    if (l_left > 1) {
-      --l_left;
-      l_w += WN * 1024;
-      l_x += SK * 1024;
-      if constexpr (CONV) {
+      for (int q = 0; q < WN; ++q) w[r].v[q] = gload16(l_wb[r] + q * 1024 + off);
+      l_wb[r] += WN * 1024;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    v4i* dst = slot + wave * XC * FRAG;
+    if constexpr (CONV) {
+#pragma unroll
+      for (int f = 0; f < XC; ++f) {
+        const int r = c_r[f], q = c_q[f], c0 = c_c0[f];
+        const bool inside = r < p.ckh && (unsigned)(c_h0 + r) < (unsigned)p.cH && (unsigned)(c_w0 + q) < (unsigned)p.cW;
+        // out of the resource's range: zeros
+        const unsigned at = inside ? (unsigned)(c_off + (r * p.cW + q) * p.cC + c0) : 0xFFFFFFF0u;
+        bload16<0>(l_x, dst + f * FRAG, at, 0);
         // the 64-k steps run tap-major, channel-minor (C is a multiple of 64); the position is stepped, not divided out
-#pragma unroll
-        for (int f = 0; f < XC; ++f) {
-          c_c0[f] += SK * 64;
-          while (c_c0[f] >= p.cC) {
-            c_c0[f] -= p.cC;
-            if (++c_q[f] == p.ckw) { c_q[f] = 0; ++c_r[f]; }
-          }
+        c_c0[f] += SK * 64;
+        while (c_c0[f] >= p.cC) {
+          c_c0[f] -= p.cC;
+          if (++c_q[f] == p.ckw) { c_q[f] = 0; ++c_r[f]; }
         }
       }
+    } else {   // a wave's fragments lie next to each other, here and there
+      bload16<0>(l_x, dst, l_xlane, l_xoff);
+      if constexpr (XC > 1) bload16<1024>(l_x, dst, l_xlane, l_xoff);
+      if constexpr (XC > 2) {
+        bload16<2048>(l_x, dst, l_xlane, l_xoff);
+        bload16<3072>(l_x, dst, l_xlane, l_xoff);
+      }
+      l_xoff += SK * 1024;
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
-
-  // ---- what the epilogue needs travels ahead of the ring, into LDS of this wave
+  auto wait_all = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // ---- what the epilogue needs travels beside the first stage, into LDS of this wave
   {
     const int r = lane >> 4;
     int sp = 0, br = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {   // selects on scalar registers (an indexed array would live in scratch memory)
-      sp |= r == q ? spos4[q] : 0;
+      sp |= r == q ? spos[q] : 0;
       br |= r == q ? max(rb[q], 0) * 16 + ((ups >> q) & 1 ? p.hidden : 0) : 0;
     }
     dma4(p.scales + (size_t)sp * 16 + (lane & 15), lds_addr(&lds.scl[wave][0]));
     if (p.bias != nullptr) dma4(p.bias + (size_t)m * p.bias_mstride + br + (lane & 15), lds_addr(&lds.bias[wave][0]));
-    if (OFF && !CONV) dma4(p.rowsum + (size_t)m * p.rowsum_mstride + min(t0 + lane, p.T_pad - 1), lds_addr(&lds.rs[wave][0]));
+    if (OFF && !CONV) {
+      dma4(p.rowsum + (size_t)m * p.rowsum_mstride + min(t0 + lane, p.T_pad - 1), lds_addr(&lds.rs[wave][0]));
+      if (MTB == 8) dma4(p.rowsum + (size_t)m * p.rowsum_mstride + min(t0 + 64 + lane, p.T_pad - 1), lds_addr(&lds.rs[wave][RSN - 64]));
+    }
   }
   const float sx = p.s_x[m * p.sx_mstride];
   auto window_sums = [&]() __attribute__((always_inline)) {
     if constexpr (OFF != 0 && CONV) {
       // token code sum = the channel sums of the window's pixels that lie inside the image
-      const int t = t0 + min(lane, 16 * MTB - 1);
-      const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
-      const int h0 = ho * p.cstride - p.cpad, w0_ = wo * p.cstride - p.cpad;
-      int sum = 0;
-      if (t < p.T)
-        for (int r = 0; r < p.ckh; ++r)
-          for (int q = 0; q < p.ckw; ++q)
-            if ((unsigned)(h0 + r) < (unsigned)p.cH && (unsigned)(w0_ + q) < (unsigned)p.cW)
-              sum += p.ccsum[(img * p.cH + h0 + r) * p.cW + w0_ + q];
-      lds.rs[wave][lane] = sum;
+      for (int t1 = 0; t1 < RSN; t1 += 64) {
+        const int t = t0 + min(t1 + lane, 16 * MTB - 1);
+        const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
+        const int h0 = ho * p.cstride - p.cpad, w0_ = wo * p.cstride - p.cpad;
+        // nine taps' loads in flight (one after the other they took 2.2 of the 14.5 us of a 3 x 3 layer's workgroup); a tap outside
+        // reads the first sum and drops it
+        int sum = 0, r = 0, q = 0;
+        while (r < p.ckh) {
+          int c[9];
+          bool in[9];
+#pragma unroll
+          for (int i = 0; i < 9; ++i) {
+            in[i] = t < p.T && r < p.ckh && (unsigned)(h0 + r) < (unsigned)p.cH && (unsigned)(w0_ + q) < (unsigned)p.cW;
+            c[i] = r < p.ckh ? p.ccsum[in[i] ? (img * p.cH + h0 + r) * p.cW + w0_ + q : 0] : 0;
+            if (++q == p.ckw) { q = 0; ++r; }
+          }
+#pragma unroll
+          for (int i = 0; i < 9; ++i) sum += in[i] ? c[i] : 0;
+        }
+        lds.rs[wave][t1 + lane] = sum;
+      }
     }
   };
 
@@ -246,91 +266,70 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   // ---- the walk along k with the first NI items of every bin of the tile
   auto walk = [&](auto ni) __attribute__((always_inline)) {
     constexpr int NI = decltype(ni)::value;
-    constexpr int CL = NI * WN;                         // code loads of a wave per stage
-    Codes<BITS, SK> w0[NI], w1[NI], w2[NI];
-    wload(w0);
-    __builtin_amdgcn_sched_barrier(0);
-    xload();
-    __builtin_amdgcn_sched_barrier(0);
-    advance();
-    wload(w1);
-    __builtin_amdgcn_sched_barrier(0);
-    xload();
-    __builtin_amdgcn_sched_barrier(0);
-    advance();
+    Codes<BITS, SK> w0[NI], w1[NI];
+    request(w0, xs0);
     window_sums();
-    unsigned c_slot = 0;
-
-    // One stage.  `cur` and the ring slot c_slot hold its codes and activations, requested two stages ago; `far` is
-    // free (multiplied in the stage before) and takes the codes of the stage after next.
-    auto stage = [&](Codes<BITS, SK>(&cur)[NI], Codes<BITS, SK>(&far)[NI], bool multiply) __attribute__((always_inline)) {
-      // this stage's codes have arrived: the wait the compiler places here leaves the newest loads in flight
-#pragma unroll
-      for (int r = 0; r < NI; ++r)
-#pragma unroll
-        for (int q = 0; q < WN; ++q) asm volatile("" : "+v"(cur[r].v[q]));
-      // ... and so have this wave's activations of the stage (all but the CL + XC loads behind them)
-      __builtin_amdgcn_s_waitcnt(wait_imm(CL + XC, 0));
-      asm volatile("s_barrier" ::: "memory");    // everyone's have, and the slot of the stage before is free
-      wload(far);
+    wait_all();
+    // One stage: its codes and activations have arrived (every wave waits for its own at the end of the stage before)
+    // and `far` and `free_slot`, multiplied in the stage before, take the stage that is requested now.
+    auto stage = [&](Codes<BITS, SK>(&now)[NI], const v4i* slot, Codes<BITS, SK>(&far)[NI], v4i* free_slot, bool multiply, bool ask) __attribute__((always_inline)) {
+      asm volatile("s_barrier" ::: "memory");    // everyone's have arrived, and the slot of the stage before is free
+      if (ask) request(far, free_slot);
       __builtin_amdgcn_sched_barrier(0);
-      xload();
-      __builtin_amdgcn_sched_barrier(0);
-      advance();
       if (multiply) {
         // Software pipeline of the SK 64-k steps: a wave issues in order, so everything that is not an MFMA has to sit in
         // the shadow of one.  The fragments of step j+1 are requested before step j's MFMAs start (two register
         // sets), and the codes of item r+1 are widened between the MFMAs of item r (two register sets).
-        const v4i* xs = reinterpret_cast<const v4i*>(lds.xs) + c_slot / 16 + lane;
-        v4i xf[2][MTB];
+        const v4i* xs = slot + lane;
+        v4i xf[XF][MTB];
         v4i wf[2];
 #pragma unroll
         for (int b = 0; b < MTB; ++b) xf[0][b] = xs[b * SK * FRAG];
-        wf[0] = widen<BITS, SK>(cur[0], 0);
+        wf[0] = widen<BITS, SK>(now[0], 0);
 #pragma unroll
         for (int j = 0; j < SK; ++j) {
-          if (j + 1 < SK) {
+          if (XF == 2 && j + 1 < SK) {
 #pragma unroll
-            for (int b = 0; b < MTB; ++b) xf[(j + 1) & 1][b] = xs[(b * SK + j + 1) * FRAG];
+            for (int b = 0; b < MTB; ++b) xf[(j + 1) % XF][b] = xs[(b * SK + j + 1) * FRAG];
           }
 #pragma unroll
           for (int r = 0; r < NI; ++r) {
             const int n = j * NI + r;   // item-steps so far: the register set of this one's codes
-            if (r + 1 < NI) wf[(n + 1) & 1] = widen<BITS, SK>(cur[r + 1], j);
-            else if (j + 1 < SK) wf[(n + 1) & 1] = widen<BITS, SK>(cur[0], j + 1);
+            if (r + 1 < NI) wf[(n + 1) & 1] = widen<BITS, SK>(now[r + 1], j);
+            else if (j + 1 < SK) wf[(n + 1) & 1] = widen<BITS, SK>(now[0], j + 1);
 #pragma unroll
             for (int b = 0; b < MTB; ++b)
-              acc[r][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[n & 1], xf[j & 1][b], acc[r][b], 0, 0, 0);
+              acc[r][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[n & 1], xf[j % XF][b], acc[r][b], 0, 0, 0);
             if (BITS != 8) {
               // one MFMA, then some of the unpack instructions, and so on
 #pragma unroll
               for (int b = 0; b < MTB; ++b) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 8 / MTB, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, MTB == 8 ? 1 : 8 / MTB, 0);
               }
             }
             __builtin_amdgcn_sched_barrier(0);   // keep the items apart: bounds live registers
           }
+          if (XF == 1 && j + 1 < SK) {
+#pragma unroll
+            for (int b = 0; b < MTB; ++b) xf[0][b] = xs[(b * SK + j + 1) * FRAG];
+          }
         }
       }
-      c_slot = c_slot == (RING - 1) * SLOT ? 0 : c_slot + SLOT;
+      wait_all();
     };
-    // Three stages a round, so every register set keeps its role and the ring has one exit (the compiler counts
-    // outstanding loads exactly then); behind the last stage the rest of the round multiplies nothing.
-    for (int s = 0; s < n_stage; s += RING) {
-      stage(w0, w2, active);
-      stage(w1, w0, active && s + 1 < n_stage);
-      stage(w2, w1, active && s + 2 < n_stage);
+    // Two stages a round, so that the slots and register sets keep their roles; behind an odd number of stages the second
+    // half multiplies nothing.
+    for (int s = 0; s < n_stage; s += 2) {
+      stage(w0, xs0, w1, xs1, active, s + 1 < n_stage);
+      stage(w1, xs1, w0, xs0, active && s + 1 < n_stage, s + 2 < n_stage);
     }
   };
   // (64 tokens of the ternary convolution: a second loop would spill; chain layers: see launch_gemm_bins)
   constexpr bool THREE = !(CONV && SK * MTB == 16) && MODE != MODE_CHAIN;
-  if (tile_items == 0) window_sums();
+  if (tile_items == 0) { window_sums(); wait_all(); }
   else if (THREE && tile_items == 3 && p.three) walk(std::integral_constant<int, THREE ? 3 : 4>{});
   else walk(std::integral_constant<int, 4>{});
-  // the ring's last loads write into this workgroup's LDS and registers: they end here
-  __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
-  asm volatile("" ::: "memory");
 
   // ---- epilogue: orders folded in ascending k, one output row block after the other.  A lane holds 4 channels of one
   // token per 16-token block, 64 contiguous bytes of a token per 16 lanes.
@@ -340,27 +339,27 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   int rs[MTB];
 #pragma unroll
   for (int b = 0; b < MTB; ++b) rs[b] = OFF ? lds.rs[wave][b * 16 + tl] : 0;
-  float mx = 0.f, mn = 0.f;
-  const bool two_sided = p.amax_neg != nullptr;
   // the slots as they are now, read while the orders are folded
+  const bool two_sided = p.amax_neg != nullptr;
+  float mx = 0.f, mn = 0.f;
   const uint32_t seen = p.amax_out != nullptr ? slot_seen(&p.amax_out[m]) : 0u;
   const uint32_t seen_neg = two_sided ? slot_seen(&p.amax_neg[m]) : 0u;
   const bool with_bias = p.bias != nullptr && (m == 0 || !p.apart || p.bias_mstride != 0);
   float* ym = p.y + (size_t)(p.apart ? m : 0) * p.T * p.out + 4 * g;
   const int n_res = (MODE == MODE_CHAIN && p.res != nullptr) ? (p.apart ? (m < p.res_members ? 1 : 0) : p.res_members) : 0;
   const float* resm = MODE == MODE_CHAIN ? p.res + (size_t)(p.apart ? m : 0) * p.res_mstride + 4 * g : nullptr;
-  // the skip tensor of every row block, requested together (the loop's registers are free)
-  float4 rq[MODE == MODE_CHAIN ? 4 : 1][MODE == MODE_CHAIN ? MTB : 1];
-  if (MODE == MODE_CHAIN) {
+  // the skip tensor of a row block, requested a row block ahead (two sets of registers: with all four a workgroup less fits)
+  float4 rq[MODE == MODE_CHAIN ? 2 : 1][MODE == MODE_CHAIN ? MTB : 1];
+  auto skip = [&](int r) __attribute__((always_inline)) {
+    if constexpr (MODE == MODE_CHAIN) {
+      if (n_res > 0 && ((ends >> r) & 1)) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int b = 0; b < MTB; ++b) {
-        rq[r][b] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (n_res > 0 && ((ends >> r) & 1))
-          rq[r][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(t0 + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
+        for (int b = 0; b < MTB; ++b)
+          rq[r & 1][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(t0 + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
       }
-  }
+    }
+  };
+  skip(0);
   float v[MTB][4], gate[MODE == MODE_GATED ? MTB : 1][4];
 #pragma unroll
   for (int b = 0; b < MTB; ++b)
@@ -368,6 +367,7 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
     for (int i = 0; i < 4; ++i) v[b][i] = 0.f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
+    if (r < 3) skip(r + 1);
     const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wave][r * 16 + g * 4]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
     for (int b = 0; b < MTB; ++b) {
       const int t = t0 + b * 16 + tl;
       if (MODE == MODE_CHAIN) {
-        float4 rs4 = rq[r][b];
+        float4 rs4 = n_res > 0 ? rq[r & 1][b] : make_float4(0.f, 0.f, 0.f, 0.f);
         for (int mm = 1; mm < n_res; ++mm) {   // a sum over several members, each with a skip tensor of its own
           const float4 x = *reinterpret_cast<const float4*>(resm + (size_t)mm * p.res_mstride + (size_t)min(t, p.T - 1) * p.out + rb[r] * 16);
           rs4.x += x.x; rs4.y += x.y; rs4.z += x.z; rs4.w += x.w;
@@ -437,17 +437,40 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
 }
 
 template <int BITS, int MTB, int MINW>
-int launch_cfg(BinsParams& p, int n_ct, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
-  p.order = tile_order(n_ct, ceil_div(p.T, 16 * MTB), false);
+int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
+  const int n_tt = ceil_div(p.T, 16 * MTB);
+  p.order = tile_order(n_ct, n_tt, false);
   const dim3 grid((unsigned)p.order.blocks());
-  if (p.cq8 != nullptr) {
-    if (p.res != nullptr || p.act != 0) return PIPE_EINVAL;   // implicit-GEMM convolution: plain epilogue
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true>), grid, dim3(256), st, ev0, ev1, p);
-  } else if (p.res != nullptr || p.act == PIPE_ACT_RELU) {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false>), grid, dim3(256), st, ev0, ev1, p);
-  } else if (p.act == PIPE_ACT_GELU) {
+  const int act = p.cq8 != nullptr ? 0 : p.act;
+  if (p.cq8 != nullptr && (p.res != nullptr || p.act != 0)) return PIPE_EINVAL;   // implicit-GEMM convolution: plain epilogue
+  // Workgroups per compute unit, three or four: four cover each other's epilogues and first loads better (a round of four takes
+  // 1.30 of one of three, not 1.33), but end in larger rounds.  So four where as many or fewer places are filled: 11008 x 4096 ternary, 4096
+  // tokens (4816 tiles) 197 -> 191 us, 700 tokens 46.2 -> 44.4, 3300 165 -> 162; gate||up 22016 x 4096 4 bit, 2048 tokens 398 -> 372;
+  // but 3072 x 768 4 bit with GELU, 4096 tokens (1536 tiles, two full rounds of three) 30 -> 32.  Chain layers and
+  // convolutions hold too much for four (they would spill).
+  const bool chain = p.res != nullptr || act == PIPE_ACT_RELU;
+  if constexpr (MTB == 4 && MINW == 3) {
+    const int64_t tiles = (int64_t)live_ct * n_tt, cus = pipe_resident_workgroups();
+    const bool four = (tiles + 4 * cus - 1) / (4 * cus) * 4 <= (tiles + 3 * cus - 1) / (3 * cus) * 3;
+    if (four && p.cq8 == nullptr && !chain) return launch_cfg<BITS, MTB, 4>(p, live_ct, n_ct, ev0, ev1, st);
+  }
+  if constexpr (MTB == 4 && MINW == 4) {
+    if (p.cq8 != nullptr || chain) return PIPE_EINVAL;
+  } else {
+    if (p.cq8 != nullptr) {
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true>), grid, dim3(256), st, ev0, ev1, p);
+      PIPE_HIP(hipGetLastError());
+      return PIPE_OK;
+    }
+    if (chain) {
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false>), grid, dim3(256), st, ev0, ev1, p);
+      PIPE_HIP(hipGetLastError());
+      return PIPE_OK;
+    }
+  }
+  if (act == PIPE_ACT_GELU) {
     PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GELU, false>), grid, dim3(256), st, ev0, ev1, p);
-  } else if (p.act == PIPE_ACT_SILU_GATED) {
+  } else if (act == PIPE_ACT_SILU_GATED) {
     PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GATED, false>), grid, dim3(256), st, ev0, ev1, p);
   } else {
     PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, false>), grid, dim3(256), st, ev0, ev1, p);
@@ -501,7 +524,7 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
   p.res = a.res; p.res_mstride = a.res_mstride; p.res_members = a.res_members; p.res_pre_act = a.res_pre_act;
   p.hidden = 0;
   if (a.act == PIPE_ACT_SILU_GATED) { p.hidden = e->out / 2; p.out = e->out / 2; }
-  p.cq8 = a.conv_q8; p.ccsum = a.conv_csum; p.czero = a.conv_zero;
+  p.cq8 = a.conv_q8; p.ccsum = a.conv_csum; p.cbytes = a.conv_q8 != nullptr ? (unsigned)((int64_t)a.T / (a.conv_Ho * a.conv_Wo) * a.conv_C * a.conv_H * a.conv_W) : 0u;
   p.cC = a.conv_C; p.cH = a.conv_H; p.cW = a.conv_W; p.ckh = a.conv_kh; p.ckw = a.conv_kw; p.cstride = a.conv_stride; p.cpad = a.conv_pad;
   p.cHo = a.conv_Ho; p.cWo = a.conv_Wo;
   // Token-tile height: 64 tokens amortize the unpacking of the codes best (the 4096-token layer above: 203, 245 and 317 us
@@ -516,15 +539,15 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
     mtb = tiles(64) >= 192 ? 4 : (tiles(32) >= 192 ? 2 : 1);
   }
   switch (e->bits * 8 + mtb) {
-    case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 8 * 8 + 1: return launch_cfg<8, 1, 2>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 4: return launch_cfg<4, 4, 3>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 2: return launch_cfg<4, 2, 4>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 1: return launch_cfg<4, 1, 3>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 4: return launch_cfg<2, 4, 3>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 2: return launch_cfg<2, 2, 4>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 1: return launch_cfg<2, 1, 4>(p, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 1: return launch_cfg<8, 1, 2>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 4: return launch_cfg<4, 4, 3>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 2: return launch_cfg<4, 2, 4>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 1: return launch_cfg<4, 1, 3>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 4: return launch_cfg<2, 4, 3>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 2: return launch_cfg<2, 2, 4>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 1: return launch_cfg<2, 1, 4>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
     default: return PIPE_EINVAL;
   }
 }
