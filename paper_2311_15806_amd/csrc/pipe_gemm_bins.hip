@@ -10,9 +10,9 @@
 //     235 us), and none at all where every bin holds row blocks that its member pruned, which only get their bias;
 //   - the activations of a tile are fetched once, not once per order;
 //   - no fp32 running sum lives through the loop: int32 accumulators only, the orders are folded behind it.
-// Data paths of a stage (SK 64-k steps, one or two packed code tiles per item), requested while the stage before is multiplied:
-//   - packed codes: L2 -> registers, 16 bytes per lane, two register sets, widened to int8 between the MFMAs of the item before;
-//   - activations: L2 -> LDS without passing through registers, already in the MFMA operand layout, two slots.
+// Data paths of a stage (SK 64-k steps, one or two packed code tiles per item), requested DP stages before it is multiplied:
+//   - packed codes: L2 -> registers, 16 bytes per lane, DP + 1 register sets, widened to int8 between the MFMAs of the item before;
+//   - activations: L2 -> LDS without passing through registers, already in the MFMA operand layout, DP + 1 slots.
 // Bound by the matrix pipe and the issue slots around it (a ternary stage of 64 tokens: 64 MFMAs against 112 unpack instructions, 16
 // LDS reads and 8 loads per wave), and by what a workgroup does outside its loop (4.3 of 27.5 us of a 16-stage tile), which other
 // workgroups have to cover: 150 vector registers and 35 KB of LDS let three share a compute unit, and four where the fragments
@@ -21,6 +21,12 @@
 // and 191 with two and four workgroups); a workgroup that walks several tiles loses (220 us: 768 fixed walks fill the chip worse than
 // the dispatcher does); tiles of 128 tokens, two workgroups, lose on ternary codes (214) and win a little on 4 bits (gate||up
 // 22016 x 4096, 2048 tokens 364 against 372).
+// Where the chip holds more waves than the tiles bring: a full chip (four workgroups a unit) spends 4176 cycles on the four's 4096 MFMA cycles of
+// a ternary stage; a tile alone spends 1490 on the 512 of a 4-bit stage, 390 of them on its own loads after the barrier, at the 16 cycles
+// per KiB that the unit's address path takes, 230 on the first fragments, and deeper prefetch changes nothing (wait: 50 cycles).  So (G = 2)
+// two groups of 4 waves share a tile, half of k each, and (DP = 2) the loads of a stage two ahead are asked for one by one between
+// the multiplies: through buffer resources, so that those behind the last stage read nothing and every wait stays an exact count.
+// A 4-bit stage pair of 1024 MFMA cycles then takes 1700 (2050 for a convolution's gathers): the loads that miss the L1 bound it.  Times at launch_gemm_bins.
 // Measured against one pass per order (pipe_gemm.hip, same box): 11008 x 4096 ternary, K = 4, 4096 tokens 227 -> 203 us,
 // 333 tokens 62 -> 30 us; 3x3 convolution 256 x 256 of 6272 pixels, 4 bit, K = 3 35.5 -> 18.4 us; 3072 x 768 and back, 4 bit,
 // K = 3, 4096 tokens 81 -> 60 us; eight 2048 x 2048 ternary layers, two members of 4 orders, 4096 tokens 676 -> 591 us
@@ -68,6 +74,7 @@ struct BinsParams {
   const int8_t* cq8;              // CONV (implicit GEMM), as in pipe_gemm.hip
   const int32_t* ccsum;
   unsigned cbytes;
+  int one_tap;                    // 1: a stage's 64-k steps share a tap (its address is stepped once: 2 to 4 % with two groups)
   int cC, cH, cW, ckh, ckw, cstride, cpad, cHo, cWo;
 };
 
@@ -95,38 +102,38 @@ template <int OFFS>
 __device__ __forceinline__ void bload16(__amdgpu_buffer_rsrc_t base, v4i* dst, unsigned lane_off, unsigned off) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(base, (__attribute__((address_space(3))) void*)dst, 16, lane_off, off, OFFS, 0);
 }
-// ... and 4 bytes per lane from its own address
-__device__ __forceinline__ void dma4(const void* g, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(g) : "memory");
-}
 // s_waitcnt: at most vm vector-memory and lgkm LDS / scalar operations outstanding
 constexpr int wait_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm << 8) | ((vm >> 4) << 14); }
 
-template <int BITS, int MTB, int MINW, int MODE, bool CONV>
-__global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p) {
+// G groups of 4 waves take a tile's walk along k in G parts, each with slots of its own; their sums meet in LDS behind the loop and
+// every group finishes MTB / G of the token blocks.
+template <int BITS, int MTB, int MINW, int MODE, bool CONV, int G, int DP>
+__global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsParams p) {
   constexpr int OFF = BITS == 8 ? 0 : (BITS == 4 ? 8 : 1);
-  constexpr int SK = BITS == 2 || MTB == 1 ? 4 : 2;   // 64-k steps per stage
+  constexpr int SK = BITS == 2 || MTB == 1 || (G == 2 && MTB == 2) ? 4 : 2;   // 64-k steps per stage
   constexpr int XC = MTB * SK / 4;                    // activation fragments (1 KiB) a wave loads per stage
   constexpr int WN = Codes<BITS, SK>::N;
   constexpr int XF = MTB == 4 && MINW == 4 ? 1 : 2;   // register sets of activation fragments
-  static_assert(MTB == 8 || TOK_TILE % (16 * MTB) == 0, "token tile");
-  constexpr int RSN = MTB > 4 ? 16 * MTB : 64;
+  static_assert(TOK_TILE % (16 * MTB) == 0 && MTB % G == 0, "token tile");
+  constexpr int MB = MTB / G;                         // token blocks a group finishes
+  constexpr int SLOT = G * MTB * SK * FRAG;
   struct Side {
-    float scl[4][64];                                 // per wave: row scales of its items
-    float bias[4][64];                                // ... bias of their output rows
-    int rs[4][RSN];                                   // ... code sums of the tile's tokens
+    float scl[4 * G][64];                             // per wave: row scales of its items
+    float bias[4 * G][64];                            // ... bias of their output rows
+    int rs[4 * G][64];                                // ... code sums of the tokens it finishes
   };
   // One array per slot: the compiler tells their LDS-direct loads and reads apart by the array, and so waits before a read
   // for nothing but the slot's own loads.
-  __shared__ v4i xs0[MTB * SK * FRAG], xs1[MTB * SK * FRAG];
+  __shared__ alignas(1024) v4i xs0[SLOT], xs1[SLOT], xs2[DP > 1 ? SLOT : 1];
   __shared__ Side lds;
-  static_assert(sizeof(Side) + 2 * MTB * SK * 1024 <= 65536, "LDS-direct loads reach the first 64 KiB");
+  static_assert((DP + 1) * SLOT * 16 <= 65536, "LDS-direct loads reach the first 64 KiB");
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = wid & 3, grp = G == 1 ? 0 : wid >> 2;
   if (p.zero_big != nullptr)
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < p.zero_big_n; i += gridDim.x * 256) p.zero_big[i] = 0u;
-  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<256>(p.zero_after, p.zero_n);
+    for (int i = blockIdx.x * (256 * G) + threadIdx.x; i < p.zero_big_n; i += gridDim.x * (256 * G)) p.zero_big[i] = 0u;
+  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<256 * G>(p.zero_after, p.zero_n);
 
   int ct, tt;
   if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
@@ -138,7 +145,9 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   const int tile_items = info[3] >> 1;                    // items that any bin of the tile multiplies: 4, 3 or none
 
   // ---- load cursor: the stage requested next
-  const int n_stage = p.nks / SK;
+  const int n_all = p.nks / SK, n_max = (n_all + G - 1) / G;   // stages of the tile, of a group
+  const int s0 = grp * n_max, n_stage = G == 1 ? n_all : max(0, min(n_max, n_all - s0));
+  const int tg = t0 + grp * (16 * MB);                         // first token that this group finishes
   const int64_t rb_bytes = (int64_t)p.nks * 8 * BITS * 16;   // packed codes of a row block
   const int xb = wave * XC / SK, xj = wave * XC - xb * SK;   // this wave's fragments: token block, first 64-k step
   // activations come through a buffer resource of the tile's fragments (of the whole image, CONV): base in scalar registers, a
@@ -146,14 +155,22 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   const __amdgpu_buffer_rsrc_t l_x = __builtin_amdgcn_make_buffer_rsrc(
       CONV ? (void*)p.cq8 : (void*)(p.qx + (int64_t)m * p.qx_mstride + (int64_t)(t0 / 16) * p.nks * 1024), 0,
       CONV ? p.cbytes : (unsigned)(min(MTB, (p.T_pad - t0) / 16) * p.nks * 1024), 0x00020000);
-  const unsigned l_xlane = (unsigned)(xb * p.nks + xj) * 1024 + lane * 16;
+  unsigned l_xlane = (unsigned)(xb * p.nks + xj + s0 * SK) * 1024 + lane * 16;
   unsigned l_xoff = 0;
   const uint8_t* l_wb[4];
+  __amdgpu_buffer_rsrc_t l_w[4];   // groups: a resource of each item's codes, up to the end of the group's part
+  unsigned l_woff = s0 * (WN * 1024) + lane * 16;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) l_wb[r] = p.codes + pos[r] * rb_bytes;
+  for (int r = 0; r < 4; ++r) {
+    const uint8_t* c = p.codes + pos[r] * rb_bytes;
+    if constexpr (DP == 1) l_wb[r] = c;
+    else l_w[r] = __builtin_amdgcn_make_buffer_rsrc((void*)c, 0, (unsigned)((s0 + n_stage) * WN * 1024), 0x00020000);
+  }
   constexpr int NCB = CONV ? XC : 1;
   int c_off = 0, c_h0 = 0, c_w0 = 0;         // CONV: this lane's pixel: offset of the window's first tap, its row and column
   int c_r[NCB], c_q[NCB], c_c0[NCB];         // wave-uniform: tap and first channel of the 64-k step each fragment loads next
+  unsigned c_at = 0;                         // one tap a stage: this lane's offset in it
+  const bool one_tap = CONV && p.one_tap;
   if constexpr (CONV) {
     const int t = t0 + xb * 16 + (lane & 15);
     const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
@@ -163,57 +180,90 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
     c_off = ((img * p.cH + h0) * p.cW + c_w0) * p.cC + (lane >> 4) * 16;   // used only for taps inside the image
 #pragma unroll
     for (int f = 0; f < XC; ++f) {
-      const int tap = ((xj + f) * 64) / p.cC;
-      c_c0[f] = (xj + f) * 64 - tap * p.cC;
+      const int tap = ((s0 * SK + xj + f) * 64) / p.cC;
+      c_c0[f] = (s0 * SK + xj + f) * 64 - tap * p.cC;
       c_r[f] = tap / p.ckw;
       c_q[f] = tap - c_r[f] * p.ckw;
     }
   }
-  // requests a stage: the items' codes, this wave's share of the activations
-  auto request = [&](auto& w, v4i* slot) __attribute__((always_inline)) {
-    constexpr int NI = (int)std::extent<std::remove_reference_t<decltype(w)>>::value;
-    unsigned off = lane * 16;
-    asm volatile("" : "+v"(off));   // a 32-bit offset next to the loads: they take the scalar base + offset form
-#pragma unroll
-    for (int r = 0; r < NI; ++r) {
-#pragma unroll
-      for (int q = 0; q < WN; ++q) w[r].v[q] = gload16(l_wb[r] + q * 1024 + off);
-      l_wb[r] += WN * 1024;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    v4i* dst = slot + wave * XC * FRAG;
+  // out of the resource's range (zeros) where the tap lies outside the image
+  auto tap_at = [&](int r, int q) __attribute__((always_inline)) {
+    const bool inside = r < p.ckh && (unsigned)(c_h0 + r) < (unsigned)p.cH && (unsigned)(c_w0 + q) < (unsigned)p.cW;
+    return inside ? (unsigned)(c_off + (r * p.cW + q) * p.cC) : 0xFFF00000u;
+  };
+  if constexpr (CONV) c_at = tap_at(c_r[0], c_q[0]);
+  // requests a stage: the items' codes (the i-th 16 bytes per lane), this wave's share of the activations (fragment f)
+  auto ask_codes = [&](auto& w, int i) __attribute__((always_inline)) {
+    w[i / WN].v[i % WN] = (v4u)__builtin_amdgcn_raw_buffer_load_b128(l_w[i / WN], l_woff + (i % WN) * 1024, 0, 0);
+  };
+  auto ask_acts = [&](v4i* slot, auto frag) __attribute__((always_inline)) {
+    constexpr int f = decltype(frag)::value;
+    v4i* dst = slot + (grp * MTB * SK + wave * XC) * FRAG;
     if constexpr (CONV) {
+      if (one_tap) bload16<0>(l_x, dst + f * FRAG, c_at, c_c0[0] + f * 64);
+      else bload16<0>(l_x, dst + f * FRAG, tap_at(c_r[f], c_q[f]), c_c0[f]);
+    } else {   // a wave's fragments lie next to each other, here and there
+      bload16<f * 1024>(l_x, dst, l_xlane, l_xoff);
+    }
+  };
+  auto ask_next = [&]() __attribute__((always_inline)) {   // moves on to the next stage
+    if constexpr (DP > 1) l_woff += WN * 1024;
+    if constexpr (!CONV) {
+      if (DP == 1) l_xoff += SK * 1024; else l_xlane += SK * 1024;
+    } else if (one_tap) {
+      c_c0[0] += SK * 64;
+      if (c_c0[0] >= p.cC) {
+        c_c0[0] -= p.cC;
+        if (++c_q[0] == p.ckw) { c_q[0] = 0; ++c_r[0]; }
+        c_at = tap_at(c_r[0], c_q[0]);
+      }
+    } else {
 #pragma unroll
-      for (int f = 0; f < XC; ++f) {
-        const int r = c_r[f], q = c_q[f], c0 = c_c0[f];
-        const bool inside = r < p.ckh && (unsigned)(c_h0 + r) < (unsigned)p.cH && (unsigned)(c_w0 + q) < (unsigned)p.cW;
-        // out of the resource's range: zeros
-        const unsigned at = inside ? (unsigned)(c_off + (r * p.cW + q) * p.cC + c0) : 0xFFFFFFF0u;
-        bload16<0>(l_x, dst + f * FRAG, at, 0);
-        // the 64-k steps run tap-major, channel-minor (C is a multiple of 64); the position is stepped, not divided out
+      for (int f = 0; f < XC; ++f) {   // the 64-k steps run tap-major, channel-minor (C is a multiple of 64); the position is stepped, not divided out
         c_c0[f] += SK * 64;
         while (c_c0[f] >= p.cC) {
           c_c0[f] -= p.cC;
           if (++c_q[f] == p.ckw) { c_q[f] = 0; ++c_r[f]; }
         }
       }
-    } else {   // a wave's fragments lie next to each other, here and there
-      bload16<0>(l_x, dst, l_xlane, l_xoff);
-      if constexpr (XC > 1) bload16<1024>(l_x, dst, l_xlane, l_xoff);
-      if constexpr (XC > 2) {
-        bload16<2048>(l_x, dst, l_xlane, l_xoff);
-        bload16<3072>(l_x, dst, l_xlane, l_xoff);
-      }
-      l_xoff += SK * 1024;
     }
+  };
+  auto ask_part = [&](auto& w, v4i* slot, int i) __attribute__((always_inline)) {   // the i-th load of a stage
+    if (i >= XC) ask_codes(w, i - XC);
+    else if (i == 0) ask_acts(slot, std::integral_constant<int, 0>{});
+    else if (i == 1) ask_acts(slot, std::integral_constant<int, (XC > 1 ? 1 : 0)>{});
+    else if (i == 2) ask_acts(slot, std::integral_constant<int, (XC > 2 ? 2 : 0)>{});
+    else ask_acts(slot, std::integral_constant<int, (XC > 2 ? 3 : 0)>{});
+  };
+  auto request = [&](auto& w, v4i* slot) __attribute__((always_inline)) {
+    constexpr int NI = (int)std::extent<std::remove_reference_t<decltype(w)>>::value;
+    if constexpr (DP == 1) {
+      unsigned off = lane * 16;
+      asm volatile("" : "+v"(off));   // a 32-bit offset next to the loads: they take the scalar base + offset form
+#pragma unroll
+      for (int r = 0; r < NI; ++r) {
+#pragma unroll
+        for (int q = 0; q < WN; ++q) w[r].v[q] = gload16(l_wb[r] + q * 1024 + off);
+        l_wb[r] += WN * 1024;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < XC; ++i) ask_part(w, slot, i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < XC + NI * WN; ++i) ask_part(w, slot, i);
+    }
+    ask_next();
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto wait_all = [&]() __attribute__((always_inline)) {
-    __builtin_amdgcn_s_waitcnt(wait_imm(0, 0));
+  auto wait_for = [&](auto left) __attribute__((always_inline)) {   // until all but the last `left` loads have arrived
+    __builtin_amdgcn_s_waitcnt(wait_imm(decltype(left)::value, 0));
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
   // ---- what the epilogue needs travels beside the first stage, into LDS of this wave
+  float e_scl, e_bias = 0.f;
+  int e_rs = 0;
   {
     const int r = lane >> 4;
     int sp = 0, br = 0;
@@ -222,19 +272,16 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
       sp |= r == q ? spos[q] : 0;
       br |= r == q ? max(rb[q], 0) * 16 + ((ups >> q) & 1 ? p.hidden : 0) : 0;
     }
-    dma4(p.scales + (size_t)sp * 16 + (lane & 15), lds_addr(&lds.scl[wave][0]));
-    if (p.bias != nullptr) dma4(p.bias + (size_t)m * p.bias_mstride + br + (lane & 15), lds_addr(&lds.bias[wave][0]));
-    if (OFF && !CONV) {
-      dma4(p.rowsum + (size_t)m * p.rowsum_mstride + min(t0 + lane, p.T_pad - 1), lds_addr(&lds.rs[wave][0]));
-      if (MTB == 8) dma4(p.rowsum + (size_t)m * p.rowsum_mstride + min(t0 + 64 + lane, p.T_pad - 1), lds_addr(&lds.rs[wave][RSN - 64]));
-    }
+    e_scl = p.scales[(size_t)sp * 16 + (lane & 15)];
+    if (p.bias != nullptr) e_bias = p.bias[(size_t)m * p.bias_mstride + br + (lane & 15)];
+    if (OFF && !CONV) e_rs = p.rowsum[(size_t)m * p.rowsum_mstride + min(tg + lane, p.T_pad - 1)];
   }
   const float sx = p.s_x[m * p.sx_mstride];
   auto window_sums = [&]() __attribute__((always_inline)) {
     if constexpr (OFF != 0 && CONV) {
       // token code sum = the channel sums of the window's pixels that lie inside the image
-      for (int t1 = 0; t1 < RSN; t1 += 64) {
-        const int t = t0 + min(t1 + lane, 16 * MTB - 1);
+      {
+        const int t = tg + min(lane, 16 * MB - 1);
         const int wo = t % p.cWo, ho = (t / p.cWo) % p.cHo, img = t / (p.cWo * p.cHo);
         const int h0 = ho * p.cstride - p.cpad, w0_ = wo * p.cstride - p.cpad;
         // nine taps' loads in flight (one after the other they took 2.2 of the 14.5 us of a 3 x 3 layer's workgroup); a tap outside
@@ -252,9 +299,15 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
 #pragma unroll
           for (int i = 0; i < 9; ++i) sum += in[i] ? c[i] : 0;
         }
-        lds.rs[wave][t1 + lane] = sum;
+        e_rs = sum;
       }
     }
+  };
+
+  auto side = [&]() __attribute__((always_inline)) {
+    lds.scl[wid][lane] = e_scl;
+    lds.bias[wid][lane] = e_bias;
+    if (OFF) lds.rs[wid][lane] = e_rs;
   };
 
   v4i acc[4][MTB];
@@ -266,21 +319,24 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   // ---- the walk along k with the first NI items of every bin of the tile
   auto walk = [&](auto ni) __attribute__((always_inline)) {
     constexpr int NI = decltype(ni)::value;
-    Codes<BITS, SK> w0[NI], w1[NI];
+    constexpr int AHEAD = (DP - 1) * (NI * WN + XC);   // loads in flight behind those of the next stage
+    Codes<BITS, SK> w0[NI], w1[NI], w2[DP > 1 ? NI : 1];
     request(w0, xs0);
+    if constexpr (DP > 1) request(w1, xs1);
     window_sums();
-    wait_all();
+    side();
+    wait_for(std::integral_constant<int, AHEAD>{});
     // One stage: its codes and activations have arrived (every wave waits for its own at the end of the stage before)
     // and `far` and `free_slot`, multiplied in the stage before, take the stage that is requested now.
     auto stage = [&](Codes<BITS, SK>(&now)[NI], const v4i* slot, Codes<BITS, SK>(&far)[NI], v4i* free_slot, bool multiply, bool ask) __attribute__((always_inline)) {
       asm volatile("s_barrier" ::: "memory");    // everyone's have arrived, and the slot of the stage before is free
-      if (ask) request(far, free_slot);
+      if (DP == 1 ? ask : !multiply) request(far, free_slot);
       __builtin_amdgcn_sched_barrier(0);
       if (multiply) {
         // Software pipeline of the SK 64-k steps: a wave issues in order, so everything that is not an MFMA has to sit in
         // the shadow of one.  The fragments of step j+1 are requested before step j's MFMAs start (two register
         // sets), and the codes of item r+1 are widened between the MFMAs of item r (two register sets).
-        const v4i* xs = slot + lane;
+        const v4i* xs = slot + grp * (MTB * SK * FRAG) + lane;
         v4i xf[XF][MTB];
         v4i wf[2];
 #pragma unroll
@@ -295,6 +351,13 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
 #pragma unroll
           for (int r = 0; r < NI; ++r) {
             const int n = j * NI + r;   // item-steps so far: the register set of this one's codes
+            if constexpr (DP > 1) {     // its share of the loads that are requested now
+              constexpr int TOT = NI * WN + XC, STEPS = SK * NI;
+#pragma unroll
+              for (int i = n * TOT / STEPS; i < (n + 1) * TOT / STEPS; ++i) ask_part(far, free_slot, i);
+              if (n == STEPS - 1) ask_next();
+              __builtin_amdgcn_sched_barrier(0);
+            }
             if (r + 1 < NI) wf[(n + 1) & 1] = widen<BITS, SK>(now[r + 1], j);
             else if (j + 1 < SK) wf[(n + 1) & 1] = widen<BITS, SK>(now[0], j + 1);
 #pragma unroll
@@ -316,29 +379,64 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
           }
         }
       }
-      wait_all();
+      wait_for(std::integral_constant<int, AHEAD>{});
     };
     // Two stages a round, so that the slots and register sets keep their roles; behind an odd number of stages the second
     // half multiplies nothing.
-    for (int s = 0; s < n_stage; s += 2) {
-      stage(w0, xs0, w1, xs1, active, s + 1 < n_stage);
-      stage(w1, xs1, w0, xs0, active && s + 1 < n_stage, s + 2 < n_stage);
+    if constexpr (DP == 1) {
+      for (int s = 0; s < n_stage; s += 2) {
+        stage(w0, xs0, w1, xs1, active, s + 1 < n_stage);
+        stage(w1, xs1, w0, xs0, active && s + 1 < n_stage, s + 2 < n_stage);
+      }
+    } else {
+      for (int s = 0;; s += 3) {
+        stage(w0, xs0, w2, xs2, active && s < n_stage, true);
+        if (s + 1 >= n_max) break;
+        stage(w1, xs1, w0, xs0, active && s + 1 < n_stage, true);
+        if (s + 2 >= n_max) break;
+        stage(w2, xs2, w1, xs1, active && s + 2 < n_stage, true);
+        if (s + 3 >= n_max) break;
+      }
+      wait_for(std::integral_constant<int, 0>{});   // the slots are written to the end
     }
   };
   // (64 tokens of the ternary convolution: a second loop would spill; chain layers: see launch_gemm_bins)
   constexpr bool THREE = !(CONV && SK * MTB == 16) && MODE != MODE_CHAIN;
-  if (tile_items == 0) { window_sums(); wait_all(); }
+  if (tile_items == 0) { window_sums(); side(); }
   else if (THREE && tile_items == 3 && p.three) walk(std::integral_constant<int, THREE ? 3 : 4>{});
   else walk(std::integral_constant<int, 4>{});
+
+  // ---- the groups' sums meet: in step i a group hands the token blocks of the i-th group behind it over
+  v4i own[4][MB];
+  if constexpr (G == 1) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int b = 0; b < MB; ++b) own[r][b] = acc[r][b];
+  } else {
+    // one token block after the other, through 16 KiB of each of two slots
+    static_assert(G == 2 && SLOT >= 16 * FRAG, "exchange");
+    v4i* mine = (grp == 0 ? xs0 : xs1) + wave * (4 * FRAG) + lane;
+    const v4i* other = (grp == 0 ? xs1 : xs0) + wave * (4 * FRAG) + lane;
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+      __syncthreads();   // the slots have been read
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mine[r * FRAG] = grp == 0 ? acc[r][MB + b] : acc[r][b];
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) own[r][b] = (grp == 0 ? acc[r][b] : acc[r][MB + b]) + other[r * FRAG];
+    }
+  }
 
   // ---- epilogue: orders folded in ascending k, one output row block after the other.  A lane holds 4 channels of one
   // token per 16-token block, 64 contiguous bytes of a token per 16 lanes.
   int lane_e = lane;
   asm volatile("" : "+v"(lane_e));   // keeps the epilogue's addresses out of the loop's live range
   const int tl = lane_e & 15, g = lane_e >> 4;
-  int rs[MTB];
+  int rs[MB];
 #pragma unroll
-  for (int b = 0; b < MTB; ++b) rs[b] = OFF ? lds.rs[wave][b * 16 + tl] : 0;
+  for (int b = 0; b < MB; ++b) rs[b] = OFF ? lds.rs[wid][b * 16 + tl] : 0;
   // the slots as they are now, read while the orders are folded
   const bool two_sided = p.amax_neg != nullptr;
   float mx = 0.f, mn = 0.f;
@@ -349,49 +447,49 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   const int n_res = (MODE == MODE_CHAIN && p.res != nullptr) ? (p.apart ? (m < p.res_members ? 1 : 0) : p.res_members) : 0;
   const float* resm = MODE == MODE_CHAIN ? p.res + (size_t)(p.apart ? m : 0) * p.res_mstride + 4 * g : nullptr;
   // the skip tensor of a row block, requested a row block ahead (two sets of registers: with all four a workgroup less fits)
-  float4 rq[MODE == MODE_CHAIN ? 2 : 1][MODE == MODE_CHAIN ? MTB : 1];
+  float4 rq[MODE == MODE_CHAIN ? 2 : 1][MODE == MODE_CHAIN ? MB : 1];
   auto skip = [&](int r) __attribute__((always_inline)) {
     if constexpr (MODE == MODE_CHAIN) {
       if (n_res > 0 && ((ends >> r) & 1)) {
 #pragma unroll
-        for (int b = 0; b < MTB; ++b)
-          rq[r & 1][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(t0 + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
+        for (int b = 0; b < MB; ++b)
+          rq[r & 1][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(tg + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
       }
     }
   };
   skip(0);
-  float v[MTB][4], gate[MODE == MODE_GATED ? MTB : 1][4];
+  float v[MB][4], gate[MODE == MODE_GATED ? MB : 1][4];
 #pragma unroll
-  for (int b = 0; b < MTB; ++b)
+  for (int b = 0; b < MB; ++b)
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[b][i] = 0.f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     if (r < 3) skip(r + 1);
-    const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wave][r * 16 + g * 4]);
+    const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wid][r * 16 + g * 4]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float s = p.fold_sx ? sc[i] * sx : sc[i];
 #pragma unroll
-      for (int b = 0; b < MTB; ++b) v[b][i] = fmaf(s, (float)(acc[r][b][i] - OFF * rs[b]), v[b][i]);
+      for (int b = 0; b < MB; ++b) v[b][i] = fmaf(s, (float)(own[r][b][i] - OFF * rs[b]), v[b][i]);
     }
     if (!((ends >> r) & 1)) continue;
     v4f bb = v4f{0.f, 0.f, 0.f, 0.f};
-    if (with_bias) bb = *reinterpret_cast<const v4f*>(&lds.bias[wave][r * 16 + g * 4]);
+    if (with_bias) bb = *reinterpret_cast<const v4f*>(&lds.bias[wid][r * 16 + g * 4]);
 #pragma unroll
-    for (int b = 0; b < MTB; ++b)
+    for (int b = 0; b < MB; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[b][i] = p.fold_sx ? v[b][i] + bb[i] : fmaf(sx, v[b][i], bb[i]);   // same rounding as the other contraction kernels
     if (MODE == MODE_GATED && !((ups >> r) & 1)) {
 #pragma unroll
-      for (int b = 0; b < MTB; ++b)
+      for (int b = 0; b < MB; ++b)
 #pragma unroll
         for (int i = 0; i < 4; ++i) { gate[b][i] = v[b][i]; v[b][i] = 0.f; }
       continue;
     }
 #pragma unroll
-    for (int b = 0; b < MTB; ++b) {
-      const int t = t0 + b * 16 + tl;
+    for (int b = 0; b < MB; ++b) {
+      const int t = tg + b * 16 + tl;
       if (MODE == MODE_CHAIN) {
         float4 rs4 = n_res > 0 ? rq[r & 1][b] : make_float4(0.f, 0.f, 0.f, 0.f);
         for (int mm = 1; mm < n_res; ++mm) {   // a sum over several members, each with a skip tensor of its own
@@ -436,7 +534,7 @@ __global__ __launch_bounds__(256, MINW) void gemm_bins_kernel(const BinsParams p
   }
 }
 
-template <int BITS, int MTB, int MINW>
+template <int BITS, int MTB, int MINW, int G = 1, int DP = G>
 int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   const int n_tt = ceil_div(p.T, 16 * MTB);
   p.order = tile_order(n_ct, n_tt, false);
@@ -449,31 +547,31 @@ int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t 
   // but 3072 x 768 4 bit with GELU, 4096 tokens (1536 tiles, two full rounds of three) 30 -> 32.  Chain layers and
   // convolutions hold too much for four (they would spill).
   const bool chain = p.res != nullptr || act == PIPE_ACT_RELU;
-  if constexpr (MTB == 4 && MINW == 3) {
+  if constexpr (MTB == 4 && MINW == 3 && DP == 1) {
     const int64_t tiles = (int64_t)live_ct * n_tt, cus = pipe_resident_workgroups();
     const bool four = (tiles + 4 * cus - 1) / (4 * cus) * 4 <= (tiles + 3 * cus - 1) / (3 * cus) * 3;
     if (four && p.cq8 == nullptr && !chain) return launch_cfg<BITS, MTB, 4>(p, live_ct, n_ct, ev0, ev1, st);
   }
-  if constexpr (MTB == 4 && MINW == 4) {
+  if constexpr (MTB == 4 && MINW == 4 && DP == 1) {
     if (p.cq8 != nullptr || chain) return PIPE_EINVAL;
   } else {
     if (p.cq8 != nullptr) {
-      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true>), grid, dim3(256), st, ev0, ev1, p);
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
       PIPE_HIP(hipGetLastError());
       return PIPE_OK;
     }
     if (chain) {
-      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false>), grid, dim3(256), st, ev0, ev1, p);
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
       PIPE_HIP(hipGetLastError());
       return PIPE_OK;
     }
   }
   if (act == PIPE_ACT_GELU) {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GELU, false>), grid, dim3(256), st, ev0, ev1, p);
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GELU, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
   } else if (act == PIPE_ACT_SILU_GATED) {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GATED, false>), grid, dim3(256), st, ev0, ev1, p);
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GATED, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
   } else {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, false>), grid, dim3(256), st, ev0, ev1, p);
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
   }
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
@@ -533,21 +631,51 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
   // tokens: 22 us each).  Around the line of 192 tiles the choice is within 7 % of the best height for the 3 x 3 convolution 256 x 256 4 bit,
   // K = 3 (147 tiles of 64: 17.8 against 17.5 us; 196: 18.1 and 18.0) and for layers of 3072 x 768, 1024 x 1024 and 4096 x 4096 at 2, 4
   // and 8 bits; far below it 16 tokens lose to 32 by up to a quarter at 8 bits (128 x 128 convolution of 4704 pixels, K = 2: 14.0 and 11.0 us).
-  int mtb = g_tiled_mtb;
+  int mtb = g_tiled_mtb, groups = 1, ahead = 1;
   if (mtb != 1 && mtb != 2 && mtb != 4) {
     auto tiles = [&](int tokens) { return (int64_t)tb->n_ct * ceil_div(a.T, tokens); };
     mtb = tiles(64) >= 192 ? 4 : (tiles(32) >= 192 ? 2 : 1);
+    // Two groups of waves along k where the tiles leave places on the chip and the walk is long enough (24 64-k steps) for the second
+    // prologue and the exchange.  Tiles of 32 tokens where one each fills the compute units (4 bits, and ternary, where two share a unit
+    // on long walks): 768 x 3072 4 bit, K = 3, 1000 tokens 26.1 -> 21.9 us a call, 150 tokens 19.6 -> 18.5; 4096 x 11008, K = 4,
+    // 140 tokens 52.6 -> 33.3; 3x3 convolution of 512 x 7 x 7, 32 images 33.3 -> 26.0; 2048 x 2048 ternary, 200 tokens 15.9 -> 14.9;
+    // 4096 x 11008 ternary, 400 tokens 70.5 -> 64.7; with 16 steps equal (2048 x 1024, 300 tokens), with 12 slower (convolution of 64 channels
+    // 14.7 -> 16.7), and with more tiles slower (4096 x 4096 4 bit, 400 tokens, 520 tiles 33.7 -> 38.0).  Else of 64 tokens: 4096 x 11008 4 bit, 200
+    // tokens 57.0 -> 43.2; 768 x 3072, 2000 tokens 32.2 -> 28.8; convolution of 256 x 14 x 14, 32 images 27.5 -> 25.6; 8 bits, whose codes
+    // need the registers, only so: 4096 x 11008, K = 2, 300 tokens 69.9 -> 51.7 (26 tiles lose: 18.8 -> 22.3).
+    const int64_t cus = pipe_resident_workgroups();
+    if (e->nks >= 24) {
+      if (e->bits < 8 && tiles(32) <= (e->bits == 2 && e->nks >= 64 ? 2 * cus : cus)) { groups = 2; mtb = 2; }
+      else if (e->bits > 2 && tiles(64) <= cus && tiles(64) >= cus / 4) { groups = 2; mtb = 4; }
+    }
+    // Ternary tiles of 64 tokens that the chip holds at once ask for their loads between the multiplies, two stages ahead: 11008 x 4096, 333
+    // tokens (456 tiles) 37.4 -> 35.3 us a call; 4096 x 11008, 400 tokens 70.5 -> 66.3; but 4096 tokens 227 -> 243, and 4 bits
+    // the same (768 x 3072, 4096 tokens 44.1 -> 42.9; 4096 x 4096, 700 tokens 42.7 -> 45.4).
+    if (groups == 1 && mtb == 4 && e->bits == 2 && tiles(64) <= 2 * cus) ahead = 2;
   }
+  const int sk = e->bits == 2 || mtb == 1 || (groups == 2 && mtb == 2) ? 4 : 2;   // as in the kernel
+  p.one_tap = a.conv_q8 != nullptr && a.conv_C % (sk * 64) == 0;
+  const int live = tb->n_four + tb->n_three;
+  if (groups == 2) {
+    switch (e->bits * 8 + mtb) {
+      case 8 * 8 + 4: return launch_cfg<8, 4, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+      case 4 * 8 + 4: return launch_cfg<4, 4, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+      case 4 * 8 + 2: return launch_cfg<4, 2, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+      case 2 * 8 + 2: return launch_cfg<2, 2, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+      default: return PIPE_EINVAL;
+    }
+  }
+  if (ahead == 2) return launch_cfg<2, 4, 2, 1, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
   switch (e->bits * 8 + mtb) {
-    case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 8 * 8 + 1: return launch_cfg<8, 1, 2>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 4: return launch_cfg<4, 4, 3>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 2: return launch_cfg<4, 2, 4>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 1: return launch_cfg<4, 1, 3>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 4: return launch_cfg<2, 4, 3>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 2: return launch_cfg<2, 2, 4>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 1: return launch_cfg<2, 1, 4>(p, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 8 * 8 + 1: return launch_cfg<8, 1, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 4: return launch_cfg<4, 4, 3>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 2: return launch_cfg<4, 2, 4>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 4 * 8 + 1: return launch_cfg<4, 1, 3>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 4: return launch_cfg<2, 4, 3>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 2: return launch_cfg<2, 2, 4>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
+    case 2 * 8 + 1: return launch_cfg<2, 1, 4>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
     default: return PIPE_EINVAL;
   }
 }

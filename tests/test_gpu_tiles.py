@@ -35,7 +35,13 @@ LAYERS = [(16, 100, 4, 1, 1.0, 16, [1], 129),
           (320, 1030, 4, 3, 0.5, 32, [2, 1], 257),
           (256, 700, 8, 2, 1.0, 16, [1, 1], 191),
           (2048, 512, 3, 4, 0.5, 64, [2, 2], 400),   # 64-token tiles
-          (4096, 260, 2, 3, 0.5, 64, [3], 321)]
+          (4096, 260, 2, 3, 0.5, 64, [3], 321),
+          (4096, 1000, 2, 4, 0.5, 64, [4], 381),     # ternary, loads between the multiplies two stages ahead
+          (48, 1500, 4, 3, 0.5, 16, [3], 129),       # two groups along k: 24 steps ...
+          (320, 1700, 4, 4, 0.5, 16, [2, 2], 150),   # ... seven stages, four and three
+          (2048, 1800, 4, 4, 0.5, 16, [4], 501),     # ... tiles of 64 tokens
+          (2048, 1700, 2, 4, 0.5, 16, [4], 200),
+          (1024, 1800, 8, 2, 1.0, 16, [2], 502)]
 
 
 @pytest.mark.parametrize("O,I,bits,K,gamma,group,split,T", LAYERS)
@@ -222,3 +228,44 @@ def test_gelu_values(pipe, scale):
     err = (h.view(T, I).cpu().double() - ref).abs()
     assert bool((err <= 2.0 ** -23 * a.abs() + 1e-14).all()), float((err / a.abs().clamp(min=1e-30)).max())
     l1.free(), l2.free()
+
+
+# Two groups along k in the other epilogues and for convolutions: the sums are exact integers, so the height that is set by hand, which
+# runs with one group, gives the same bits.  nks = 28 and 36 steps; the convolutions have one tap a stage or several.
+@pytest.mark.parametrize("kind,T,C,k", [("gelu", 300, 1696, 0), ("gated", 300, 1696, 0), ("chain", 300, 1696, 0), ("chain", 1100, 1696, 0),
+                                        ("conv", 3, 256, 3), ("conv", 30, 256, 3), ("conv", 3, 64, 5), ("conv8", 40, 256, 3), ("conv2", 3, 256, 3)])
+def test_two_groups_equal_one(pipe, kind, T, C, k):
+    rng = np.random.default_rng(T + C)
+    made = []
+
+    def expand(O, I, bits=4):
+        made.append(pipe.pipe_expand(dev(_weight(O + I, O, I)), bits, 3, 0.5, 16))
+        return made[-1]
+
+    if kind in ("gelu", "gated"):
+        act = pipe.PIPE_ACT_GELU if kind == "gelu" else pipe.PIPE_ACT_SILU_GATED
+        l1, l2 = expand(512 if kind == "gelu" else 3200, C), expand(1008, 512 if kind == "gelu" else 1600)
+        x = dev(rng.standard_normal((T, C)).astype(np.float32))
+        call = lambda: pipe.pipe_mlp_forward(l1, l2, act, x, split=[2, 1], bias1=None, bias2=None, return_hidden=True)
+    elif kind == "chain":
+        R = pipe.PIPE_ACT_RELU
+        layers = [(expand(C, C), None, R, -1, True), (expand(C, C), None, R, 0, True), (expand(304, C), None, pipe.PIPE_ACT_NONE, -1, True)]
+        x = dev(rng.standard_normal((T, C)).astype(np.float32))
+        call = lambda: (pipe.pipe_chain_forward(layers, x, split=[2, 1]),)
+    else:
+        bits = {"conv": 4, "conv8": 8, "conv2": 2}[kind]
+        e = pipe.pipe_expand_conv2d(dev(_weight(C, 256, C * k * k)), C, k, k, bits, 3, 0.5, 16)
+        made.append(e)
+        x = dev(rng.standard_normal((T, C, 14, 13)).astype(np.float32))
+        call = lambda: (pipe.pipe_forward_conv2d(e, x, k, k, 1, k // 2, split=[3]),)
+    got = call()
+    for tile in (16, 32, 64):
+        pipe.pipe_set_token_tile(tile)
+        try:
+            one = call()
+        finally:
+            pipe.pipe_set_token_tile(0)
+        for a, b in zip(got, one):
+            assert torch.equal(a, b), "token tile %d" % tile
+    for e in made:
+        e.free()
