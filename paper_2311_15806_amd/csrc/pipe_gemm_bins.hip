@@ -78,7 +78,7 @@ struct BinsParams {
   int cC, cH, cW, ckh, ckw, cstride, cpad, cHo, cWo;
 };
 
-enum { MODE_PLAIN = 0, MODE_GELU = 2, MODE_GATED = 3, MODE_CHAIN = 4 };
+enum { MODE_PLAIN = 0, MODE_GELU = 2, MODE_GATED = 3, MODE_CHAIN = 4, MODE_RELU = 5 };
 
 // Packed codes of one item for one stage of SK 64-k steps.
 template <int BITS, int SK>
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
     }
   };
   // (64 tokens of the ternary convolution: a second loop would spill; chain layers: see launch_gemm_bins)
-  constexpr bool THREE = !(CONV && SK * MTB == 16) && MODE != MODE_CHAIN;
+  constexpr bool THREE = !(CONV && SK * MTB == 16) && MODE != MODE_CHAIN && MODE != MODE_RELU;
   if (tile_items == 0) { window_sums(); side(); }
   else if (THREE && tile_items == 3 && p.three) walk(std::integral_constant<int, THREE ? 3 : 4>{});
   else walk(std::integral_constant<int, 4>{});
@@ -446,18 +446,20 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
   float* ym = p.y + (size_t)(p.apart ? m : 0) * p.T * p.out + 4 * g;
   const int n_res = (MODE == MODE_CHAIN && p.res != nullptr) ? (p.apart ? (m < p.res_members ? 1 : 0) : p.res_members) : 0;
   const float* resm = MODE == MODE_CHAIN ? p.res + (size_t)(p.apart ? m : 0) * p.res_mstride + 4 * g : nullptr;
-  // the skip tensor of a row block, requested a row block ahead (two sets of registers: with all four a workgroup less fits)
-  float4 rq[MODE == MODE_CHAIN ? 2 : 1][MODE == MODE_CHAIN ? MB : 1];
+  // the skip tensor of a row block, requested a row block ahead (two sets of registers: with all four a workgroup less fits), or
+  // with it where four workgroups cover it
+  constexpr int RQ = MINW == 4 ? 1 : 2;
+  float4 rq[MODE == MODE_CHAIN ? RQ : 1][MODE == MODE_CHAIN ? MB : 1];
   auto skip = [&](int r) __attribute__((always_inline)) {
     if constexpr (MODE == MODE_CHAIN) {
       if (n_res > 0 && ((ends >> r) & 1)) {
 #pragma unroll
         for (int b = 0; b < MB; ++b)
-          rq[r & 1][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(tg + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
+          rq[r & (RQ - 1)][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(tg + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
       }
     }
   };
-  skip(0);
+  if (RQ == 2) skip(0);
   float v[MB][4], gate[MODE == MODE_GATED ? MB : 1][4];
 #pragma unroll
   for (int b = 0; b < MB; ++b)
@@ -465,7 +467,8 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
     for (int i = 0; i < 4; ++i) v[b][i] = 0.f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    if (r < 3) skip(r + 1);
+    if (RQ == 1) skip(r);
+    else if (r < 3) skip(r + 1);
     const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wid][r * 16 + g * 4]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
     for (int b = 0; b < MB; ++b) {
       const int t = tg + b * 16 + tl;
       if (MODE == MODE_CHAIN) {
-        float4 rs4 = n_res > 0 ? rq[r & 1][b] : make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 rs4 = n_res > 0 ? rq[r & (RQ - 1)][b] : make_float4(0.f, 0.f, 0.f, 0.f);
         for (int mm = 1; mm < n_res; ++mm) {   // a sum over several members, each with a skip tensor of its own
           const float4 x = *reinterpret_cast<const float4*>(resm + (size_t)mm * p.res_mstride + (size_t)min(t, p.T - 1) * p.out + rb[r] * 16);
           rs4.x += x.x; rs4.y += x.y; rs4.z += x.z; rs4.w += x.w;
@@ -507,6 +510,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
+        if (MODE == MODE_RELU) v[b][i] = fmaxf(v[b][i], 0.f);
         if (MODE == MODE_GELU) v[b][i] = gelu_erf(v[b][i]);
         if (MODE == MODE_GATED) v[b][i] = gate[b][i] / (1.f + expf(-gate[b][i])) * v[b][i];
       }
@@ -544,16 +548,27 @@ int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t 
   // Workgroups per compute unit, three or four: four cover each other's epilogues and first loads better (a round of four takes
   // 1.30 of one of three, not 1.33), but end in larger rounds.  So four where as many or fewer places are filled: 11008 x 4096 ternary, 4096
   // tokens (4816 tiles) 197 -> 191 us, 700 tokens 46.2 -> 44.4, 3300 165 -> 162; gate||up 22016 x 4096 4 bit, 2048 tokens 398 -> 372;
-  // but 3072 x 768 4 bit with GELU, 4096 tokens (1536 tiles, two full rounds of three) 30 -> 32.  Chain layers and
-  // convolutions hold too much for four (they would spill).
+  // but 3072 x 768 4 bit with GELU, 4096 tokens (1536 tiles, two full rounds of three) 30 -> 32.  Chain layers
+  // without a skip tensor have a mode of their own, the others request theirs a row block at a time: eight 2048 x 2048 ternary layers, two members
+  // of 4 orders, 4096 tokens 682 -> 658 us, six 4-bit ones of two members of 2 orders, 2500 tokens 444 -> 423.  Convolutions hold too much for four (they would spill).
   const bool chain = p.res != nullptr || act == PIPE_ACT_RELU;
   if constexpr (MTB == 4 && MINW == 3 && DP == 1) {
     const int64_t tiles = (int64_t)live_ct * n_tt, cus = pipe_resident_workgroups();
     const bool four = (tiles + 4 * cus - 1) / (4 * cus) * 4 <= (tiles + 3 * cus - 1) / (3 * cus) * 3;
-    if (four && p.cq8 == nullptr && !chain) return launch_cfg<BITS, MTB, 4>(p, live_ct, n_ct, ev0, ev1, st);
+    if (four && p.cq8 == nullptr) return launch_cfg<BITS, MTB, 4>(p, live_ct, n_ct, ev0, ev1, st);
   }
   if constexpr (MTB == 4 && MINW == 4 && DP == 1) {
-    if (p.cq8 != nullptr || chain) return PIPE_EINVAL;
+    if (p.cq8 != nullptr) return PIPE_EINVAL;
+    if (chain && p.res == nullptr) {
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_RELU, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+      PIPE_HIP(hipGetLastError());
+      return PIPE_OK;
+    }
+    if (chain) {
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+      PIPE_HIP(hipGetLastError());
+      return PIPE_OK;
+    }
   } else {
     if (p.cq8 != nullptr) {
       PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);

@@ -232,7 +232,7 @@ def test_gelu_values(pipe, scale):
 
 # Two groups along k in the other epilogues and for convolutions: the sums are exact integers, so the height that is set by hand, which
 # runs with one group, gives the same bits.  nks = 28 and 36 steps; the convolutions have one tap a stage or several.
-@pytest.mark.parametrize("kind,T,C,k", [("gelu", 300, 1696, 0), ("gated", 300, 1696, 0), ("chain", 300, 1696, 0), ("chain", 1100, 1696, 0),
+@pytest.mark.parametrize("kind,T,C,k", [("gelu", 300, 1696, 0), ("gated", 300, 1696, 0), ("chain", 300, 1696, 0), ("chain", 1100, 1696, 0), ("chain", 13000, 512, 0), ("chain2", 13000, 512, 0),
                                         ("conv", 3, 256, 3), ("conv", 30, 256, 3), ("conv", 3, 64, 5), ("conv8", 40, 256, 3), ("conv2", 3, 256, 3)])
 def test_two_groups_equal_one(pipe, kind, T, C, k):
     rng = np.random.default_rng(T + C)
@@ -247,9 +247,10 @@ def test_two_groups_equal_one(pipe, kind, T, C, k):
         l1, l2 = expand(512 if kind == "gelu" else 3200, C), expand(1008, 512 if kind == "gelu" else 1600)
         x = dev(rng.standard_normal((T, C)).astype(np.float32))
         call = lambda: pipe.pipe_mlp_forward(l1, l2, act, x, split=[2, 1], bias1=None, bias2=None, return_hidden=True)
-    elif kind == "chain":
+    elif kind in ("chain", "chain2"):   # (816 to 1020 tiles of 64 tokens: four workgroups per compute unit)
         R = pipe.PIPE_ACT_RELU
-        layers = [(expand(C, C), None, R, -1, True), (expand(C, C), None, R, 0, True), (expand(304, C), None, pipe.PIPE_ACT_NONE, -1, True)]
+        bits = 4 if kind == "chain" else 2
+        layers = [(expand(C, C, bits), None, R, -1, True), (expand(C, C, bits), None, R, 0, True), (expand(304, C, bits), None, pipe.PIPE_ACT_NONE, -1, True)]
         x = dev(rng.standard_normal((T, C)).astype(np.float32))
         call = lambda: (pipe.pipe_chain_forward(layers, x, split=[2, 1]),)
     else:
