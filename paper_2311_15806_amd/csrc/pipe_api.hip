@@ -770,6 +770,7 @@ const TileBins* pipe_get_bins(const pipe_expansion* ce, const GemmArgs& a, int* 
       const int most = std::max(std::max(bins[c].info[3], bins[c + 1].info[3]), std::max(bins[c + 2].info[3], bins[c + 3].info[3]));
       if ((most == 0) != (dead_ones == 1)) continue;
       if (most > 0) ++(most > 3 ? t.n_four : t.n_three);
+      ++(most > 0 ? t.live_ct : t.dead_ct)[bins[c].info[0]];
       for (int w = 0; w < 4; ++w) {
         ordered.push_back(bins[c + w]);
         ordered.back().info[3] = (bins[c + w].info[3] > 0 ? 1 : 0) | (most > 3 ? 4 : most > 0 ? 3 : 0) << 1;
@@ -922,7 +923,8 @@ static int run_gemm(const GemmArgs& a0, bool small, hipStream_t st) {
   bool timed = false;
   int rc = timing_events(&a.ev_start, &a.ev_stop, &timed);
   if (rc) return rc;
-  rc = small ? launch_gemm_stream(a, st) : pipe_bins_apply(a) ? launch_gemm_bins(a, st) : launch_gemm_tiled(a, st);
+  rc = small ? launch_gemm_stream(a, st)
+       : pipe_bins_apply(a) ? launch_gemm_bins(a, st) : pipe_sum_apply(a) ? launch_gemm_sum(a, st) : launch_gemm_tiled(a, st);
   if (timed && rc == PIPE_OK) g_events_used += 2;
   return rc;
 }

@@ -69,6 +69,8 @@ struct BinsParams {
   long long res_mstride;
   int res_members, res_pre_act;
   int hidden;                     // MODE_GATED: rows are gate [0,H) and up [H,2H), y is [M,T,H]
+  int later;                      // 1: MODE_SUM
+  int dead_ct, dead_gap;          // column tiles from dead_ct on lie dead_gap further on
   int three;                      // 1: tiles of 3 items walk with 3
   TileOrder order;
   const int8_t* cq8;              // CONV (implicit GEMM), as in pipe_gemm.hip
@@ -78,7 +80,8 @@ struct BinsParams {
   int cC, cH, cW, ckh, ckw, cstride, cpad, cHo, cWo;
 };
 
-enum { MODE_PLAIN = 0, MODE_GELU = 2, MODE_GATED = 3, MODE_CHAIN = 4, MODE_RELU = 5 };
+enum { MODE_PLAIN = 0, MODE_GELU = 2, MODE_GATED = 3, MODE_CHAIN = 4, MODE_RELU = 5,
+       MODE_SUM = 6 };   // a member of a sum behind the first: y is read, its orders are added, y is written
 
 // Packed codes of one item for one stage of SK 64-k steps.
 template <int BITS, int SK>
@@ -138,6 +141,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
   int ct, tt;
   if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
   const int t0 = tt * (16 * MTB);
+  if (ct >= p.dead_ct) ct += p.dead_gap;
   const TileBin* bin = p.bins + ct * 4 + wave;
   const v4i pos = cload(&bin->pos, 0), spos = cload(&bin->spos, 0), rb = cload(&bin->rb, 0), info = cload(&bin->info, 0);
   const int m = info[0], ends = info[1], ups = info[2];   // member; items that end a row block; items of an up block
@@ -449,13 +453,21 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
   // the skip tensor of a row block, requested a row block ahead (two sets of registers: with all four a workgroup less fits), or
   // with it where four workgroups cover it
   constexpr int RQ = MINW == 4 ? 1 : 2;
-  float4 rq[MODE == MODE_CHAIN ? RQ : 1][MODE == MODE_CHAIN ? MB : 1];
+  constexpr bool READS = MODE == MODE_CHAIN || MODE == MODE_SUM;
+  float4 rq[READS ? RQ : 1][READS ? MB : 1];
   auto skip = [&](int r) __attribute__((always_inline)) {
     if constexpr (MODE == MODE_CHAIN) {
       if (n_res > 0 && ((ends >> r) & 1)) {
 #pragma unroll
         for (int b = 0; b < MB; ++b)
           rq[r & (RQ - 1)][b] = *reinterpret_cast<const float4*>(resm + (size_t)min(tg + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
+      }
+    }
+    if constexpr (MODE == MODE_SUM) {   // what the members before have left, with the row block's first item
+      if (rb[r] >= 0 && (r == 0 || ((ends >> (r - 1)) & 1))) {
+#pragma unroll
+        for (int b = 0; b < MB; ++b)
+          rq[r & (RQ - 1)][b] = *reinterpret_cast<const float4*>(ym + (size_t)min(tg + b * 16 + tl, p.T - 1) * p.out + rb[r] * 16);
       }
     }
   };
@@ -469,6 +481,15 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
   for (int r = 0; r < 4; ++r) {
     if (RQ == 1) skip(r);
     else if (r < 3) skip(r + 1);
+    if constexpr (MODE == MODE_SUM) {
+      if (rb[r] >= 0 && (r == 0 || ((ends >> (r - 1)) & 1))) {
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+          const float4 y0 = rq[r & (RQ - 1)][b];
+          v[b][0] = y0.x; v[b][1] = y0.y; v[b][2] = y0.z; v[b][3] = y0.w;
+        }
+      }
+    }
     const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wid][r * 16 + g * 4]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -581,7 +602,9 @@ int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t 
       return PIPE_OK;
     }
   }
-  if (act == PIPE_ACT_GELU) {
+  if (p.later) {
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_SUM, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+  } else if (act == PIPE_ACT_GELU) {
     PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GELU, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
   } else if (act == PIPE_ACT_SILU_GATED) {
     PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GATED, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
@@ -592,10 +615,66 @@ int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t 
   return PIPE_OK;
 }
 
+// The tiles' height, groups and loads ahead, by how many there are
+int launch_tiles(BinsParams& p, int bits, int live, int n_ct, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
+  // Token-tile height: 64 tokens amortize the unpacking of the codes best (the 4096-token layer above: 203, 245 and 317 us
+  // with 64, 32 and 16), and a second tile on a compute unit costs less than twice one; so the tallest that still gives
+  // three quarters of the 256 compute units a tile (256 tokens of that layer, 304 tiles of 64: 29.4, 27.2 and 29.1 us; 129
+  // tokens: 22 us each).  Around the line of 192 tiles the choice is within 7 % of the best height for the 3 x 3 convolution 256 x 256 4 bit,
+  // K = 3 (147 tiles of 64: 17.8 against 17.5 us; 196: 18.1 and 18.0) and for layers of 3072 x 768, 1024 x 1024 and 4096 x 4096 at 2, 4
+  // and 8 bits; far below it 16 tokens lose to 32 by up to a quarter at 8 bits (128 x 128 convolution of 4704 pixels, K = 2: 14.0 and 11.0 us).
+  int mtb = g_tiled_mtb, groups = 1, ahead = 1;
+  if (mtb != 1 && mtb != 2 && mtb != 4) {
+    auto tiles = [&](int tokens) { return (int64_t)n_ct * ceil_div(p.T, tokens); };
+    mtb = tiles(64) >= 192 ? 4 : (tiles(32) >= 192 ? 2 : 1);
+    // Two groups of waves along k where the tiles leave places on the chip and the walk is long enough (24 64-k steps) for the second
+    // prologue and the exchange.  Tiles of 32 tokens where one each fills the compute units (4 bits, and ternary, where two share a unit
+    // on long walks): 768 x 3072 4 bit, K = 3, 1000 tokens 26.1 -> 21.9 us a call, 150 tokens 19.6 -> 18.5; 4096 x 11008, K = 4,
+    // 140 tokens 52.6 -> 33.3; 3x3 convolution of 512 x 7 x 7, 32 images 33.3 -> 26.0; 2048 x 2048 ternary, 200 tokens 15.9 -> 14.9;
+    // 4096 x 11008 ternary, 400 tokens 70.5 -> 64.7; with 16 steps equal (2048 x 1024, 300 tokens), with 12 slower (convolution of 64 channels
+    // 14.7 -> 16.7), and with more tiles slower (4096 x 4096 4 bit, 400 tokens, 520 tiles 33.7 -> 38.0).  Else of 64 tokens: 4096 x 11008 4 bit, 200
+    // tokens 57.0 -> 43.2; 768 x 3072, 2000 tokens 32.2 -> 28.8; convolution of 256 x 14 x 14, 32 images 27.5 -> 25.6; 8 bits, whose codes
+    // need the registers, only so: 4096 x 11008, K = 2, 300 tokens 69.9 -> 51.7 (26 tiles lose: 18.8 -> 22.3).
+    const int64_t cus = pipe_resident_workgroups();
+    if (p.nks >= 24) {
+      if (bits < 8 && tiles(32) <= (bits == 2 && p.nks >= 64 ? 2 * cus : cus)) { groups = 2; mtb = 2; }
+      else if (bits > 2 && tiles(64) <= cus && tiles(64) >= cus / 4) { groups = 2; mtb = 4; }
+    }
+    // Ternary tiles of 64 tokens that the chip holds at once ask for their loads between the multiplies, two stages ahead: 11008 x 4096, 333
+    // tokens (456 tiles) 37.4 -> 35.3 us a call; 4096 x 11008, 400 tokens 70.5 -> 66.3; but 4096 tokens 227 -> 243, and 4 bits
+    // the same (768 x 3072, 4096 tokens 44.1 -> 42.9; 4096 x 4096, 700 tokens 42.7 -> 45.4).
+    if (groups == 1 && mtb == 4 && bits == 2 && tiles(64) <= 2 * cus) ahead = 2;
+  }
+  const int sk = bits == 2 || mtb == 1 || (groups == 2 && mtb == 2) ? 4 : 2;   // as in the kernel
+  p.one_tap = p.cq8 != nullptr && p.cC % (sk * 64) == 0;
+  if (groups == 2) {
+    switch (bits * 8 + mtb) {
+      case 8 * 8 + 4: return launch_cfg<8, 4, 2, 2>(p, live, n_ct, ev0, ev1, st);
+      case 4 * 8 + 4: return launch_cfg<4, 4, 2, 2>(p, live, n_ct, ev0, ev1, st);
+      case 4 * 8 + 2: return launch_cfg<4, 2, 2, 2>(p, live, n_ct, ev0, ev1, st);
+      case 2 * 8 + 2: return launch_cfg<2, 2, 2, 2>(p, live, n_ct, ev0, ev1, st);
+      default: return PIPE_EINVAL;
+    }
+  }
+  if (ahead == 2) return launch_cfg<2, 4, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+  switch (bits * 8 + mtb) {
+    case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, live, n_ct, ev0, ev1, st);
+    case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, live, n_ct, ev0, ev1, st);
+    case 8 * 8 + 1: return launch_cfg<8, 1, 2>(p, live, n_ct, ev0, ev1, st);
+    case 4 * 8 + 4: return launch_cfg<4, 4, 3>(p, live, n_ct, ev0, ev1, st);
+    case 4 * 8 + 2: return launch_cfg<4, 2, 4>(p, live, n_ct, ev0, ev1, st);
+    case 4 * 8 + 1: return launch_cfg<4, 1, 3>(p, live, n_ct, ev0, ev1, st);
+    case 2 * 8 + 4: return launch_cfg<2, 4, 3>(p, live, n_ct, ev0, ev1, st);
+    case 2 * 8 + 2: return launch_cfg<2, 2, 4>(p, live, n_ct, ev0, ev1, st);
+    case 2 * 8 + 1: return launch_cfg<2, 1, 4>(p, live, n_ct, ev0, ev1, st);
+    default: return PIPE_EINVAL;
+  }
+}
+
 }  // namespace
 
 // Members whose outputs stay apart each have their own bins; members that share one input and are summed are one set of
-// orders.  A sum over members with inputs of their own, a member with more orders than a bin holds, a gate||up pair that
+// orders.  A sum over members with inputs of their own (but see pipe_sum_apply), a member with more orders than a bin holds, a gate||up pair that
 // may need more than a bin (3 orders and more), and the integer export run pass by pass (pipe_gemm.hip).
 bool pipe_bins_apply(const GemmArgs& a) {
   if (a.acc_out != nullptr) return false;
@@ -632,6 +711,7 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
   // all kept 104.8 -> 97.4), and the chains' layers by any (eight 2048 x 2048 ternary layers, two members of 4 orders, 2000 tokens 404 ->
   // 439 us; five, K = 3, all kept, 1000 tokens 145 -> 155): they walk with 4.
   p.three = a.act != PIPE_ACT_GELU || tb->n_four * 8 <= tb->n_three;
+  p.later = 0; p.dead_ct = tb->n_ct; p.dead_gap = 0;
   p.T = a.T; p.T_pad = a.T_pad; p.out = e->out; p.nks = e->nks;
   p.apart = !a.reduce; p.fold_sx = a.reduce && a.M > 1; p.act = a.act;
   p.res = a.res; p.res_mstride = a.res_mstride; p.res_members = a.res_members; p.res_pre_act = a.res_pre_act;
@@ -640,57 +720,60 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
   p.cq8 = a.conv_q8; p.ccsum = a.conv_csum; p.cbytes = a.conv_q8 != nullptr ? (unsigned)((int64_t)a.T / (a.conv_Ho * a.conv_Wo) * a.conv_C * a.conv_H * a.conv_W) : 0u;
   p.cC = a.conv_C; p.cH = a.conv_H; p.cW = a.conv_W; p.ckh = a.conv_kh; p.ckw = a.conv_kw; p.cstride = a.conv_stride; p.cpad = a.conv_pad;
   p.cHo = a.conv_Ho; p.cWo = a.conv_Wo;
-  // Token-tile height: 64 tokens amortize the unpacking of the codes best (the 4096-token layer above: 203, 245 and 317 us
-  // with 64, 32 and 16), and a second tile on a compute unit costs less than twice one; so the tallest that still gives
-  // three quarters of the 256 compute units a tile (256 tokens of that layer, 304 tiles of 64: 29.4, 27.2 and 29.1 us; 129
-  // tokens: 22 us each).  Around the line of 192 tiles the choice is within 7 % of the best height for the 3 x 3 convolution 256 x 256 4 bit,
-  // K = 3 (147 tiles of 64: 17.8 against 17.5 us; 196: 18.1 and 18.0) and for layers of 3072 x 768, 1024 x 1024 and 4096 x 4096 at 2, 4
-  // and 8 bits; far below it 16 tokens lose to 32 by up to a quarter at 8 bits (128 x 128 convolution of 4704 pixels, K = 2: 14.0 and 11.0 us).
-  int mtb = g_tiled_mtb, groups = 1, ahead = 1;
-  if (mtb != 1 && mtb != 2 && mtb != 4) {
-    auto tiles = [&](int tokens) { return (int64_t)tb->n_ct * ceil_div(a.T, tokens); };
-    mtb = tiles(64) >= 192 ? 4 : (tiles(32) >= 192 ? 2 : 1);
-    // Two groups of waves along k where the tiles leave places on the chip and the walk is long enough (24 64-k steps) for the second
-    // prologue and the exchange.  Tiles of 32 tokens where one each fills the compute units (4 bits, and ternary, where two share a unit
-    // on long walks): 768 x 3072 4 bit, K = 3, 1000 tokens 26.1 -> 21.9 us a call, 150 tokens 19.6 -> 18.5; 4096 x 11008, K = 4,
-    // 140 tokens 52.6 -> 33.3; 3x3 convolution of 512 x 7 x 7, 32 images 33.3 -> 26.0; 2048 x 2048 ternary, 200 tokens 15.9 -> 14.9;
-    // 4096 x 11008 ternary, 400 tokens 70.5 -> 64.7; with 16 steps equal (2048 x 1024, 300 tokens), with 12 slower (convolution of 64 channels
-    // 14.7 -> 16.7), and with more tiles slower (4096 x 4096 4 bit, 400 tokens, 520 tiles 33.7 -> 38.0).  Else of 64 tokens: 4096 x 11008 4 bit, 200
-    // tokens 57.0 -> 43.2; 768 x 3072, 2000 tokens 32.2 -> 28.8; convolution of 256 x 14 x 14, 32 images 27.5 -> 25.6; 8 bits, whose codes
-    // need the registers, only so: 4096 x 11008, K = 2, 300 tokens 69.9 -> 51.7 (26 tiles lose: 18.8 -> 22.3).
-    const int64_t cus = pipe_resident_workgroups();
-    if (e->nks >= 24) {
-      if (e->bits < 8 && tiles(32) <= (e->bits == 2 && e->nks >= 64 ? 2 * cus : cus)) { groups = 2; mtb = 2; }
-      else if (e->bits > 2 && tiles(64) <= cus && tiles(64) >= cus / 4) { groups = 2; mtb = 4; }
+  return launch_tiles(p, e->bits, tb->n_four + tb->n_three, tb->n_ct, a.ev_start, a.ev_stop, st);
+}
+
+// The sum over two members with inputs of their own (the second layer of an MLP, the last of a chain), one launch of the single-pass kernel
+// per member: the first leaves its part in y, the second starts from it, so every output is summed as pass by pass, in
+// ascending order, to the same bits.  y is written, read and written again (it fits the last level cache), which long walks are worth:
+// see pipe_sum_apply.
+int launch_gemm_sum(const GemmArgs& a, hipStream_t st) {
+  GemmArgs apart = a;
+  apart.reduce = 0;
+  int rc = PIPE_OK;
+  const TileBins* tb = pipe_get_bins(a.e, apart, &rc);
+  if (tb == nullptr) return rc;
+  const pipe_expansion* e = a.e;
+  BinsParams p{};
+  p.qx = a.qx; p.qx_mstride = a.qx_mstride; p.rowsum = a.rowsum; p.rowsum_mstride = a.rowsum_mstride;
+  p.s_x = a.s_x; p.sx_mstride = a.sx_mstride;
+  p.codes = e->codes_dev; p.scales = e->scales_all_dev; p.y = a.y;
+  p.T = a.T; p.T_pad = a.T_pad; p.out = e->out; p.nks = e->nks;
+  p.fold_sx = 1; p.three = 1;
+  int n_dead = 0, dead0 = 0, live0 = 0;
+  for (int m = 0; m < a.M; ++m) n_dead += tb->dead_ct[m];
+  for (int m = 0; m < a.M; dead0 += tb->dead_ct[m], live0 += tb->live_ct[m], ++m) {
+    const bool last = m == a.M - 1;
+    p.later = m > 0;
+    if (last) {
+      p.bias = a.bias;
+      p.zero_after = a.zero_after; p.zero_n = a.zero_n; p.zero_big = a.zero_big; p.zero_big_n = a.zero_big_n;
     }
-    // Ternary tiles of 64 tokens that the chip holds at once ask for their loads between the multiplies, two stages ahead: 11008 x 4096, 333
-    // tokens (456 tiles) 37.4 -> 35.3 us a call; 4096 x 11008, 400 tokens 70.5 -> 66.3; but 4096 tokens 227 -> 243, and 4 bits
-    // the same (768 x 3072, 4096 tokens 44.1 -> 42.9; 4096 x 4096, 700 tokens 42.7 -> 45.4).
-    if (groups == 1 && mtb == 4 && e->bits == 2 && tiles(64) <= 2 * cus) ahead = 2;
+    // column tiles of row blocks that this member pruned: only for the first value of y, and for the bias
+    const int dead = m == 0 || (last && (a.bias != nullptr || tb->live_ct[m] == 0)) ? tb->dead_ct[m] : 0;
+    p.bins = tb->bins_dev + 4 * (size_t)(dead > 0 ? dead0 : n_dead + live0);
+    p.dead_ct = dead;
+    p.dead_gap = dead > 0 ? n_dead + live0 - dead0 - dead : 0;
+    const int n_ct = dead + tb->live_ct[m];
+    if (n_ct == 0) continue;
+    // timed as one: the first launch records the begin, the last the end
+    const hipEvent_t ev0 = m == 0 ? a.ev_start : nullptr, ev1 = last ? a.ev_stop : nullptr;
+    rc = launch_tiles(p, e->bits, tb->live_ct[m], n_ct, ev0, ev1, st);
+    if (rc != PIPE_OK) return rc;
   }
-  const int sk = e->bits == 2 || mtb == 1 || (groups == 2 && mtb == 2) ? 4 : 2;   // as in the kernel
-  p.one_tap = a.conv_q8 != nullptr && a.conv_C % (sk * 64) == 0;
-  const int live = tb->n_four + tb->n_three;
-  if (groups == 2) {
-    switch (e->bits * 8 + mtb) {
-      case 8 * 8 + 4: return launch_cfg<8, 4, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-      case 4 * 8 + 4: return launch_cfg<4, 4, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-      case 4 * 8 + 2: return launch_cfg<4, 2, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-      case 2 * 8 + 2: return launch_cfg<2, 2, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-      default: return PIPE_EINVAL;
-    }
-  }
-  if (ahead == 2) return launch_cfg<2, 4, 2, 1, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-  switch (e->bits * 8 + mtb) {
-    case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 8 * 8 + 1: return launch_cfg<8, 1, 2>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 4: return launch_cfg<4, 4, 3>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 2: return launch_cfg<4, 2, 4>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 4 * 8 + 1: return launch_cfg<4, 1, 3>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 4: return launch_cfg<2, 4, 3>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 2: return launch_cfg<2, 2, 4>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    case 2 * 8 + 1: return launch_cfg<2, 1, 4>(p, live, tb->n_ct, a.ev_start, a.ev_stop, st);
-    default: return PIPE_EINVAL;
-  }
+  return PIPE_OK;
+}
+
+// Against the pass-by-pass kernel, which multiplies a member's orders one walk after the other in tiles that run the most passes of their row
+// blocks (whole MLP calls, us): 4096-11008-4096 gated 4 bit, members of 2 orders, 300 tokens 218 -> 166, 500 268 -> 203, 1000 374 -> 338, 2048 630 -> 621;
+// ternary, 1500 tokens 419 -> 358; K = 3 in 2 and 1, 538 -> 444; 768-3072-768 GELU, 2500 tokens 113 -> 94, 4096 140 -> 128.  The worst
+// seen: 1024-4096-1024, K = 3 in 2 and 1, 4096 tokens 156.6 -> 159.5 (384 and 128 tiles).  Walks of 8 to 32 64-k steps (the last layer of a
+// chain) are within 0.5 % either way and stay one launch; more than two members would read and write y once more each.
+bool pipe_sum_apply(const GemmArgs& a) {
+  if (a.acc_out != nullptr || a.M != 2 || !a.reduce || (a.qx_mstride == 0 && a.sx_mstride == 0) || a.e->nks < 48) return false;
+  if (a.act != PIPE_ACT_NONE || a.res != nullptr || a.amax_out != nullptr || a.conv_q8 != nullptr || a.bias_mstride != 0) return false;
+  if (a.T <= 0 || a.T_pad % TOK_TILE != 0 || a.T_pad < a.T) return false;   // (launch_gemm_tiled reports it)
+  for (int m = 0; m < a.M; ++m)
+    if (a.member_hi[m] - a.member_lo[m] + 1 > 4) return false;
+  return true;
 }

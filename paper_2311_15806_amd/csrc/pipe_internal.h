@@ -105,6 +105,8 @@ struct TileBins {
   unsigned long long member_nib = 0;   // as in PassTables
   int M = 0, gated = 0;                // members apart (joined members count as one)
   int n_ct = 0, n_four = 0, n_three = 0;   // tiles; those that multiply 4 items, and 3
+  int dead_ct[PIPE_MAX_K] = {0}, live_ct[PIPE_MAX_K] = {0};   // per member: its tiles that multiply nothing, and the others (all members' dead
+                                       // ones lie first, member after member, then the live ones likewise)
   TileBin* bins_dev = nullptr;         // [4 * n_ct]
 };
 // Work units of the resident decode kernel (pipe_resident.hip), built on first use per expansion.
@@ -428,7 +430,7 @@ struct GemmArgs {
 #define PIPE_LAUNCH(kernel, grid, block, st, ev0, ev1, ...)                                   \
   do {                                                                                       \
     if (pipe_dry_run()) break;                                                               \
-    if ((ev0) != nullptr) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev0, ev1, 0, __VA_ARGS__); \
+    if ((ev0) != nullptr || (ev1) != nullptr) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, ev0, ev1, 0, __VA_ARGS__); \
     else hipLaunchKernelGGL(kernel, grid, block, 0, st, __VA_ARGS__);                         \
   } while (0)
 int launch_gemm_tiled(const GemmArgs& a, hipStream_t st);
@@ -436,6 +438,8 @@ int launch_gemm_tiled(const GemmArgs& a, hipStream_t st);
 bool pipe_bins_apply(const GemmArgs& a);
 const TileBins* pipe_get_bins(const pipe_expansion* e, const GemmArgs& a, int* rc);
 int launch_gemm_bins(const GemmArgs& a, hipStream_t st);
+bool pipe_sum_apply(const GemmArgs& a);   // ... for a sum over two members, a launch each
+int launch_gemm_sum(const GemmArgs& a, hipStream_t st);
 // depthwise layers: dense per-order codes and scales (built once), then the forward kernel
 int pipe_depthwise_prepare(pipe_expansion* e, hipStream_t st);
 int launch_quantize_to_nhwc(const float* x, int N, int C, int HW, float s_static, MaxOf amax, float qmax,

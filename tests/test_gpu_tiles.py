@@ -270,3 +270,26 @@ def test_two_groups_equal_one(pipe, kind, T, C, k):
             assert torch.equal(a, b), "token tile %d" % tile
     for e in made:
         e.free()
+
+
+# The sum over two members with inputs of their own, a launch per member: second layers of 48 steps and more, in every height and with one and two
+# groups, with row blocks that the second member pruned.  Both kernels add the same exact integers in the same order.
+@pytest.mark.parametrize("bits,out,hidden,K,gamma,split,T,bias",
+                         [(4, 48, 3072, 3, 0.34, [2, 1], 129, True), (4, 1040, 3100, 3, 0.25, [2, 1], 300, False),
+                          (4, 4096, 3100, 4, 0.5, [2, 2], 500, True), (4, 2048, 3080, 2, 0.1, [1, 1], 1000, True),
+                          (2, 512, 3072, 4, 0.25, [1, 3], 200, True), (2, 4096, 3072, 4, 0.5, [2, 2], 700, False),
+                          (8, 1024, 3072, 2, 0.5, [1, 1], 150, True), (8, 2048, 3072, 2, 1.0, [1, 1], 900, False)])
+def test_sum_over_members_equals_its_parts(pipe, bits, out, hidden, K, gamma, split, T, bias):
+    rng = np.random.default_rng(out + T)
+    hidden -= hidden % 16
+    l1 = pipe.pipe_expand(dev(_weight(out, hidden, 64)), bits, K, 1.0, 16)
+    l2 = pipe.pipe_expand(dev(_weight(out + 1, out, hidden)), bits, K, gamma, 16)
+    x = dev(rng.standard_normal((T, 64)).astype(np.float32))
+    b2 = dev(rng.standard_normal(out).astype(np.float32)) if bias else None
+    call = lambda v: pipe.pipe_mlp_forward_given_scales(l1, l2, pipe.PIPE_ACT_GELU, v, 0.03, [0.01, 0.003], split=split, bias2=b2,
+                                                        return_hidden=True)
+    y, h = call(x)
+    parts = [call(x[a:z].contiguous()) for a, z in _parts(T)]
+    assert torch.equal(h, torch.cat([p[1] for p in parts], dim=1))
+    assert torch.equal(y, torch.cat([p[0] for p in parts], dim=0))
+    l1.free(), l2.free()
