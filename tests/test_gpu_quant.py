@@ -58,7 +58,7 @@ def test_codes_are_those_of_the_division(pipe, s):
     e.free()
 
 
-@pytest.mark.parametrize("T,I", [(129, 4), (140, 68), (300, 516), (1000, 4100)])
+@pytest.mark.parametrize("T,I", [(33, 1028), (129, 4), (140, 68), (300, 516), (1000, 4100)])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_dynamic_scale_over_the_parts_of_the_reduction(pipe, T, I, shift):
     """The largest magnitude in the first, a middle and the last element; inputs that are not 16-byte aligned."""
