@@ -1,5 +1,5 @@
 // Tiled int8-MFMA kernel of the expanded layer (App. B, Eq. (define_dre)), one pass over k per order, for what the
-// single-pass kernel (pipe_gemm_bins.hip) does not take: sums over members with inputs of their own, members of more than 4
+// single-pass kernel (pipe_gemm_bins.hip) does not take: sums over members with inputs of their own (most over two go there as well), members of more than 4
 // orders, gate||up pairs of more than 2, and the integer export:
 //   y[t,o] = sum_m ( s_x,m * sum_{k in member m} s_k[o] * acc_k[t,o]  (+ b[o] if m = 0) )
 //   acc_k[t,o] = sum_i Qx[t,i] * q_k[o,i]          (exact, int32)

@@ -766,14 +766,18 @@ int launch_gemm_sum(const GemmArgs& a, hipStream_t st) {
 
 // Against the pass-by-pass kernel, which multiplies a member's orders one walk after the other in tiles that run the most passes of their row
 // blocks (whole MLP calls, us): 4096-11008-4096 gated 4 bit, members of 2 orders, 300 tokens 218 -> 166, 500 268 -> 203, 1000 374 -> 338, 2048 630 -> 621;
-// ternary, 1500 tokens 419 -> 358; K = 3 in 2 and 1, 538 -> 444; 768-3072-768 GELU, 2500 tokens 113 -> 94, 4096 140 -> 128.  The worst
-// seen: 1024-4096-1024, K = 3 in 2 and 1, 4096 tokens 156.6 -> 159.5 (384 and 128 tiles).  Walks of 8 to 32 64-k steps (the last layer of a
-// chain) are within 0.5 % either way and stay one launch; more than two members would read and write y once more each.
+// ternary, 1500 tokens 419 -> 358; 768-3072-768 GELU, 2500 tokens 113 -> 94, 4096 140 -> 128.  A member of a single order has a launch's
+// fixed parts for half the work: from 192 tiles of 64 tokens on it gains (K = 3 in 2 and 1, 1500 tokens, 192 tiles 538 -> 444), with 128 and 44 it
+// loses (1024-4096-1024, 4096 tokens 156.6 -> 159.5; 2048-5504-2048 gated, 652 tokens 103.5 -> 106.2).  Walks of 8 to 32 64-k steps (the last layer
+// of a chain) are within 0.5 % either way and stay one launch; more than two members would read and write y once more each.
 bool pipe_sum_apply(const GemmArgs& a) {
   if (a.acc_out != nullptr || a.M != 2 || !a.reduce || (a.qx_mstride == 0 && a.sx_mstride == 0) || a.e->nks < 48) return false;
   if (a.act != PIPE_ACT_NONE || a.res != nullptr || a.amax_out != nullptr || a.conv_q8 != nullptr || a.bias_mstride != 0) return false;
   if (a.T <= 0 || a.T_pad % TOK_TILE != 0 || a.T_pad < a.T) return false;   // (launch_gemm_tiled reports it)
-  for (int m = 0; m < a.M; ++m)
-    if (a.member_hi[m] - a.member_lo[m] + 1 > 4) return false;
+  for (int m = 0; m < a.M; ++m) {
+    const int orders = a.member_hi[m] - a.member_lo[m] + 1;
+    if (orders > 4) return false;
+    if (orders == 1 && (int64_t)ceil_div(a.e->orders[a.member_lo[m]].n_kept * a.e->rbpg, 16) * ceil_div(a.T, 64) < 192) return false;
+  }
   return true;
 }

@@ -275,10 +275,11 @@ def test_two_groups_equal_one(pipe, kind, T, C, k):
 # The sum over two members with inputs of their own, a launch per member: second layers of 48 steps and more, in every height and with one and two
 # groups, with row blocks that the second member pruned.  Both kernels add the same exact integers in the same order.
 @pytest.mark.parametrize("bits,out,hidden,K,gamma,split,T,bias",
-                         [(4, 48, 3072, 3, 0.34, [2, 1], 129, True), (4, 1040, 3100, 3, 0.25, [2, 1], 300, False),
-                          (4, 4096, 3100, 4, 0.5, [2, 2], 500, True), (4, 2048, 3080, 2, 0.1, [1, 1], 1000, True),
-                          (2, 512, 3072, 4, 0.25, [1, 3], 200, True), (2, 4096, 3072, 4, 0.5, [2, 2], 700, False),
-                          (8, 1024, 3072, 2, 0.5, [1, 1], 150, True), (8, 2048, 3072, 2, 1.0, [1, 1], 900, False)])
+                         [(4, 48, 3072, 4, 0.34, [2, 2], 129, True), (4, 1040, 3100, 4, 0.1, [2, 2], 300, False),
+                          (4, 1040, 3100, 3, 0.25, [2, 1], 300, True), (4, 4096, 3100, 4, 0.5, [2, 2], 500, True),
+                          (4, 2048, 3080, 4, 0.1, [2, 2], 1000, True), (4, 4096, 3080, 2, 1.0, [1, 1], 800, False),
+                          (2, 512, 3072, 4, 0.25, [2, 2], 200, True), (2, 4096, 3072, 4, 0.5, [2, 2], 700, False),
+                          (8, 1024, 3072, 4, 0.5, [2, 2], 150, True), (8, 2048, 3072, 4, 0.25, [2, 2], 900, False)])
 def test_sum_over_members_equals_its_parts(pipe, bits, out, hidden, K, gamma, split, T, bias):
     rng = np.random.default_rng(out + T)
     hidden -= hidden % 16
