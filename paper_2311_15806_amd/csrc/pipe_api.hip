@@ -733,7 +733,7 @@ const TileBins* pipe_get_bins(const pipe_expansion* ce, const GemmArgs& a, int* 
         for (const Item& it : items[units[i]]) {
           b.pos[n] = it.pos; b.spos[n] = it.spos; b.rb[n] = it.rb;
           if (it.pos >= 0 && first_pos < 0) first_pos = it.pos;
-          ends |= it.end << n;
+          ends |= it.end << n | (it.pos >= 0 ? 1 : 0) << (4 + n);
           ups |= it.up << n;
           ++n;
           if (it.pos >= 0) used = n;

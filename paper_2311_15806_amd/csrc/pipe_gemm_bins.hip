@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
   if (ct >= p.dead_ct) ct += p.dead_gap;
   const TileBin* bin = p.bins + ct * 4 + wave;
   const v4i pos = cload(&bin->pos, 0), spos = cload(&bin->spos, 0), rb = cload(&bin->rb, 0), info = cload(&bin->info, 0);
-  const int m = info[0], ends = info[1], ups = info[2];   // member; items that end a row block; items of an up block
+  const int m = info[0], ends = info[1], ups = info[2];   // member; items that end a row block (and, << 4, that have codes); items of an up block
   const bool active = info[3] & 1;
   const int tile_items = info[3] >> 1;                    // items that any bin of the tile multiplies: 4, 3 or none
 
@@ -490,12 +490,15 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
         }
       }
     }
-    const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wid][r * 16 + g * 4]);
+    // (a row block that a later member of a sum pruned keeps what is there, also where the member's scale is infinite)
+    if (MODE != MODE_SUM || ((ends >> (4 + r)) & 1)) {
+      const v4f sc = *reinterpret_cast<const v4f*>(&lds.scl[wid][r * 16 + g * 4]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float s = p.fold_sx ? sc[i] * sx : sc[i];
+      for (int i = 0; i < 4; ++i) {
+        const float s = p.fold_sx ? sc[i] * sx : sc[i];
 #pragma unroll
-      for (int b = 0; b < MB; ++b) v[b][i] = fmaf(s, (float)(own[r][b][i] - OFF * rs[b]), v[b][i]);
+        for (int b = 0; b < MB; ++b) v[b][i] = fmaf(s, (float)(own[r][b][i] - OFF * rs[b]), v[b][i]);
+      }
     }
     if (!((ends >> r) & 1)) continue;
     v4f bb = v4f{0.f, 0.f, 0.f, 0.f};

@@ -99,7 +99,7 @@ struct TileBin {
   int32_t pos __attribute__((vector_size(16)));    // positions of the items' codes
   int32_t spos __attribute__((vector_size(16)));   // ... and of their row scales (zero_pos: an item without an order)
   int32_t rb __attribute__((vector_size(16)));     // output row block of the item (of a gate||up layer: the hidden block)
-  int32_t info __attribute__((vector_size(16)));   // member; mask of items that end a row block; mask of items of up blocks; bit 0: the bin multiplies, then how many items its tile does (4, 3 or 0)
+  int32_t info __attribute__((vector_size(16)));   // member; mask of items that end a row block, and << 4 of those with codes; mask of items of up blocks; bit 0: the bin multiplies, then how many items its tile does (4, 3 or 0)
 };
 struct TileBins {
   unsigned long long member_nib = 0;   // as in PassTables

@@ -294,3 +294,26 @@ def test_sum_over_members_equals_its_parts(pipe, bits, out, hidden, K, gamma, sp
     assert torch.equal(h, torch.cat([p[1] for p in parts], dim=1))
     assert torch.equal(y, torch.cat([p[0] for p in parts], dim=0))
     l1.free(), l2.free()
+
+
+# A member's infinite scale reaches only the row blocks that it has orders of: those that the second member pruned keep the first one's sum, in a
+# tile of their own (with a bias) or beside others' items.  One and two groups along k.
+@pytest.mark.parametrize("bias", [False, True])
+@pytest.mark.parametrize("bits,out,hidden,T", [(4, 1040, 3104, 300), (2, 4096, 3072, 700), (8, 2048, 3072, 900)])
+def test_infinite_member_scale_leaves_pruned_row_blocks(pipe, bits, out, hidden, T, bias):
+    rng = np.random.default_rng(out + T)
+    l1 = pipe.pipe_expand(dev(_weight(out, hidden, 64)), bits, 4, 1.0, 16)
+    l2 = pipe.pipe_expand(dev(_weight(out + 1, out, hidden)), bits, 4, 0.25, 16)
+    x = dev(rng.standard_normal((T, 64)).astype(np.float32))
+    b2 = dev(rng.standard_normal(out).astype(np.float32)) if bias else None
+    call = lambda s_h: pipe.pipe_mlp_forward_given_scales(l1, l2, pipe.PIPE_ACT_GELU, x, 0.03, s_h, split=[2, 2], bias2=b2)
+    kept = np.zeros(out // 16, dtype=bool)
+    for k in (3, 4):
+        kept[l2.order(k)[0]] = True
+    rows = torch.from_numpy(np.repeat(~kept, 16)).to("cuda:0")
+    assert 0 < int(rows.sum()) < out
+    finite, infinite = call([0.01, 0.003]), call([0.01, float("inf")])
+    assert bool(torch.isfinite(finite).all())
+    assert torch.equal(infinite[:, rows], finite[:, rows])
+    assert not bool(torch.isfinite(infinite[:, ~rows]).any())      # (codes of zero times infinity)
+    l1.free(), l2.free()
