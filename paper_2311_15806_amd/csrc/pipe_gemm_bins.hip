@@ -22,11 +22,14 @@
 // the dispatcher does); tiles of 128 tokens, two workgroups, lose on ternary codes (214) and win a little on 4 bits (gate||up
 // 22016 x 4096, 2048 tokens 364 against 372).
 // Where the chip holds more waves than the tiles bring: a full chip (four workgroups a unit) spends 4176 cycles on the four's 4096 MFMA cycles of
-// a ternary stage; a tile alone spends 1490 on the 512 of a 4-bit stage, 390 of them on its own loads after the barrier, at the 16 cycles
-// per KiB that the unit's address path takes, 230 on the first fragments, and deeper prefetch changes nothing (wait: 50 cycles).  So (G = 2)
+// a ternary stage; a tile alone spends 1560 on the 512 of a 4-bit stage of a convolution, 390 of them on its own loads after the barrier, at the 16 cycles
+// per KiB that the unit's address path takes, 230 on the first fragments.  So (G = 2)
 // two groups of 4 waves share a tile, half of k each, and (DP = 2) the loads of a stage two ahead are asked for one by one between
 // the multiplies: through buffer resources, so that those behind the last stage read nothing and every wait stays an exact count.
-// A 4-bit stage pair of 1024 MFMA cycles then takes 1700 (2050 for a convolution's gathers): the loads that miss the L1 bound it.  Times at launch_gemm_bins.
+// (Exact in the code that the compiler makes of it, too: see the loop.  With waits that reached into the loads in flight the calls took 1 to 4 %
+// longer: 4096 x 11008 4 bit, 200 tokens 42.0 -> 40.5 us, ternary, 400 tokens 66.6 -> 64.1, 4096 x 4096 8 bit, 500 tokens 30.2 -> 29.3.)
+// A stage of two groups, 1024 MFMA cycles, then takes 1490 at 4 bits (768 x 3072, 2000 tokens) and 2240 with a convolution's gathers (256 x 14 x 14, 32 images);
+// one group with two stages in flight 840 and 1500 for its 512, one with one in flight 1180 and 1560.
 // Measured against one pass per order (pipe_gemm.hip, same box): 11008 x 4096 ternary, K = 4, 4096 tokens 227 -> 203 us,
 // 333 tokens 62 -> 30 us; 3x3 convolution 256 x 256 of 6272 pixels, 4 bit, K = 3 35.5 -> 18.4 us; 3072 x 768 and back, 4 bit,
 // K = 3, 4096 tokens 81 -> 60 us; eight 2048 x 2048 ternary layers, two members of 4 orders, 4096 tokens 676 -> 591 us
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
     // and `far` and `free_slot`, multiplied in the stage before, take the stage that is requested now.
     auto stage = [&](Codes<BITS, SK>(&now)[NI], const v4i* slot, Codes<BITS, SK>(&far)[NI], v4i* free_slot, bool multiply, bool ask) __attribute__((always_inline)) {
       asm volatile("s_barrier" ::: "memory");    // everyone's have arrived, and the slot of the stage before is free
-      if (DP == 1 ? ask : !multiply) request(far, free_slot);
+      if (DP == 1 && ask) request(far, free_slot);
       __builtin_amdgcn_sched_barrier(0);
       if (multiply) {
         // Software pipeline of the SK 64-k steps: a wave issues in order, so everything that is not an MFMA has to sit in
@@ -355,7 +358,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
 #pragma unroll
           for (int r = 0; r < NI; ++r) {
             const int n = j * NI + r;   // item-steps so far: the register set of this one's codes
-            if constexpr (DP > 1) {     // its share of the loads that are requested now
+            if (DP > 1 && ask) {        // its share of the loads that are requested now
               constexpr int TOT = NI * WN + XC, STEPS = SK * NI;
 #pragma unroll
               for (int i = n * TOT / STEPS; i < (n + 1) * TOT / STEPS; ++i) ask_part(far, free_slot, i);
@@ -383,24 +386,28 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
           }
         }
       }
-      wait_for(std::integral_constant<int, AHEAD>{});
+      if (DP == 1 || ask) wait_for(std::integral_constant<int, AHEAD>{});
+      else wait_for(std::integral_constant<int, 0>{});
     };
-    // Two stages a round, so that the slots and register sets keep their roles; behind an odd number of stages the second
-    // half multiplies nothing.
+    // Two (three) stages a round, so that the slots and register sets keep their roles.  One stage in flight: behind an odd number of stages
+    // the second half multiplies nothing.
     if constexpr (DP == 1) {
       for (int s = 0; s < n_stage; s += 2) {
         stage(w0, xs0, w1, xs1, active, s + 1 < n_stage);
         stage(w1, xs1, w0, xs0, active && s + 1 < n_stage, s + 2 < n_stage);
       }
     } else {
-      for (int s = 0;; s += 3) {
-        stage(w0, xs0, w2, xs2, active && s < n_stage, true);
-        if (s + 1 >= n_max) break;
-        stage(w1, xs1, w0, xs0, active && s + 1 < n_stage, true);
-        if (s + 2 >= n_max) break;
-        stage(w2, xs2, w1, xs1, active && s + 2 < n_stage, true);
-        if (s + 3 >= n_max) break;
+      // Two in flight: every stage multiplies, also of a wave without items (codes of the all-zero position) and of a group behind its
+      // part (codes out of range, zeros), and the loop has one exit.  With a path that requests a stage and multiplies nothing, or one out of the middle,
+      // the compiler takes the registers that loads are writing to for others and makes a stage wait for all of them first (cycles: see above).
+      int s = 0;
+      for (; s + 3 <= n_max; s += 3) {
+        stage(w0, xs0, w2, xs2, true, true);
+        stage(w1, xs1, w0, xs0, true, true);
+        stage(w2, xs2, w1, xs1, true, true);
       }
+      if (s < n_max) stage(w0, xs0, w2, xs2, true, false);
+      if (s + 1 < n_max) stage(w1, xs1, w0, xs0, true, false);
       wait_for(std::integral_constant<int, 0>{});   // the slots are written to the end
     }
   };
