@@ -65,3 +65,18 @@ def test_stages_wait_for_nothing_in_flight(kernels):
         assert stages >= 3, m.groups()
         checked += 1
     assert checked >= 20
+
+
+def test_gathers_are_as_many_as_the_loads_they_replace(kernels):
+    """A convolution's stage requests each fragment at one place, at an address that was ready before (whether or not a stage has several
+    taps): its kernel holds no more loads into LDS than the one for patches that lie in memory."""
+    count = {}
+    for name, code in kernels.items():
+        m = KERNEL.search(name)
+        if m is not None and m.group(4) == "0":
+            count[m.groups()] = sum(ins.startswith("buffer_load") and ins.endswith(" lds") for ins in code)
+    convolutions = [k for k in count if k[4] == "1"]
+    assert len(convolutions) >= 9
+    for k in convolutions:
+        plain = k[:4] + ("0",) + k[5:]
+        assert 0 < count[k] <= count[plain], (k, count[k], count[plain])
