@@ -641,39 +641,68 @@ int launch_tiles(BinsParams& p, int bits, int live, int n_ct, hipEvent_t ev0, hi
   // K = 3 (147 tiles of 64: 17.8 against 17.5 us; 196: 18.1 and 18.0) and for layers of 3072 x 768, 1024 x 1024 and 4096 x 4096 at 2, 4
   // and 8 bits; far below it 16 tokens lose to 32 by up to a quarter at 8 bits (128 x 128 convolution of 4704 pixels, K = 2: 14.0 and 11.0 us).
   int mtb = g_tiled_mtb, groups = 1, ahead = 1;
+  const int64_t cus = pipe_resident_workgroups();
+  auto tiles = [&](int tokens) { return (int64_t)n_ct * ceil_div(p.T, tokens); };
+  // tiles of this height that the fullest of the 8 XCDs is dealt; whether each has a compute unit for itself
+  auto fullest = [&](int tokens) {
+    const TileOrder o = tile_order(n_ct, ceil_div(p.T, tokens), false);
+    const int64_t chunks = (o.n_tt + o.toks - 1) / o.toks, rest = n_ct % o.strip;   // of a strip; column tiles of the last one
+    return ((n_ct / o.strip * chunks + 7) / 8 * o.strip + (rest > 0 ? (chunks + 7) / 8 * rest : 0)) * o.toks;
+  };
+  auto alone = [&](int tokens) { return fullest(tokens) * 8 <= cus; };
   if (mtb != 1 && mtb != 2 && mtb != 4) {
-    auto tiles = [&](int tokens) { return (int64_t)n_ct * ceil_div(p.T, tokens); };
     mtb = tiles(64) >= 192 ? 4 : (tiles(32) >= 192 ? 2 : 1);
-    // Two groups of waves along k where the tiles leave places on the chip and the walk is long enough (24 64-k steps) for the second
-    // prologue and the exchange.  Tiles of 32 tokens where one each fills the compute units (4 bits, and ternary, where two share a unit
-    // on long walks): 768 x 3072 4 bit, K = 3, 1000 tokens 26.1 -> 21.9 us a call, 150 tokens 19.6 -> 18.5; 4096 x 11008, K = 4,
-    // 140 tokens 52.6 -> 33.3; 3x3 convolution of 512 x 7 x 7, 32 images 33.3 -> 26.0; 2048 x 2048 ternary, 200 tokens 15.9 -> 14.9;
-    // 4096 x 11008 ternary, 400 tokens 70.5 -> 64.7; with 16 steps equal (2048 x 1024, 300 tokens), with 12 slower (convolution of 64 channels
-    // 14.7 -> 16.7), and with more tiles slower (4096 x 4096 4 bit, 400 tokens, 520 tiles 33.7 -> 38.0).  Else of 64 tokens: 4096 x 11008 4 bit, 200
-    // tokens 57.0 -> 43.2; 768 x 3072, 2000 tokens 32.2 -> 28.8; convolution of 256 x 14 x 14, 32 images 27.5 -> 25.6; 8 bits, whose codes
-    // need the registers, only so: 4096 x 11008, K = 2, 300 tokens 69.9 -> 51.7 (26 tiles lose: 18.8 -> 22.3).
-    const int64_t cus = pipe_resident_workgroups();
-    if (p.nks >= 24) {
-      if (bits < 8 && tiles(32) <= (bits == 2 && p.nks >= 64 ? 2 * cus : cus)) { groups = 2; mtb = 2; }
-      else if (bits > 2 && tiles(64) <= cus && tiles(64) >= cus / 4) { groups = 2; mtb = 4; }
+    // What a tile that is alone on its compute unit spends beside its multiplies nothing else covers, so there its loads are asked for two stages ahead
+    // and between the multiplies, and the lowest height is taken that still leaves every tile alone: on the fullest XCD as well (768 x 3072
+    // 8 bit, K = 2, 2600 tokens, 246 tiles of which one XCD's 32 units get 36: 42.5 us against 39.8 one stage ahead).  Calls, us, as here and
+    // with two groups of 32 or 64 tokens or as above:
+    //   16 tokens: 768 x 3072 4 bit, K = 3, 150 tokens 16.0 / 18.3, ternary, 250 tokens 15.9 / 17.9, 8 bit, K = 2, 600 tokens 22.1 / 23.6; convolution of
+    //   256 x 14 x 14, 5 images, 4 bit 17.6 / 19.3, 8 bit 18.5 / 22.4; of ternary ones a stage's few loads are better in one go (17.5; so 18.1);
+    //   8 bits, 32 or 64 tokens (two groups hold a compute unit each and share its path to the L1, which 8-bit codes fill): 4096 x 4096, 200 tokens
+    //   24.1 / 27.4, 500 tokens 28.7 / 30.7; 768 x 3072, 1000 tokens 24.4 / 26.8; convolution of 512 x 7 x 7, 32 images 27.3 / 32.4.
+    // 8 bits, at most two low tiles a unit where the last high one would be half empty: 11008 x 4096, 160 tokens 33.2 / 35.0 (three: 190 tokens 46.5 / 36.0;
+    // none saved: 3072 x 768, K = 2, half kept, 700 tokens 21.1 / 19.8).
+    // Two groups of waves along k, 2 and 4 bits, where the walk is long enough (24 64-k steps) for the second prologue and the exchange: 4096 x 11008 4 bit,
+    // K = 4, 140 tokens 32.5 / 37.2 with one group, 300 tokens 44.1 / 45.2; 4096 x 4096, 130 tokens 19.3 / 20.3; convolution of
+    // 256 x 14 x 14, 32 images 25.0 / 26.2; 3x3 of 512 x 7 x 7, 20 images, ternary 24.2 / 26.7.
+    // Tiles of 64 tokens that the chip holds two of a unit also ask two stages ahead: 11008 x 4096 ternary, 333
+    // tokens (456 tiles) 33.7 / 37.4, 4096 x 11008 4 bit, 420 tokens 63.3 / 69.7, gate||up 11008 x 2048, 216 tokens (480 tiles) a whole MLP 65.8 / 70.6;
+    // at 4 bits not where an XCD's units are dealt all of the two (1536 x 2048, 1700 tokens 34.1 / 32.2; 4096 x 4096, 700 tokens 46.0 / 44.2), and never
+    // a ternary convolution (128 rows of 64 x 56 x 56, 8 images 25.9 / 24.3) or 8 bits (4096 x 4096, 600 tokens 38.8 / 36.5).
+    if (p.nks >= (bits == 8 ? 8 : 16)) {
+      if (alone(16)) { mtb = 1; ahead = bits == 2 && p.cq8 != nullptr ? 1 : 2; }
+      else if (bits == 8) {
+        if (alone(32) || alone(64)) { mtb = alone(32) ? 2 : 4; ahead = 2; }
+        else if (tiles(32) < 2 * tiles(64) && fullest(32) * 8 <= 2 * cus) mtb = 2;
+      }
+      else if (p.nks >= 24 && alone(32)) { mtb = 2; groups = 2; }
+      else if (p.nks >= 24 && bits == 4 && alone(64)) { mtb = 4; groups = 2; }
+      else if ((p.nks >= 24 || tiles(64) >= 192) && !(bits == 2 && p.cq8 != nullptr) &&
+               (bits == 2 ? tiles(64) <= 2 * cus : fullest(64) * 64 <= 15 * cus)) { mtb = 4; ahead = 2; }
     }
-    // Ternary tiles of 64 tokens that the chip holds at once ask for their loads between the multiplies, two stages ahead: 11008 x 4096, 333
-    // tokens (456 tiles) 37.4 -> 35.3 us a call; 4096 x 11008, 400 tokens 70.5 -> 66.3; but 4096 tokens 227 -> 243, and 4 bits
-    // the same (768 x 3072, 4096 tokens 44.1 -> 42.9; 4096 x 4096, 700 tokens 42.7 -> 45.4).
-    if (groups == 1 && mtb == 4 && bits == 2 && tiles(64) <= 2 * cus) ahead = 2;
   }
   const int sk = bits == 2 || mtb == 1 || (groups == 2 && mtb == 2) ? 4 : 2;   // as in the kernel
   p.one_tap = p.cq8 != nullptr && p.cC % (sk * 64) == 0;
   if (groups == 2) {
     switch (bits * 8 + mtb) {
-      case 8 * 8 + 4: return launch_cfg<8, 4, 2, 2>(p, live, n_ct, ev0, ev1, st);
       case 4 * 8 + 4: return launch_cfg<4, 4, 2, 2>(p, live, n_ct, ev0, ev1, st);
       case 4 * 8 + 2: return launch_cfg<4, 2, 2, 2>(p, live, n_ct, ev0, ev1, st);
       case 2 * 8 + 2: return launch_cfg<2, 2, 2, 2>(p, live, n_ct, ev0, ev1, st);
       default: return PIPE_EINVAL;
     }
   }
-  if (ahead == 2) return launch_cfg<2, 4, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+  if (ahead == 2) {
+    switch (bits * 8 + mtb) {
+      case 8 * 8 + 4: return launch_cfg<8, 4, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+      case 8 * 8 + 2: return launch_cfg<8, 2, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+      case 8 * 8 + 1: return launch_cfg<8, 1, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+      case 4 * 8 + 4: return launch_cfg<4, 4, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+      case 4 * 8 + 1: return launch_cfg<4, 1, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+      case 2 * 8 + 4: return launch_cfg<2, 4, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+      case 2 * 8 + 1: return launch_cfg<2, 1, 2, 1, 2>(p, live, n_ct, ev0, ev1, st);
+      default: return PIPE_EINVAL;
+    }
+  }
   switch (bits * 8 + mtb) {
     case 8 * 8 + 4: return launch_cfg<8, 4, 2>(p, live, n_ct, ev0, ev1, st);
     case 8 * 8 + 2: return launch_cfg<8, 2, 2>(p, live, n_ct, ev0, ev1, st);

@@ -37,11 +37,18 @@ LAYERS = [(16, 100, 4, 1, 1.0, 16, [1], 129),
           (2048, 512, 3, 4, 0.5, 64, [2, 2], 400),   # 64-token tiles
           (4096, 260, 2, 3, 0.5, 64, [3], 321),
           (4096, 1000, 2, 4, 0.5, 64, [4], 381),     # ternary, loads between the multiplies two stages ahead
-          (48, 1500, 4, 3, 0.5, 16, [3], 129),       # two groups along k: 24 steps ...
-          (320, 1700, 4, 4, 0.5, 16, [2, 2], 150),   # ... seven stages, four and three
-          (2048, 1800, 4, 4, 0.5, 16, [4], 501),     # ... tiles of 64 tokens
-          (2048, 1700, 2, 4, 0.5, 16, [4], 200),
-          (1024, 1800, 8, 2, 1.0, 16, [2], 502)]
+          (48, 1500, 4, 3, 0.5, 16, [3], 129),       # the same with tiles of 16 tokens: six stages ...
+          (320, 1700, 4, 4, 0.5, 16, [2, 2], 150),   # ... seven
+          (2048, 1800, 4, 4, 0.5, 16, [4], 501),     # two groups along k, tiles of 64 tokens
+          (2048, 1700, 2, 4, 0.5, 16, [4], 200),     # ... of 32
+          (1024, 1800, 8, 2, 1.0, 16, [2], 502),
+          (48, 2000, 2, 4, 0.34, 16, [4], 193),      # 16 tokens, two stages ahead, eight of them
+          (2048, 1700, 4, 4, 0.5, 16, [4], 300),     # two groups, 32 tokens, seven stages: four and three
+          (4096, 2000, 4, 4, 0.5, 16, [4], 390),     # 64 tokens, two stages ahead, 16 of them ...
+          (4096, 1700, 4, 3, 0.5, 16, [2, 1], 420),  # ... 14
+          (2048, 1100, 8, 2, 1.0, 16, [2], 400),     # 8 bits, two ahead: 32 tokens ...
+          (4096, 700, 8, 2, 1.0, 16, [1, 1], 257),   # ... 64
+          (11008, 300, 8, 2, 1.0, 16, [2], 130)]     # 8 bits, two low tiles a compute unit
 
 
 @pytest.mark.parametrize("O,I,bits,K,gamma,group,split,T", LAYERS)
@@ -192,7 +199,7 @@ def test_workgroups_per_unit_change_nothing(pipe, O, I, bits, K, gamma, split, T
     """Many 64-token tiles, served by the variant with one register set of fragments or by the one with two: 32-token tiles (other
     loops) give the same bits."""
     rng = np.random.default_rng(O + T)
-    l1 = pipe.pipe_expand(dev(_weight(O + I, O, I)), bits, K, gamma, 16)
+    l1, l2 = pipe.pipe_expand(dev(_weight(O + I, O, I)), bits, K, gamma, 16), None
     x = dev(rng.standard_normal((T, I)).astype(np.float32))
     b = dev(rng.standard_normal(O).astype(np.float32))
     if act == "plain":
@@ -210,6 +217,8 @@ def test_workgroups_per_unit_change_nothing(pipe, O, I, bits, K, gamma, split, T
             pipe.pipe_set_token_tile(0)
     assert torch.equal(got[0], got[32]) and torch.equal(got[64], got[32])
     l1.free()
+    if l2 is not None:
+        l2.free()
 
 
 @pytest.mark.parametrize("scale", [0.05, 1.0, 6.0])
@@ -230,10 +239,12 @@ def test_gelu_values(pipe, scale):
     l1.free(), l2.free()
 
 
-# Two groups along k in the other epilogues and for convolutions: the sums are exact integers, so the height that is set by hand, which
-# runs with one group, gives the same bits.  nks = 28 and 36 steps; the convolutions have one tap a stage or several.
+# Two groups along k and two stages ahead in the other epilogues and for convolutions: the sums are exact integers, so the height that is set by
+# hand, which runs with one of each, gives the same bits.  nks = 28 and 36 steps; the convolutions have one tap a stage or several.
 @pytest.mark.parametrize("kind,T,C,k", [("gelu", 300, 1696, 0), ("gated", 300, 1696, 0), ("chain", 300, 1696, 0), ("chain", 1100, 1696, 0), ("chain", 13000, 512, 0), ("chain2", 13000, 512, 0),
-                                        ("conv", 3, 256, 3), ("conv", 30, 256, 3), ("conv", 3, 64, 5), ("conv8", 40, 256, 3), ("conv2", 3, 256, 3)])
+                                        ("conv", 3, 256, 3), ("conv", 30, 256, 3), ("conv", 3, 64, 5), ("conv8", 40, 256, 3), ("conv2", 3, 256, 3),
+                                        ("conv", 12, 256, 3), ("conv", 30, 192, 3), ("conv", 60, 256, 3), ("conv", 60, 64, 5), ("conv8", 3, 256, 3), ("conv8", 12, 64, 5), ("conv8", 40, 192, 3),
+                                        ("conv2", 12, 256, 3), ("conv2", 30, 64, 5), ("gated", 500, 1696, 0)])
 def test_two_groups_equal_one(pipe, kind, T, C, k):
     rng = np.random.default_rng(T + C)
     made = []

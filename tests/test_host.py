@@ -2,6 +2,7 @@
 leaves behind when one of its allocations fails."""
 import ctypes as C
 import os
+import re
 import sys
 
 import pytest
@@ -175,10 +176,42 @@ def any_number_of_images_is_served(rt):
         assert fused(32, 600, 28, nhwc, x=(1 << 40) + 4)
 
 
+def _tile(names):
+    """(bits, blocks of 16 tokens, groups along k, stages ahead) of the one single-pass launch among `names`."""
+    found = [re.search(r"gemm_bins_kernelILi(\d)ELi(\d)ELi\dELi\dELb[01]ELi(\d)ELi(\d)E", n) for n in names]
+    (m,) = [f for f in found if f]
+    return tuple(int(g) for g in m.groups())
+
+
+def tiles_follow_the_units_they_leave(rt):
+    """Height, groups and loads ahead of the single-pass kernel by the tiles that 256 compute units in 8 dies are dealt (each of these
+    sizes was slower another way)."""
+    for rows, inp, bits, K, T, want in (
+            (768, 3072, 8, 2, 600, (8, 1, 1, 2)), (768, 3072, 8, 2, 1000, (8, 2, 1, 2)), (768, 3072, 8, 2, 1800, (8, 4, 1, 2)),
+            (768, 3072, 8, 2, 2600, (8, 4, 1, 1)),                                        # one die is dealt more tiles than it has units
+            (4096, 4096, 8, 2, 200, (8, 2, 1, 2)), (4096, 4096, 8, 2, 500, (8, 4, 1, 2)), (4096, 4096, 8, 2, 600, (8, 4, 1, 1)),
+            (11008, 4096, 8, 2, 160, (8, 2, 1, 1)), (11008, 4096, 8, 2, 190, (8, 4, 1, 1)), (2304, 768, 8, 2, 700, (8, 4, 1, 1)),
+            (768, 3072, 4, 2, 250, (4, 1, 1, 2)), (4096, 11008, 4, 2, 200, (4, 2, 2, 2)), (4096, 4096, 4, 2, 400, (4, 4, 2, 2)),
+            (4096, 4096, 4, 2, 600, (4, 4, 1, 2)), (4096, 4096, 4, 2, 4096, (4, 4, 1, 1)), (3072, 768, 4, 2, 200, (4, 1, 1, 1)),
+            (768, 3072, 2, 2, 250, (2, 1, 1, 2)), (4096, 4096, 2, 2, 200, (2, 2, 2, 2)), (4096, 4096, 2, 2, 600, (2, 4, 1, 2))):
+        e = rt.expand(rows, inp, bits, K, 1.0, 16)
+        assert _linear(rt, e, T) == 0
+        assert _tile(rt.names()) == want, (rows, inp, bits, T)
+    rt.lib.pipe_expand_conv2d.argtypes = [C.c_void_p] + [C.c_int] * 6 + [C.c_float, C.c_int, C.c_void_p, C.POINTER(C.c_void_p)]
+    rt.lib.pipe_forward_conv2d.argtypes = [C.c_void_p] * 2 + [C.c_int] * 9 + [C.c_float, C.c_void_p, C.c_int, C.c_void_p, C.c_int] + [C.c_void_p] * 2
+    for rows, Ch, H, N, bits, want in ((512, 256, 14, 5, 8, (8, 1, 1, 2)), (512, 256, 14, 10, 8, (8, 2, 1, 2)), (512, 512, 7, 32, 8, (8, 2, 1, 2)),
+                                       (256, 256, 14, 5, 2, (2, 1, 1, 1)), (128, 64, 56, 8, 2, (2, 4, 1, 1)), (256, 256, 14, 5, 4, (4, 1, 1, 2))):
+        W, e = (C.c_float * (rows * Ch * 9))(), C.c_void_p()
+        assert rt.lib.pipe_expand_conv2d(W, rows, Ch, 3, 3, bits, 2, 1.0, 16, None, C.byref(e)) == 0
+        rt.names()
+        assert rt.lib.pipe_forward_conv2d(e, 1 << 40, N, Ch, H, H, 3, 3, 1, 1, 0, 0.0, None, 0, None, 1, 1 << 44, None) == 0
+        assert _tile(rt.names()) == want, (rows, Ch, N, bits)
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
                                       "any_number_of_images_is_served", "wide_layers_quantize_once",
-                                      "single_pass_tables_hold_no_needless_items"])
+                                      "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
