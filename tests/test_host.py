@@ -208,10 +208,34 @@ def tiles_follow_the_units_they_leave(rt):
         assert _tile(rt.names()) == want, (rows, Ch, N, bits)
 
 
+def a_sum_over_two_members_is_a_launch_each(rt):
+    """The second layer of an MLP: a launch of the single-pass kernel per member where the walk is long and a member of a single order
+    has 192 tiles; else one launch, pass by pass."""
+    mlp = rt.lib.pipe_mlp_forward
+    mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 5
+
+    def launches(rows, hidden, K, split, T, kept):
+        l1, l2 = rt.expand(hidden, 64, 4, K, 1.0, 16), rt.expand(rows, hidden, 4, K, 0.5 if kept else 1.0, 16, kept=kept)
+        arr = (C.c_int * len(split))(*split)
+        rt.names()
+        assert mlp(l1, l2, 1, 1 << 40, T, 0.0, arr, len(split), None, None, None, 1 << 44, None) == 0
+        names = rt.names()
+        modes = [int(m.group(1)) for m in (re.search(r"gemm_bins_kernelILi\dELi\dELi\dELi(\d)E", n) for n in names) if m]
+        return modes, sum("gemm_tiled_kernel" in n for n in names)
+
+    half = [list(range(0, 256, 2)), list(range(1, 256, 2))]
+    assert launches(4096, 3072, 3, [2, 1], 1540, half) == ([2, 0, 6], 0)      # GELU, first member, the other's on top: 8 x 25 tiles
+    assert launches(4096, 3072, 3, [2, 1], 1500, half) == ([2, 0, 6], 0)      # 8 x 24
+    assert launches(4096, 3072, 3, [2, 1], 1470, half) == ([2], 1)            # 8 x 23
+    assert launches(1040, 3072, 4, [2, 2], 300, ()) == ([2, 0, 6], 0)
+    assert launches(1040, 2816, 4, [2, 2], 300, ()) == ([2], 1)               # 44 steps
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
                                       "any_number_of_images_is_served", "wide_layers_quantize_once",
-                                      "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave"])
+                                      "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave",
+                                      "a_sum_over_two_members_is_a_launch_each"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
