@@ -23,7 +23,7 @@ def kernels(tmp_path_factory):
     out = {}
     for obj in there.glob("lib.so.*gfx950"):
         names = subprocess.run([OBJDUMP, "--syms", str(obj)], check=True, capture_output=True, text=True).stdout
-        if "gemm_bins_kernel" not in names:
+        if "gemm_bins_kernel" not in names and "gemm_stream_kernel" not in names:
             continue
         name = None
         for line in subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", str(obj)], check=True, capture_output=True, text=True).stdout.splitlines():
@@ -80,3 +80,10 @@ def test_gathers_are_as_many_as_the_loads_they_replace(kernels):
     for k in convolutions:
         plain = k[:4] + ("0",) + k[5:]
         assert 0 < count[k] <= count[plain], (k, count[k], count[plain])
+
+
+def test_streaming_kernel_raises_a_slot_once(kernels):
+    """The maxima of a workgroup's outputs reach a member's slot by one raise per side, not by one per wave, row block and member."""
+    counts = [sum("atomic" in ins and "max" in ins for ins in code) for name, code in kernels.items()
+              if re.search(r"gemm_stream_kernelILi\dELi\dELi\dELb0E", name)]
+    assert len(counts) >= 9 and all(0 < c <= 2 for c in counts), counts
