@@ -377,7 +377,6 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   // epilogue: exact integer sum over the waves, then the fixed-order fp32 sum (same evaluation
   // order as the tiled kernel): one member, or members kept apart:
   //   y_m = s_x,m * (sum_k s_k * a_k) + b;  members summed: y = sum_m sum_k (s_k * s_x,m) * a_k + b.
-  const bool two_sided = p.amax_neg != nullptr;
   unsigned mxm[R], mnm[R];   // this wave's largest magnitudes (two-sided: largest values, and of their negatives), as the slots hold them
 #pragma unroll
   for (int m = 0; m < R; ++m) mxm[m] = mnm[m] = 0u;
@@ -422,6 +421,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       else if (p.act == PIPE_ACT_RELU) v = fmaxf(v, 0.f);
       if (!p.res_pre_act) v += rsum;
       if (p.amax_out != nullptr) {
+        const bool two_sided = p.amax_neg != nullptr;
         float mx = tg < p.T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
 #pragma unroll
         for (int s = 32; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
     }
     __syncthreads();
     const int m = threadIdx.x & (R - 1), neg = threadIdx.x / R;
-    if (neg < (two_sided ? 2 : 1) && m < p.M) {
+    if (neg < (p.amax_neg != nullptr ? 2 : 1) && m < p.M) {
       unsigned mx = 0u;
 #pragma unroll
       for (int w = 0; w < NW; ++w) mx = max(mx, smx[neg * R + m][w]);
