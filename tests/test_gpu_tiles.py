@@ -48,7 +48,9 @@ LAYERS = [(16, 100, 4, 1, 1.0, 16, [1], 129),
           (4096, 1700, 4, 3, 0.5, 16, [2, 1], 420),  # ... 14
           (2048, 1100, 8, 2, 1.0, 16, [2], 400),     # 8 bits, two ahead: 32 tokens ...
           (4096, 700, 8, 2, 1.0, 16, [1, 1], 257),   # ... 64
-          (11008, 300, 8, 2, 1.0, 16, [2], 130)]     # 8 bits, two low tiles a compute unit
+          (11008, 300, 8, 2, 1.0, 16, [2], 130),     # 8 bits, two low tiles a compute unit
+          (3072, 768, 4, 3, 0.5, 16, [3], 333),      # 4 bits, 32 tokens, two ahead: six stages ...
+          (2048, 1000, 4, 4, 0.5, 16, [1, 3], 280)]  # ... eight
 
 
 @pytest.mark.parametrize("O,I,bits,K,gamma,group,split,T", LAYERS)

@@ -192,7 +192,7 @@ def tiles_follow_the_units_they_leave(rt):
             (4096, 4096, 8, 2, 200, (8, 2, 1, 2)), (4096, 4096, 8, 2, 500, (8, 4, 1, 2)), (4096, 4096, 8, 2, 600, (8, 4, 1, 1)),
             (11008, 4096, 8, 2, 160, (8, 2, 1, 1)), (11008, 4096, 8, 2, 190, (8, 4, 1, 1)), (2304, 768, 8, 2, 700, (8, 4, 1, 1)),
             (768, 3072, 4, 2, 250, (4, 1, 1, 2)), (4096, 11008, 4, 2, 200, (4, 2, 2, 2)), (4096, 4096, 4, 2, 400, (4, 4, 2, 2)),
-            (4096, 4096, 4, 2, 600, (4, 4, 1, 2)), (4096, 4096, 4, 2, 4096, (4, 4, 1, 1)), (3072, 768, 4, 2, 200, (4, 1, 1, 1)),
+            (4096, 4096, 4, 2, 600, (4, 4, 1, 2)), (4096, 4096, 4, 2, 4096, (4, 4, 1, 1)), (3072, 768, 4, 2, 300, (4, 2, 1, 2)), (3072, 512, 4, 2, 300, (4, 2, 1, 1)),
             (768, 3072, 2, 2, 250, (2, 1, 1, 2)), (4096, 4096, 2, 2, 200, (2, 2, 2, 2)), (4096, 4096, 2, 2, 600, (2, 4, 1, 2))):
         e = rt.expand(rows, inp, bits, K, 1.0, 16)
         assert _linear(rt, e, T) == 0
