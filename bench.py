@@ -84,14 +84,22 @@ def parse():
     return ap.parse_args()
 
 
+def summed_by_member(cfg):
+    """Whether the last layer, a sum over two members with inputs of their own, takes a launch of the single-pass kernel for each above 128
+    tokens: walks of 48 64-k steps and more, members of 2 to 4 orders (of a single one only with many tiles: no workload here)."""
+    steps = -(-cfg.layers[-1].in_features // 256) * 4
+    return cfg.kind not in ("linear", "conv2d") and len(cfg.split) == 2 and steps >= 48 and all(2 <= s <= 4 for s in cfg.split)
+
+
 def tiled_kernels(cfg):
     """The contraction kernels of a workload's layers above 128 tokens: one pass where a member has at most 4 orders (a gate and its
-    up block 2), pass by pass otherwise and where members with inputs of their own are summed (the last layer of an ensemble)."""
+    up block 2), pass by pass otherwise and where members with inputs of their own are summed in one launch."""
     M, K = len(cfg.split), cfg.layers[0].K
     one_pass = max(cfg.split) <= (2 if cfg.kind == "mlp_gated" else 4)
     if cfg.kind in ("linear", "conv2d"):
         return "gemm_bins_kernel" if K <= 4 else "gemm_tiled_kernel"
-    names = ["gemm_bins_kernel" if one_pass else "gemm_tiled_kernel", "gemm_bins_kernel" if M == 1 and K <= 4 else "gemm_tiled_kernel"]
+    last = summed_by_member(cfg) or (M == 1 and K <= 4)
+    names = ["gemm_bins_kernel" if one_pass else "gemm_tiled_kernel", "gemm_bins_kernel" if last else "gemm_tiled_kernel"]
     return " + ".join(dict.fromkeys(names))
 
 
@@ -276,7 +284,8 @@ def main():
             ops = 2.0 * T * self.macs_per_token
             alg_bytes = self.stream_bytes + self.io_bytes(T)
             return dict(tokens=T, ms_per_step=step_ms, kernel_ms_per_step=per_step_kernel_ms,
-                        kernel_launches_per_step=k_n / steps, step_mode=mode,
+                        # (a sum by members is timed as one)
+                        kernel_launches_per_step=k_n / steps + (T > 128 and summed_by_member(self.cfg)), step_mode=mode,
                         eff_tops=ops / (step_ms * 1e-3) / 1e12,
                         kernel_eff_tops=ops / (per_step_kernel_ms * 1e-3) / 1e12 if k_ms > 0 else None,
                         tokens_per_s=T / (step_ms * 1e-3),
