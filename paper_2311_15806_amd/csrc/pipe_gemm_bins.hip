@@ -15,8 +15,8 @@
 //   - activations: L2 -> LDS without passing through registers, already in the MFMA operand layout, DP + 1 slots.
 // Bound by the matrix pipe and the issue slots around it (a ternary stage of 64 tokens: 64 MFMAs against 112 unpack instructions, 16
 // LDS reads and 8 loads per wave), and by what a workgroup does outside its loop (4.3 of 27.5 us of a 16-stage tile), which other
-// workgroups have to cover: 150 vector registers and 35 KB of LDS let three share a compute unit, and four where the fragments
-// have one register set (126 registers; see launch_cfg for which).  A third stage in flight costs the registers and a fifth more loads
+// workgroups have to cover: 144 to 153 vector registers and 35 KB of LDS let three share a compute unit, and four where the fragments
+// have one register set (128 registers, the most that four can have; see launch_cfg for which).  A third stage in flight costs the registers and a fifth more loads
 // (each tile then requests stages behind its last) and gains nothing (11008 x 4096 ternary, 4096 tokens 203 us against 198 with two
 // and 191 with two and four workgroups); a workgroup that walks several tiles loses (220 us: 768 fixed walks fill the chip worse than
 // the dispatcher does); tiles of 128 tokens, two workgroups, lose on ternary codes (214) and win a little on 4 bits (gate||up
@@ -28,8 +28,8 @@
 // the multiplies: through buffer resources, so that those behind the last stage read nothing and every wait stays an exact count.
 // (Exact in the code that the compiler makes of it, too: see the loop.  With waits that reached into the loads in flight the calls took 1 to 4 %
 // longer: 4096 x 11008 4 bit, 200 tokens 42.0 -> 40.5 us, ternary, 400 tokens 66.6 -> 64.1, 4096 x 4096 8 bit, 500 tokens 30.2 -> 29.3.)
-// A stage of two groups, 1024 MFMA cycles, then takes 1490 at 4 bits (768 x 3072, 2000 tokens) and 2240 with a convolution's gathers (256 x 14 x 14, 32 images);
-// one group with two stages in flight 840 and 1500 for its 512, one with one in flight 1180 and 1560.
+// A stage of two groups, 1024 MFMA cycles, then takes 1490 at 4 bits (768 x 3072, 2000 tokens) and 2150 with a convolution's gathers (256 x 14 x 14, 32 images);
+// one group with two stages in flight 840 and 1230 for its 512, one with one in flight 1180 and 1560; at 8 bits 890 and 1410.
 // Measured against one pass per order (pipe_gemm.hip, same box): 11008 x 4096 ternary, K = 4, 4096 tokens 227 -> 203 us,
 // 333 tokens 62 -> 30 us; 3x3 convolution 256 x 256 of 6272 pixels, 4 bit, K = 3 35.5 -> 18.4 us; 3072 x 768 and back, 4 bit,
 // K = 3, 4096 tokens 81 -> 60 us; eight 2048 x 2048 ternary layers, two members of 4 orders, 4096 tokens 676 -> 591 us
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
 #pragma unroll
               for (int b = 0; b < MTB; ++b) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, MTB == 8 ? 1 : 8 / MTB, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 8 / MTB, 0);
               }
             }
             __builtin_amdgcn_sched_barrier(0);   // keep the items apart: bounds live registers
@@ -585,7 +585,7 @@ int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t 
   if (p.cq8 != nullptr && (p.res != nullptr || p.act != 0)) return PIPE_EINVAL;   // implicit-GEMM convolution: plain epilogue
   // Workgroups per compute unit, three or four: four cover each other's epilogues and first loads better (a round of four takes
   // 1.30 of one of three, not 1.33), but end in larger rounds.  So four where as many or fewer places are filled: 11008 x 4096 ternary, 4096
-  // tokens (4816 tiles) 197 -> 191 us, 700 tokens 46.2 -> 44.4, 3300 165 -> 162; gate||up 22016 x 4096 4 bit, 2048 tokens 398 -> 372;
+  // tokens (4864 tiles) 197 -> 191 us, 700 tokens 46.2 -> 44.4, 3300 165 -> 162; gate||up 22016 x 4096 4 bit, 2048 tokens 398 -> 372;
   // but 3072 x 768 4 bit with GELU, 4096 tokens (1536 tiles, two full rounds of three) 30 -> 32.  Chain layers
   // without a skip tensor have a mode of their own, the others request theirs a row block at a time: eight 2048 x 2048 ternary layers, two members
   // of 4 orders, 4096 tokens 682 -> 658 us, six 4-bit ones of two members of 2 orders, 2500 tokens 444 -> 423.  Convolutions hold too much for four (they would spill).
@@ -756,8 +756,9 @@ int launch_gemm_bins(const GemmArgs& a, hipStream_t st) {
   // The shorter walk of tiles with 3 items pays wherever they are the rule, and for plain and gate||up layers also next to tiles of
   // 4 (4096 x 4096 4 bit, K = 4, half the groups kept, 4096 tokens: 174.7 -> 161 us a call; gate||up 22016 x 4096, 2048 tokens, the
   // MLP 665 -> 641).  GELU layers lose by the mixture (768 x 3072 and back, K = 3, half the groups kept, 4096 tokens 81.5 -> 82.6;
-  // all kept 104.8 -> 97.4), and the chains' layers by any (eight 2048 x 2048 ternary layers, two members of 4 orders, 2000 tokens 404 ->
-  // 439 us; five, K = 3, all kept, 1000 tokens 145 -> 155): they walk with 4.
+  // all kept 104.8 -> 97.4).  The chains' layers walk with 4: with 3 for tiles of 3 they gain or lose by how the rounds fall (eight 2048 x 2048
+  // ternary layers, two members of 4 orders, 1000, 2000, 3000 and 4096 tokens 302 -> 284, 412 -> 435, 532 -> 535 and 654 -> 653 us; one member of 4
+  // orders, 4000 tokens 403 -> 424, 4 bit, 1500 tokens 273 -> 249).
   p.three = a.act != PIPE_ACT_GELU || tb->n_four * 8 <= tb->n_three;
   p.later = 0; p.dead_ct = tb->n_ct; p.dead_gap = 0;
   p.T = a.T; p.T_pad = a.T_pad; p.out = e->out; p.nks = e->nks;

@@ -33,12 +33,6 @@ __device__ __forceinline__ T cload(const T* base, size_t idx) {
   return ((cptr)(unsigned long long)base)[idx];
 }
 
-// The LDS byte address of an object in shared memory.
-template <class T>
-__device__ __forceinline__ unsigned lds_addr(T* p) {
-  return (unsigned)(uintptr_t)(__attribute__((address_space(3))) T*)p;
-}
-
 // Which tile a workgroup computes.  Blocks i, i + 8, ... of a launch run on one XCD (one L2): chunks of `strip` column tiles
 // x `toks` token tiles, column by column, are dealt to the 8 XCDs in turn, strip after strip (heaviest column tiles first).
 struct TileOrder {
