@@ -18,25 +18,18 @@ __global__ void zero_u32_kernel(uint32_t* p, int n) {
   if (i < n) p[i] = 0u;
 }
 
-// Shows every float4 of x4[0..n4) to take() at least once: for a maximum, the last one may stand in for those behind it.  Thread `tid`
-// of workgroups that stride by `stride` together; this one's first element is x4[first].  Eight 16-byte loads in flight, and to the end as many
-// as are left (one by one: 333 x 4096, 7.98 loads a thread, 4.8 -> 4.0 us; sixteen in flight, or two sets of eight in turn,
-// change nothing: 4096 x 4096 at 17 us), but not eight for the last one or two: of many small workgroups that read everything
-// those take time (2 x 3072, 1.5 loads a thread, 4.3 -> 4.9 us).
+// Shows every float4 of x4[0..n4) from x4[i] on, `stride` apart, to take() at least once, N 16-byte loads in flight to the end: for a
+// maximum, the last one may stand in for those behind it (what was left of eight used to be loaded one by one: 333 x 4096, 7.98 loads a
+// thread, 4.8 -> 4.0 us; sixteen in flight, or two sets of eight in turn, change nothing: 4096 x 4096 at 17 us).
 template <int N, class Take>
-__device__ __forceinline__ void scan4_some(const float4* __restrict__ x4, int64_t n4, int64_t i, int64_t stride, Take take) {
-  float4 v[N];
+__device__ __forceinline__ void scan4(const float4* __restrict__ x4, int64_t n4, int64_t i, int64_t stride, Take take) {
+  for (; i < n4; i += N * stride) {
+    float4 v[N];
 #pragma unroll
-  for (int u = 0; u < N; ++u) v[u] = x4[min(i + u * stride, n4 - 1)];
+    for (int u = 0; u < N; ++u) v[u] = x4[min(i + u * stride, n4 - 1)];
 #pragma unroll
-  for (int u = 0; u < N; ++u) take(v[u]);
-}
-template <class Take>
-__device__ __forceinline__ void scan4(const float4* __restrict__ x4, int64_t n4, int64_t first, int tid, int64_t stride, Take take) {
-  for (; first + 4 * stride < n4; first += 8 * stride) scan4_some<8>(x4, n4, first + tid, stride, take);
-  if (first + 2 * stride < n4) scan4_some<4>(x4, n4, first + tid, stride, take);
-  else if (first + stride < n4) scan4_some<2>(x4, n4, first + tid, stride, take);
-  else if (first < n4) scan4_some<1>(x4, n4, first + tid, stride, take);
+    for (int u = 0; u < N; ++u) take(v[u]);
+  }
 }
 __device__ __forceinline__ float absmax4(const float4& v) {
   return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)));
@@ -55,7 +48,7 @@ __global__ __launch_bounds__(BLK) void absmax_kernel(const float* __restrict__ x
   const int64_t i0 = (int64_t)blockIdx.x * BLK + threadIdx.x;
   if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
     const int64_t n4 = n >> 2;
-    scan4(reinterpret_cast<const float4*>(x), n4, (int64_t)blockIdx.x * BLK, threadIdx.x, stride, [&](const float4& v) { m = fmaxf(m, absmax4(v)); });
+    scan4<8>(reinterpret_cast<const float4*>(x), n4, i0, stride, [&](const float4& v) { m = fmaxf(m, absmax4(v)); });
     for (int64_t i = (n4 << 2) + i0; i < n; i += stride) m = fmaxf(m, fabsf(x[i]));
   } else {
     for (int64_t i = i0; i < n; i += stride) m = fmaxf(m, fabsf(x[i]));
@@ -269,7 +262,12 @@ __global__ __launch_bounds__(SBLK) void quantize_small_kernel(const float* __res
     const int64_t cnt = (int64_t)T * in;
     if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
       const int64_t n4 = cnt >> 2;
-      scan4(reinterpret_cast<const float4*>(x), n4, 0, threadIdx.x, SBLK, [&](const float4& v) { mx = fmaxf(mx, absmax4(v)); });
+      // (every workgroup reads everything: eight loads for the last one or two would take 2 x 3072 from 4.3 to 4.9 us)
+      const int64_t eights = (n4 + 6 * SBLK - 1) / (8 * SBLK) * (8 * SBLK);   // in batches of eight but for a rest of up to two a thread
+      const float4* x4 = reinterpret_cast<const float4*>(x);
+      auto take = [&](const float4& v) { mx = fmaxf(mx, absmax4(v)); };
+      scan4<8>(x4, min(eights, n4), threadIdx.x, SBLK, take);
+      scan4<2>(x4, n4, eights + threadIdx.x, SBLK, take);
       for (int64_t j = (n4 << 2) + threadIdx.x; j < cnt; j += SBLK) mx = fmaxf(mx, fabsf(x[j]));
     } else {
       for (int64_t j = threadIdx.x; j < cnt; j += SBLK) mx = fmaxf(mx, fabsf(x[j]));
@@ -480,7 +478,7 @@ __global__ __launch_bounds__(BLK) void minmax_kernel(const float* __restrict__ x
   int64_t done = 0;
   if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
     const int64_t n4 = n >> 2;
-    scan4(reinterpret_cast<const float4*>(x), n4, (int64_t)blockIdx.x * BLK, threadIdx.x, stride, [&](const float4& v) { take(v.x); take(v.y); take(v.z); take(v.w); });
+    scan4<8>(reinterpret_cast<const float4*>(x), n4, i0, stride, [&](const float4& v) { take(v.x); take(v.y); take(v.z); take(v.w); });
     done = n4 << 2;
   }
   for (int64_t i = done + i0; i < n; i += stride) take(x[i]);
