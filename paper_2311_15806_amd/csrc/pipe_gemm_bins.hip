@@ -664,22 +664,23 @@ int launch_tiles(BinsParams& p, int bits, int live, int n_ct, hipEvent_t ev0, hi
     // none saved: 3072 x 768, K = 2, half kept, 700 tokens 21.1 / 19.8).
     // Two groups of waves along k, 2 and 4 bits, where the walk is long enough (24 64-k steps) for the second prologue and the exchange: 4096 x 11008 4 bit,
     // K = 4, 140 tokens 32.5 / 37.2 with one group, 300 tokens 44.1 / 45.2; 4096 x 4096, 130 tokens 19.3 / 20.3; convolution of
-    // 256 x 14 x 14, 32 images 25.0 / 26.2; 3x3 of 512 x 7 x 7, 20 images, ternary 24.2 / 26.7.  Shorter 4-bit walks, 32 tokens, one group, ahead: 3072 x 768,
+    // 256 x 14 x 14, 32 images 25.0 / 26.2; 3x3 of 512 x 7 x 7, 20 images, ternary 24.2 / 26.7; long ternary walks also with two
+    // low tiles a unit where the high ones would not be alone: 4096 x 11008, 350 tokens 59.8 / 63.0 (300 tokens, alone 47.3 / 44.6).  Shorter 4-bit walks, 32 tokens, one group, ahead: 3072 x 768,
     // 300 tokens, affine codes 14.4 / 15.0, 2048 x 1024, 250 tokens 13.0 / 13.8; ternary ones and convolutions gain nothing.
     // Tiles of 64 tokens that the chip holds two of a unit also ask two stages ahead: 11008 x 4096 ternary, 333
     // tokens (456 tiles) 33.7 / 37.4, 4096 x 11008 4 bit, 420 tokens 63.3 / 69.7, gate||up 11008 x 2048, 216 tokens (480 tiles) a whole MLP 65.8 / 70.6;
-    // at 4 bits not where an XCD's units are dealt all of the two (1536 x 2048, 1700 tokens 34.1 / 32.2; 4096 x 4096, 700 tokens 46.0 / 44.2), and never
-    // a ternary convolution (128 rows of 64 x 56 x 56, 8 images 25.9 / 24.3) or 8 bits (4096 x 4096, 600 tokens 38.8 / 36.5).
+    // at 4 bits not where an XCD's units are dealt all of the two (1536 x 2048, 1700 tokens 34.1 / 32.2; 4096 x 4096, 700 tokens 46.0 / 44.2), nor
+    // ternary convolutions of shorter walks (128 rows of 64 x 56 x 56, 8 images 25.9 / 24.3; 72 steps, 512 x 7 x 7, 40 images 30.7 / 32.5), nor 8 bits (4096 x 4096, 600 tokens 38.8 / 36.5).
     const bool conv = p.cq8 != nullptr;
     if (p.nks >= (bits == 8 ? 8 : 16) && alone(16)) { mtb = 1; ahead = bits == 2 && conv ? 1 : 2; }
     else if (bits == 8) {
       if (p.nks >= 8 && (alone(32) || alone(64))) { mtb = alone(32) ? 2 : 4; ahead = 2; }
       else if (p.nks >= 8 && tiles(32) < 2 * tiles(64) && fullest(32) * 8 <= 2 * cus) mtb = 2;
     }
-    else if (p.nks >= 24 && alone(32)) { mtb = 2; groups = 2; }
+    else if (p.nks >= 24 && (alone(32) || (bits == 2 && !conv && p.nks >= 64 && tiles(32) <= 2 * cus && !alone(64)))) { mtb = 2; groups = 2; }
     else if (p.nks >= 24 && bits == 4 && alone(64)) { mtb = 4; groups = 2; }
     else if (p.nks >= 12 && p.nks < 24 && bits == 4 && !conv && alone(32)) { mtb = 2; ahead = 2; }
-    else if ((p.nks >= 24 || (p.nks >= 16 && tiles(64) >= 192)) && !(bits == 2 && conv) &&
+    else if ((p.nks >= 24 || (p.nks >= 16 && tiles(64) >= 192)) && !(bits == 2 && conv && p.nks < 64) &&
              (bits == 2 ? tiles(64) <= 2 * cus : fullest(64) * 64 <= 15 * cus)) { mtb = 4; ahead = 2; }
   }
   const int sk = bits == 2 || mtb == 1 || (groups == 2 && mtb == 2) ? 4 : 2;   // as in the kernel

@@ -267,7 +267,7 @@ def test_gelu_of_infinities(pipe, T):
 @pytest.mark.parametrize("kind,T,C,k", [("gelu", 300, 1696, 0), ("gated", 300, 1696, 0), ("chain", 300, 1696, 0), ("chain", 1100, 1696, 0), ("chain", 13000, 512, 0), ("chain2", 13000, 512, 0),
                                         ("conv", 3, 256, 3), ("conv", 30, 256, 3), ("conv", 3, 64, 5), ("conv8", 40, 256, 3), ("conv2", 3, 256, 3),
                                         ("conv", 12, 256, 3), ("conv", 30, 192, 3), ("conv", 60, 256, 3), ("conv", 60, 64, 5), ("conv8", 3, 256, 3), ("conv8", 12, 64, 5), ("conv8", 40, 192, 3),
-                                        ("conv2", 12, 256, 3), ("conv2", 30, 64, 5), ("gated", 500, 1696, 0)])
+                                        ("conv2", 12, 256, 3), ("conv2", 30, 64, 5), ("conv2", 60, 512, 3), ("gated", 500, 1696, 0)])
 def test_two_groups_equal_one(pipe, kind, T, C, k):
     rng = np.random.default_rng(T + C)
     made = []

@@ -193,14 +193,15 @@ def tiles_follow_the_units_they_leave(rt):
             (11008, 4096, 8, 2, 160, (8, 2, 1, 1)), (11008, 4096, 8, 2, 190, (8, 4, 1, 1)), (2304, 768, 8, 2, 700, (8, 4, 1, 1)),
             (768, 3072, 4, 2, 250, (4, 1, 1, 2)), (4096, 11008, 4, 2, 200, (4, 2, 2, 2)), (4096, 4096, 4, 2, 400, (4, 4, 2, 2)),
             (4096, 4096, 4, 2, 600, (4, 4, 1, 2)), (4096, 4096, 4, 2, 4096, (4, 4, 1, 1)), (3072, 768, 4, 2, 300, (4, 2, 1, 2)), (3072, 512, 4, 2, 300, (4, 2, 1, 1)),
-            (768, 3072, 2, 2, 250, (2, 1, 1, 2)), (4096, 4096, 2, 2, 200, (2, 2, 2, 2)), (4096, 4096, 2, 2, 600, (2, 4, 1, 2))):
+            (768, 3072, 2, 2, 250, (2, 1, 1, 2)), (4096, 4096, 2, 2, 200, (2, 2, 2, 2)), (4096, 4096, 2, 2, 600, (2, 4, 1, 2)),
+            (4096, 11008, 2, 2, 500, (2, 4, 1, 2)), (6144, 4096, 2, 2, 322, (2, 4, 1, 2)), (5632, 4096, 2, 2, 322, (2, 2, 2, 2)), (5632, 3072, 2, 2, 322, (2, 4, 1, 2))):
         e = rt.expand(rows, inp, bits, K, 1.0, 16)
         assert _linear(rt, e, T) == 0
         assert _tile(rt.names()) == want, (rows, inp, bits, T)
     rt.lib.pipe_expand_conv2d.argtypes = [C.c_void_p] + [C.c_int] * 6 + [C.c_float, C.c_int, C.c_void_p, C.POINTER(C.c_void_p)]
     rt.lib.pipe_forward_conv2d.argtypes = [C.c_void_p] * 2 + [C.c_int] * 9 + [C.c_float, C.c_void_p, C.c_int, C.c_void_p, C.c_int] + [C.c_void_p] * 2
     for rows, Ch, H, N, bits, want in ((512, 256, 14, 5, 8, (8, 1, 1, 2)), (512, 256, 14, 10, 8, (8, 2, 1, 2)), (512, 512, 7, 32, 8, (8, 2, 1, 2)),
-                                       (256, 256, 14, 5, 2, (2, 1, 1, 1)), (128, 64, 56, 8, 2, (2, 4, 1, 1)), (256, 256, 14, 5, 4, (4, 1, 1, 2))):
+                                       (256, 256, 14, 5, 2, (2, 1, 1, 1)), (128, 64, 56, 8, 2, (2, 4, 1, 1)), (512, 512, 7, 60, 2, (2, 4, 1, 2)), (256, 256, 14, 5, 4, (4, 1, 1, 2))):
         W, e = (C.c_float * (rows * Ch * 9))(), C.c_void_p()
         assert rt.lib.pipe_expand_conv2d(W, rows, Ch, 3, 3, bits, 2, 1.0, 16, None, C.byref(e)) == 0
         rt.names()
