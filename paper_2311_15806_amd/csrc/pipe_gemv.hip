@@ -124,6 +124,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   constexpr int BIN_WORDS = sizeof(StreamBin) / 4;
   static_assert(BIN_WORDS <= 64, "bin descriptor is fetched with one load per lane");
   __shared__ int part[NW][R][256];   // each wave's partial tiles
+  __shared__ unsigned s_mx[2 * R];   // the members' largest magnitudes (two-sided: largest values, then of their negatives), as the slots hold them
   __shared__ int s_last;
 
   if (QFUSE) request_arguments<sizeof(StreamParams)>();
@@ -335,6 +336,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
 #pragma unroll
   for (int r = 0; r < R; ++r)
     *reinterpret_cast<v4i*>(&part[wave][r][lane * 4]) = acc[r];
+  if (threadIdx.x < 2 * R) s_mx[threadIdx.x] = 0u;
   __syncthreads();
 
   // A split bin: every workgroup writes its integer partial tiles to its own slice of the bin's
@@ -377,9 +379,6 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   // epilogue: exact integer sum over the waves, then the fixed-order fp32 sum (same evaluation
   // order as the tiled kernel): one member, or members kept apart:
   //   y_m = s_x,m * (sum_k s_k * a_k) + b;  members summed: y = sum_m sum_k (s_k * s_x,m) * a_k + b.
-  unsigned mxm[R], mnm[R];   // this wave's largest magnitudes (two-sided: largest values, and of their negatives), as the slots hold them
-#pragma unroll
-  for (int m = 0; m < R; ++m) mxm[m] = mnm[m] = 0u;
   for (int o = o_first; o < n_out; o += O_STEP) {
     // a row block's items are adjacent, in ascending order k
     const int col = out_rb(o) * 16 + ch;
@@ -425,12 +424,12 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
         float mx = tg < p.T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
 #pragma unroll
         for (int s = 32; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-        mxm[m] = max(mxm[m], __float_as_uint(mx));
+        if (lane == 0) atomicMax(&s_mx[m], __float_as_uint(mx));
         if (two_sided) {
           float mn = tg < p.T ? fmaxf(-v, 0.f) : 0.f;
 #pragma unroll
           for (int s = 32; s > 0; s >>= 1) mn = fmaxf(mn, __shfl_xor(mn, s, 64));
-          mnm[m] = max(mnm[m], __float_as_uint(mn));
+          if (lane == 0) atomicMax(&s_mx[R + m], __float_as_uint(mn));
         }
       }
       if (tg < p.T) p.y[((size_t)(p.reduce ? 0 : m) * p.T + tg) * p.out + col] = v;
@@ -440,22 +439,10 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   // together all find the slot low), the longer the quicker the activation ran: MLP 1024-4096-1024 4 bit, K = 3 in 2 and 1, GELU, 32 tokens
   // 33.8 us with erff and 37.1 with the polynomial, 79 tokens 49.5; so 25.4 and 34.5; six 2048 x 2048 ternary layers of two members, 128 tokens 201 -> 131.
   if (!ACC_OUT && p.amax_out != nullptr) {
-    __shared__ unsigned smx[2 * R][NW];
-    if (lane == 0) {
-#pragma unroll
-      for (int m = 0; m < R; ++m) {
-        smx[m][wave] = mxm[m];
-        smx[R + m][wave] = mnm[m];
-      }
-    }
     __syncthreads();
     const int m = threadIdx.x & (R - 1), neg = threadIdx.x / R;
-    if (neg < (p.amax_neg != nullptr ? 2 : 1) && m < p.M) {
-      unsigned mx = 0u;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) mx = max(mx, smx[neg * R + m][w]);
-      slot_raise(neg ? &p.amax_neg[m] : &p.amax_out[m], __uint_as_float(mx));
-    }
+    if (neg < (p.amax_neg != nullptr ? 2 : 1) && m < p.M)
+      slot_raise(neg ? &p.amax_neg[m] : &p.amax_out[m], __uint_as_float(s_mx[threadIdx.x]));
   }
 }
 
