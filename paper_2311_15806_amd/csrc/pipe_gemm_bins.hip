@@ -671,7 +671,10 @@ int launch_tiles(BinsParams& p, int bits, int live, int n_ct, hipEvent_t ev0, hi
     // tokens (456 tiles) 33.7 / 37.4, 4096 x 11008 4 bit, 420 tokens 63.3 / 69.7, gate||up 11008 x 2048, 216 tokens (480 tiles) a whole MLP 65.8 / 70.6;
     // at 4 bits not where an XCD's units are dealt all of the two (1536 x 2048, 1700 tokens 34.1 / 32.2; 4096 x 4096, 700 tokens 46.0 / 44.2), nor
     // ternary convolutions of shorter walks (128 rows of 64 x 56 x 56, 8 images 25.9 / 24.3; 72 steps, 512 x 7 x 7, 40 images 30.7 / 32.5), nor 8 bits (4096 x 4096, 600 tokens 38.8 / 36.5).
-    const bool conv = p.cq8 != nullptr;
+    // Chain layers of 16 to 23 steps gain by it only while a unit holds one tile: what follows the walk there (skip tensor, ReLU, maxima) is covered by
+    // the four workgroups of the loads one stage ahead (two 1024 x 1024 layers and a head, 4 bit, K = 4, 1700 tokens, 432 tiles 133.9 / 114.1,
+    // 1100 tokens, 288 tiles 107.6 / 101.6; half the groups kept, 1112 tokens, 216 tiles 108.6 / 106.6; 1280 wide, 240 tiles 98.2 / 107.0).
+    const bool conv = p.cq8 != nullptr, chain = p.res != nullptr || p.act == PIPE_ACT_RELU;
     if (p.nks >= (bits == 8 ? 8 : 16) && alone(16)) { mtb = 1; ahead = bits == 2 && conv ? 1 : 2; }
     else if (bits == 8) {
       if (p.nks >= 8 && (alone(32) || alone(64))) { mtb = alone(32) ? 2 : 4; ahead = 2; }
@@ -680,7 +683,7 @@ int launch_tiles(BinsParams& p, int bits, int live, int n_ct, hipEvent_t ev0, hi
     else if (p.nks >= 24 && (alone(32) || (bits == 2 && !conv && p.nks >= 64 && tiles(32) <= 2 * cus && !alone(64)))) { mtb = 2; groups = 2; }
     else if (p.nks >= 24 && bits == 4 && alone(64)) { mtb = 4; groups = 2; }
     else if (p.nks >= 12 && p.nks < 24 && bits == 4 && !conv && alone(32)) { mtb = 2; ahead = 2; }
-    else if ((p.nks >= 24 || (p.nks >= 16 && tiles(64) >= 192)) && !(bits == 2 && conv && p.nks < 64) &&
+    else if ((p.nks >= 24 || (p.nks >= 16 && tiles(64) >= 192 && !(chain && tiles(64) > cus))) && !(bits == 2 && conv && p.nks < 64) &&
              (bits == 2 ? tiles(64) <= 2 * cus : fullest(64) * 64 <= 15 * cus)) { mtb = 4; ahead = 2; }
   }
   const int sk = bits == 2 || mtb == 1 || (groups == 2 && mtb == 2) ? 4 : 2;   // as in the kernel

@@ -208,6 +208,18 @@ def tiles_follow_the_units_they_leave(rt):
         assert rt.lib.pipe_forward_conv2d(e, 1 << 40, N, Ch, H, H, 3, 3, 1, 1, 0, 0.0, None, 0, None, 1, 1 << 44, None) == 0
         assert _tile(rt.names()) == want, (rows, Ch, N, bits)
 
+    class Layer(C.Structure):   # pipe_chain_layer
+        _fields_ = [("e", C.c_void_p), ("bias", C.c_void_p), ("act", C.c_int), ("skip", C.c_int), ("pre_act", C.c_int), ("conv", C.c_int * 4), ("s_in", C.c_void_p)]
+
+    rt.lib.pipe_chain_forward.argtypes = [C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 3
+    for width, T, want in ((1024, 1000, (4, 4, 1, 2)), (1024, 1100, (4, 4, 1, 1)), (1536, 700, (4, 4, 1, 2))):   # 256, 288 and 264 tiles of 64
+        e = rt.expand(width, width, 4, 4, 1.0, 16)
+        arr = (Layer * 2)(Layer(e, None, 3, -1), Layer(e, None, 0, -1))
+        rt.names()
+        assert rt.lib.pipe_chain_forward(arr, 2, 1 << 40, T, 0.0, (C.c_int * 1)(4), 1, None, 1 << 44, None) == 0
+        names = [n for n in rt.names() if "gemm_bins_kernel" in n]
+        assert _tile(names[:1]) == want, (width, T, names)
+
 
 def a_sum_over_two_members_is_a_launch_each(rt):
     """The second layer of an MLP: a launch of the single-pass kernel per member where the walk is long and a member of a single order
