@@ -230,3 +230,32 @@ def test_resident_limits_layers_and_descriptor_space(pipe):
         assert torch.equal(y1, y2)
     for e in up + down:
         e.free()
+
+
+@pytest.mark.parametrize("out,bits,K,gamma,split,act,T", [
+    (5008, 2, 4, 0.25, [2, 2], "relu", 16),   # 345 bins on 256 units: one unit of up to 8 items each, sums without items
+    (5008, 4, 4, 1.0, None, "gelu", 9),       # 313 bins of 4: half of the second sub-units hold nothing
+    (18000, 8, 1, 1.0, None, "none", 5),      # up to 5 output row blocks a unit
+    (24000, 4, 2, 0.5, [1, 1], "relu", 3),    # more bins than twice the units: bins as they are
+    (122880, 2, 4, 1.0, [2, 2], "relu", 2),   # more outputs a workgroup than its stash holds
+    (150000, 2, 4, 1.0, None, "last", 3),     # more units a workgroup than have their scales fetched ahead
+])
+def test_resident_units_of_wide_layers(pipe, out, bits, K, gamma, split, act, T):
+    """Layers of few inputs and many outputs, whose units the host deals differently, against the per-layer launches bit for bit."""
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(out + T)
+    mk = lambda o, i: pipe.pipe_expand(torch.randn(o, i, generator=g, device="cuda:0") * (1.5 / i ** 0.5), bits, K, gamma, 16)
+    first, wide = mk(96, 80), mk(out, 96)
+    b = lambda n: torch.randn(n, generator=g, device="cuda:0") * 0.1
+    es = [first, wide]
+    layers = [(first, b(96), ACT["relu"], -1, True), (wide, b(out), ACT["none" if act == "last" else act], -1, True)]
+    if act != "last":
+        es.append(mk(64, out))
+        layers.append((es[-1], b(64), ACT["none"], -1, True))
+    x = torch.randn(T, 80, generator=g, device="cuda:0")
+    (y1, a1), (y2, a2) = _both(pipe, lambda: pipe.pipe_chain_forward(layers, x, split=split, return_acts=True))
+    assert torch.equal(y1, y2)
+    for u, v in zip(a1, a2):
+        assert torch.equal(u, v)
+    for e in es:
+        e.free()
