@@ -623,48 +623,66 @@ __global__ __launch_bounds__(BLK) void row_code_sums_kernel(const int8_t* __rest
   if (threadIdx.x == 0) wsum[o] = sm[0];
 }
 
-// Convolution input for the implicit GEMM: channels-last int8 codes [N, H, W, C] and, per pixel,
-// the sum of its C codes (added into csum, zero on entry).  NCHW input: 32 channels x 32 pixels per
-// workgroup through LDS, so that reads run along the pixels and writes along the channels; NHWC input:
-// element-wise, a group of 32 consecutive threads holds 32 consecutive channels of one pixel (C is a
-// multiple of 64).
-__global__ __launch_bounds__(BLK) void quantize_nhwc_sums_kernel(const float* __restrict__ x, int C, int HW, int nhwc,
+// Convolution input for the implicit GEMM: channels-last int8 codes [N, H, W, C] and, per pixel, the sum of its C codes (added into
+// csum, zero on entry: one atomic per pixel and CH channels).  A workgroup takes 4096 elements, CH channels (a multiple of 64 divides C)
+// of 4096 / CH neighbouring pixels of an image, through LDS: reads run along the layout's own inner dimension, 16 bytes a lane where
+// its rows allow (`vec`), writes are 16 channels a lane.  Bound by the trip to memory: four loads a lane in flight, then one store
+// (32 images of 256 x 14 x 14: tiles of 32 x 32 one byte a store 7.2 us, these 4.1).
+template <int CH>
+__global__ __launch_bounds__(BLK) void quantize_nhwc_sums_kernel(const float* __restrict__ x, int C, int HW, int nhwc, int vec,
                                                                  float s_static, MaxOf amax,
                                                                  int8_t* __restrict__ q8, int32_t* __restrict__ csum,
                                                                  float* __restrict__ scale_out) {
-  __shared__ int8_t tile[32][33];
-  const int n = blockIdx.z, c0 = blockIdx.y * 32, p0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
-  float xv[4];   // requested before the scale is known
+  constexpr int P = 4096 / CH, ROW = CH + 16;   // pixels; bytes of a pixel in LDS (16 apart: other banks)
+  __shared__ alignas(16) uint8_t tile[P * ROW];
+  const int n = blockIdx.z, c0 = blockIdx.y * CH, p0 = blockIdx.x * P, tid = threadIdx.x;
+  // four neighbours along the input's inner dimension: pixels of a channel, or channels of a pixel
+  const int per_row = nhwc ? CH / 4 : P / 4, step = BLK / per_row;   // quads of a row, rows of a pass
+  const int quad = (tid % per_row) * 4, row = tid / per_row;
+  float xv[4][4];   // requested before the scale is known
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int c = nhwc ? c0 + tx : c0 + ty + 8 * j, pp = nhwc ? p0 + ty + 8 * j : p0 + tx;
-    xv[j] = c < C && pp < HW ? x[nhwc ? ((size_t)n * HW + pp) * C + c : ((size_t)n * C + c) * HW + pp] : 0.f;
+    const int r = row + j * step;
+    const int c = nhwc ? c0 + quad : c0 + r, p = nhwc ? p0 + r : p0 + quad;
+    const size_t at = nhwc ? ((size_t)n * HW + p) * C + c : ((size_t)n * C + c) * HW + p;
+    if (vec) {
+      const float4 v = p < HW ? *reinterpret_cast<const float4*>(x + at) : make_float4(0.f, 0.f, 0.f, 0.f);
+      xv[j][0] = v.x; xv[j][1] = v.y; xv[j][2] = v.z; xv[j][3] = v.w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xv[j][i] = (nhwc ? p : p + i) < HW ? x[at + i] : 0.f;
+    }
   }
   const float s = s_static > 0.f ? s_static : __fdiv_rn(max_of_by_wave(amax), c_act_qmax);
-  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && scale_out) *scale_out = s;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && tid == 0 && scale_out) *scale_out = s;
   const SymCodes cd(s);
-  int qv[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) qv[j] = cd.live() ? (cd.d.fast ? cd.code<true>(xv[j]) : cd.code<false>(xv[j])) : 0;
-  if (!nhwc) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tile[ty + 8 * j][tx] = (int8_t)qv[j];
-    __syncthreads();
-  }
+  const bool live = cd.live();
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int pp = p0 + ty + 8 * j, c = c0 + tx;
-    int v = 0;
-    if (c < C && pp < HW) {
-      v = nhwc ? qv[j] : (int)tile[tx][ty + 8 * j];
-      q8[((size_t)n * HW + pp) * C + c] = (int8_t)v;
-    }
-    // the 32 threads of a half wave hold 32 channels of one pixel
-    int sum = v;
+    const int r = row + j * step;
+    int q[4];
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if (tx == 0 && pp < HW && sum != 0) atomicAdd(&csum[(size_t)n * HW + pp], sum);
+    for (int i = 0; i < 4; ++i) q[i] = live ? (cd.d.fast ? cd.code<true>(xv[j][i]) : cd.code<false>(xv[j][i])) : 0;
+    if (nhwc) {
+      *reinterpret_cast<uint32_t*>(&tile[r * ROW + quad]) = pack4(q[0], q[1], q[2], q[3]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tile[(quad + i) * ROW + r] = (uint8_t)q[i];
+    }
+  }
+  __syncthreads();
+  constexpr int CHUNKS = CH / 16;   // lanes of a pixel
+  const int px = tid / CHUNKS, ck = tid % CHUNKS, p = p0 + px;
+  const uint4 w = *reinterpret_cast<const uint4*>(&tile[px * ROW + ck * 16]);
+  int sum = __builtin_amdgcn_sdot4((int)w.x, 0x01010101, 0, false);
+  sum = __builtin_amdgcn_sdot4((int)w.y, 0x01010101, sum, false);
+  sum = __builtin_amdgcn_sdot4((int)w.z, 0x01010101, sum, false);
+  sum = __builtin_amdgcn_sdot4((int)w.w, 0x01010101, sum, false);
+#pragma unroll
+  for (int o = CHUNKS / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (p < HW) {
+    *reinterpret_cast<uint4*>(q8 + ((size_t)n * HW + p) * C + c0 + ck * 16) = w;
+    if (ck == 0 && sum != 0) atomicAdd(&csum[(size_t)n * HW + p], sum);
   }
 }
 
@@ -672,8 +690,15 @@ __global__ __launch_bounds__(BLK) void quantize_nhwc_sums_kernel(const float* __
 
 int launch_quantize_nhwc_sums(const float* x, int N, int C, int HW, int nhwc, float s_static, MaxOf amax,
                               int8_t* q8, int32_t* csum, float* scale_out, hipStream_t st) {
-  PIPE_KLAUNCH(quantize_nhwc_sums_kernel, dim3(ceil_div(HW, 32), ceil_div(C, 32), N), dim3(BLK), 0, st, x, C, HW, nhwc, s_static,
-               amax, q8, csum, scale_out);
+  if (C % 64 != 0) return PIPE_ESHAPE;
+  // rows of whole 16-byte loads: pixels of a channel, or channels of a pixel, in a tensor that begins on 16 bytes
+  const int vec = (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (nhwc || HW % 4 == 0);
+  if (C % 128 == 0)
+    PIPE_KLAUNCH(quantize_nhwc_sums_kernel<128>, dim3(ceil_div(HW, 32), C / 128, N), dim3(BLK), 0, st, x, C, HW, nhwc, vec, s_static, amax, q8,
+                 csum, scale_out);
+  else
+    PIPE_KLAUNCH(quantize_nhwc_sums_kernel<64>, dim3(ceil_div(HW, 64), C / 64, N), dim3(BLK), 0, st, x, C, HW, nhwc, vec, s_static, amax, q8,
+                 csum, scale_out);
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
 }

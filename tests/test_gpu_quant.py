@@ -83,3 +83,29 @@ def test_dynamic_scale_over_the_parts_of_the_reduction(pipe, T, I, shift):
         assert sa == float(sar) and z == zr
         assert np.array_equal(qa.cpu().numpy(), np.clip(np.rint(x / sar) + f32(zr), 0, 255).astype(np.uint8).reshape(T, I))
     e.free()
+
+
+@pytest.mark.parametrize("C,H,W,N", [(64, 1, 3, 2), (64, 9, 7, 3), (128, 7, 7, 2), (192, 4, 17, 2), (256, 6, 6, 1)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_channels_last_codes_and_sums(pipe, C, H, W, N, shift):
+    """Codes and per-pixel sums of a convolution's input at the edges of its tiles of 4096 elements, both layouts, inputs that are not
+    16-byte aligned: a pointwise layer's accumulators and outputs (bit for bit) against the codes."""
+    rng = np.random.default_rng(C + H + W)
+    x = rng.standard_normal((N, C, H, W)).astype(f32)
+    e = pipe.pipe_expand_conv2d(dev(rng.standard_normal((32, C)).astype(f32)), C, 1, 1, 4, 1, 1.0, 16)
+    _, _, codes = e.order(1)
+    s = f32(f32(np.abs(x).max()) / f32(127))
+    q = _codes(x.reshape(-1), s).reshape(x.shape).astype(np.int64)
+    want = np.einsum("nchw,oc->nhwo", q, codes.astype(np.int64)).reshape(-1, 32)
+    ys = []
+    for nhwc in (False, True):
+        xl = np.ascontiguousarray(x.transpose(0, 2, 3, 1)) if nhwc else x
+        buf = torch.empty(x.size + 4, dtype=torch.float32, device="cuda")
+        xd = buf[shift:shift + x.size].view(*xl.shape)
+        xd.copy_(dev(xl))
+        acc, _, sx = pipe.pipe_forward_conv2d_acc(e, xd, 1, 1, 1, 0, nhwc=nhwc)
+        assert float(sx.item()) == float(s)
+        assert np.array_equal(acc.cpu().numpy()[0], want)
+        ys.append(pipe.pipe_forward_conv2d(e, xd, 1, 1, 1, 0, nhwc=nhwc))
+    assert torch.equal(ys[0], ys[1])
+    e.free()
