@@ -523,25 +523,28 @@ __global__ __launch_bounds__(BLK) void quantize_asym_kernel(const float* __restr
                                                             uint8_t* __restrict__ qx_rowmajor, float* __restrict__ scale_out,
                                                             int32_t* __restrict__ dz_out, const float* __restrict__ bias,
                                                             const float* __restrict__ C, float* __restrict__ bias_eff, int n_out) {
+  float off = 0.f;   // the scale times the zero point's distance from the codes' middle
   auto make = [&]() {
-    AsymCodes cd(max_of(hi_max), max_of(nlo_max), qa, shift);
+    float hi, nlo;
+    max_of_two(hi_max, nlo_max, &hi, &nlo);
+    AsymCodes cd(hi, nlo, qa, shift);
     cd.rows = qx_rowmajor;
     const int dz = cd.live() ? shift - (int)cd.zf : 0;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
       scale_out[0] = cd.d.s;
       dz_out[0] = dz;
     }
-    if (C != nullptr) {
-      const float f = cd.d.s * (float)dz;
-      const int nb = gridDim.x * gridDim.y;
-      for (int o = (blockIdx.y * gridDim.x + blockIdx.x) * BLK + threadIdx.x; o < n_out; o += nb * BLK)
-        bias_eff[o] = (bias != nullptr ? bias[o] : 0.f) + f * C[o];
-    }
+    off = cd.d.s * (float)dz;
     return cd;
   };
   auto fetch = [=](int t, int k) { return x[(size_t)t * in + k]; };
   const bool vec = (in & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 && qx_rowmajor == nullptr;
   quantize_block(make, fetch, T, in, in_pad, qx_frag, rowsum, vec ? x : nullptr);
+  if (C != nullptr) {
+    const int nb = gridDim.x * gridDim.y;
+    for (int o = (blockIdx.y * gridDim.x + blockIdx.x) * BLK + threadIdx.x; o < n_out; o += nb * BLK)
+      bias_eff[o] = (bias != nullptr ? bias[o] : 0.f) + off * C[o];
+  }
 }
 
 // every element of a tensor once, in its own layout (the convolution's first step): code minus shift
