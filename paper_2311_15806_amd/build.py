@@ -13,17 +13,20 @@ OBJ_DIR = os.path.join(HERE, "_build")
 
 # (source, extra flags).  The files whose fp32 results feed rounding decisions are built
 # with floating-point contraction off.
+# Kernels of a few microseconds get their scalar arguments in registers with the launch, instead of loading them from
+# host memory first: 0.15 us of a launch (1000 x 768 affine codes, 32 x 256 x 14 x 14 and 32 x 384 x 28 x 28 images, calls of 20 to 29 us -0.9 %).
+PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 SOURCES = [
     ("pipe_api.hip", []),
     ("pipe_expand.hip", ["-ffp-contract=off"]),
-    ("pipe_quant.hip", ["-ffp-contract=off"]),
+    ("pipe_quant.hip", ["-ffp-contract=off"] + PRELOAD),
     ("pipe_gemm.hip", []),
     ("pipe_gemm_bins.hip", []),
     ("pipe_gemv.hip", []),
     ("pipe_resident.hip", []),
     ("pipe_probe.hip", []),
     ("pipe_diag.hip", ["-ffp-contract=off"]),
-    ("pipe_depthwise.hip", ["-ffp-contract=off"]),
+    ("pipe_depthwise.hip", ["-ffp-contract=off"] + PRELOAD),
 ]
 
 COMMON = [
