@@ -21,7 +21,7 @@ SOURCES = [
     ("pipe_expand.hip", ["-ffp-contract=off"]),
     ("pipe_quant.hip", ["-ffp-contract=off"] + PRELOAD),
     ("pipe_gemm.hip", []),
-    ("pipe_gemm_bins.hip", []),
+    ("pipe_gemm_bins.hip", PRELOAD),
     ("pipe_gemv.hip", []),
     ("pipe_resident.hip", []),
     ("pipe_probe.hip", []),

@@ -114,7 +114,8 @@ constexpr int wait_imm(int vm, int lgkm) { return (vm & 15) | (7 << 4) | (lgkm <
 // G groups of 4 waves take a tile's walk along k in G parts, each with slots of its own; their sums meet in LDS behind the loop and
 // every group finishes MTB / G of the token blocks.
 template <int BITS, int MTB, int MINW, int MODE, bool CONV, int G, int DP>
-__global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsParams p) {
+__global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const TileBin* __restrict__ a_bins, const uint8_t* __restrict__ a_codes, int a_n_ct, int a_n_tt,
+                                                                  int a_strip, int a_toks, int a_dead_ct, int a_dead_gap, int a_nks, const BinsParams p) {
   constexpr int OFF = BITS == 8 ? 0 : (BITS == 4 ? 8 : 1);
   constexpr int SK = BITS == 2 || MTB == 1 || (G == 2 && MTB == 2) ? 4 : 2;   // 64-k steps per stage
   constexpr int XC = MTB * SK / 4;                    // activation fragments (1 KiB) a wave loads per stage
@@ -137,39 +138,41 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wave = wid & 3, grp = G == 1 ? 0 : wid >> 2;
+  // The tile's descriptor first, from arguments that come in registers with the launch: the others are on their way from host memory
+  // meanwhile.
+  int ct, tt;
+  const bool mine = TileOrder{a_n_ct, a_n_tt, a_strip, a_toks}.tile(blockIdx.x, &ct, &tt);
+  const int t0 = tt * (16 * MTB);
+  if (ct >= a_dead_ct) ct += a_dead_gap;
+  const TileBin* bin = a_bins + (mine ? ct : 0) * 4 + wave;
+  const v4i pos = cload(&bin->pos, 0), spos = cload(&bin->spos, 0), rb = cload(&bin->rb, 0), info = cload(&bin->info, 0);
   if (p.zero_big != nullptr)
     for (int i = blockIdx.x * (256 * G) + threadIdx.x; i < p.zero_big_n; i += gridDim.x * (256 * G)) p.zero_big[i] = 0u;
   if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<256 * G>(p.zero_after, p.zero_n);
-
-  int ct, tt;
-  if (!p.order.tile(blockIdx.x, &ct, &tt)) return;
-  const int t0 = tt * (16 * MTB);
-  if (ct >= p.dead_ct) ct += p.dead_gap;
-  const TileBin* bin = p.bins + ct * 4 + wave;
-  const v4i pos = cload(&bin->pos, 0), spos = cload(&bin->spos, 0), rb = cload(&bin->rb, 0), info = cload(&bin->info, 0);
+  if (!mine) return;
   const int m = info[0], ends = info[1], ups = info[2];   // member; items that end a row block (and, << 4, that have codes); items of an up block
   const bool active = info[3] & 1;
   const int tile_items = info[3] >> 1;                    // items that any bin of the tile multiplies: 4, 3 or none
 
   // ---- load cursor: the stage requested next
-  const int n_all = p.nks / SK, n_max = (n_all + G - 1) / G;   // stages of the tile, of a group
+  const int n_all = a_nks / SK, n_max = (n_all + G - 1) / G;   // stages of the tile, of a group
   const int s0 = grp * n_max, n_stage = G == 1 ? n_all : max(0, min(n_max, n_all - s0));
   const int tg = t0 + grp * (16 * MB);                         // first token that this group finishes
-  const int64_t rb_bytes = (int64_t)p.nks * 8 * BITS * 16;   // packed codes of a row block
+  const int64_t rb_bytes = (int64_t)a_nks * 8 * BITS * 16;   // packed codes of a row block
   const int xb = wave * XC / SK, xj = wave * XC - xb * SK;   // this wave's fragments: token block, first 64-k step
   // activations come through a buffer resource of the tile's fragments (of the whole image, CONV): base in scalar registers, a
   // lane's offset that does not change and the stage's offset in a scalar register
   const __amdgpu_buffer_rsrc_t l_x = __builtin_amdgcn_make_buffer_rsrc(
-      CONV ? (void*)p.cq8 : (void*)(p.qx + (int64_t)m * p.qx_mstride + (int64_t)(t0 / 16) * p.nks * 1024), 0,
-      CONV ? p.cbytes : (unsigned)(min(MTB, (p.T_pad - t0) / 16) * p.nks * 1024), 0x00020000);
-  unsigned l_xlane = (unsigned)(xb * p.nks + xj + s0 * SK) * 1024 + lane * 16;
+      CONV ? (void*)p.cq8 : (void*)(p.qx + (int64_t)m * p.qx_mstride + (int64_t)(t0 / 16) * a_nks * 1024), 0,
+      CONV ? p.cbytes : (unsigned)(min(MTB, (p.T_pad - t0) / 16) * a_nks * 1024), 0x00020000);
+  unsigned l_xlane = (unsigned)(xb * a_nks + xj + s0 * SK) * 1024 + lane * 16;
   unsigned l_xoff = 0;
   const uint8_t* l_wb[4];
   __amdgpu_buffer_rsrc_t l_w[4];   // groups: a resource of each item's codes, up to the end of the group's part
   unsigned l_woff = s0 * (WN * 1024) + lane * 16;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const uint8_t* c = p.codes + pos[r] * rb_bytes;
+    const uint8_t* c = a_codes + pos[r] * rb_bytes;
     if constexpr (DP == 1) l_wb[r] = c;
     else l_w[r] = __builtin_amdgcn_make_buffer_rsrc((void*)c, 0, (unsigned)((s0 + n_stage) * WN * 1024), 0x00020000);
   }
@@ -576,6 +579,8 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const BinsPara
   }
 }
 
+#define PIPE_BINS_ARGS p.bins, p.codes, p.order.n_ct, p.order.n_tt, p.order.strip, p.order.toks, p.dead_ct, p.dead_gap, p.nks, p
+
 template <int BITS, int MTB, int MINW, int G = 1, int DP = G>
 int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t ev1, hipStream_t st) {
   const int n_tt = ceil_div(p.T, 16 * MTB);
@@ -598,35 +603,35 @@ int launch_cfg(BinsParams& p, int live_ct, int n_ct, hipEvent_t ev0, hipEvent_t 
   if constexpr (MTB == 4 && MINW == 4 && DP == 1) {
     if (p.cq8 != nullptr) return PIPE_EINVAL;
     if (chain && p.res == nullptr) {
-      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_RELU, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_RELU, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
       PIPE_HIP(hipGetLastError());
       return PIPE_OK;
     }
     if (chain) {
-      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
       PIPE_HIP(hipGetLastError());
       return PIPE_OK;
     }
   } else {
     if (p.cq8 != nullptr) {
-      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, true, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
       PIPE_HIP(hipGetLastError());
       return PIPE_OK;
     }
     if (chain) {
-      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+      PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_CHAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
       PIPE_HIP(hipGetLastError());
       return PIPE_OK;
     }
   }
   if (p.later) {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_SUM, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_SUM, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
   } else if (act == PIPE_ACT_GELU) {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GELU, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GELU, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
   } else if (act == PIPE_ACT_SILU_GATED) {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GATED, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_GATED, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
   } else {
-    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, p);
+    PIPE_LAUNCH((gemm_bins_kernel<BITS, MTB, MINW, MODE_PLAIN, false, G, DP>), grid, dim3(256 * G), st, ev0, ev1, PIPE_BINS_ARGS);
   }
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
