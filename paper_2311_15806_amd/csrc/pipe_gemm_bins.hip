@@ -336,6 +336,7 @@ __global__ __launch_bounds__(256 * G, MINW) void gemm_bins_kernel(const TileBin*
   // ---- the walk along k with the first NI items of every bin of the tile
   auto walk = [&](auto ni) __attribute__((always_inline)) {
     constexpr int NI = decltype(ni)::value;
+    asm volatile("; %0 items" ::"i"(NI));   // keeps the walks apart: what they request first would be requested before the branch between them
     constexpr int AHEAD = (DP - 1) * (NI * WN + XC);   // loads in flight behind those of the next stage
     Codes<BITS, SK> w0[NI], w1[NI], w2[DP > 1 ? NI : 1];
     request(w0, xs0);
