@@ -464,7 +464,7 @@ int pipe_first_predictor_size(const double* norms, const double* lam, int L, int
                               double logit_norm, double ratio, int* K1_out);
 
 /* Kernel selection for pipe_forward / pipe_mlp_forward (tuning and tests):
- * 0 = automatic by token count, 1 = tiled MFMA kernel, 2 = weight-streaming
+ * 0 = automatic by tokens and layer, 1 = tiled MFMA kernel, 2 = weight-streaming
  * small-batch kernel.  Returns PIPE_EINVAL for other values.                    */
 int pipe_set_kernel(int which);
 

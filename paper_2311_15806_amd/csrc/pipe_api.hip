@@ -792,10 +792,73 @@ const TileBins* pipe_get_bins(const pipe_expansion* ce, const GemmArgs& a, int* 
 }
 
 // ------------------------------------------------------------------ forward
+// This call's 17 to 128 tokens go to the tiled kernels (see routed)
+static thread_local bool t_tiled = false;
+constexpr int STREAM_ONLY_T = 16;   // batches that stream whatever the layer
+
 static bool use_stream_kernel(const pipe_expansion* e, int T, bool acc_out = false) {
   if (g_kernel_choice == 1) return false;
   if (e->K > 4 && acc_out) return false;   // bins of more than 4 items have no integer export
-  return T <= PIPE_STREAM_MAX_T;
+  return T <= PIPE_STREAM_MAX_T && !(t_tiled && T > STREAM_ONLY_T);
+}
+
+// Runs a call whose 17 to 128 tokens the tiled kernels serve faster with those; where their schedules or scratch are not there (under
+// capture, or for want of memory), with the streaming kernel, which needs neither.  Both give the same bits.  A call fails for these
+// reasons before it has launched anything.
+template <class Call>
+static int routed(bool tiled, Call call) {
+  if (tiled) {
+    struct Route {
+      Route() { t_tiled = true; }
+      ~Route() { t_tiled = false; }
+    } route;
+    const int rc = call();
+    if (rc != PIPE_ENOTREADY && rc != PIPE_ENOMEM && rc != PIPE_EDEVICE) return rc;
+  }
+  return call();
+}
+
+// Where 17 to 128 tokens are tiled: the streaming kernel runs a workgroup per bin and 16 tokens, each along the whole of k, the tiled one walks along k
+// once for up to 64.  A walk costs about what 400 such workgroups do; at 8 and 2 bits a step of a long walk costs more beside them.  Calls, us, streamed / tiled:
+//   11008 x 4096 4 bit, K = 4, half kept, 20 tokens 25.9 / 20.6, 64 36.7 / 22.6, 128 59.0 / 28.9; ternary 32 19.8 / 17.2, 128 39.6 / 23.9;
+//   4096 x 4096 4 bit 32 tokens 16.3 / 16.3, 64 20.0 / 16.6; ternary 64 16.0 / 16.9, 96 19.6 / 17.2; 8 bit, K = 2 64 19.0 / 20.3, 96 21.5 / 20.7;
+//   4096 x 11008 4 bit 32 tokens 24.1 / 27.1, 48 28.9 / 27.2; ternary 96 27.5 / 30.1, 128 32.5 / 30.6; 8 bit 96 38.8 / 39.4, 128 46.0 / 40.1;
+//   3072 x 768 4 bit 48 tokens 11.9 / 13.8, 96 18.5 / 13.9; 2048 x 2048 ternary 64 13.6 / 14.0, 128 14.9 / 13.8; 768 x 3072 never (4 bit, 128 15.4 / 15.8).
+static bool linear_tiled(const pipe_expansion* e, int T, int M, int reduce_members) {
+  if (!e || g_kernel_choice != 0 || T <= STREAM_ONLY_T || T > PIPE_STREAM_MAX_T || e->bin_cap != 4 || (M > 1 && !reduce_members)) return false;
+  return 2 * (int64_t)e->n_bins * ceil_div(T, 16) >= 800 + (e->bits == 4 ? 0 : (e->bits == 8 ? 6 : 5)) * e->nks;
+}
+
+static bool single_order(const int* split, int M) {
+  for (int m = 0; split != nullptr && M > 1 && m < M; ++m)
+    if (split[m] == 1) return true;
+  return false;
+}
+
+// The same for a two-layer MLP (a gated one also saves the launch that multiplies SiLU(gate) into up; the sum over members of a single
+// order runs pass by pass).  Calls, us, streamed / tiled:
+//   gated, one member: 2048-5504-2048 4 bit, K = 3, 64 tokens 42.1 / 40.1, 100 58.1 / 43.7; 4096-11008 64 82.3 / 84.2, 100 121 / 96; ternary 64 63.7 / 72.6, 100 93 / 80;
+//   two of two orders: 4096-11008 4 bit 36 tokens 102 / 104, 64 124 / 106, 128 210 / 114; of 2 and 1: 64 96 / 119, 100 140 / 125;
+//   GELU, one member: 768-3072 4 bit, K = 3, 64 tokens 23.5 / 26.7, 100 30.4 / 27.6; two of two orders: 1024-4096 100 43.8 / 41.1, 768-3072 100 37.7 / 38.1;
+//   of 2 and 1: 128 34.0 / 44.9.
+static bool mlp_tiled(const pipe_expansion* l1, const pipe_expansion* l2, int act, int T, const int* split, int M) {
+  if (!l1 || !l2 || g_kernel_choice != 0 || T > PIPE_STREAM_MAX_T || M > 2 || l1->bin_cap != 4 || l2->bin_cap != 4 || l1->bits == 8 || l2->bits == 8) return false;
+  const bool two = split != nullptr && M == 2, one_order = single_order(split, M);
+  if (act == PIPE_ACT_SILU_GATED) return l1->n_rb % 2 == 0 && T > (two ? (one_order ? 96 : 48) : 64);
+  return T > 64 && (!two || (!one_order && l2->nks >= 64));
+}
+
+// ... and for a chain of fully-connected layers, whose members hold at most 4 orders: six layers of 2048 x 2048, us, streamed / tiled:
+// ternary, two members of 2 orders, 64 tokens 96.6 / 90.5, 100 130 / 94 (1024 wide 69.4 / 75.0, 93 / 77); 4 bit, one of 4, 64 73.0 / 73.8, 100 96 / 76;
+// two of 4 (bins of 8: streamed in two chunks), 64 146 / 100, 128 198 / 111; one of 8 (pass by pass) 112 / 203.
+static bool chain_tiled(const pipe_chain_layer* layers, int L, int T, const int* split, int M) {
+  if (!layers || L < 1 || g_kernel_choice != 0 || T <= 48 || T > PIPE_STREAM_MAX_T || M > 2) return false;
+  for (int l = 0; l < L; ++l) {
+    const pipe_expansion* e = layers[l].e;
+    if (!e || e->bits == 8 || layers[l].kh != 0) return false;
+    if (split == nullptr || M < 2 ? e->K > 4 : (split[0] > 4 || split[1] > 4)) return false;
+  }
+  return T > (layers[0].e->K > 4 ? 48 : 64);
 }
 
 struct ActBuffers {
@@ -890,9 +953,20 @@ static bool fuse_decode_quant(const pipe_expansion* e, int T, const float* x_dev
          e->in % 4 == 0 && (x0 & 15) == 0 && e->bin_cap == 4 && apart;
 }
 
-static int quantize_input(const float* x_dev, int T, int in, int in_pad, float s_x, const ActBuffers& b, bool small,
+// One launch, in which every token's workgroup scans the whole input for the maximum, or two: from 128 Ki elements on, from 64 Ki where the contraction is
+// long enough that the third launch of a call is not what it waits for (768 x 3072, 60 tokens 15.9 -> 14.3 us; 4096 x 4096 8 bit, 48 tokens
+// 22.6 -> 19.0, 20 17.5 -> 16.8; 4096 x 11008, 64 49.4 -> 29.6; but 768 x 3072, 24 12.5 -> 14.4, 2048 x 2048, 34
+// 13.8 -> 14.9: the third launch is then what the call waits for).
+static bool quantize_in_one(const pipe_expansion* e, int T, float s_x) {
+  if (T > PIPE_QUANT1_MAX_T) return false;
+  const int64_t n = (int64_t)T * e->in;
+  return s_x > 0.f || n <= 65536 || (n <= 131072 && (int64_t)e->n_bins * ceil_div(T, 16) * e->nks <= 12288);
+}
+
+static int quantize_input(const pipe_expansion* e, const float* x_dev, int T, float s_x, const ActBuffers& b, bool small,
                           int8_t* qx_rowmajor, float* scale_out, hipStream_t st) {
-  if (small && T <= PIPE_QUANT1_MAX_T)
+  const int in = e->in, in_pad = e->in_pad;
+  if (small && quantize_in_one(e, T, s_x))
     return launch_quantize_small(x_dev, 0, 1, T, in, in_pad, s_x, nullptr, b.qx, 0, b.rowsum, qx_rowmajor, scale_out, st);
   // The reduction kernel also clears the code sums, so a dynamic scale costs two launches and no memset.
   const bool dynamic = !(s_x > 0.f);
@@ -935,9 +1009,8 @@ static void fill_members(GemmArgs& a, int M, const int* lo, const int* hi) {
   for (int m = 0; m < M; ++m) { a.member_lo[m] = lo[m]; a.member_hi[m] = hi[m]; }
 }
 
-extern "C" int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, float s_x,
-                            const int* split, int M, const float* bias_dev, int reduce_members,
-                            float* y_dev, void* stream) {
+static int forward_impl(const pipe_expansion* e, const float* x_dev, int T, float s_x, const int* split, int M, const float* bias_dev,
+                        int reduce_members, float* y_dev, void* stream) {
   if (!e || T < 0) return PIPE_EINVAL;
   if (e->conv_C > 0) return PIPE_EINVAL;   // stored tap-major: only the convolution entry points read it
   int lo[PIPE_MAX_K], hi[PIPE_MAX_K], Mm = 1;
@@ -954,7 +1027,7 @@ extern "C" int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, 
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   const bool fused = fuse_decode_quant(e, T, x_dev, small, y_dev, (size_t)(reduce_members ? 1 : Mm) * T * e->out);
   if (!fused) {
-    rc = quantize_input(x_dev, T, e->in, e->in_pad, s_x, b, small, nullptr, b.scale, st);
+    rc = quantize_input(e, x_dev, T, s_x, b, small, nullptr, b.scale, st);
     if (rc) return rc;
   }
   GemmArgs a{};
@@ -965,6 +1038,13 @@ extern "C" int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, 
   fill_members(a, Mm, lo, hi);
   rc = run_gemm(a, small, st);
   return rc;
+}
+
+extern "C" int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, float s_x,
+                            const int* split, int M, const float* bias_dev, int reduce_members,
+                            float* y_dev, void* stream) {
+  return routed(linear_tiled(e, T, M, reduce_members),
+                [&]() { return forward_impl(e, x_dev, T, s_x, split, M, bias_dev, reduce_members, y_dev, stream); });
 }
 
 extern "C" int pipe_prepare(const pipe_expansion* e, const int* split, int M, int T_max, void* stream) {
@@ -978,6 +1058,8 @@ extern "C" int pipe_prepare(const pipe_expansion* e, const int* split, int M, in
   int rc = pipe_forward(e, fake_x, T_max, 1.f, split, M, nullptr, 1, fake_y, stream);
   if (rc == PIPE_OK && T_max > PIPE_STREAM_MAX_T + 1)
     rc = pipe_forward(e, fake_x, PIPE_STREAM_MAX_T + 1, 1.f, split, M, nullptr, 1, fake_y, stream);
+  if (rc == PIPE_OK && T_max <= PIPE_STREAM_MAX_T)   // fewer tokens may stream where T_max do not
+    rc = forward_impl(e, fake_x, T_max, 1.f, split, M, nullptr, 1, fake_y, stream);
   return rc;
 }
 
@@ -995,7 +1077,7 @@ extern "C" int pipe_forward_acc(const pipe_expansion* e, const float* x_dev, int
   if (rc) return rc;
   int lo = 0, hi = e->K - 1;
   if (acc_dev && !small && (rc = ensure_tables(e, 1, &lo, &hi, 2)) != PIPE_OK) return rc;
-  rc = quantize_input(x_dev, T, e->in, e->in_pad, s_x, b, small, qx_dev, b.scale, st);
+  rc = quantize_input(e, x_dev, T, s_x, b, small, qx_dev, b.scale, st);
   if (rc) return rc;
   if (s_x_out_dev) PIPE_HIP(hipMemcpyAsync(s_x_out_dev, b.scale, sizeof(float), hipMemcpyDeviceToDevice, st));
   if (!acc_dev) return PIPE_OK;
@@ -1067,7 +1149,7 @@ extern "C" int pipe_forward_noalloc(const pipe_expansion* e, const float* x_dev,
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   const bool fused = fuse_decode_quant(e, T, x_dev, small, y_dev, (size_t)(reduce_members ? 1 : Mm) * T * e->out);
   if (!fused) {
-    rc = quantize_input(x_dev, T, e->in, e->in_pad, s_x, b, small, nullptr, b.scale, st);
+    rc = quantize_input(e, x_dev, T, s_x, b, small, nullptr, b.scale, st);
     if (rc) return rc;
   }
   GemmArgs a{};
@@ -1158,8 +1240,8 @@ static int asym_quantize(const pipe_expansion* e, const float* x_dev, int T, con
   return rc;
 }
 
-extern "C" int pipe_forward_asymmetric(const pipe_expansion* e, const float* x_dev, int T, const int* split, int M,
-                                       const float* bias_dev, float* y_dev, void* stream) {
+static int forward_asym_impl(const pipe_expansion* e, const float* x_dev, int T, const int* split, int M,
+                             const float* bias_dev, float* y_dev, void* stream) {
   if (!e || T < 0) return PIPE_EINVAL;
   if (e->conv_C > 0) return PIPE_EINVAL;   // stored tap-major: only the convolution entry points read it
   int lo[PIPE_MAX_K], hi[PIPE_MAX_K], Mm = 1;
@@ -1185,6 +1267,11 @@ extern "C" int pipe_forward_asymmetric(const pipe_expansion* e, const float* x_d
   a.y = y_dev; a.acc_out = nullptr; a.amax_out = nullptr;
   fill_members(a, Mm, lo, hi);
   return run_gemm(a, small, st);
+}
+
+extern "C" int pipe_forward_asymmetric(const pipe_expansion* e, const float* x_dev, int T, const int* split, int M,
+                                       const float* bias_dev, float* y_dev, void* stream) {
+  return routed(linear_tiled(e, T, M, 1), [&]() { return forward_asym_impl(e, x_dev, T, split, M, bias_dev, y_dev, stream); });
 }
 
 extern "C" int pipe_forward_conv2d_asymmetric(const pipe_expansion* e, const float* x_dev, int N, int C, int H, int W,
@@ -1595,7 +1682,7 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
 
   const bool fused = fuse_decode_quant(l1, T, x_dev, small, h, (size_t)Mm * T * H);
   if (!fused) {
-    rc = quantize_input(x_dev, T, l1->in, l1->in_pad, s_x, b, small, nullptr, b.scale, st);
+    rc = quantize_input(l1, x_dev, T, s_x, b, small, nullptr, b.scale, st);
     if (rc) return rc;
   }
   // The members' max|h| slots are zero on entry: cleared when the workspace is allocated and,
@@ -1766,7 +1853,9 @@ extern "C" int pipe_mlp_forward(const pipe_expansion* l1, const pipe_expansion* 
                                 const float* x_dev, int T, float s_x, const int* split, int M,
                                 const float* bias1_dev, const float* bias2_dev, float* h_dev,
                                 float* y_dev, void* stream) {
-  return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, nullptr, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream);
+  return routed(mlp_tiled(l1, l2, act, T, split, M), [&]() {
+    return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, nullptr, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream);
+  });
 }
 
 extern "C" int pipe_mlp_forward_given_scales(const pipe_expansion* l1, const pipe_expansion* l2, int act,
@@ -1774,7 +1863,9 @@ extern "C" int pipe_mlp_forward_given_scales(const pipe_expansion* l1, const pip
                                              int M, const float* bias1_dev, const float* bias2_dev, float* h_dev,
                                              float* y_dev, void* stream) {
   if (!(s_x > 0.f) || s_h_host == nullptr) return PIPE_EINVAL;
-  return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, s_h_host, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream);
+  return routed(mlp_tiled(l1, l2, act, T, split, M), [&]() {
+    return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, s_h_host, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream);
+  });
 }
 
 extern "C" int pipe_prepare_mlp(const pipe_expansion* l1, const pipe_expansion* l2, int act, const int* split, int M,
@@ -1786,6 +1877,8 @@ extern "C" int pipe_prepare_mlp(const pipe_expansion* l1, const pipe_expansion* 
   int rc = pipe_mlp_forward(l1, l2, act, fake_x, T_max, 1.f, split, M, nullptr, nullptr, nullptr, fake_y, stream);
   if (rc == PIPE_OK && T_max > PIPE_STREAM_MAX_T + 1)
     rc = pipe_mlp_forward(l1, l2, act, fake_x, PIPE_STREAM_MAX_T + 1, 1.f, split, M, nullptr, nullptr, nullptr, fake_y, stream);
+  if (rc == PIPE_OK && T_max <= PIPE_STREAM_MAX_T)   // fewer tokens may stream where T_max do not
+    rc = mlp_forward_impl(l1, l2, act, fake_x, T_max, 1.f, nullptr, split, M, nullptr, nullptr, nullptr, fake_y, stream);
   return rc;
 }
 
@@ -1956,7 +2049,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
         rc = launch_quantize_im2col(x_dev, N, Cin[0], Hin[0], Win[0], ly.kh, ly.kw, ly.stride, ly.pad, 1, Hin[1], Win[1],
                                     e->in_pad, T_pad, s_x, input_max(b, Tin[0] * Cin[0]), q8, b.qx, b.rowsum, b.scale, st);
       } else {
-        rc = quantize_input(x_dev, T, e->in, e->in_pad, s_x, b, small[0], nullptr, b.scale, st);
+        rc = quantize_input(e, x_dev, T, s_x, b, small[0], nullptr, b.scale, st);
       }
       if (rc) return rc;
       a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;
@@ -2033,13 +2126,15 @@ extern "C" int pipe_chain_forward(const pipe_chain_layer* layers, int L, const f
   if (!layers || L < 1 || T < 0) return PIPE_EINVAL;
   for (int l = 0; l < L; ++l)
     if (layers[l].kh != 0 || layers[l].kw != 0) return PIPE_EINVAL;   // convolution layers need the grid: pipe_chain_forward_conv
-  return chain_forward_grid(layers, L, x_dev, T, 1, 1, s_x, split, M, acts_dev, y_dev, stream);
+  return routed(chain_tiled(layers, L, T, split, M),
+                [&]() { return chain_forward_grid(layers, L, x_dev, T, 1, 1, s_x, split, M, acts_dev, y_dev, stream); });
 }
 
 extern "C" int pipe_chain_forward_conv(const pipe_chain_layer* layers, int L, const float* x_dev, int N, int H, int W,
                                        float s_x, const int* split, int M, float* const* acts_dev, float* y_dev,
                                        void* stream) {
-  return chain_forward_grid(layers, L, x_dev, N, H, W, s_x, split, M, acts_dev, y_dev, stream);
+  return routed(H == 1 && W == 1 && chain_tiled(layers, L, N, split, M),
+                [&]() { return chain_forward_grid(layers, L, x_dev, N, H, W, s_x, split, M, acts_dev, y_dev, stream); });
 }
 
 // Member chains with asymmetric activation codes (Sec. 4.3): the same driver as above for fully-connected
@@ -2227,5 +2322,8 @@ extern "C" int pipe_prepare_chain(const pipe_chain_layer* layers, int L, int N, 
   DryScope dry;
   const float* fake_x = reinterpret_cast<const float*>(uintptr_t(256));
   float* fake_y = reinterpret_cast<float*>(uintptr_t(512));
-  return chain_forward_grid(layers, L, fake_x, N, H, W, 1.f, split, M, nullptr, fake_y, stream);
+  int rc = routed(H == 1 && W == 1 && chain_tiled(layers, L, N, split, M),
+                  [&]() { return chain_forward_grid(layers, L, fake_x, N, H, W, 1.f, split, M, nullptr, fake_y, stream); });
+  if (rc == PIPE_OK) rc = chain_forward_grid(layers, L, fake_x, N, H, W, 1.f, split, M, nullptr, fake_y, stream);   // fewer tokens may stream where N do not
+  return rc;
 }

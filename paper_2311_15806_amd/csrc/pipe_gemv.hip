@@ -1,4 +1,4 @@
-// Weight-streaming kernel of the expanded layer for decode-sized batches (T <= 128), where the
+// Weight-streaming kernel of the expanded layer for decode-sized batches (T <= 16, and up to 128 where the dispatch finds it faster), where the
 // path is bound by reading the packed codes from HBM once (App. B, Eq. (define_dre), same
 // arithmetic as the tiled kernel).
 //

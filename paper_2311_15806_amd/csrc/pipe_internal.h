@@ -42,13 +42,13 @@ static inline int64_t round_up64(int64_t a, int64_t b) { return (a + b - 1) / b 
 // hold every order of n_out output row blocks (items of one output row block are adjacent and
 // in ascending order k).
 constexpr int STREAM_BIN_CAP = 16;
-constexpr int PIPE_STREAM_MAX_T = 128;   // the weight-streaming kernel serves up to this many tokens
+constexpr int PIPE_STREAM_MAX_T = 128;   // the weight-streaming kernel serves up to this many tokens (of 17 and more only where it is the faster one, see the rules at routed)
 // The streaming kernel quantizes small batches itself (one launch instead of two): every workgroup repeats the work, which
 // pays up to 4096 codes (a token counts in_features rounded up to 256) in up to 1024 bins of the layer, and for a single token up to
 // 8192 codes.  Two launches against one: 2 tokens of 4096 14.6 and 14.8 us a call; 16 tokens of 256 into 32000 channels, two 8-bit orders
 // (1000 bins) 14.1 and 13.7, into 50000 (1563 bins) 19.9 and 20.7, into 100000 31.0 and 36.0.
 constexpr int PIPE_FUSED_QUANT_MAX = 4096, PIPE_FUSED_QUANT_MAX_1 = 8192, PIPE_FUSED_QUANT_BINS = 1024;
-constexpr int PIPE_QUANT1_MAX_T = 64;    // the one-launch quantizer (every token's workgroup scans the whole input for the maximum) up to this many
+constexpr int PIPE_QUANT1_MAX_T = 64;    // the one-launch quantizer (every token's workgroup scans the whole input for the maximum) up to this many; larger inputs take two (quantize_in_one)
 constexpr int PIPE_MAX_SPLIT = 8;   // workgroups per bin of the weight-streaming kernel, at most
 struct StreamBin {
   int32_t n_items, n_out;

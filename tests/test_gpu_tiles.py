@@ -353,3 +353,54 @@ def test_infinite_member_scale_leaves_pruned_row_blocks(pipe, bits, out, hidden,
     assert torch.equal(infinite[:, rows], finite[:, rows])
     assert not bool(torch.isfinite(infinite[:, ~rows]).any())      # (codes of zero times infinity)
     l1.free(), l2.free()
+
+
+@pytest.mark.parametrize("kind,T", [("linear", 17), ("linear", 64), ("linear", 65), ("linear", 128), ("asymmetric", 40), ("gelu", 64), ("gelu", 65),
+                                    ("gated", 48), ("gated", 49), ("gated21", 97), ("chain", 65), ("chain8", 49)])
+def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
+    """Calls that the tiled kernels serve by rule, against the streaming kernel, bit for bit; and captured where only the streaming kernel is
+    ready (its scratch, no tile schedules), replayed with other inputs."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    mk = lambda o, i, bits, K, group=16: pipe.pipe_expand(torch.randn(o, i, generator=g, device="cuda") * (1.5 / i ** 0.5), bits, K, 0.5, group)
+    xs = [torch.randn(T, 320, generator=g, device="cuda") * s for s in (1.0, 3.0)]
+    x = xs[0].clone()
+    if kind in ("linear", "asymmetric"):
+        es = [mk(8192, 320, 4, 4)]          # 320 bins: 17 tokens are past the line
+        call = (lambda: pipe.pipe_forward(es[0], x)) if kind == "linear" else (lambda: pipe.pipe_forward_asymmetric(es[0], x))
+    elif kind in ("gelu", "gated", "gated21"):
+        up = 2 if kind != "gelu" else 1
+        K, split = {"gelu": (3, None), "gated": (4, [2, 2]), "gated21": (3, [2, 1])}[kind]
+        es = [mk(up * 1088, 320, 4, K), mk(320, 1088, 4, K)]
+        act = pipe.PIPE_ACT_GELU if kind == "gelu" else pipe.PIPE_ACT_SILU_GATED
+        call = lambda: pipe.pipe_mlp_forward(es[0], es[1], act, x, split=split)
+    else:
+        K, split = (4, [2, 2]) if kind == "chain" else (8, [4, 4])
+        es = [mk(320, 320, 2, K) for _ in range(3)]
+        layers = [(es[0], None, 3, -1, True), (es[1], None, 3, 1, True), (es[2], None, 0, -1, True)]
+        call = lambda: pipe.pipe_chain_forward(layers, x, split=split)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    pipe.pipe_set_kernel(2)
+    try:
+        with torch.cuda.stream(side):       # sizes the streaming kernel's scratch there
+            streamed = []
+            for v in xs:
+                x.copy_(v)
+                streamed.append(call().clone())
+    finally:
+        pipe.pipe_set_kernel(0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        out = call()
+    for rep in range(4):
+        x.copy_(xs[rep % 2])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, streamed[rep % 2]), rep
+    for v, want in zip(xs, streamed):       # eager: the rule's route
+        x.copy_(v)
+        assert torch.equal(call(), want)
+    for e in es:
+        e.free()

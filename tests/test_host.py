@@ -244,11 +244,46 @@ def a_sum_over_two_members_is_a_launch_each(rt):
     assert launches(1040, 2816, 4, [2, 2], 300, ()) == ([2], 1)               # 44 steps
 
 
+def unprepared_batches_stream(rt):
+    """17 to 128 tokens of a layer that the tiled kernel serves by rule: where an allocation of its schedule fails, or under capture without
+    one, the streaming kernel runs, once; a prepared layer is captured tiled."""
+    def kernels():
+        names = rt.names()
+        return sum("gemm_stream_kernel" in n for n in names), sum("gemm_bins_kernel" in n for n in names)
+
+    e = rt.expand(8192, 320, 4, 2, 1.0, 16)
+    assert _linear(rt, e, 16) == 0 and kernels() == (1, 0)
+    assert _linear(rt, e, 200) == 0 and kernels() == (0, 1)                       # this stream's scratch is there
+    for nth in range(1, 9):
+        e = rt.expand(8192, 320, 4, 2, 1.0, 16)
+        rt.names()
+        rt.host.host_fail(nth)
+        assert _linear(rt, e, 64) == 0
+        rt.host.host_fail(0)
+        first = kernels()
+        assert first in ((1, 0), (0, 1))
+        assert _linear(rt, e, 64) == 0 and kernels() == (0, 1)
+        if first == (0, 1):
+            break
+    assert 2 <= nth < 8
+    e = rt.expand(8192, 320, 4, 2, 1.0, 16)
+    rt.names()
+    rt.host.host_capture(1)
+    assert _linear(rt, e, 64) == 0 and kernels() == (1, 0)
+    assert _linear(rt, e, 200) == ENOTREADY and kernels() == (0, 0)
+    rt.host.host_capture(0)
+    rt.lib.pipe_prepare.argtypes = [C.c_void_p] * 2 + [C.c_int] * 2 + [C.c_void_p]
+    assert rt.lib.pipe_prepare(e, None, 0, 128, None) == 0 and kernels() == (0, 0)
+    rt.host.host_capture(1)
+    assert _linear(rt, e, 64) == 0 and kernels() == (0, 1)
+    rt.host.host_capture(0)
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
                                       "any_number_of_images_is_served", "wide_layers_quantize_once",
                                       "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave",
-                                      "a_sum_over_two_members_is_a_launch_each"])
+                                      "a_sum_over_two_members_is_a_launch_each", "unprepared_batches_stream"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
