@@ -22,7 +22,7 @@ SOURCES = [
     ("pipe_quant.hip", ["-ffp-contract=off"] + PRELOAD),
     ("pipe_gemm.hip", []),
     ("pipe_gemm_bins.hip", PRELOAD),
-    ("pipe_gemv.hip", []),
+    ("pipe_gemv.hip", PRELOAD),
     ("pipe_resident.hip", []),
     ("pipe_probe.hip", []),
     ("pipe_diag.hip", ["-ffp-contract=off"]),

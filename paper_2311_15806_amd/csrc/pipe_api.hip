@@ -963,10 +963,10 @@ static bool quantize_in_one(const pipe_expansion* e, int T, float s_x) {
   return s_x > 0.f || n <= 65536 || (n <= 131072 && (int64_t)e->n_bins * ceil_div(T, 16) * e->nks <= 12288);
 }
 
-static int quantize_input(const pipe_expansion* e, const float* x_dev, int T, float s_x, const ActBuffers& b, bool small,
+static int quantize_input(const pipe_expansion* e, const float* x_dev, int T, float s_x, const ActBuffers& b,
                           int8_t* qx_rowmajor, float* scale_out, hipStream_t st) {
   const int in = e->in, in_pad = e->in_pad;
-  if (small && quantize_in_one(e, T, s_x))
+  if (quantize_in_one(e, T, s_x))   // (a tile reads behind the last 16 tokens what was there before, and stores nothing of it)
     return launch_quantize_small(x_dev, 0, 1, T, in, in_pad, s_x, nullptr, b.qx, 0, b.rowsum, qx_rowmajor, scale_out, st);
   // The reduction kernel also clears the code sums, so a dynamic scale costs two launches and no memset.
   const bool dynamic = !(s_x > 0.f);
@@ -1027,7 +1027,7 @@ static int forward_impl(const pipe_expansion* e, const float* x_dev, int T, floa
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   const bool fused = fuse_decode_quant(e, T, x_dev, small, y_dev, (size_t)(reduce_members ? 1 : Mm) * T * e->out);
   if (!fused) {
-    rc = quantize_input(e, x_dev, T, s_x, b, small, nullptr, b.scale, st);
+    rc = quantize_input(e, x_dev, T, s_x, b, nullptr, b.scale, st);
     if (rc) return rc;
   }
   GemmArgs a{};
@@ -1077,7 +1077,7 @@ extern "C" int pipe_forward_acc(const pipe_expansion* e, const float* x_dev, int
   if (rc) return rc;
   int lo = 0, hi = e->K - 1;
   if (acc_dev && !small && (rc = ensure_tables(e, 1, &lo, &hi, 2)) != PIPE_OK) return rc;
-  rc = quantize_input(e, x_dev, T, s_x, b, small, qx_dev, b.scale, st);
+  rc = quantize_input(e, x_dev, T, s_x, b, qx_dev, b.scale, st);
   if (rc) return rc;
   if (s_x_out_dev) PIPE_HIP(hipMemcpyAsync(s_x_out_dev, b.scale, sizeof(float), hipMemcpyDeviceToDevice, st));
   if (!acc_dev) return PIPE_OK;
@@ -1149,7 +1149,7 @@ extern "C" int pipe_forward_noalloc(const pipe_expansion* e, const float* x_dev,
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   const bool fused = fuse_decode_quant(e, T, x_dev, small, y_dev, (size_t)(reduce_members ? 1 : Mm) * T * e->out);
   if (!fused) {
-    rc = quantize_input(e, x_dev, T, s_x, b, small, nullptr, b.scale, st);
+    rc = quantize_input(e, x_dev, T, s_x, b, nullptr, b.scale, st);
     if (rc) return rc;
   }
   GemmArgs a{};
@@ -1682,7 +1682,7 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
 
   const bool fused = fuse_decode_quant(l1, T, x_dev, small, h, (size_t)Mm * T * H);
   if (!fused) {
-    rc = quantize_input(l1, x_dev, T, s_x, b, small, nullptr, b.scale, st);
+    rc = quantize_input(l1, x_dev, T, s_x, b, nullptr, b.scale, st);
     if (rc) return rc;
   }
   // The members' max|h| slots are zero on entry: cleared when the workspace is allocated and,
@@ -2049,7 +2049,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
         rc = launch_quantize_im2col(x_dev, N, Cin[0], Hin[0], Win[0], ly.kh, ly.kw, ly.stride, ly.pad, 1, Hin[1], Win[1],
                                     e->in_pad, T_pad, s_x, input_max(b, Tin[0] * Cin[0]), q8, b.qx, b.rowsum, b.scale, st);
       } else {
-        rc = quantize_input(e, x_dev, T, s_x, b, small[0], nullptr, b.scale, st);
+        rc = quantize_input(e, x_dev, T, s_x, b, nullptr, b.scale, st);
       }
       if (rc) return rc;
       a.qx = b.qx; a.rowsum = b.rowsum; a.s_x = b.scale;

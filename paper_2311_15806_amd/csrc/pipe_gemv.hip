@@ -15,7 +15,7 @@
 // token block, on the same XCD, so that the bin still comes from HBM once.  Expansions with more
 // than 4 orders have bins of 8, 12 or 16 items: gemm_stream_multi_kernel streams them four at a
 // time and keeps the integer tiles of the whole bin in LDS for one epilogue.
-#include "pipe_internal.h"
+#include "pipe_codes.h"
 
 #include <algorithm>
 
@@ -24,6 +24,8 @@ int g_stream_ksplit = 0;   // 0: automatic
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int R = 4;  // items processed concurrently by a wave (independent load streams)
 
@@ -55,25 +57,21 @@ struct StreamParams {
   int n_tb;                // 16-token blocks: one workgroup per (bin, k share, token block)
   int n_bins;
   int thr0, thr1, thr2;    // bins of 4, fullest first: how many hold 4, at least 3, at least 2 items
-  int zero_pos;            // an all-zero position (codes and scales): read for the items a bin does not have
   const float* x_f32;      // QFUSE: the fp32 input [T, in], quantized by every workgroup itself
   float s_static;          // QFUSE: given activation scale, or <= 0 for max|x| / act_qmax
   float act_qmax;          // QFUSE: largest activation code
   int in;                  // QFUSE: in_features (multiple of 4)
   int32_t* ws_sum;         // [n_bins][ksplit][cap][256] partial tiles of split bins
   uint32_t* ws_cnt;        // [n_bins] arrival counters, zero between launches
-  int member_lo[PIPE_MAX_K];
-  int member_hi[PIPE_MAX_K];
-  int member_of[PIPE_MAX_K];
+  uint32_t member_lo[PIPE_MAX_K / 4], member_hi[PIPE_MAX_K / 4], member_of[PIPE_MAX_K / 4];   // a byte each: a launch copies its arguments on the host
 };
 
-// uniform dynamic index into a kernel-argument array without forcing it into scratch memory
-template <class T>
-__device__ __forceinline__ T pick(const T (&a)[PIPE_MAX_K], int k) {
-  T v = a[0];
+// byte k of a kernel-argument array, k uniform, without forcing the array into scratch memory
+__device__ __forceinline__ int pick(const uint32_t (&a)[PIPE_MAX_K / 4], int k) {
+  uint32_t v = a[0];
 #pragma unroll
-  for (int i = 1; i < PIPE_MAX_K; ++i) v = (i == k) ? a[i] : v;
-  return v;
+  for (int i = 1; i < PIPE_MAX_K / 4; ++i) v = (i == k >> 2) ? a[i] : v;
+  return (int)(v >> (k & 3) * 8 & 255u);
 }
 
 // The sum over a wave whose lanes are all active, by data-parallel moves within the vector unit
@@ -102,6 +100,10 @@ __device__ __forceinline__ void unpack_step(const uint4& w, int j, v4i& o) {
   }
 }
 
+// A partial tile in LDS: 16 words left out behind each 64, so that the 4 tokens x 16 channels a wave sums lie in different banks
+constexpr int PART_WORDS = 4 * 80;
+__device__ __forceinline__ int part_word(int i) { return i + (i >> 6) * 16; }
+
 // XM = number of distinct activation tensors the items of a bin can read: 1 (one input for all
 // orders), or 2 / 4 (one input per ensemble member, at most XM members).
 // XMASK: the batch does not fill its last 16-token block; the activation loads of that block are
@@ -111,9 +113,17 @@ __device__ __forceinline__ void unpack_step(const uint4& w, int j, v4i& o) {
 // arithmetic as the quantizer kernels (IEEE division, round half to even) while its first codes are
 // on their way, and builds its activation fragments from there.
 constexpr int QF_T = 16, QF_IN = 8192;   // tokens; codes of all tokens
+constexpr int QF_THREADS = 512;          // of a workgroup that quantizes, each up to QF_IN / 4 / QF_THREADS quads
+// What the first loads need comes as scalar arguments ahead of the struct: they are in registers with the launch, while the struct has to be
+// read from host memory.  Two to a word: a launch costs the host 0.01 us an argument.
 template <int BITS, int NW, int XM, bool ACC_OUT, bool XMASK, bool QFUSE = false>
-__global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)) <= 4) ? 4 : 2) void gemm_stream_kernel(const StreamParams p) {
-  static_assert(!QFUSE || (XM == 1 && !ACC_OUT), "the fused quantizer serves one shared input");
+__global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)) <= 8) ? 4 : 2) void gemm_stream_kernel(
+    const uint8_t* a_codes, const StreamBin* a_bins, const void* a_x, uint64_t a_nb_t0, uint64_t a_t1_t2, uint64_t a_in_mg, uint64_t a_sp_T,
+    const StreamParams p) {
+  const int a_n_bins = (int)a_nb_t0, a_thr0 = (int)(a_nb_t0 >> 32), a_thr1 = (int)a_t1_t2, a_thr2 = (int)(a_t1_t2 >> 32);
+  const int a_in = (int)a_in_mg, a_split = (int)a_sp_T, a_T = (int)(a_sp_T >> 32);
+  const unsigned a_magic = (unsigned)(a_in_mg >> 32);
+  static_assert(!QFUSE || (XM == 1 && !ACC_OUT && NW * 64 == QF_THREADS), "the fused quantizer serves one shared input");
   __shared__ __attribute__((aligned(16))) uint8_t s_qx[QFUSE ? QF_IN : 16];
   __shared__ float s_red[NW];
   __shared__ int s_rs[QF_T];
@@ -123,121 +133,127 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   constexpr int NX = XM * STEPS;
   constexpr int BIN_WORDS = sizeof(StreamBin) / 4;
   static_assert(BIN_WORDS <= 64, "bin descriptor is fetched with one load per lane");
-  __shared__ int part[NW][R][256];   // each wave's partial tiles
+  __shared__ __attribute__((aligned(16))) int part[NW][R][PART_WORDS];   // each wave's partial tiles
   __shared__ unsigned s_mx[2 * R];   // the members' largest magnitudes (two-sided: largest values, then of their negatives), as the slots hold them
   __shared__ int s_last;
 
-  if (QFUSE) request_arguments<sizeof(StreamParams)>();
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n_tiles = (p.nks * 64) / KSUP;
-  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<NW * 64>(p.zero_after, p.zero_n);
-  if (p.zero_big != nullptr)
-    for (int i = blockIdx.x * (NW * 64) + threadIdx.x; i < p.zero_big_n; i += gridDim.x * (NW * 64)) p.zero_big[i] = 0u;
+  const int in_pad_q = (a_in + 255) & ~255;
+  const int n_tiles = in_pad_q / KSUP;
 
   // Block index -> (bin, k share, token block).  Blocks are handed to the XCDs round robin, so the
   // workgroups that stream the same bin (for different token blocks or k shares) get indices that
   // are equal modulo 8: they run on one XCD and the bin comes from HBM once, then from that L2.
-  const int subs = p.ksplit * p.n_tb;
-  const int grp = (int)blockIdx.x / (8 * subs), within = (int)blockIdx.x - grp * (8 * subs);
-  const int bin = grp * 8 + (within & 7), sub = within >> 3;
-  const int ksp = sub % p.ksplit, tb = sub / p.ksplit;
-  if (bin >= p.n_bins) return;   // padding of the last group of eight bins
+  // A bin has several k shares or several token blocks, not both; a_magic divides by their number.
+  const int ksplit = a_split & 255, n_tb = a_split >> 8, subs = ksplit * n_tb;
+  const int g8 = (int)(blockIdx.x >> 3);
+  const int grp = subs == 1 ? g8 : (int)__umulhi(g8, a_magic);
+  const int bin = grp * 8 + (int)(blockIdx.x & 7), sub = g8 - grp * subs;
+  const int ksp = ksplit > 1 ? sub : 0, tb = ksplit > 1 ? 0 : sub;
+  if (bin >= a_n_bins) return;   // padding of the last group of eight bins
 
   // epilogue role of this thread: 256 threads per output row block, thread = (token t, channel ch)
   const int e = threadIdx.x & 255;
   const int t = e >> 4, ch = e & 15;   // token inside this workgroup's 16-token block
   const int tg = tb * 16 + t;          // token of the call
-  const int fidx = ((ch >> 2) * 16 + t) * 4 + (ch & 3);   // lane*4 + i of the MFMA result layout
+  const int fidx = part_word(((ch >> 2) * 16 + t) * 4 + (ch & 3));   // lane*4 + i of the MFMA result layout
   const int o_first = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   constexpr int O_STEP = (NW * 64) / 256;
-  const bool fold_sx = p.reduce && p.M > 1;
 
   // ---- everything that does not depend on the bin descriptor is requested first: where the bin's
   // stored row blocks sit in the schedule-ordered buffers follows from the bin's index (below), so
   // the code stream (the HBM traffic that bounds this kernel) starts at once.  Wave w streams
-  // tiles w, w+NW, ...; two tiles per item are in flight.
-  // this workgroup's share of the k tiles
-  const int tile_lo = (int)((long long)n_tiles * ksp / p.ksplit), tile_hi = (int)((long long)n_tiles * (ksp + 1) / p.ksplit);
+  // tiles w, w+NW, ..., one tile per item in flight: with exact waits two, three and four were the slower the more (11008 x 4096 8 bit, 16 tokens,
+  // call 24.2 us / 27.1 / 29.8 / 30.3; 4 bit, one token 12.2 / 14.2; six ternary layers of 2048, two members, 50 tokens 77.8 / 89.6).
+  // All loads go through buffer resources that end with this workgroup's share of the k tiles: an item that the bin does not have, a tile beyond
+  // the share and a token beyond the batch read as zero without any access, so no load is behind a branch and every wait is an exact count.
+  const int tile_lo = ksplit > 1 ? (int)__umulhi(n_tiles * ksp, a_magic) : 0;
+  const int tile_hi = ksplit > 1 ? (int)__umulhi(n_tiles * (ksp + 1), a_magic) : n_tiles;
+  // quantizing workgroups request their input before the codes: it is what they wait for first (results return in order)
+  constexpr int XQ = QF_IN / 4 / QF_THREADS;
+  v4f xq[QFUSE ? XQ : 1];
+  const __amdgpu_buffer_rsrc_t l_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(a_x), 0, (unsigned)(a_T * a_in * 4), 0x00020000);
+  if constexpr (QFUSE) {
+#pragma unroll
+    for (int i = 0; i < XQ; ++i) xq[i] = (v4f)__builtin_amdgcn_raw_buffer_load_b128(l_q, (threadIdx.x + i * QF_THREADS) * 16, 0, 0);
+  }
+  auto load_d = [&]() __attribute__((always_inline)) { return reinterpret_cast<const int32_t*>(a_bins + bin)[min(lane, BIN_WORDS - 1)]; };
+  int d0 = 0;
+  if (XM > 1) d0 = load_d();   // says which activations an item multiplies
   // the bin's first position and item count, from its index: the bins lie without gaps, fullest first
-  const int b3 = max(bin - p.thr0, 0), b2 = max(bin - p.thr1, 0), b1 = max(bin - p.thr2, 0);
-  const int n_here = bin < p.thr0 ? 4 : (bin < p.thr1 ? 3 : (bin < p.thr2 ? 2 : 1));
+  const int b3 = max(bin - a_thr0, 0), b2 = max(bin - a_thr1, 0), b1 = max(bin - a_thr2, 0);
+  const int n_here = bin < a_thr0 ? 4 : (bin < a_thr1 ? 3 : (bin < a_thr2 ? 2 : 1));
   const int pos0 = 4 * bin - b3 - b2 - b1;
-  size_t posr[R];
+  __amdgpu_buffer_rsrc_t l_w[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) posr[r] = (size_t)(r < n_here ? pos0 + r : p.zero_pos);
-  const uint8_t* wb[R];
+  for (int r = 0; r < R; ++r)
+    l_w[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a_codes) + (size_t)(pos0 + (r < n_here ? r : 0)) * n_tiles * 1024, 0,
+                                               r < n_here ? (unsigned)tile_hi * 1024u : 0u, 0x00020000);
+  v4u w[R];
+  v4i x[NX];
+  auto load_w = [&](int tl, v4u (&w)[R]) __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < R; ++r) wb[r] = p.codes + posr[r] * (size_t)n_tiles * 1024;
-  const int d0 = lane < BIN_WORDS ? reinterpret_cast<const int32_t*>(p.bins + bin)[lane] : 0;
-  uint4 w0[R], w1[R], x0[NX], x1[NX];
-  auto load_w = [&](int tl, uint4 (&w)[R]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) w[r] = reinterpret_cast<const uint4*>(wb[r] + (size_t)tl * 1024)[lane];
+    for (int r = 0; r < R; ++r) w[r] = (v4u)__builtin_amdgcn_raw_buffer_load_b128(l_w[r], tl * 1024 + lane * 16, 0, 0);
   };
-  // member m's activations (members beyond M repeat the last one; never used)
-  const uint8_t* xb[XM];
+  // member m's activations
+  const size_t x_tb = (size_t)tb * in_pad_q * 16;
+  __amdgpu_buffer_rsrc_t l_x[XM];
+  if constexpr (!QFUSE) {
 #pragma unroll
-  for (int m = 0; m < XM; ++m) xb[m] = p.qx + (size_t)(m < p.M ? m : p.M - 1) * p.qx_mstride + (size_t)tb * p.nks * 1024;
-  // lanes of tokens beyond the batch keep the zeros they start with: their codes are zero anyway, and
-  // a load instruction costs the memory pipeline only its active lanes (one token in sixteen at T = 1)
-  const bool xlive = tb * 16 + (lane & 15) < p.T;
-  const bool xfull = !XMASK || tb * 16 + 16 <= p.T;   // uniform: a whole block needs no lane mask
-  const int in_pad_q = p.nks * 64;
-  auto load_x = [&](int tl, uint4 (&x)[NX]) __attribute__((always_inline)) {
+    for (int m = 0; m < XM; ++m) {
+      const bool on = m == 0 || m < p.M;
+      l_x[m] = __builtin_amdgcn_make_buffer_rsrc((uint8_t*)const_cast<void*>(a_x) + (m > 0 && on ? (size_t)m * p.qx_mstride : 0) + x_tb, 0,
+                                                 on ? (unsigned)(tile_hi * STEPS) * 1024u : 0u, 0x00020000);
+    }
+  }
+  const unsigned x_off = !XMASK || tb * 16 + (lane & 15) < a_T ? lane * 16u : 0x80000000u;
+  auto load_x = [&](int tl, v4i (&x)[NX]) __attribute__((always_inline)) {
     if constexpr (QFUSE) {
-      // the fragment of a 64-k step: lane (kc, n) holds codes 16 kc .. 16 kc + 15 of token n
-      if ((lane & 15) < p.T) {
+      // the fragment of a 64-k step: lane (kc, n) holds codes 16 kc .. 16 kc + 15 of token n (of the last one beyond it: never stored)
+      const uint8_t* row = &s_qx[min(lane & 15, a_T - 1) * in_pad_q + (lane >> 4) * 16];
+      const int at = min(tl, tile_hi - 1) * STEPS;
 #pragma unroll
-        for (int j = 0; j < STEPS; ++j)
-          x[j] = *reinterpret_cast<const uint4*>(&s_qx[(size_t)(lane & 15) * in_pad_q + (size_t)(tl * STEPS + j) * 64 + (lane >> 4) * 16]);
-      }
-    } else if (xfull) {
-#pragma unroll
-      for (int m = 0; m < XM; ++m)
-#pragma unroll
-        for (int j = 0; j < STEPS; ++j) x[m * STEPS + j] = reinterpret_cast<const uint4*>(xb[m] + (size_t)(tl * STEPS + j) * 1024)[lane];
-    } else if (xlive) {
+      for (int j = 0; j < STEPS; ++j) x[j] = *reinterpret_cast<const v4i*>(row + (at + j) * 64);
+    } else {
 #pragma unroll
       for (int m = 0; m < XM; ++m)
 #pragma unroll
-        for (int j = 0; j < STEPS; ++j) x[m * STEPS + j] = reinterpret_cast<const uint4*>(xb[m] + (size_t)(tl * STEPS + j) * 1024)[lane];
+        for (int j = 0; j < STEPS; ++j) x[m * STEPS + j] = (v4i)__builtin_amdgcn_raw_buffer_load_b128(l_x[m], x_off + (tl * STEPS + j) * 1024u, 0, 0);
     }
   };
-#pragma unroll
-  for (int j = 0; j < NX; ++j) { x0[j] = make_uint4(0, 0, 0, 0); x1[j] = make_uint4(0, 0, 0, 0); }
   int tl = tile_lo + wave;
-  if (tl < tile_hi) { load_w(tl, w0); if (!QFUSE) load_x(tl, x0); }
-  if (tl + NW < tile_hi) { load_w(tl + NW, w1); if (!QFUSE) load_x(tl + NW, x1); }
+  load_w(tl, w);
+  if (!QFUSE) load_x(tl, x);
+  __builtin_amdgcn_sched_barrier(0);
+  request_arguments<sizeof(StreamParams) + 56>();
+  if (XM == 1) d0 = load_d();
   // epilogue operands that need no descriptor: row scales (same positions), and per member the
   // activation scale and this thread's token code sum
+  const bool fold_sx = p.reduce && p.M > 1;
   float scv[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) scv[r] = p.scales[posr[r] * 16 + ch];
+  for (int r = 0; r < R; ++r) scv[r] = p.scales[(size_t)(pos0 + (r < n_here ? r : 0)) * 16 + ch];
   float sxm[R];
   int rsm[R];
   if constexpr (!QFUSE) {
 #pragma unroll
-    for (int m = 0; m < R; ++m) {       // at most R members (K <= R)
+    for (int m = 0; m < R; ++m) {       // at most R members (K <= R), and XM where each has its own input
+      if (XM > 1 && m >= XM) { sxm[m] = 0.f; rsm[m] = 0; continue; }
       const int mm = m < p.M ? m : p.M - 1;
       sxm[m] = p.s_x[mm * p.sx_mstride];
       rsm[m] = OFF ? p.rowsum[(size_t)mm * p.rowsum_mstride + tg] : 0;
     }
   } else {
     // ---- quantize the input here (the codes already requested are on their way meanwhile)
-    const int in = p.in;
-    const float4* x4 = reinterpret_cast<const float4*>(p.x_f32);
-    const int n4 = (p.T * in) >> 2;
+    const int n4 = (a_T * a_in) >> 2;
     if ((int)threadIdx.x < QF_T) s_rs[threadIdx.x] = 0;
     float s_act = p.s_static;
     if (!(s_act > 0.f)) {
       float mx = 0.f;
-      for (int i = threadIdx.x; i < n4; i += NW * 64) {
-        const float4 v = x4[i];
-        mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-      }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      for (int i = 0; i < XQ; ++i) mx = fmaxf(mx, fmaxf(fmaxf(fabsf(xq[i].x), fabsf(xq[i].y)), fmaxf(fabsf(xq[i].z), fabsf(xq[i].w))));
+      mx = wave_max(mx);
       if (lane == 0) s_red[wave] = mx;
       __syncthreads();
       mx = s_red[0];
@@ -248,47 +264,82 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       __syncthreads();   // the cleared code sums
     }
     const bool live_q = s_act > 0.f;
-    auto q1 = [&](float v) __attribute__((always_inline)) {
-      const float q = fminf(fmaxf(rintf(__fdiv_rn(v, s_act)), -p.act_qmax), p.act_qmax);
-      return live_q ? (int)q : 0;
-    };
-    int sum_1 = 0;   // a single token: one sum per wave at the end
-    for (int i = threadIdx.x; i < n4; i += NW * 64) {
-      const float4 v = x4[i];
-      const int tq = (i * 4) / in, k = i * 4 - tq * in;   // in is a multiple of 4: one token per float4
+    const Divisor div(s_act);
+    const float per_row = __builtin_amdgcn_rcpf((float)a_in);
+    const bool by_wave = a_T == 1 || a_in % 256 == 0;   // a wave's 64 quads lie in one row (behind the input they are zero)
+    auto quantize = [&](auto fast, int i, const v4f& v) __attribute__((always_inline)) {
+      auto q1 = [&](float f) __attribute__((always_inline)) {
+        const float q = fminf(fmaxf(rintf(div.template quotient<decltype(fast)::value>(f)), -p.act_qmax), p.act_qmax);
+        return live_q ? (int)q : 0;
+      };
+      // in_features is a multiple of 4: one token per quad.  The estimate is exact: the quotient, up to 16, is at least 1/2 / 8192 from
+      // the next whole number.
+      const int tq = a_T == 1 ? 0 : min((int)(((float)(i * 4) + 0.5f) * per_row), a_T - 1);
       const int a = q1(v.x), b = q1(v.y), c = q1(v.z), d = q1(v.w);
-      *reinterpret_cast<uint32_t*>(&s_qx[(size_t)tq * in_pad_q + k]) =
-          (uint32_t)(uint8_t)a | ((uint32_t)(uint8_t)b << 8) | ((uint32_t)(uint8_t)c << 16) | ((uint32_t)(uint8_t)d << 24);
-      const int sum4 = a + b + c + d;
-      if (p.T == 1) {
-        sum_1 += sum4;
-      } else if (in % 256 == 0) {   // a wave's 64 quads lie in one row
-        const int sum = wave_sum(sum4);
-        if (lane == 0) atomicAdd(&s_rs[tq], sum);
-      } else if (sum4 != 0) {
-        atomicAdd(&s_rs[tq], sum4);
-      }
-    }
-    if (p.T == 1) {
-      const int sum = wave_sum(sum_1);
-      if (lane == 0) atomicAdd(&s_rs[0], sum);
+      if (i < n4) *reinterpret_cast<uint32_t*>(&s_qx[tq * in_pad_q + i * 4 - tq * a_in]) = pack4(a, b, c, d);
+      int sum = a + b + c + d;
+      if (by_wave) sum = wave_sum(sum);
+      if (by_wave ? lane == 0 : sum != 0) atomicAdd(&s_rs[tq], sum);
+    };
+    if (div.fast) {
+#pragma unroll
+      for (int u = 0; u < XQ; ++u)
+        if (u * QF_THREADS + wave * 64 < n4) quantize(std::true_type{}, threadIdx.x + u * QF_THREADS, xq[u]);
+    } else {
+#pragma unroll 1
+      for (int u = 0; u * QF_THREADS + wave * 64 < n4; ++u)
+        quantize(std::false_type{}, threadIdx.x + u * QF_THREADS, (v4f)__builtin_amdgcn_raw_buffer_load_b128(l_q, (threadIdx.x + u * QF_THREADS) * 16, 0, 0));
     }
     // codes beyond in_features are zero
-    const int pad4 = (in_pad_q - in) >> 2;
-    for (int i = threadIdx.x; i < p.T * pad4; i += NW * 64) {
-      const int tq = i / pad4, k = in + (i - tq * pad4) * 4;
+    const int pad4 = (in_pad_q - a_in) >> 2;
+    for (int i = threadIdx.x; i < a_T * pad4; i += NW * 64) {
+      const int tq = i / pad4, k = a_in + (i - tq * pad4) * 4;
       *reinterpret_cast<uint32_t*>(&s_qx[(size_t)tq * in_pad_q + k]) = 0u;
     }
     __syncthreads();
-    const int rs_q = (OFF && tg < p.T) ? s_rs[min(tg, QF_T - 1)] : 0;
+    const int rs_q = (OFF && tg < a_T) ? s_rs[min(tg, QF_T - 1)] : 0;
 #pragma unroll
     for (int m = 0; m < R; ++m) { sxm[m] = s_act; rsm[m] = rs_q; }
-    if (tl < tile_hi) load_x(tl, x0);
-    if (tl + NW < tile_hi) load_x(tl + NW, x1);
   }
 
-  // ---- the descriptor: scalar reads out of one vector register
+  // ---- the descriptor: scalar reads out of one vector register, with one input only behind the codes (it arrives after them)
   auto word = [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(d0, i); };
+  int itm[R];   // which activation tensor item r reads
+#pragma unroll
+  for (int r = 0; r < R; ++r) itm[r] = XM == 1 ? 0 : pick(p.member_of, word(2 + (r < n_here ? r : 0)));
+
+  v4i acc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[r] = v4i{0, 0, 0, 0};
+  auto mul_tile = [&](v4u (&w)[R], v4i (&x)[NX]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < STEPS; ++j) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        v4i xf = x[j];
+#pragma unroll
+        for (int m = 1; m < XM; ++m) {   // uniform select, component by component
+          const bool pickm = itm[r] == m;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) xf[c] = pickm ? x[m * STEPS + j][c] : xf[c];
+        }
+        v4i wf;
+        unpack_step<BITS>(make_uint4(w[r].x, w[r].y, w[r].z, w[r].w), j, wf);
+        acc[r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf, xf, acc[r], 0, 0, 0);
+      }
+    }
+  };
+  // The first tile stands apart: behind it are the epilogue's operands, of which the loop's waits know nothing.
+  if (QFUSE) load_x(tl, x);
+  mul_tile(w, x);
+  for (tl += NW; tl < tile_hi; tl += NW) {
+    load_w(tl, w);
+    load_x(tl, x);
+    mul_tile(w, x);
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    *reinterpret_cast<v4i*>(&part[wave][r][part_word(lane * 4)]) = acc[r];
   const int n_items = word(0), n_out = word(1);
   int itk[R], its[R];
 #pragma unroll
@@ -298,44 +349,9 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
     its[r] = on ? word(2 + STREAM_BIN_CAP + r) : -1;
   }
   auto out_rb = [&](int o) __attribute__((always_inline)) { return word(2 + 2 * STREAM_BIN_CAP + o); };
-  int itm[R];   // which activation tensor item r reads
-#pragma unroll
-  for (int r = 0; r < R; ++r) itm[r] = XM == 1 ? 0 : pick(p.member_of, itk[r]);
-
-  v4i acc[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) acc[r] = v4i{0, 0, 0, 0};
-  auto mul_tile = [&](uint4 (&w)[R], uint4 (&x)[NX]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < STEPS; ++j) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        v4i xf = v4i{(int)x[j].x, (int)x[j].y, (int)x[j].z, (int)x[j].w};
-#pragma unroll
-        for (int m = 1; m < XM; ++m) {   // uniform select, component by component
-          const bool pickm = itm[r] == m;
-          xf[0] = pickm ? (int)x[m * STEPS + j].x : xf[0];
-          xf[1] = pickm ? (int)x[m * STEPS + j].y : xf[1];
-          xf[2] = pickm ? (int)x[m * STEPS + j].z : xf[2];
-          xf[3] = pickm ? (int)x[m * STEPS + j].w : xf[3];
-        }
-        v4i wf;
-        unpack_step<BITS>(w[r], j, wf);
-        acc[r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf, xf, acc[r], 0, 0, 0);
-      }
-    }
-  };
-  for (; tl < tile_hi; tl += 2 * NW) {
-    mul_tile(w0, x0);
-    if (tl + 2 * NW < tile_hi) { load_w(tl + 2 * NW, w0); load_x(tl + 2 * NW, x0); }
-    if (tl + NW < tile_hi) {
-      mul_tile(w1, x1);
-      if (tl + 3 * NW < tile_hi) { load_w(tl + 3 * NW, w1); load_x(tl + 3 * NW, x1); }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-    *reinterpret_cast<v4i*>(&part[wave][r][lane * 4]) = acc[r];
+  if (blockIdx.x == 0 && p.zero_after != nullptr) slots_clear<NW * 64>(p.zero_after, p.zero_n);
+  if (p.zero_big != nullptr)
+    for (int i = (bin * subs + sub) * (NW * 64) + threadIdx.x; i < p.zero_big_n; i += a_n_bins * subs * (NW * 64)) p.zero_big[i] = 0u;
   if (threadIdx.x < 2 * R) s_mx[threadIdx.x] = 0u;
   __syncthreads();
 
@@ -351,26 +367,26 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   // counter raised; the reader's device-scope loads bypass its own caches.  A release/acquire pair
   // on the counter would express the same order in the model; its cache write-back and invalidate
   // measured 11 to 34 us per exchange on this chip, more than the kernel.
-  if (p.ksplit > 1) {
-    int32_t* ws = p.ws_sum + ((size_t)bin * p.ksplit + ksp) * (R * 256);
+  if (ksplit > 1) {
+    int32_t* ws = p.ws_sum + ((size_t)bin * ksplit + ksp) * (R * 256);
     for (int i = threadIdx.x; i < R * 256; i += NW * 64) {
       int a = 0;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) a += (&part[w][0][0])[i];
+      for (int w = 0; w < NW; ++w) a += part[w][i >> 8][part_word(i & 255)];
       __hip_atomic_store(&ws[i], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(&p.ws_cnt[bin], 1u) == (unsigned)(p.ksplit - 1);
+    if (threadIdx.x == 0) s_last = atomicAdd(&p.ws_cnt[bin], 1u) == (unsigned)(ksplit - 1);
     __syncthreads();
     if (!s_last) return;
-    const int32_t* wsb = p.ws_sum + (size_t)bin * p.ksplit * (R * 256);
+    const int32_t* wsb = p.ws_sum + (size_t)bin * ksplit * (R * 256);
     for (int i = threadIdx.x; i < R * 256; i += NW * 64) {
       int a = 0;
-      for (int q = 0; q < p.ksplit; ++q) a += __hip_atomic_load(&wsb[(size_t)q * (R * 256) + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      (&part[0][0][0])[i] = a;
+      for (int q = 0; q < ksplit; ++q) a += __hip_atomic_load(&wsb[(size_t)q * (R * 256) + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      part[0][i >> 8][part_word(i & 255)] = a;
 #pragma unroll
-      for (int w = 1; w < NW; ++w) (&part[w][0][0])[i] = 0;
+      for (int w = 1; w < NW; ++w) part[w][i >> 8][part_word(i & 255)] = 0;
     }
     if (threadIdx.x == 0) __hip_atomic_store(&p.ws_cnt[bin], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
@@ -422,13 +438,11 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       if (p.amax_out != nullptr) {
         const bool two_sided = p.amax_neg != nullptr;
         float mx = tg < p.T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
-#pragma unroll
-        for (int s = 32; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
+        mx = wave_max(mx);
         if (lane == 0) atomicMax(&s_mx[m], __float_as_uint(mx));
         if (two_sided) {
           float mn = tg < p.T ? fmaxf(-v, 0.f) : 0.f;
-#pragma unroll
-          for (int s = 32; s > 0; s >>= 1) mn = fmaxf(mn, __shfl_xor(mn, s, 64));
+          mn = wave_max(mn);
           if (lane == 0) atomicMax(&s_mx[R + m], __float_as_uint(mn));
         }
       }
@@ -695,18 +709,25 @@ int launch_multi_cap(const StreamParams& p, int n_bins, int cap, int xm, const G
   }
 }
 
+// a bin's workgroups are subs = ksplit * n_tb, of which one factor is 1: the first whole number above (2^32 - 1) / subs, ceil(2^32 / subs), gives floor(i / subs) as the product's upper half while
+// 7 i < 2^32
+inline uint64_t two_words(int lo, uint32_t hi) { return (uint64_t)(uint32_t)lo | (uint64_t)hi << 32; }
+#define PIPE_STREAM_ARGS(x)                                                                                              \
+  p.codes, p.bins, (const void*)(x), two_words(p.n_bins, p.thr0), two_words(p.thr1, p.thr2),                             \
+      two_words(p.in, 0xffffffffu / (unsigned)(p.ksplit * p.n_tb) + 1u), two_words(p.ksplit | p.n_tb << 8, p.T), p
+
 template <int BITS, int NW>
 int launch_nw(const StreamParams& p, int n_bins, int xm, bool acc_out, const GemmArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)((n_bins + 7) / 8 * 8 * p.ksplit * p.n_tb)), blk(NW * 64);
   if (p.x_f32 != nullptr) {
     // no quantizer launch: the contraction quantizes its few tokens itself
     if (xm != 1 || acc_out || p.T > QF_T || p.T * p.nks * 64 > QF_IN || p.in % 4 != 0 || p.n_tb != 1) return PIPE_EINVAL;
-    PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true>), grid, blk, st, a.ev_start, a.ev_stop, p);
+    PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.x_f32));
     PIPE_HIP(hipGetLastError());
     return PIPE_OK;
   }
   const bool xmask = p.T % 16 != 0;
-#define PIPE_STREAM_LAUNCH(XMV, ACC, MASK) PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, XMV, ACC, MASK>), grid, blk, st, a.ev_start, a.ev_stop, p)
+#define PIPE_STREAM_LAUNCH(XMV, ACC, MASK) PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, XMV, ACC, MASK>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.qx))
 #define PIPE_STREAM_PICK(XMV)                                                     \
   do {                                                                            \
     if (acc_out) { if (xmask) PIPE_STREAM_LAUNCH(XMV, true, true); else PIPE_STREAM_LAUNCH(XMV, true, false); }   \
@@ -749,14 +770,18 @@ int launch_gemm_stream(const GemmArgs& a, hipStream_t st) {
     else ks = std::min(256 / (e->n_bins > 0 ? e->n_bins : 1), std::min(PIPE_MAX_SPLIT, n_tiles / 16));
     p.n_tb = a.T_pad / 16;
     p.n_bins = e->n_bins;
-    p.thr0 = e->bin_thr[0]; p.thr1 = e->bin_thr[1]; p.thr2 = e->bin_thr[2]; p.zero_pos = e->zero_pos;
+    p.thr0 = e->bin_thr[0]; p.thr1 = e->bin_thr[1]; p.thr2 = e->bin_thr[2];
     if (p.n_tb > 1) ks = 1;   // several token blocks already multiply the workgroups
     p.ksplit = std::max(ks, 1);
     p.ws_sum = e->split_sum_dev; p.ws_cnt = e->split_cnt_dev;
   }
-  for (int m = 0; m < PIPE_MAX_K; ++m) { p.member_lo[m] = a.member_lo[m]; p.member_hi[m] = a.member_hi[m]; p.member_of[m] = 0; }
-  for (int m = 0; m < a.M; ++m)
-    for (int k = a.member_lo[m]; k <= a.member_hi[m]; ++k) p.member_of[k] = m;
+  static_assert(PIPE_MAX_K % 4 == 0 && PIPE_MAX_K <= 255, "members as bytes");
+  for (int i = 0; i < PIPE_MAX_K / 4; ++i) p.member_lo[i] = p.member_hi[i] = p.member_of[i] = 0u;
+  for (int m = 0; m < a.M; ++m) {
+    p.member_lo[m >> 2] |= (uint32_t)a.member_lo[m] << (m & 3) * 8;
+    p.member_hi[m >> 2] |= (uint32_t)a.member_hi[m] << (m & 3) * 8;
+    for (int k = a.member_lo[m]; k <= a.member_hi[m]; ++k) p.member_of[k >> 2] |= (uint32_t)m << (k & 3) * 8;
+  }
   // distinct activation tensors: one, or one per member
   const int xm = (a.qx_mstride == 0 || a.M <= 1) ? 1 : (a.M <= 2 ? 2 : 4);
   const bool acc_out = a.acc_out != nullptr;
