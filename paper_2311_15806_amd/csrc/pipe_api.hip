@@ -820,10 +820,10 @@ static int routed(bool tiled, Call call) {
 
 // Where 17 to 128 tokens are tiled: the streaming kernel runs a workgroup per bin and 16 tokens, each along the whole of k, the tiled one walks along k
 // once for up to 64.  A walk costs about what 400 such workgroups do; at 8 and 2 bits a step of a long walk costs more beside them.  Calls, us, streamed / tiled:
-//   11008 x 4096 4 bit, K = 4, half kept, 20 tokens 25.9 / 20.6, 64 36.7 / 22.6, 128 59.0 / 28.9; ternary 32 19.8 / 17.2, 128 39.6 / 23.9;
-//   4096 x 4096 4 bit 32 tokens 16.3 / 16.3, 64 20.0 / 16.6; ternary 64 16.0 / 16.9, 96 19.6 / 17.2; 8 bit, K = 2 64 19.0 / 20.3, 96 21.5 / 20.7;
-//   4096 x 11008 4 bit 32 tokens 24.1 / 27.1, 48 28.9 / 27.2; ternary 96 27.5 / 30.1, 128 32.5 / 30.6; 8 bit 96 38.8 / 39.4, 128 46.0 / 40.1;
-//   3072 x 768 4 bit 48 tokens 11.9 / 13.8, 96 18.5 / 13.9; 2048 x 2048 ternary 64 13.6 / 14.0, 128 14.9 / 13.8; 768 x 3072 never (4 bit, 128 15.4 / 15.8).
+//   11008 x 4096 4 bit, K = 4, half kept, 20 tokens 23.3 / 20.5, 64 32 / 22.4, 128 52 / 29; ternary 32 17.7 / 17.4, 64 22.8 / 18.7;
+//   4096 x 4096 4 bit 32 tokens 15.2 / 16.3, 64 17.9 / 16.7; ternary 64 14.7 / 17.1, 128 19.7 / 17.6; 8 bit, K = 2 64 18.8 / 20.4, 96 21.3 / 20.6;
+//   4096 x 11008 4 bit 32 tokens 22.9 / 27.2, 48 26.8 / 27.3, 96 37.1 / 30.5; ternary 96 26.3 / 30.3, 128 29.7 / 30.7; 8 bit 96 38.9 / 39.2, 128 49.6 / 40.2;
+//   3072 x 768 4 bit 48 tokens 11.1 / 11.2, 96 15.9 / 14.0; 2048 x 2048 ternary 64 12.6 / 14.0, 128 14.2 / 13.9; 768 x 3072 never (4 bit, 96 14.0 / 15.7).
 static bool linear_tiled(const pipe_expansion* e, int T, int M, int reduce_members) {
   if (!e || g_kernel_choice != 0 || T <= STREAM_ONLY_T || T > PIPE_STREAM_MAX_T || e->bin_cap != 4 || (M > 1 && !reduce_members)) return false;
   return 2 * (int64_t)e->n_bins * ceil_div(T, 16) >= 800 + (e->bits == 4 ? 0 : (e->bits == 8 ? 6 : 5)) * e->nks;
@@ -837,20 +837,20 @@ static bool single_order(const int* split, int M) {
 
 // The same for a two-layer MLP (a gated one also saves the launch that multiplies SiLU(gate) into up; the sum over members of a single
 // order runs pass by pass).  Calls, us, streamed / tiled:
-//   gated, one member: 2048-5504-2048 4 bit, K = 3, 64 tokens 42.1 / 40.1, 100 58.1 / 43.7; 4096-11008 64 82.3 / 84.2, 100 121 / 96; ternary 64 63.7 / 72.6, 100 93 / 80;
-//   two of two orders: 4096-11008 4 bit 36 tokens 102 / 104, 64 124 / 106, 128 210 / 114; of 2 and 1: 64 96 / 119, 100 140 / 125;
-//   GELU, one member: 768-3072 4 bit, K = 3, 64 tokens 23.5 / 26.7, 100 30.4 / 27.6; two of two orders: 1024-4096 100 43.8 / 41.1, 768-3072 100 37.7 / 38.1;
-//   of 2 and 1: 128 34.0 / 44.9.
+//   gated, one member: 2048-5504-2048 4 bit, K = 3, 64 tokens 38.6 / 40.4, 100 50.4 / 43.8; 4096-11008 64 76.5 / 84.3, 100 112 / 97; ternary 64 55.4 / 72.7,
+//   100 81.7 / 80.6, 128 89.1 / 81.0; two of two orders: 4096-11008 4 bit 36 tokens 92 / 105, 64 110 / 107, 100 152 / 116; 2048-5504 64 48.9 / 51.5, 100 65.4 / 52.5;
+//   of 2 and 1: 4096-11008 100 130 / 125, 128 151 / 126; 2048-5504 100 55.8 / 59.0, 128 63.1 / 59.5;
+//   GELU, one member: 768-3072 ternary, 64 tokens 22.9 / 24.7, 100 27.2 / 26.6; two of two orders: 1024-4096 4 bit, 100 36.8 / 41.5, 128 37.9 / 41.7; of 2 and 1: 128 31.5 / 44.7.
 static bool mlp_tiled(const pipe_expansion* l1, const pipe_expansion* l2, int act, int T, const int* split, int M) {
   if (!l1 || !l2 || g_kernel_choice != 0 || T > PIPE_STREAM_MAX_T || M > 2 || l1->bin_cap != 4 || l2->bin_cap != 4 || l1->bits == 8 || l2->bits == 8) return false;
-  const bool two = split != nullptr && M == 2, one_order = single_order(split, M);
-  if (act == PIPE_ACT_SILU_GATED) return l1->n_rb % 2 == 0 && T > (two ? (one_order ? 96 : 48) : 64);
-  return T > 64 && (!two || (!one_order && l2->nks >= 64));
+  const bool two = split != nullptr && M == 2;
+  if (act == PIPE_ACT_SILU_GATED) return l1->n_rb % 2 == 0 && T > (two && single_order(split, M) ? 112 : 64);
+  return T > 64 && !two;
 }
 
-// ... and for a chain of fully-connected layers, whose members hold at most 4 orders: six layers of 2048 x 2048, us, streamed / tiled:
-// ternary, two members of 2 orders, 64 tokens 96.6 / 90.5, 100 130 / 94 (1024 wide 69.4 / 75.0, 93 / 77); 4 bit, one of 4, 64 73.0 / 73.8, 100 96 / 76;
-// two of 4 (bins of 8: streamed in two chunks), 64 146 / 100, 128 198 / 111; one of 8 (pass by pass) 112 / 203.
+// ... and for a chain of fully-connected layers, whose members hold at most 4 orders, us, streamed / tiled: six layers of 2048 x 2048 ternary, two members
+// of 2 orders, 64 tokens 75 / 92, 128 97.0 / 95.5; 4 bit, one of 4, 64 65 / 75, 100 88 / 76 (1024 wide, whose 16 steps of k are too short a walk, 63.4 / 68.9);
+// two of 4 (bins of 8: streamed in two chunks), 64 148 / 101, 128 198 / 110, 512 wide 64 83 / 66; one of 8 (pass by pass) 112 / 203.
 static bool chain_tiled(const pipe_chain_layer* layers, int L, int T, const int* split, int M) {
   if (!layers || L < 1 || g_kernel_choice != 0 || T <= 48 || T > PIPE_STREAM_MAX_T || M > 2) return false;
   for (int l = 0; l < L; ++l) {
@@ -858,7 +858,7 @@ static bool chain_tiled(const pipe_chain_layer* layers, int L, int T, const int*
     if (!e || e->bits == 8 || layers[l].kh != 0) return false;
     if (split == nullptr || M < 2 ? e->K > 4 : (split[0] > 4 || split[1] > 4)) return false;
   }
-  return T > (layers[0].e->K > 4 ? 48 : 64);
+  return layers[0].e->K > 4 || (T > 64 && layers[0].e->nks >= 24);
 }
 
 struct ActBuffers {

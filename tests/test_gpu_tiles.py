@@ -356,14 +356,15 @@ def test_infinite_member_scale_leaves_pruned_row_blocks(pipe, bits, out, hidden,
 
 
 @pytest.mark.parametrize("kind,T", [("linear", 17), ("linear", 64), ("linear", 65), ("linear", 128), ("asymmetric", 40), ("gelu", 64), ("gelu", 65),
-                                    ("gated", 48), ("gated", 49), ("gated21", 97), ("chain", 65), ("chain8", 49)])
+                                    ("gated", 64), ("gated", 65), ("gated21", 113), ("chain", 65), ("chain8", 49)])
 def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
     """Calls that the tiled kernels serve by rule, against the streaming kernel, bit for bit; and captured where only the streaming kernel is
     ready (its scratch, no tile schedules), replayed with other inputs."""
     g = torch.Generator(device="cuda")
     g.manual_seed(T)
     mk = lambda o, i, bits, K, group=16: pipe.pipe_expand(torch.randn(o, i, generator=g, device="cuda") * (1.5 / i ** 0.5), bits, K, 0.5, group)
-    xs = [torch.randn(T, 320, generator=g, device="cuda") * s for s in (1.0, 3.0)]
+    wide = 1552 if kind == "chain" else 320
+    xs = [torch.randn(T, wide, generator=g, device="cuda") * s for s in (1.0, 3.0)]
     x = xs[0].clone()
     if kind in ("linear", "asymmetric"):
         es = [mk(8192, 320, 4, 4)]          # 320 bins: 17 tokens are past the line
@@ -376,7 +377,7 @@ def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
         call = lambda: pipe.pipe_mlp_forward(es[0], es[1], act, x, split=split)
     else:
         K, split = (4, [2, 2]) if kind == "chain" else (8, [4, 4])
-        es = [mk(320, 320, 2, K) for _ in range(3)]
+        es = [mk(wide, wide, 2, K) for _ in range(3)]
         layers = [(es[0], None, 3, -1, True), (es[1], None, 3, 1, True), (es[2], None, 0, -1, True)]
         call = lambda: pipe.pipe_chain_forward(layers, x, split=split)
     side = torch.cuda.Stream()
