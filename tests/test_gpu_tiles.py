@@ -405,3 +405,24 @@ def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
         assert torch.equal(call(), want)
     for e in es:
         e.free()
+
+
+@pytest.mark.parametrize("bits,T,n_in,scale,static", [(2, 1, 8192, 1.0, 0.0), (4, 1, 8188, 1.0, 0.0), (8, 1, 4, 1.0, 0.02), (4, 16, 252, 1.0, 0.0), (2, 3, 1028, 1.0, 0.0),
+                                                      (8, 4, 1024, 1.0, 0.01), (4, 15, 20, 1.0, 0.0), (4, 2, 2048, 1e-30, 0.0), (2, 5, 516, 1e30, 0.0), (8, 16, 256, 0.0, 0.0)])
+def test_streaming_kernel_quantizes_its_tokens(pipe, bits, T, n_in, scale, static):
+    """Codes from the streaming kernel's own quantizer against the launch of its own, bit for bit: the largest input, quads that end a row or the
+    batch inside a wave, one quad, scales beyond the short division's range, NaN and infinities under a given scale."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + n_in)
+    e = pipe.pipe_expand(torch.randn(176, n_in, generator=g, device="cuda") / n_in ** 0.5, bits, 2, 0.5, 16)   # bins past a group of eight
+    x = torch.randn(T, n_in, generator=g, device="cuda") * scale
+    if static > 0:
+        x[0, 0], x[-1, -1], x[0, 1] = float("nan"), float("inf"), -float("inf")
+    try:
+        pipe.pipe_set_decode_fusion(False)
+        want = pipe.pipe_forward(e, x, s_x=static)
+    finally:
+        pipe.pipe_set_decode_fusion(True)
+    assert torch.equal(pipe.pipe_forward(e, x, s_x=static), want)
+    assert bool(torch.isfinite(want).all())
+    e.free()
