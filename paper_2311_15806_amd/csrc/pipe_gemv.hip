@@ -461,7 +461,8 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
 }
 
 // Bins of CAP = 4 * NCH items (expansions with 5 to 16 orders).  The workgroup streams the bin in
-// chunks of R = 4 items exactly as above (waves split k, two tiles per item in flight), reduces
+// chunks of R = 4 items exactly as above (waves split k, one tile per item in flight; with two, and every wave raising the maxima itself, seven layers of 2048
+// ternary with two members of 4 orders took 138 us at 40 tokens instead of 92.7, 94.6 at 16 instead of 81.8), reduces
 // each chunk's per-wave tiles into isum and runs one epilogue over all items: per output row
 // block and member the items are summed in ascending order k, the same fp32 order as everywhere.
 // XM = 1: all items read one activation tensor; XM = 4: one stream per item of the chunk (its
@@ -478,6 +479,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
   static_assert(BIN_WORDS <= 64, "bin descriptor is fetched with one load per lane");
   __shared__ int part[NW][R][256];   // each wave's partial tiles of the current chunk
   __shared__ int isum[CAP][256];     // the bin's integer tiles, summed over the waves
+  __shared__ unsigned s_mx[2 * PIPE_MAX_K];   // the members' largest magnitudes, as above
   __shared__ int s_last;
 
   const int lane = threadIdx.x & 63;
@@ -519,6 +521,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
   auto stage_member_operands = [&]() __attribute__((always_inline)) {
     if ((int)threadIdx.x < p.M) s_sx[threadIdx.x] = my_sx;
     if (OFF && (int)threadIdx.x < p.M * 16) s_rs[threadIdx.x >> 4][threadIdx.x & 15] = my_rs;
+    if (threadIdx.x < 2 * PIPE_MAX_K) s_mx[threadIdx.x] = 0u;
   };
 
   // One chunk of R items streamed by WPC waves (wave slot wk of WPC takes tiles wk, wk+WPC, ...);
@@ -534,16 +537,15 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
       const uint8_t* wb[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) wb[r] = p.codes + (pos0 + r) * (size_t)n_tiles * 1024;
-      uint4 w0[R], w1[R], x0[NX], x1[NX];
+      uint4 w0[R], x0[NX];
       auto load_w = [&](int tl, uint4 (&w)[R]) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < R; ++r) w[r] = reinterpret_cast<const uint4*>(wb[r] + (size_t)tl * 1024)[lane];
       };
 #pragma unroll
-      for (int r = 0; r < R; ++r) { w0[r] = make_uint4(0, 0, 0, 0); w1[r] = make_uint4(0, 0, 0, 0); }
+      for (int r = 0; r < R; ++r) { w0[r] = make_uint4(0, 0, 0, 0); }
       int tl = tile_lo + wk;
       if (tl < tile_hi) load_w(tl, w0);
-      if (tl + wpc < tile_hi) load_w(tl + wpc, w1);
       const int n_items = word(0);
       const uint8_t* xb[XM];
 #pragma unroll
@@ -560,9 +562,8 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
           for (int j = 0; j < STEPS; ++j) x[s * STEPS + j] = reinterpret_cast<const uint4*>(xb[s] + (size_t)(tl * STEPS + j) * 1024)[lane];
       };
 #pragma unroll
-      for (int j = 0; j < NX; ++j) { x0[j] = make_uint4(0, 0, 0, 0); x1[j] = make_uint4(0, 0, 0, 0); }
+      for (int j = 0; j < NX; ++j) { x0[j] = make_uint4(0, 0, 0, 0); }
       if (tl < tile_hi) load_x(tl, x0);
-      if (tl + wpc < tile_hi) load_x(tl + wpc, x1);
       auto mul_tile = [&](uint4 (&w)[R], uint4 (&x)[NX]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < STEPS; ++j) {
@@ -576,13 +577,11 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
           }
         }
       };
-      for (; tl < tile_hi; tl += 2 * wpc) {
+      if (tl < tile_hi) mul_tile(w0, x0);
+      for (tl += wpc; tl < tile_hi; tl += wpc) {   // one tile in flight, as above
+        load_w(tl, w0);
+        load_x(tl, x0);
         mul_tile(w0, x0);
-        if (tl + 2 * wpc < tile_hi) { load_w(tl + 2 * wpc, w0); load_x(tl + 2 * wpc, x0); }
-        if (tl + wpc < tile_hi) {
-          mul_tile(w1, x1);
-          if (tl + 3 * wpc < tile_hi) { load_w(tl + 3 * wpc, w1); load_x(tl + 3 * wpc, x1); }
-        }
       }
     }
 #pragma unroll
@@ -675,18 +674,22 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
       if (p.amax_out != nullptr) {
         const bool two_sided = p.amax_neg != nullptr;
         float mx = tg < p.T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
-#pragma unroll
-        for (int s = 32; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-        if (lane == 0) slot_raise(&p.amax_out[m], mx);
+        mx = wave_max(mx);
+        if (lane == 0) atomicMax(&s_mx[m], __float_as_uint(mx));
         if (two_sided) {
           float mn = tg < p.T ? fmaxf(-v, 0.f) : 0.f;
-#pragma unroll
-          for (int s = 32; s > 0; s >>= 1) mn = fmaxf(mn, __shfl_xor(mn, s, 64));
-          if (lane == 0) slot_raise(&p.amax_neg[m], mn);
+          mn = wave_max(mn);
+          if (lane == 0) atomicMax(&s_mx[PIPE_MAX_K + m], __float_as_uint(mn));
         }
       }
       if (tg < p.T) p.y[((size_t)(p.reduce ? 0 : m) * p.T + tg) * p.out + col] = v;
     }
+  }
+  if (p.amax_out != nullptr) {   // one raise of a member's slot per workgroup
+    __syncthreads();
+    const int m = threadIdx.x & (PIPE_MAX_K - 1), neg = threadIdx.x / PIPE_MAX_K;
+    if (neg < (p.amax_neg != nullptr ? 2 : 1) && m < p.M)
+      slot_raise(neg ? &p.amax_neg[m] : &p.amax_out[m], __uint_as_float(s_mx[threadIdx.x]));
   }
 }
 
