@@ -850,15 +850,16 @@ static bool mlp_tiled(const pipe_expansion* l1, const pipe_expansion* l2, int ac
 
 // ... and for a chain of fully-connected layers, whose members hold at most 4 orders, us, streamed / tiled: six layers of 2048 x 2048 ternary, two members
 // of 2 orders, 64 tokens 75 / 92, 128 97.0 / 95.5; 4 bit, one of 4, 64 65 / 75, 100 88 / 76 (1024 wide, whose 16 steps of k are too short a walk, 63.4 / 68.9);
-// two of 4 (bins of 8: streamed in two chunks), 64 148 / 101, 128 198 / 110, 512 wide 64 83 / 66; one of 8 (pass by pass) 112 / 203.
+// two of 4 (bins of 8: streamed in two chunks), 64 92 / 100, 84 122 / 103, 128 130 / 109, 512 wide 64 67 / 64, 84 72.5 / 67.5; 4 bit, two of 3, 64 87 / 98,
+// 100 99 / 100; one of 8 (pass by pass) 112 / 203.
 static bool chain_tiled(const pipe_chain_layer* layers, int L, int T, const int* split, int M) {
-  if (!layers || L < 1 || g_kernel_choice != 0 || T <= 48 || T > PIPE_STREAM_MAX_T || M > 2) return false;
+  if (!layers || L < 1 || g_kernel_choice != 0 || T <= 64 || T > PIPE_STREAM_MAX_T || M > 2) return false;
   for (int l = 0; l < L; ++l) {
     const pipe_expansion* e = layers[l].e;
     if (!e || e->bits == 8 || layers[l].kh != 0) return false;
     if (split == nullptr || M < 2 ? e->K > 4 : (split[0] > 4 || split[1] > 4)) return false;
   }
-  return layers[0].e->K > 4 || (T > 64 && layers[0].e->nks >= 24);
+  return layers[0].e->K > 4 || layers[0].e->nks >= 24;
 }
 
 struct ActBuffers {
