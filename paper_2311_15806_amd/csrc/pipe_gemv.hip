@@ -115,7 +115,8 @@ __device__ __forceinline__ int part_word(int i) { return i + (i >> 6) * 16; }
 constexpr int QF_T = 16, QF_IN = 8192;   // tokens; codes of all tokens
 constexpr int QF_THREADS = 512;          // of a workgroup that quantizes, each up to QF_IN / 4 / QF_THREADS quads
 // What the first loads need comes as scalar arguments ahead of the struct: they are in registers with the launch, while the struct has to be
-// read from host memory.  Two to a word: a launch costs the host 0.01 us an argument.
+// read from host memory.  Two to a word: thirteen arguments cost the
+// host 0.15 us a launch, these eight 0.05 to 0.1 (256 x 256, where the host is all there is: 7.0 us before and 6.8 to 7.2 now).
 template <int BITS, int NW, int XM, bool ACC_OUT, bool XMASK, bool QFUSE = false>
 __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)) <= 8) ? 4 : 2) void gemm_stream_kernel(
     const uint8_t* a_codes, const StreamBin* a_bins, const void* a_x, uint64_t a_nb_t0, uint64_t a_t1_t2, uint64_t a_in_mg, uint64_t a_sp_T,
