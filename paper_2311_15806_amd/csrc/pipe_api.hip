@@ -1051,16 +1051,13 @@ extern "C" int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, 
 extern "C" int pipe_prepare(const pipe_expansion* e, const int* split, int M, int T_max, void* stream) {
   if (!e || T_max < 1) return PIPE_EINVAL;
   DryScope dry;
-  // the addresses are never dereferenced: nothing is launched in a dry run.  Two passes: the
-  // largest batch sizes the scratch, and whichever kernel serves it gets its schedule; batches
-  // up to T_max may also take the tiled kernel's path, whose schedule the second pass builds.
+  // the addresses are never dereferenced: nothing is launched in a dry run.  The largest batch sizes
+  // the scratch, and whichever kernel serves it gets its schedule; the second pass is the most tokens
+  // that the streaming kernel serves, which needs no schedule, whatever serves T_max.
   const float* fake_x = reinterpret_cast<const float*>(uintptr_t(256));
   float* fake_y = reinterpret_cast<float*>(uintptr_t(512));
   int rc = pipe_forward(e, fake_x, T_max, 1.f, split, M, nullptr, 1, fake_y, stream);
-  if (rc == PIPE_OK && T_max > PIPE_STREAM_MAX_T + 1)
-    rc = pipe_forward(e, fake_x, PIPE_STREAM_MAX_T + 1, 1.f, split, M, nullptr, 1, fake_y, stream);
-  if (rc == PIPE_OK && T_max <= PIPE_STREAM_MAX_T)   // fewer tokens may stream where T_max do not
-    rc = forward_impl(e, fake_x, T_max, 1.f, split, M, nullptr, 1, fake_y, stream);
+  if (rc == PIPE_OK) rc = forward_impl(e, fake_x, std::min(T_max, PIPE_STREAM_MAX_T), 1.f, split, M, nullptr, 1, fake_y, stream);
   return rc;
 }
 
@@ -1548,7 +1545,7 @@ static bool resident_eligible(const pipe_expansion* const* es, int L, int T, int
   if (!g_decode_resident || g_kernel_choice == 1) return false;
   // automatic: where it measured faster (short chains of few tokens only when no maxima are exchanged)
   if (g_decode_resident == 1 && L < 3 && T <= 8 && !given_scales) return false;   // (per layer against resident: gated MLP 4096 x 11008, 8 tokens 60.2 and 58.1 us, 16 tokens 66.7 and 60.9; GELU MLP 768 x 3072, one token 17.1 and 21.3, 9 tokens 22.2 and 21.6)
-  if (T < 1 || T > 16 || M > PIPE_RES_MAX_M || L > PIPE_RES_MAX_LAYERS) return false;
+  if (T < 1 || T > PIPE_RES_MAX_T || M > PIPE_RES_MAX_M || L > PIPE_RES_MAX_LAYERS) return false;
   if (es[0]->in % 4 != 0 || (reinterpret_cast<uintptr_t>(x_dev) & 15) != 0) return false;
   for (int l = 0; l < L; ++l)
     if (es[l]->bin_cap != 4 || es[l]->K > 4 || es[l]->bits != es[0]->bits) return false;
@@ -1664,7 +1661,9 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
       ls[1].e = l2; ls[1].bias = bias2_dev; ls[1].out = y_dev; ls[1].act = PIPE_ACT_NONE; ls[1].res_pre_act = 1;
       ls[1].s_in = s_h_host;
       rc = run_resident(ls, 2, x_dev, T, s_x, Mm, lo, hi, st);
-      if (rc != 1) return rc;   // 1: does not fit the resident kernel, per-layer launches below
+      // 1: does not fit the resident kernel, per-layer launches below (which a preparation sets up as well: fewer tokens, or an input of
+      // another alignment, take them)
+      if (rc != 1 && !(rc == PIPE_OK && pipe_dry_run())) return rc;
     }
   }
   // the tiled kernel pairs gate and up blocks in one workgroup and writes h directly; otherwise
@@ -1876,10 +1875,9 @@ extern "C" int pipe_prepare_mlp(const pipe_expansion* l1, const pipe_expansion* 
   const float* fake_x = reinterpret_cast<const float*>(uintptr_t(256));
   float* fake_y = reinterpret_cast<float*>(uintptr_t(512));
   int rc = pipe_mlp_forward(l1, l2, act, fake_x, T_max, 1.f, split, M, nullptr, nullptr, nullptr, fake_y, stream);
-  if (rc == PIPE_OK && T_max > PIPE_STREAM_MAX_T + 1)
-    rc = pipe_mlp_forward(l1, l2, act, fake_x, PIPE_STREAM_MAX_T + 1, 1.f, split, M, nullptr, nullptr, nullptr, fake_y, stream);
-  if (rc == PIPE_OK && T_max <= PIPE_STREAM_MAX_T)   // fewer tokens may stream where T_max do not
-    rc = mlp_forward_impl(l1, l2, act, fake_x, T_max, 1.f, nullptr, split, M, nullptr, nullptr, nullptr, fake_y, stream);
+  // the most tokens that the streaming kernel and the resident launch serve, whatever serves T_max
+  for (int T : {PIPE_STREAM_MAX_T, PIPE_RES_MAX_T})
+    if (rc == PIPE_OK) rc = mlp_forward_impl(l1, l2, act, fake_x, std::min(T, T_max), 1.f, nullptr, split, M, nullptr, nullptr, nullptr, fake_y, stream);
   return rc;
 }
 
@@ -2325,6 +2323,9 @@ extern "C" int pipe_prepare_chain(const pipe_chain_layer* layers, int L, int N, 
   float* fake_y = reinterpret_cast<float*>(uintptr_t(512));
   int rc = routed(H == 1 && W == 1 && chain_tiled(layers, L, N, split, M),
                   [&]() { return chain_forward_grid(layers, L, fake_x, N, H, W, 1.f, split, M, nullptr, fake_y, stream); });
-  if (rc == PIPE_OK) rc = chain_forward_grid(layers, L, fake_x, N, H, W, 1.f, split, M, nullptr, fake_y, stream);   // fewer tokens may stream where N do not
+  // the most tokens that the streaming kernel and the resident launch serve, whatever serves N
+  for (int T : {PIPE_STREAM_MAX_T, PIPE_RES_MAX_T})
+    if (rc == PIPE_OK && (T >= N || (H == 1 && W == 1)))
+      rc = chain_forward_grid(layers, L, fake_x, std::min(T, N), H, W, 1.f, split, M, nullptr, fake_y, stream);
   return rc;
 }

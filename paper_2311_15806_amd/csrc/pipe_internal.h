@@ -116,6 +116,7 @@ struct TileBins {
 //             items 0-3 the gate block's orders (slot 0), 4-7 the up block's (slot 1), order -1 = absent,
 //             out_rb = {hidden block, gate row block, up row block}
 constexpr int PIPE_RES_MAX_LAYERS = 16;
+constexpr int PIPE_RES_MAX_T = 16;        // tokens
 constexpr int PIPE_RES_MAX_G = 1024;      // workgroups of the resident kernel
 constexpr int PIPE_RES_FLAGS = 2048;      // its flag words: workgroups times copies
 constexpr int PIPE_RES_MAX_M = 2;

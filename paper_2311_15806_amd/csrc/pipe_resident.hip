@@ -1055,7 +1055,7 @@ int pipe_resident_workgroups() {
 }
 
 int launch_resident_chain(const ResidentArgs& a, hipStream_t st) {
-  if (a.L < 1 || a.L > PIPE_RES_MAX_LAYERS || a.T < 1 || a.T > 16 || a.M < 1 || a.M > PIPE_RES_MAX_M) return PIPE_ESHAPE;
+  if (a.L < 1 || a.L > PIPE_RES_MAX_LAYERS || a.T < 1 || a.T > PIPE_RES_MAX_T || a.M < 1 || a.M > PIPE_RES_MAX_M) return PIPE_ESHAPE;
   ResParams p;
   std::memset(&p, 0, sizeof(p));
   p.L = a.L; p.T = a.T; p.M = a.M; p.G = a.G;

@@ -403,3 +403,37 @@ def test_two_expansions_on_two_streams_at_once():
         assert torch.equal(outs_a[rep], ref_a[rep % 2]), "stream a, call %d" % rep
         assert torch.equal(outs_b[2 * rep], ref_b[rep % 2]) and torch.equal(outs_b[2 * rep + 1], ref_b[(rep + 1) % 2])
     ga.free(); gb.free()
+
+
+@pytest.mark.parametrize("T", [7, 16, 64, 100])
+def test_capture_of_fewer_tokens_than_prepared(T):
+    """A gated MLP and a chain prepared for 300 tokens: calls of fewer, which other kernels serve, are captured with no eager call before."""
+    import paper_2311_15806_amd.binding as pipe
+    w = wl.scaled(wl.C5, out_div=8, in_div=8, tokens=300)
+    wc = wl.residual_stack(128, 2, 64, 4, 4, 0.5, 16, 300, (2, 2))
+    es, gs = ([pipe.pipe_expand(torch.from_numpy(wl.make_weight(v, l)).cuda(), s.bits, s.K, s.gamma, s.group)
+               for l, s in enumerate(v.layers)] for v in (w, wc))
+    act = {"none": 0, "gelu": 1, "relu": 3}
+    layers = [(g, None, act[c[0]], c[1], c[2]) for g, c in zip(gs, wc.chain)]
+    xs = [torch.from_numpy(wl.make_input(v)).cuda()[:T].contiguous() for v in (w, wc)]
+    outs = [torch.empty((T, v.layers[-1].out_features), device="cuda") for v in (w, wc)]
+    split = list(w.split)
+    prepare = (lambda: pipe.pipe_prepare_mlp(es[0], es[1], pipe.PIPE_ACT_SILU_GATED, 300, split=split),
+               lambda: pipe.pipe_prepare_chain(layers, 300, split=[2, 2]))
+    call = (lambda out: pipe.pipe_mlp_forward(es[0], es[1], pipe.PIPE_ACT_SILU_GATED, xs[0], split=split, out=out),
+            lambda out: pipe.pipe_chain_forward(layers, xs[1], split=[2, 2], out=out))
+    for i in range(2):
+        side = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            prepare[i]()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            call[i](outs[i])
+        for rep in range(3):
+            outs[i].zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(outs[i], call[i](None))
+    for e in es + gs:
+        e.free()

@@ -13,6 +13,10 @@ import _host_hip
 ENOTREADY, ENOMEM = -6, -3
 
 
+class Layer(C.Structure):   # pipe_chain_layer
+    _fields_ = [("e", C.c_void_p), ("bias", C.c_void_p), ("act", C.c_int), ("skip", C.c_int), ("pre_act", C.c_int), ("conv", C.c_int * 4), ("s_in", C.c_void_p)]
+
+
 def _linear(rt, e, T, split=None, reduce=1):
     rt.lib.pipe_forward.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_float, C.c_void_p, C.c_int, C.c_void_p, C.c_int] + [C.c_void_p] * 2
     arr = (C.c_int * len(split))(*split) if split else None
@@ -208,9 +212,6 @@ def tiles_follow_the_units_they_leave(rt):
         assert rt.lib.pipe_forward_conv2d(e, 1 << 40, N, Ch, H, H, 3, 3, 1, 1, 0, 0.0, None, 0, None, 1, 1 << 44, None) == 0
         assert _tile(rt.names()) == want, (rows, Ch, N, bits)
 
-    class Layer(C.Structure):   # pipe_chain_layer
-        _fields_ = [("e", C.c_void_p), ("bias", C.c_void_p), ("act", C.c_int), ("skip", C.c_int), ("pre_act", C.c_int), ("conv", C.c_int * 4), ("s_in", C.c_void_p)]
-
     rt.lib.pipe_chain_forward.argtypes = [C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 3
     for width, T, want in ((1024, 1000, (4, 4, 1, 2)), (1024, 1100, (4, 4, 1, 1)), (1536, 700, (4, 4, 1, 2))):   # 256, 288 and 264 tiles of 64
         e = rt.expand(width, width, 4, 4, 1.0, 16)
@@ -279,11 +280,50 @@ def unprepared_batches_stream(rt):
     rt.host.host_capture(0)
 
 
+def prepared_calls_allocate_nothing(rt):
+    """After a preparation for T_max tokens every call of no more is served under capture: tiled, streamed (a gated layer's raw outputs
+    have a buffer of their own there), in one resident launch, and from inputs that the resident launch does not take."""
+    mlp, chain, prep_mlp, prep_chain = (getattr(rt.lib, "pipe_" + n) for n in ("mlp_forward", "chain_forward", "prepare_mlp", "prepare_chain"))
+    mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 5
+    prep_mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_int, C.c_void_p]
+    chain.argtypes = [C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 3
+    prep_chain.argtypes = [C.c_void_p] + [C.c_int] * 4 + [C.c_void_p, C.c_int, C.c_void_p]
+
+    def captured(call, t_max, stream, what):
+        for T in sorted({1, 8, 9, 16, 17, 33, 64, 65, 100, 112, 113, 128, 129, 200, t_max}):
+            if T > t_max:
+                break
+            for x in (1 << 40, (1 << 40) + 4):
+                rt.host.host_fail(0)
+                rt.host.host_capture(1)
+                rc = call(T, x, stream)
+                rt.host.host_capture(0)
+                assert (rc, rt.host.host_mallocs()) == (0, 0), (what, t_max, T, x & 15, rc)
+
+    stream = 0
+    for t_max in (6, 16, 40, 100, 128, 129, 130, 300):
+        for act, split in ((2, (2, 2)), (2, (3, 1)), (2, None), (1, (2, 2)), (1, None)):
+            K = sum(split) if split else 3
+            l1, l2 = rt.expand((2 if act == 2 else 1) * 512, 320, 4, K, 1.0, 16), rt.expand(320, 512, 4, K, 1.0, 16)
+            arr, M = ((C.c_int * len(split))(*split), len(split)) if split else (None, 0)
+            stream += 4096                        # one that nobody has used
+            assert prep_mlp(l1, l2, act, arr, M, t_max, stream) == 0
+            captured(lambda T, x, st: mlp(l1, l2, act, x, T, 0.0, arr, M, None, None, None, 1 << 44, st), t_max, stream, (act, split))
+        for K, split in ((4, (2, 2)), (3, None), (8, (4, 4))):
+            arr, M = ((C.c_int * len(split))(*split), len(split)) if split else (None, 0)
+            es = [rt.expand(320, 320, 4, K, 1.0, 16) for _ in range(3)]
+            layers = (Layer * 3)(*[Layer(e, None, 0, -1) for e in es])
+            stream += 4096
+            assert prep_chain(layers, 3, t_max, 1, 1, arr, M, stream) == 0
+            captured(lambda T, x, st: chain(layers, 3, x, T, 0.0, arr, M, None, 1 << 44, st), t_max, stream, ("chain", split))
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
                                       "any_number_of_images_is_served", "wide_layers_quantize_once",
                                       "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave",
-                                      "a_sum_over_two_members_is_a_launch_each", "unprepared_batches_stream"])
+                                      "a_sum_over_two_members_is_a_launch_each", "unprepared_batches_stream",
+                                      "prepared_calls_allocate_nothing"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
