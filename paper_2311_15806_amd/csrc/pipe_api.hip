@@ -792,30 +792,28 @@ const TileBins* pipe_get_bins(const pipe_expansion* ce, const GemmArgs& a, int* 
 }
 
 // ------------------------------------------------------------------ forward
-// This call's 17 to 128 tokens go to the tiled kernels (see routed)
-static thread_local bool t_tiled = false;
+// How a call runs: whether its 17 to 128 tokens go to the tiled kernels, and, set by the call, whether its schedules and scratch are there
+// and it has begun to launch.
+struct Route {
+  bool tiled, begun;
+};
 constexpr int STREAM_ONLY_T = 16;   // batches that stream whatever the layer
 
-static bool use_stream_kernel(const pipe_expansion* e, int T, bool acc_out = false) {
+static bool use_stream_kernel(const pipe_expansion* e, int T, bool acc_out = false, bool tiled = false) {
   if (g_kernel_choice == 1) return false;
   if (e->K > 4 && acc_out) return false;   // bins of more than 4 items have no integer export
-  return T <= PIPE_STREAM_MAX_T && !(t_tiled && T > STREAM_ONLY_T);
+  return T <= PIPE_STREAM_MAX_T && !(tiled && T > STREAM_ONLY_T);
 }
 
-// Runs a call whose 17 to 128 tokens the tiled kernels serve faster with those; where their schedules or scratch are not there (under
-// capture, or for want of memory), with the streaming kernel, which needs neither.  Both give the same bits.  A call fails for these
-// reasons before it has launched anything.
+// Runs a call whose 17 to 128 tokens the tiled kernels serve faster with those; where it cannot begin, because their schedules or scratch are
+// not there (under capture, or for want of memory), with the streaming kernel, which needs neither.  Both give the same bits.
 template <class Call>
 static int routed(bool tiled, Call call) {
-  if (tiled) {
-    struct Route {
-      Route() { t_tiled = true; }
-      ~Route() { t_tiled = false; }
-    } route;
-    const int rc = call();
-    if (rc != PIPE_ENOTREADY && rc != PIPE_ENOMEM && rc != PIPE_EDEVICE) return rc;
-  }
-  return call();
+  Route route{tiled, false};
+  const int rc = call(route);
+  if (!tiled || route.begun || (rc != PIPE_ENOTREADY && rc != PIPE_ENOMEM && rc != PIPE_EDEVICE)) return rc;
+  route.tiled = false;
+  return call(route);
 }
 
 // Where 17 to 128 tokens are tiled: the streaming kernel runs a workgroup per bin and 16 tokens, each along the whole of k, the tiled one walks along k
@@ -1011,7 +1009,7 @@ static void fill_members(GemmArgs& a, int M, const int* lo, const int* hi) {
 }
 
 static int forward_impl(const pipe_expansion* e, const float* x_dev, int T, float s_x, const int* split, int M, const float* bias_dev,
-                        int reduce_members, float* y_dev, void* stream) {
+                        int reduce_members, float* y_dev, void* stream, Route& route) {
   if (!e || T < 0) return PIPE_EINVAL;
   if (e->conv_C > 0) return PIPE_EINVAL;   // stored tap-major: only the convolution entry points read it
   int lo[PIPE_MAX_K], hi[PIPE_MAX_K], Mm = 1;
@@ -1021,11 +1019,12 @@ static int forward_impl(const pipe_expansion* e, const float* x_dev, int T, floa
   if (!x_dev || !y_dev) return PIPE_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   CallScope scope(stream);
-  const bool small = use_stream_kernel(e, T);
+  const bool small = use_stream_kernel(e, T, false, route.tiled);
   ActBuffers b;
   rc = get_act_buffers(T, e->in_pad, small, &b);
   if (rc) return rc;
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
+  route.begun = true;
   const bool fused = fuse_decode_quant(e, T, x_dev, small, y_dev, (size_t)(reduce_members ? 1 : Mm) * T * e->out);
   if (!fused) {
     rc = quantize_input(e, x_dev, T, s_x, b, nullptr, b.scale, st);
@@ -1045,7 +1044,7 @@ extern "C" int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, 
                             const int* split, int M, const float* bias_dev, int reduce_members,
                             float* y_dev, void* stream) {
   return routed(linear_tiled(e, T, M, reduce_members),
-                [&]() { return forward_impl(e, x_dev, T, s_x, split, M, bias_dev, reduce_members, y_dev, stream); });
+                [&](Route& r) { return forward_impl(e, x_dev, T, s_x, split, M, bias_dev, reduce_members, y_dev, stream, r); });
 }
 
 extern "C" int pipe_prepare(const pipe_expansion* e, const int* split, int M, int T_max, void* stream) {
@@ -1057,7 +1056,8 @@ extern "C" int pipe_prepare(const pipe_expansion* e, const int* split, int M, in
   const float* fake_x = reinterpret_cast<const float*>(uintptr_t(256));
   float* fake_y = reinterpret_cast<float*>(uintptr_t(512));
   int rc = pipe_forward(e, fake_x, T_max, 1.f, split, M, nullptr, 1, fake_y, stream);
-  if (rc == PIPE_OK) rc = forward_impl(e, fake_x, std::min(T_max, PIPE_STREAM_MAX_T), 1.f, split, M, nullptr, 1, fake_y, stream);
+  Route streamed{};
+  if (rc == PIPE_OK) rc = forward_impl(e, fake_x, std::min(T_max, PIPE_STREAM_MAX_T), 1.f, split, M, nullptr, 1, fake_y, stream, streamed);
   return rc;
 }
 
@@ -1239,7 +1239,7 @@ static int asym_quantize(const pipe_expansion* e, const float* x_dev, int T, con
 }
 
 static int forward_asym_impl(const pipe_expansion* e, const float* x_dev, int T, const int* split, int M,
-                             const float* bias_dev, float* y_dev, void* stream) {
+                             const float* bias_dev, float* y_dev, void* stream, Route& route) {
   if (!e || T < 0) return PIPE_EINVAL;
   if (e->conv_C > 0) return PIPE_EINVAL;   // stored tap-major: only the convolution entry points read it
   int lo[PIPE_MAX_K], hi[PIPE_MAX_K], Mm = 1;
@@ -1251,11 +1251,12 @@ static int forward_asym_impl(const pipe_expansion* e, const float* x_dev, int T,
   CallScope scope(stream);
   rc = asym_prepare(e, st);
   if (rc) return rc;
-  const bool small = use_stream_kernel(e, T);
+  const bool small = use_stream_kernel(e, T, false, route.tiled);
   ActBuffers b;
   rc = get_act_buffers(T, e->in_pad, small, &b);
   if (rc) return rc;
   if (!small && (rc = ensure_tables(e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
+  route.begun = true;
   int32_t* dz = nullptr;
   rc = asym_quantize(e, x_dev, T, b, nullptr, &dz, st, bias_dev, e->asym_C_dev);
   if (rc) return rc;
@@ -1269,7 +1270,7 @@ static int forward_asym_impl(const pipe_expansion* e, const float* x_dev, int T,
 
 extern "C" int pipe_forward_asymmetric(const pipe_expansion* e, const float* x_dev, int T, const int* split, int M,
                                        const float* bias_dev, float* y_dev, void* stream) {
-  return routed(linear_tiled(e, T, M, 1), [&]() { return forward_asym_impl(e, x_dev, T, split, M, bias_dev, y_dev, stream); });
+  return routed(linear_tiled(e, T, M, 1), [&](Route& r) { return forward_asym_impl(e, x_dev, T, split, M, bias_dev, y_dev, stream, r); });
 }
 
 extern "C" int pipe_forward_conv2d_asymmetric(const pipe_expansion* e, const float* x_dev, int N, int C, int H, int W,
@@ -1621,7 +1622,7 @@ extern "C" int pipe_resident_status(void* stream, int* status_out) {
 static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, int act,
                             const float* x_dev, int T, float s_x, const float* s_h_host, const int* split, int M,
                             const float* bias1_dev, const float* bias2_dev, float* h_dev,
-                            float* y_dev, void* stream) {
+                            float* y_dev, void* stream, Route& route) {
   if (!l1 || !l2 || T < 0) return PIPE_EINVAL;
   if (l1->conv_C > 0 || l2->conv_C > 0) return PIPE_EINVAL;
   if (act != PIPE_ACT_GELU && act != PIPE_ACT_SILU_GATED) return PIPE_EINVAL;
@@ -1638,7 +1639,7 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
   if (!x_dev || !y_dev) return PIPE_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   CallScope scope(stream);
-  const bool small = use_stream_kernel(l1, T);   // both layers have the same K
+  const bool small = use_stream_kernel(l1, T, false, route.tiled);   // both layers have the same K
   ActBuffers b;
   rc = get_act_buffers(T, l1->in_pad, small, &b);
   if (rc) return rc;
@@ -1678,6 +1679,7 @@ static int mlp_forward_impl(const pipe_expansion* l1, const pipe_expansion* l2, 
     if ((rc = ensure_tables(l1, Mm, lo, hi, paired ? 1 : 0)) != PIPE_OK) return rc;
     if ((rc = ensure_tables(l2, Mm, lo, hi, 0)) != PIPE_OK) return rc;
   }
+  route.begun = true;
   if (pipe_dry_run()) return PIPE_OK;
 
   const bool fused = fuse_decode_quant(l1, T, x_dev, small, h, (size_t)Mm * T * H);
@@ -1853,8 +1855,8 @@ extern "C" int pipe_mlp_forward(const pipe_expansion* l1, const pipe_expansion* 
                                 const float* x_dev, int T, float s_x, const int* split, int M,
                                 const float* bias1_dev, const float* bias2_dev, float* h_dev,
                                 float* y_dev, void* stream) {
-  return routed(mlp_tiled(l1, l2, act, T, split, M), [&]() {
-    return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, nullptr, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream);
+  return routed(mlp_tiled(l1, l2, act, T, split, M), [&](Route& r) {
+    return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, nullptr, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream, r);
   });
 }
 
@@ -1863,8 +1865,8 @@ extern "C" int pipe_mlp_forward_given_scales(const pipe_expansion* l1, const pip
                                              int M, const float* bias1_dev, const float* bias2_dev, float* h_dev,
                                              float* y_dev, void* stream) {
   if (!(s_x > 0.f) || s_h_host == nullptr) return PIPE_EINVAL;
-  return routed(mlp_tiled(l1, l2, act, T, split, M), [&]() {
-    return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, s_h_host, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream);
+  return routed(mlp_tiled(l1, l2, act, T, split, M), [&](Route& r) {
+    return mlp_forward_impl(l1, l2, act, x_dev, T, s_x, s_h_host, split, M, bias1_dev, bias2_dev, h_dev, y_dev, stream, r);
   });
 }
 
@@ -1876,8 +1878,9 @@ extern "C" int pipe_prepare_mlp(const pipe_expansion* l1, const pipe_expansion* 
   float* fake_y = reinterpret_cast<float*>(uintptr_t(512));
   int rc = pipe_mlp_forward(l1, l2, act, fake_x, T_max, 1.f, split, M, nullptr, nullptr, nullptr, fake_y, stream);
   // the most tokens that the streaming kernel and the resident launch serve, whatever serves T_max
+  Route streamed{};
   for (int T : {PIPE_STREAM_MAX_T, PIPE_RES_MAX_T})
-    if (rc == PIPE_OK) rc = mlp_forward_impl(l1, l2, act, fake_x, std::min(T, T_max), 1.f, nullptr, split, M, nullptr, nullptr, nullptr, fake_y, stream);
+    if (rc == PIPE_OK) rc = mlp_forward_impl(l1, l2, act, fake_x, std::min(T, T_max), 1.f, nullptr, split, M, nullptr, nullptr, nullptr, fake_y, stream, streamed);
   return rc;
 }
 
@@ -1920,7 +1923,7 @@ static int chain_tensors(const pipe_chain_layer* layers, int L, int Mm, const st
 }
 
 static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float* x_dev, int N, int H0, int W0,
-                              float s_x, const int* split, int M, float* const* acts_dev, float* y_dev, void* stream) {
+                              float s_x, const int* split, int M, float* const* acts_dev, float* y_dev, void* stream, Route& route) {
   if (!layers || L < 1 || N < 0 || H0 < 1 || W0 < 1) return PIPE_EINVAL;
   std::vector<int> Hin(L + 1), Win(L + 1), Cin(L);
   std::vector<int64_t> Tin(L + 1);
@@ -1965,7 +1968,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
   int T_pad_max = 0;
   size_t qh_bytes = 0, q8_bytes = 0;
   for (int l = 0; l < L; ++l) {
-    small[l] = use_stream_kernel(layers[l].e, (int)Tin[l + 1]);
+    small[l] = use_stream_kernel(layers[l].e, (int)Tin[l + 1], false, route.tiled);
     Tpad[l] = (int)round_up64(Tin[l + 1], small[l] ? 16 : TOK_TILE);
     T_pad_max = std::max(T_pad_max, Tpad[l]);
     if (l > 0) qh_bytes = std::max(qh_bytes, (size_t)Mm * Tpad[l] * layers[l].e->in_pad);
@@ -2024,6 +2027,7 @@ static int chain_forward_grid(const pipe_chain_layer* layers, int L, const float
   }
   for (int l = 0; l < L; ++l)
     if (!small[l] && (rc = ensure_tables(layers[l].e, Mm, lo, hi, 0)) != PIPE_OK) return rc;
+  route.begun = true;
   if (pipe_dry_run()) return PIPE_OK;
   if (t_ws->slots_dirty) {
     rc = launch_zero_u32(b.slots, PIPE_SLOT_LINES * PIPE_SLOT_WORDS, st);
@@ -2126,14 +2130,14 @@ extern "C" int pipe_chain_forward(const pipe_chain_layer* layers, int L, const f
   for (int l = 0; l < L; ++l)
     if (layers[l].kh != 0 || layers[l].kw != 0) return PIPE_EINVAL;   // convolution layers need the grid: pipe_chain_forward_conv
   return routed(chain_tiled(layers, L, T, split, M),
-                [&]() { return chain_forward_grid(layers, L, x_dev, T, 1, 1, s_x, split, M, acts_dev, y_dev, stream); });
+                [&](Route& r) { return chain_forward_grid(layers, L, x_dev, T, 1, 1, s_x, split, M, acts_dev, y_dev, stream, r); });
 }
 
 extern "C" int pipe_chain_forward_conv(const pipe_chain_layer* layers, int L, const float* x_dev, int N, int H, int W,
                                        float s_x, const int* split, int M, float* const* acts_dev, float* y_dev,
                                        void* stream) {
   return routed(H == 1 && W == 1 && chain_tiled(layers, L, N, split, M),
-                [&]() { return chain_forward_grid(layers, L, x_dev, N, H, W, s_x, split, M, acts_dev, y_dev, stream); });
+                [&](Route& r) { return chain_forward_grid(layers, L, x_dev, N, H, W, s_x, split, M, acts_dev, y_dev, stream, r); });
 }
 
 // Member chains with asymmetric activation codes (Sec. 4.3): the same driver as above for fully-connected
@@ -2322,10 +2326,11 @@ extern "C" int pipe_prepare_chain(const pipe_chain_layer* layers, int L, int N, 
   const float* fake_x = reinterpret_cast<const float*>(uintptr_t(256));
   float* fake_y = reinterpret_cast<float*>(uintptr_t(512));
   int rc = routed(H == 1 && W == 1 && chain_tiled(layers, L, N, split, M),
-                  [&]() { return chain_forward_grid(layers, L, fake_x, N, H, W, 1.f, split, M, nullptr, fake_y, stream); });
+                  [&](Route& r) { return chain_forward_grid(layers, L, fake_x, N, H, W, 1.f, split, M, nullptr, fake_y, stream, r); });
   // the most tokens that the streaming kernel and the resident launch serve, whatever serves N
+  Route streamed{};
   for (int T : {PIPE_STREAM_MAX_T, PIPE_RES_MAX_T})
     if (rc == PIPE_OK && (T >= N || (H == 1 && W == 1)))
-      rc = chain_forward_grid(layers, L, fake_x, std::min(T, N), H, W, 1.f, split, M, nullptr, fake_y, stream);
+      rc = chain_forward_grid(layers, L, fake_x, std::min(T, N), H, W, 1.f, split, M, nullptr, fake_y, stream, streamed);
   return rc;
 }

@@ -18,13 +18,14 @@ typedef void (*launch_fn)(const char* name, uint32_t gx, uint32_t gy, uint32_t g
 static struct { const void* f; const char* name; } reg[4096];
 static int n_reg;
 static launch_fn on_launch;
-static long mallocs, fail_at;
+static long mallocs, fail_at, launches, fail_launch;
 static int capturing;
 static grid_t cfg_g, cfg_b;
 static size_t cfg_shmem;
 static void* cfg_st;
 void host_set(launch_fn f) { on_launch = f; }
 void host_fail(long nth) { mallocs = 0; fail_at = nth; }     /* the nth allocation from now on fails; 0: none */
+void host_fail_launch(long nth) { launches = 0; fail_launch = nth; }   /* the same of launches */
 long host_mallocs(void) { return mallocs; }
 void host_capture(int on) { capturing = on; }
 void** __hipRegisterFatBinary(const void* d) { static void* h; (void)d; return &h; }
@@ -41,6 +42,8 @@ int __hipPopCallConfiguration(grid_t* g, grid_t* b, size_t* s, void** st) { *g =
 static int last;
 int hipLaunchKernel(const void* f, grid_t g, grid_t b, void** args, size_t s, void* st) {
   (void)s; (void)st;
+  ++launches;
+  if (fail_launch > 0 && launches == fail_launch) return last = 9;
   /* the runtime's limit: fewer than 2^32 threads in x */
   if (g.x == 0 || g.y == 0 || g.z == 0 || g.y > 65535 || g.z > 65535 || (uint64_t)g.x * b.x >= (1ull << 32)) return last = 9;
   for (int i = 0; i < n_reg; ++i)
@@ -93,7 +96,7 @@ class Runtime:
 
     def __init__(self, shim):
         self.host = C.CDLL(shim, mode=os.RTLD_GLOBAL | os.RTLD_NOW)
-        self.host.host_fail.argtypes = [C.c_long]
+        self.host.host_fail.argtypes = self.host.host_fail_launch.argtypes = [C.c_long]
         self.host.host_mallocs.restype = C.c_long
         self.lib = C.CDLL(LIB)
         self.launches = []

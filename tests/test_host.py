@@ -10,7 +10,7 @@ import pytest
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import _host_hip
 
-ENOTREADY, ENOMEM = -6, -3
+ENOTREADY, EDEVICE, ENOMEM = -6, -4, -3
 
 
 class Layer(C.Structure):   # pipe_chain_layer
@@ -318,12 +318,42 @@ def prepared_calls_allocate_nothing(rt):
             captured(lambda T, x, st: chain(layers, 3, x, T, 0.0, arr, M, None, 1 << 44, st), t_max, stream, ("chain", split))
 
 
+def failed_launches_are_reported(rt):
+    """A launch that fails in the middle of a call of 17 to 128 tokens on the tiled kernels ends the call with its error: no kernel is sent
+    behind it, and the next call starts with the maxima cleared."""
+    mlp, chain = rt.lib.pipe_mlp_forward, rt.lib.pipe_chain_forward
+    mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 5
+    chain.argtypes = [C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 3
+    rt.lib.pipe_forward_asymmetric.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int] + [C.c_void_p] * 3
+    wide = rt.expand(8192, 320, 4, 2, 1.0, 16)
+    l1, l2 = rt.expand(22016, 320, 4, 4, 1.0, 16), rt.expand(320, 11008, 4, 4, 1.0, 16)
+    es = [rt.expand(1536, 1536, 4, 4, 1.0, 16) for _ in range(3)]
+    layers, one = (Layer * 3)(*[Layer(e, None, 0, -1) for e in es]), (C.c_int * 1)(4)
+    calls = {"linear": lambda: _linear(rt, wide, 100),
+             "asymmetric": lambda: rt.lib.pipe_forward_asymmetric(wide, 1 << 40, 100, None, 0, None, 1 << 44, None),
+             "mlp": lambda: mlp(l1, l2, 2, 1 << 40, 100, 0.0, None, 0, None, None, None, 1 << 44, None),
+             "chain": lambda: chain(layers, 3, 1 << 40, 100, 0.0, one, 1, None, 1 << 44, None)}
+    for what, call in calls.items():
+        assert call() == 0
+        rt.names()
+        assert call() == 0
+        whole = [n for n in rt.names() if "kernel" in n]
+        assert any("gemm_bins_kernel" in n for n in whole) and not any("gemm_stream" in n for n in whole), whole
+        for nth in range(1, len(whole) + 1):
+            rt.host.host_fail_launch(nth)
+            assert call() == EDEVICE, (what, nth)
+            assert rt.names() == whole[:nth - 1], (what, nth)
+            rt.host.host_fail_launch(0)
+            assert call() == 0
+            assert [n for n in rt.names() if "zero_u32" not in n] == whole, (what, nth)
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
                                       "any_number_of_images_is_served", "wide_layers_quantize_once",
                                       "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave",
                                       "a_sum_over_two_members_is_a_launch_each", "unprepared_batches_stream",
-                                      "prepared_calls_allocate_nothing"])
+                                      "prepared_calls_allocate_nothing", "failed_launches_are_reported"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
