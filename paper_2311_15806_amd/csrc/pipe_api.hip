@@ -833,31 +833,58 @@ static bool single_order(const int* split, int M) {
   return false;
 }
 
-// The same for a two-layer MLP (a gated one also saves the launch that multiplies SiLU(gate) into up; the sum over members of a single
-// order runs pass by pass).  Calls, us, streamed / tiled:
-//   gated, one member: 2048-5504-2048 4 bit, K = 3, 64 tokens 38.6 / 40.4, 100 50.4 / 43.8; 4096-11008 64 76.5 / 84.3, 100 112 / 97; ternary 64 55.4 / 72.7,
-//   100 81.7 / 80.6, 128 89.1 / 81.0; two of two orders: 4096-11008 4 bit 36 tokens 92 / 105, 64 110 / 107, 100 152 / 116; 2048-5504 64 48.9 / 51.5, 100 65.4 / 52.5;
-//   of 2 and 1: 4096-11008 100 130 / 125, 128 151 / 126; 2048-5504 100 55.8 / 59.0, 128 63.1 / 59.5;
-//   GELU, one member: 768-3072 ternary, 64 tokens 22.9 / 24.7, 100 27.2 / 26.6; two of two orders: 1024-4096 4 bit, 100 36.8 / 41.5, 128 37.9 / 41.7; of 2 and 1: 128 31.5 / 44.7.
+// The same for a two-layer MLP from 65 tokens on.  What the tiled kernels lose they lose in the second layer, whose walk is the longer and whose
+// rows are the fewer, above all where the sum over two members runs pass by pass (pipe_sum_apply: below 48 steps of k, or few tiles of a
+// single order).  With few hidden channels a call is bound by its launches, of which tiles take one less (gated) or the shorter ones.
+// Calls, us, streamed / tiled (K = 3 or 4, half kept, unless said):
+//   GELU, one member (two never: 1024-4096 2 and 2, 128 tokens 37.1 / 41.9): 128-256 65 23 / 22, 256-1024 65 20.3 / 19.9, 512-2048 22.1 / 22.5, 576-2304 ternary 100 24.6 / 26.9;
+//   768-3072 4 bit 65 25.4 / 27.4, 97 28.3 / 27.7; 1024-4096 ternary 65 27.3 / 28.6, 97 31.0 / 30.1; 1280-5120, all kept, 74 35.4 / 31.0; 2048-8192 65 36 / 39, 4 bit 97 44.0 / 39.5;
+//   gated, one member: 128-256 65 26.1 / 24.3; 512-1024, K = 2, 90 27.8 / 22.9; 576-1152 4 bit 72 29.0 / 31.1; 1024-2752 65 31.7 / 31.9; 2048-5504 64 38.0 / 40.0, 65 43.1 / 40.2, 4096-11008 65 78 / 64;
+//   two of two orders, 4 bit: 1024-2752 65 37.4 / 45.3, 113 44.7 / 46.3; 1408-2816, all kept, 81 44 / 58; 2048-5504 65 51.6 / 51.7, 97 66.3 / 52.4; 4096-11008 65 104 / 86;
+//   ternary: 1024-2752 80 37 / 43, 97 43 / 41; 2048-5504 65 51 / 50, 97 65 / 51;
+//   2 and 1: 1024-2752 80 35 / 36, 113 42 / 36; 4096-11008 80 83 / 87, 113 114 / 89; 4 bit: 512-1376 113 34 / 31; 2048-5504 97 57 / 59, 113 63 / 59; 1472-5888, a quarter kept, 126 57 / 67.
 static bool mlp_tiled(const pipe_expansion* l1, const pipe_expansion* l2, int act, int T, const int* split, int M) {
-  if (!l1 || !l2 || g_kernel_choice != 0 || T > PIPE_STREAM_MAX_T || M > 2 || l1->bin_cap != 4 || l2->bin_cap != 4 || l1->bits == 8 || l2->bits == 8) return false;
-  const bool two = split != nullptr && M == 2;
-  if (act == PIPE_ACT_SILU_GATED) return l1->n_rb % 2 == 0 && T > (two && single_order(split, M) ? 112 : 64);
-  return T > 64 && !two;
+  if (!l1 || !l2 || g_kernel_choice != 0 || T <= 64 || T > PIPE_STREAM_MAX_T || M > 2 || l1->bin_cap != 4 || l2->bin_cap != 4 || l1->bits == 8 || l2->bits == 8) return false;
+  const bool two = split != nullptr && M == 2, short_walk = l2->nks < 48;
+  auto surplus = [T](const pipe_expansion* e) {   // twice the streaming kernel's workgroups beyond the line of linear_tiled, times the steps of k that each walks
+    return (2 * (int64_t)e->n_bins * ceil_div(T, 16) - 800 - (e->bits == 4 ? 1 : 5) * e->nks) * e->nks;
+  };
+  if (act != PIPE_ACT_SILU_GATED) return !two && (short_walk || T > 96 || surplus(l1) + surplus(l2) >= 0);
+  if (l1->n_rb % 2 != 0) return false;
+  if (!two) return true;
+  if (single_order(split, M)) return T > 112 && (l2->bits != 4 || short_walk || 2 * l2->n_bins * ceil_div(T, 16) >= 1000);
+  return l2->nks <= 8 || (l2->bits == 4 ? !short_walk && linear_tiled(l2, T, 1, 1) : !short_walk || T > 96);
 }
 
-// ... and for a chain of fully-connected layers, whose members hold at most 4 orders, us, streamed / tiled: six layers of 2048 x 2048 ternary, two members
-// of 2 orders, 64 tokens 75 / 92, 128 97.0 / 95.5; 4 bit, one of 4, 64 65 / 75, 100 88 / 76 (1024 wide, whose 16 steps of k are too short a walk, 63.4 / 68.9);
-// two of 4 (bins of 8: streamed in two chunks), 64 92 / 100, 84 122 / 103, 128 130 / 109, 512 wide 64 67 / 64, 84 72.5 / 67.5; 4 bit, two of 3, 64 87 / 98,
-// 100 99 / 100; one of 8 (pass by pass) 112 / 203.
+// ... and for a chain of fully-connected layers, whose members hold at most 4 orders.  Up to 4 orders: the workgroups of the streaming kernel as above,
+// summed over the layers by the steps of k that each walks; of two members the last layer's sum costs more.  us, streamed / tiled, chains of six layers:
+//   2048 wide, ternary, one member of 4 65 tokens 73 / 81, 97 88 / 82; 4 bit 65 74 / 78, 97 95 / 80; 1024 97 70 / 75; seven of 2304, K = 3, 103 85.5 / 95.5; four of 4096, K = 4, 65 75 / 66;
+//   two of two: ternary 80 79 / 95, 97 98 / 96, 113 104 / 96; three of 1600, all kept, 108 48.5 / 55.5; four of 4096 65 84 / 81; 4 bit 65 82 / 95, 97 101 / 98; 2 and 1, 128 89 / 93;
+//   four of 3776, ternary, 2 and 1, 91 77 / 87.
+// Two of up to 8 orders in bins of 8, which are streamed in two chunks: tiles gain in each layer what the last one's sum, pass by pass below 48 steps of k, loses
+// in about three layers where half is kept, and in more where a row block has more orders; chains of longer walks are tiled whatever their length:
+//   ternary, 512 wide 65 77 / 71; 1024 80 80 / 81, 128 87 / 83, three layers 40 / 46 and 44 / 47; 2048 80 99 / 102, 97 131 / 107; eight of 1920 88 174 / 134; three of 256, a quarter
+//   kept, 90 42 / 35; 4 bit: three of 320 84 40 / 43, of 1728 100 56 / 65, four of 2240 86 93 / 88, four of 2048, all kept, 114 97 / 109; four of 4096 65 137 / 87.
+// One member of 8 (pass by pass) 64 112 / 203.
 static bool chain_tiled(const pipe_chain_layer* layers, int L, int T, const int* split, int M) {
   if (!layers || L < 1 || g_kernel_choice != 0 || T <= 64 || T > PIPE_STREAM_MAX_T || M > 2) return false;
+  const bool two = split != nullptr && M == 2;
+  int64_t streamed = 0, tiled = 0;   // twice the workgroups times steps of k, and what the tiles cost in them
+  int least = INT32_MAX;             // steps of k
   for (int l = 0; l < L; ++l) {
     const pipe_expansion* e = layers[l].e;
     if (!e || e->bits == 8 || layers[l].kh != 0) return false;
-    if (split == nullptr || M < 2 ? e->K > 4 : (split[0] > 4 || split[1] > 4)) return false;
+    if (!two ? e->K > 4 : (split[0] > 4 || split[1] > 4)) return false;
+    const int walk = two ? (l == L - 1 ? 2400 : 800) + (e->bits == 4 ? 0 : 5 * e->nks) : e->bits == 4 ? 1060 : 800 + 5 * e->nks;
+    streamed += 2 * (int64_t)e->n_bins * ceil_div(T, 16) * e->nks;
+    tiled += (int64_t)walk * e->nks;
+    least = std::min(least, e->nks);
   }
-  return layers[0].e->K > 4 || layers[0].e->nks >= 24;
+  const pipe_expansion* e = layers[L - 1].e;
+  if (e->K <= 4) return streamed >= tiled;
+  int64_t items = 0;
+  for (const PipeOrder& o : e->orders) items += (int64_t)o.pos.size();
+  return least >= 48 || (3 * (int64_t)L - 2) * e->n_rb >= 2 * items;
 }
 
 struct ActBuffers {

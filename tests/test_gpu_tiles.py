@@ -356,7 +356,7 @@ def test_infinite_member_scale_leaves_pruned_row_blocks(pipe, bits, out, hidden,
 
 
 @pytest.mark.parametrize("kind,T", [("linear", 17), ("linear", 64), ("linear", 65), ("linear", 128), ("asymmetric", 40), ("gelu", 64), ("gelu", 65),
-                                    ("gated", 64), ("gated", 65), ("gated21", 113), ("chain", 65), ("chain8", 65)])
+                                    ("gated", 64), ("gated", 65), ("gated21", 113), ("chain", 65), ("chain", 128), ("chain8", 65)])
 def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
     """Calls that the tiled kernels serve by rule, against the streaming kernel, bit for bit; and captured where only the streaming kernel is
     ready (its scratch, no tile schedules), replayed with other inputs."""
@@ -372,13 +372,14 @@ def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
     elif kind in ("gelu", "gated", "gated21"):
         up = 2 if kind != "gelu" else 1
         K, split = {"gelu": (3, None), "gated": (4, [2, 2]), "gated21": (3, [2, 1])}[kind]
-        es = [mk(up * 1088, 320, 4, K), mk(320, 1088, 4, K)]
+        hidden = 480 if kind == "gated" else 1088
+        es = [mk(up * hidden, 320, 4, K), mk(320, hidden, 4, K)]
         act = pipe.PIPE_ACT_GELU if kind == "gelu" else pipe.PIPE_ACT_SILU_GATED
         call = lambda: pipe.pipe_mlp_forward(es[0], es[1], act, x, split=split)
     else:
-        K, split = (4, [2, 2]) if kind == "chain" else (8, [4, 4])
-        es = [mk(wide, wide, 2, K) for _ in range(3)]
-        layers = [(es[0], None, 3, -1, True), (es[1], None, 3, 1, True), (es[2], None, 0, -1, True)]
+        K, split, L = (4, None, 3) if kind == "chain" else (8, [4, 4], 4)
+        es = [mk(wide, wide, 2, K) for _ in range(L)]
+        layers = [(e, None, 0 if l == L - 1 else 3, 1 if l == 1 else -1, True) for l, e in enumerate(es)]
         call = lambda: pipe.pipe_chain_forward(layers, x, split=split)
     side = torch.cuda.Stream()
     torch.cuda.synchronize()

@@ -348,12 +348,73 @@ def failed_launches_are_reported(rt):
             assert [n for n in rt.names() if "zero_u32" not in n] == whole, (what, nth)
 
 
+def batches_take_the_kernel_of_their_size(rt):
+    """MLPs and chains of 17 to 128 tokens, on both sides of each line between the kernels: the last batch that is streamed and the first that is
+    tiled.  Where a schedule of the tiled route cannot be built, or under capture, the whole call is streamed."""
+    mlp, chain = rt.lib.pipe_mlp_forward, rt.lib.pipe_chain_forward
+    mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 5
+    chain.argtypes = [C.c_void_p, C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 3
+
+    def route():
+        names = rt.names()
+        tiled = ["gemm_stream" not in n for n in names if "gemm_" in n]
+        assert tiled and len(set(tiled)) == 1, names
+        return tiled[0]
+
+    def members(split):
+        return ((C.c_int * len(split))(*split), len(split)) if split else (None, 0)
+
+    def an_mlp(act, width, hidden, bits, K, split):
+        l1, l2 = rt.expand((2 if act == 2 else 1) * hidden, width, bits, K, 1.0, 16), rt.expand(width, hidden, bits, K, 1.0, 16)
+        arr, M = members(split)
+        return lambda T: mlp(l1, l2, act, 1 << 40, T, 0.0, arr, M, None, None, None, 1 << 44, None)
+
+    def a_chain(width, L, bits, K, split):
+        es = [rt.expand(width, width, bits, K, 1.0, 16) for _ in range(L)]
+        layers, (arr, M) = (Layer * L)(*[Layer(e, None, 0, -1) for e in es]), members(split)
+        return lambda T: chain(layers, L, 1 << 40, T, 0.0, arr, M, None, 1 << 44, None)
+
+    GELU, GATED = 1, 2
+    lines = ((an_mlp, (GELU, 320, 1088, 4, 3, None), 64), (an_mlp, (GELU, 768, 3072, 4, 2, None), 96), (an_mlp, (GELU, 768, 3072, 4, 3, None), 80),
+             (an_mlp, (GELU, 320, 1088, 4, 2, (1, 1)), 128), (an_mlp, (GELU, 320, 1088, 8, 2, None), 128),
+             (an_mlp, (GATED, 320, 1088, 4, 3, None), 64), (an_mlp, (GATED, 320, 480, 4, 4, (2, 2)), 64), (an_mlp, (GATED, 320, 1088, 4, 4, (2, 2)), 128),
+             (an_mlp, (GATED, 1024, 3072, 4, 4, (2, 2)), 96), (an_mlp, (GATED, 320, 1088, 2, 4, (2, 2)), 96), (an_mlp, (GATED, 320, 3072, 2, 4, (2, 2)), 64),
+             (an_mlp, (GATED, 320, 1088, 4, 4, (3, 1)), 112), (an_mlp, (GATED, 512, 3072, 4, 4, (3, 1)), 128), (an_mlp, (GATED, 1024, 3072, 4, 4, (3, 1)), 112),
+             (a_chain, (1536, 3, 4, 4, None), 80), (a_chain, (1536, 3, 4, 4, (2, 2)), 96), (a_chain, (1536, 3, 2, 4, (2, 2)), 112), (a_chain, (320, 3, 4, 4, None), 128),
+             (a_chain, (320, 3, 4, 8, (4, 4)), 128), (a_chain, (320, 6, 4, 8, (4, 4)), 64), (a_chain, (2880, 3, 4, 8, (4, 4)), 64), (a_chain, (320, 3, 4, 8, None), 128))
+    for make, args, last in lines:
+        call = make(*args)
+        for T in (17, last, last + 1) if last < 128 else (17, 65, 97, last):
+            assert call(T) == 0
+            assert route() == (T > last), (args, T)
+    for make, args, T in ((an_mlp, (GATED, 320, 480, 4, 4, (2, 2)), 100), (an_mlp, (GELU, 320, 1088, 4, 3, None), 100), (a_chain, (320, 6, 4, 8, (4, 4)), 100)):
+        assert make(*args)(200) == 0                     # this stream's scratch is there
+        assert make(*args)(64) == 0                      # (and the streamed gated layer's)
+        streamed = 0
+        for nth in range(1, 30):
+            call = make(*args)
+            rt.names()
+            rt.host.host_fail(nth)
+            assert call(T) == 0
+            rt.host.host_fail(0)
+            if route():
+                break
+            streamed += 1
+            assert call(T) == 0 and route()
+        assert 2 <= streamed < 29, (args, streamed)      # each layer's schedules
+        call = make(*args)
+        rt.host.host_capture(1)
+        assert call(T) == 0 and not route()
+        rt.host.host_capture(0)
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
                                       "any_number_of_images_is_served", "wide_layers_quantize_once",
                                       "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave",
                                       "a_sum_over_two_members_is_a_launch_each", "unprepared_batches_stream",
-                                      "prepared_calls_allocate_nothing", "failed_launches_are_reported"])
+                                      "prepared_calls_allocate_nothing", "failed_launches_are_reported",
+                                      "batches_take_the_kernel_of_their_size"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
