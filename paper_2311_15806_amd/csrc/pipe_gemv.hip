@@ -18,6 +18,7 @@
 #include "pipe_codes.h"
 
 #include <algorithm>
+#include <type_traits>
 
 int g_stream_ksplit = 0;   // 0: automatic
 
@@ -27,7 +28,16 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+constexpr int STREAM_SCALARS = 56;   // bytes of the scalar arguments ahead of the struct
 constexpr int R = 4;  // items processed concurrently by a wave (independent load streams)
+
+// byte k of a kernel-argument array, k uniform, without forcing the array into scratch memory
+__device__ __forceinline__ int pick(const uint32_t (&a)[PIPE_MAX_K / 4], int k) {
+  uint32_t v = a[0];
+#pragma unroll
+  for (int i = 1; i < PIPE_MAX_K / 4; ++i) v = (i == k >> 2) ? a[i] : v;
+  return (int)(v >> (k & 3) * 8 & 255u);
+}
 
 struct StreamParams {
   const uint8_t* qx;
@@ -52,27 +62,49 @@ struct StreamParams {
   int zero_n;
   uint32_t* zero_big;
   int zero_big_n;
-  int T, out, K, nks, M, reduce, act;
+  int T, out, nks, M, reduce, act;
   int ksplit;              // workgroups per bin: each takes a contiguous share of the k tiles
   int n_tb;                // 16-token blocks: one workgroup per (bin, k share, token block)
   int n_bins;
-  int thr0, thr1, thr2;    // bins of 4, fullest first: how many hold 4, at least 3, at least 2 items
-  const float* x_f32;      // QFUSE: the fp32 input [T, in], quantized by every workgroup itself
   float s_static;          // QFUSE: given activation scale, or <= 0 for max|x| / act_qmax
   float act_qmax;          // QFUSE: largest activation code
-  int in;                  // QFUSE: in_features (multiple of 4)
   int32_t* ws_sum;         // [n_bins][ksplit][cap][256] partial tiles of split bins
   uint32_t* ws_cnt;        // [n_bins] arrival counters, zero between launches
   uint32_t member_lo[PIPE_MAX_K / 4], member_hi[PIPE_MAX_K / 4], member_of[PIPE_MAX_K / 4];   // a byte each: a launch copies its arguments on the host
+  __device__ __forceinline__ int lo(int m) const { return pick(member_lo, m); }
+  __device__ __forceinline__ int hi(int m) const { return pick(member_hi, m); }
+  __device__ __forceinline__ int of(int k) const { return pick(member_of, k); }
 };
 
-// byte k of a kernel-argument array, k uniform, without forcing the array into scratch memory
-__device__ __forceinline__ int pick(const uint32_t (&a)[PIPE_MAX_K / 4], int k) {
-  uint32_t v = a[0];
-#pragma unroll
-  for (int i = 1; i < PIPE_MAX_K / 4; ++i) v = (i == k >> 2) ? a[i] : v;
-  return (int)(v >> (k & 3) * 8 & 255u);
-}
+// Of a layer on its own, which quantizes its few tokens itself and has one member: the others of the fields above are what they are here.  With the
+// scalars ahead of it 112 bytes, the most that a launch passes at the lower price: of small kernels back to back, launches with up to 112 bytes of arguments
+// take 2.65 us each, with 120 and more 3.0 to 3.4.  256 x 256, 16 tokens, in a graph 4.87 us a call with the struct above and 3.90 with this one, eagerly, where the host
+// is all there is, 7.9 and 7.7; 11008 x 4096 ternary, one token, 8.6 and 7.6.
+struct StreamPlain {
+  const float *scales, *bias;
+  float* y;
+  int32_t* ws_sum;
+  uint32_t* ws_cnt;
+  int out;
+  float s_static, act_qmax;
+  static constexpr int M = 1, reduce = 1, act = PIPE_ACT_NONE, zero_n = 0, zero_big_n = 0, res_members = 0, res_pre_act = 0;
+  static constexpr long long qx_mstride = 0, bias_mstride = 0, res_mstride = 0;
+  static constexpr uint32_t *amax_out = nullptr, *amax_neg = nullptr, *zero_after = nullptr, *zero_big = nullptr;
+  static constexpr const float* res = nullptr;
+  static constexpr int32_t* acc_out = nullptr;
+  __device__ __forceinline__ int lo(int) const { return 0; }
+  __device__ __forceinline__ int hi(int) const { return PIPE_MAX_K - 1; }
+  __device__ __forceinline__ int of(int) const { return 0; }
+};
+static_assert(STREAM_SCALARS + sizeof(StreamPlain) <= 112, "arguments of a launch at the lower price");
+
+// What the host passes ahead of the struct
+struct StreamCall {
+  StreamParams p;
+  const float* x_f32;      // QFUSE: the fp32 input [T, in], quantized by every workgroup itself
+  int in;                  // in_features (QFUSE: a multiple of 4)
+  int thr0, thr1, thr2;    // bins of 4, fullest first: how many hold 4, at least 3, at least 2 items
+};
 
 // The sum over a wave whose lanes are all active, by data-parallel moves within the vector unit
 template <int CTRL, int ROWS>
@@ -114,13 +146,12 @@ __device__ __forceinline__ int part_word(int i) { return i + (i >> 6) * 16; }
 // on their way, and builds its activation fragments from there.
 constexpr int QF_T = 16, QF_IN = 8192;   // tokens; codes of all tokens
 constexpr int QF_THREADS = 512;          // of a workgroup that quantizes, each up to QF_IN / 4 / QF_THREADS quads
-// What the first loads need comes as scalar arguments ahead of the struct: they are in registers with the launch, while the struct has to be
-// read from host memory.  Two to a word: thirteen arguments cost the
-// host 0.15 us a launch, these eight 0.05 to 0.1 (256 x 256, where the host is all there is: 7.0 us before and 6.8 to 7.2 now).
-template <int BITS, int NW, int XM, bool ACC_OUT, bool XMASK, bool QFUSE = false>
+// What the first loads need comes as scalar arguments ahead of the struct, two to a word: they are in registers with the launch, while the struct has to be
+// read from memory first.
+template <int BITS, int NW, int XM, bool ACC_OUT, bool XMASK, bool QFUSE = false, class Params = StreamParams>
 __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)) <= 8) ? 4 : 2) void gemm_stream_kernel(
     const uint8_t* a_codes, const StreamBin* a_bins, const void* a_x, uint64_t a_nb_t0, uint64_t a_t1_t2, uint64_t a_in_mg, uint64_t a_sp_T,
-    const StreamParams p) {
+    const Params p) {
   const int a_n_bins = (int)a_nb_t0, a_thr0 = (int)(a_nb_t0 >> 32), a_thr1 = (int)a_t1_t2, a_thr2 = (int)(a_t1_t2 >> 32);
   const int a_in = (int)a_in_mg, a_split = (int)a_sp_T, a_T = (int)(a_sp_T >> 32);
   const unsigned a_magic = (unsigned)(a_in_mg >> 32);
@@ -227,7 +258,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   load_w(tl, w);
   if (!QFUSE) load_x(tl, x);
   __builtin_amdgcn_sched_barrier(0);
-  request_arguments<sizeof(StreamParams) + 56>();
+  request_arguments<sizeof(Params) + STREAM_SCALARS>();
   if (XM == 1) d0 = load_d();
   // epilogue operands that need no descriptor: row scales (same positions), and per member the
   // activation scale and this thread's token code sum
@@ -307,7 +338,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   auto word = [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(d0, i); };
   int itm[R];   // which activation tensor item r reads
 #pragma unroll
-  for (int r = 0; r < R; ++r) itm[r] = XM == 1 ? 0 : pick(p.member_of, word(2 + (r < n_here ? r : 0)));
+  for (int r = 0; r < R; ++r) itm[r] = XM == 1 ? 0 : p.of(word(2 + (r < n_here ? r : 0)));
 
   v4i acc[R];
 #pragma unroll
@@ -406,7 +437,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       if (m >= p.M) break;
       const int rs = rsm[m];
       const float sx = sxm[m];
-      const int k_lo = pick(p.member_lo, m), k_hi = pick(p.member_hi, m);
+      const int k_lo = p.lo(m), k_hi = p.hi(m);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (its[r] != o || itk[r] < k_lo || itk[r] > k_hi) continue;
@@ -417,7 +448,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
         const float sc = fold_sx ? scv[r] * sx : scv[r];
         yacc = fmaf(sc, (float)a, yacc);
         if (ACC_OUT) {
-          if (tg < p.T) p.acc_out[((size_t)itk[r] * p.T + tg) * p.out + col] = a;
+          if (tg < a_T) p.acc_out[((size_t)itk[r] * a_T + tg) * p.out + col] = a;
         }
       }
       if (ACC_OUT) continue;
@@ -429,7 +460,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       if (p.res != nullptr) {
         // the members summed into this output each add their own skip tensor
         const int n_res = p.reduce ? p.res_members : (m < p.res_members ? 1 : 0);
-        const float* rp = p.res + (size_t)(p.reduce ? 0 : m) * p.res_mstride + (size_t)min(tg, p.T - 1) * p.out + col;
+        const float* rp = p.res + (size_t)(p.reduce ? 0 : m) * p.res_mstride + (size_t)min(tg, a_T - 1) * p.out + col;
         for (int mm = 0; mm < n_res; ++mm) rsum += rp[(size_t)mm * p.res_mstride];
       }
       if (p.res_pre_act) v += rsum;
@@ -438,16 +469,16 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       if (!p.res_pre_act) v += rsum;
       if (p.amax_out != nullptr) {
         const bool two_sided = p.amax_neg != nullptr;
-        float mx = tg < p.T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
+        float mx = tg < a_T ? (two_sided ? fmaxf(v, 0.f) : fabsf(v)) : 0.f;
         mx = wave_max(mx);
         if (lane == 0) atomicMax(&s_mx[m], __float_as_uint(mx));
         if (two_sided) {
-          float mn = tg < p.T ? fmaxf(-v, 0.f) : 0.f;
+          float mn = tg < a_T ? fmaxf(-v, 0.f) : 0.f;
           mn = wave_max(mn);
           if (lane == 0) atomicMax(&s_mx[R + m], __float_as_uint(mn));
         }
       }
-      if (tg < p.T) p.y[((size_t)(p.reduce ? 0 : m) * p.T + tg) * p.out + col] = v;
+      if (tg < a_T) p.y[((size_t)(p.reduce ? 0 : m) * a_T + tg) * p.out + col] = v;
     }
   }
   // One raise of a member's slot per workgroup.  By every wave and row block the raises were what a launch of many tokens waited for (waves that end
@@ -553,7 +584,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
       for (int s = 0; s < XM; ++s) {
         // stream s feeds item s of the chunk: its member's tensor (items beyond the bin's last repeat it)
         const int it = min(c * R + s, n_items - 1);
-        const int mem = XM == 1 ? 0 : pick(p.member_of, word(2 + it));
+        const int mem = XM == 1 ? 0 : p.of(word(2 + it));
         xb[s] = p.qx + (size_t)mem * p.qx_mstride + (size_t)tb * p.nks * 1024;
       }
       auto load_x = [&](int tl, uint4 (&x)[NX]) __attribute__((always_inline)) {
@@ -649,7 +680,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
     for (int m = 0; m < p.M; ++m) {
       const float sx = s_sx[m];
       const int rs = OFF ? s_rs[m][t] : 0;
-      const int k_lo = pick(p.member_lo, m), k_hi = pick(p.member_hi, m);
+      const int k_lo = p.lo(m), k_hi = p.hi(m);
 #pragma unroll
       for (int r = 0; r < CAP; ++r) {
         const int kk = word(2 + r);
@@ -716,22 +747,28 @@ int launch_multi_cap(const StreamParams& p, int n_bins, int cap, int xm, const G
 // a bin's workgroups are subs = ksplit * n_tb, of which one factor is 1: the first whole number above (2^32 - 1) / subs, ceil(2^32 / subs), gives floor(i / subs) as the product's upper half while
 // 7 i < 2^32
 inline uint64_t two_words(int lo, uint32_t hi) { return (uint64_t)(uint32_t)lo | (uint64_t)hi << 32; }
-#define PIPE_STREAM_ARGS(x)                                                                                              \
-  p.codes, p.bins, (const void*)(x), two_words(p.n_bins, p.thr0), two_words(p.thr1, p.thr2),                             \
-      two_words(p.in, 0xffffffffu / (unsigned)(p.ksplit * p.n_tb) + 1u), two_words(p.ksplit | p.n_tb << 8, p.T), p
+#define PIPE_STREAM_ARGS(x, params)                                                                                      \
+  p.codes, p.bins, (const void*)(x), two_words(p.n_bins, c.thr0), two_words(c.thr1, c.thr2),                             \
+      two_words(c.in, 0xffffffffu / (unsigned)(p.ksplit * p.n_tb) + 1u), two_words(p.ksplit | p.n_tb << 8, p.T), params
 
 template <int BITS, int NW>
-int launch_nw(const StreamParams& p, int n_bins, int xm, bool acc_out, const GemmArgs& a, hipStream_t st) {
+int launch_nw(const StreamCall& c, int n_bins, int xm, bool acc_out, const GemmArgs& a, hipStream_t st) {
+  const StreamParams& p = c.p;
   const dim3 grid((unsigned)((n_bins + 7) / 8 * 8 * p.ksplit * p.n_tb)), blk(NW * 64);
-  if (p.x_f32 != nullptr) {
+  if (c.x_f32 != nullptr) {
     // no quantizer launch: the contraction quantizes its few tokens itself
-    if (xm != 1 || acc_out || p.T > QF_T || p.T * p.nks * 64 > QF_IN || p.in % 4 != 0 || p.n_tb != 1) return PIPE_EINVAL;
-    PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.x_f32));
+    if (xm != 1 || acc_out || p.T > QF_T || p.T * p.nks * 64 > QF_IN || c.in % 4 != 0 || p.n_tb != 1) return PIPE_EINVAL;
+    if (p.M == 1 && p.act == PIPE_ACT_NONE && p.res == nullptr && p.amax_out == nullptr && p.zero_after == nullptr && p.zero_big == nullptr) {
+      const StreamPlain q{p.scales, p.bias, p.y, p.ws_sum, p.ws_cnt, p.out, p.s_static, p.act_qmax};
+      PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true, StreamPlain>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(c.x_f32, q));
+    } else {
+      PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(c.x_f32, p));
+    }
     PIPE_HIP(hipGetLastError());
     return PIPE_OK;
   }
   const bool xmask = p.T % 16 != 0;
-#define PIPE_STREAM_LAUNCH(XMV, ACC, MASK) PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, XMV, ACC, MASK>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.qx))
+#define PIPE_STREAM_LAUNCH(XMV, ACC, MASK) PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, XMV, ACC, MASK>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.qx, p))
 #define PIPE_STREAM_PICK(XMV)                                                     \
   do {                                                                            \
     if (acc_out) { if (xmask) PIPE_STREAM_LAUNCH(XMV, true, true); else PIPE_STREAM_LAUNCH(XMV, true, false); }   \
@@ -753,15 +790,17 @@ int launch_gemm_stream(const GemmArgs& a, hipStream_t st) {
   if (a.T <= 0) return PIPE_OK;
   if (a.T > PIPE_STREAM_MAX_T || a.T_pad != (int)round_up64(a.T, 16) || e->K > e->bin_cap || e->bin_cap % R != 0) return PIPE_ESHAPE;
   if (e->bin_cap != R && a.acc_out != nullptr) return PIPE_EINVAL;   // the integer export of wide bins goes through the tiled kernel
-  StreamParams p;
+  StreamCall c;
+  StreamParams& p = c.p;
   p.qx = a.qx; p.qx_mstride = a.qx_mstride;
   p.rowsum = a.rowsum; p.rowsum_mstride = a.rowsum_mstride;
   p.s_x = a.s_x; p.sx_mstride = a.sx_mstride;
   p.codes = e->codes_dev; p.scales = e->scales_all_dev;
   p.bins = e->bins_dev;
   p.bias = a.bias; p.bias_mstride = a.bias_mstride; p.y = a.y; p.acc_out = a.acc_out; p.amax_out = a.amax_out; p.amax_neg = a.amax_neg; p.res = a.res; p.res_mstride = a.res_mstride; p.res_members = a.res_members; p.res_pre_act = a.res_pre_act; p.zero_after = a.zero_after; p.zero_n = a.zero_n; p.zero_big = a.zero_big; p.zero_big_n = a.zero_big_n;
-  p.T = a.T; p.out = e->out; p.K = e->K; p.nks = e->nks; p.M = a.M; p.reduce = a.reduce; p.act = a.act;
-  p.x_f32 = a.x_f32; p.s_static = a.s_static; p.act_qmax = g_act_qmax_host; p.in = e->in;
+  p.T = a.T; p.out = e->out; p.nks = e->nks; p.M = a.M; p.reduce = a.reduce; p.act = a.act;
+  p.s_static = a.s_static; p.act_qmax = g_act_qmax_host;
+  c.x_f32 = a.x_f32; c.in = e->in;
   if (a.x_f32 != nullptr && e->bin_cap != R) return PIPE_EINVAL;
   // Fewer bins than half the CUs and a long k: split each bin over several workgroups (each still
   // with at least two tiles per wave).  With more bins a split only adds the exchange through
@@ -774,7 +813,7 @@ int launch_gemm_stream(const GemmArgs& a, hipStream_t st) {
     else ks = std::min(256 / (e->n_bins > 0 ? e->n_bins : 1), std::min(PIPE_MAX_SPLIT, n_tiles / 16));
     p.n_tb = a.T_pad / 16;
     p.n_bins = e->n_bins;
-    p.thr0 = e->bin_thr[0]; p.thr1 = e->bin_thr[1]; p.thr2 = e->bin_thr[2];
+    c.thr0 = e->bin_thr[0]; c.thr1 = e->bin_thr[1]; c.thr2 = e->bin_thr[2];
     if (p.n_tb > 1) ks = 1;   // several token blocks already multiply the workgroups
     p.ksplit = std::max(ks, 1);
     p.ws_sum = e->split_sum_dev; p.ws_cnt = e->split_cnt_dev;
@@ -798,8 +837,8 @@ int launch_gemm_stream(const GemmArgs& a, hipStream_t st) {
     }
   }
   switch (e->bits) {
-    case 8: return launch_nw<8, 8>(p, e->n_bins, xm, acc_out, a, st);
-    case 4: return launch_nw<4, 8>(p, e->n_bins, xm, acc_out, a, st);
-    default: return launch_nw<2, 8>(p, e->n_bins, xm, acc_out, a, st);
+    case 8: return launch_nw<8, 8>(c, e->n_bins, xm, acc_out, a, st);
+    case 4: return launch_nw<4, 8>(c, e->n_bins, xm, acc_out, a, st);
+    default: return launch_nw<2, 8>(c, e->n_bins, xm, acc_out, a, st);
   }
 }
