@@ -627,24 +627,24 @@ __global__ __launch_bounds__(BLK) void row_code_sums_kernel(const int8_t* __rest
 }
 
 // Convolution input for the implicit GEMM: channels-last int8 codes [N, H, W, C] and, per pixel, the sum of its C codes (added into
-// csum, zero on entry: one atomic per pixel and CH channels).  A workgroup takes 4096 elements, CH channels (a multiple of 64 divides C)
-// of 4096 / CH neighbouring pixels of an image, through LDS: reads run along the layout's own inner dimension, 16 bytes a lane where
-// its rows allow (`vec`), writes are 16 channels a lane.  Bound by the trip to memory: four loads a lane in flight, then one store
-// (32 images of 256 x 14 x 14: tiles of 32 x 32 one byte a store 7.2 us, these 4.1).
-template <int CH>
+// csum, zero on entry: one atomic per pixel and 64 channels).  A workgroup takes 1024 * U elements, 64 channels of 16 * U neighbouring pixels
+// of an image, through LDS: reads run along the layout's own inner dimension, 16 bytes a lane where its rows allow (`vec`), writes are 16
+// channels a lane.  Bound by the trip to memory: U loads a lane in flight, then one store (32 images of 256 x 14 x 14: tiles of 32 x 32, one byte
+// a store, 7.2 us, these 4.7).
+template <int U>
 __global__ __launch_bounds__(BLK) void quantize_nhwc_sums_kernel(const float* __restrict__ x, int C, int HW, int nhwc, int vec,
                                                                  float s_static, MaxOf amax,
                                                                  int8_t* __restrict__ q8, int32_t* __restrict__ csum,
                                                                  float* __restrict__ scale_out) {
-  constexpr int P = 4096 / CH, ROW = CH + 16;   // pixels; bytes of a pixel in LDS (16 apart: other banks)
+  constexpr int CH = 64, P = 1024 * U / CH, ROW = CH + 16;   // channels, pixels; bytes of a pixel in LDS (16 apart: other banks)
   __shared__ alignas(16) uint8_t tile[P * ROW];
   const int n = blockIdx.z, c0 = blockIdx.y * CH, p0 = blockIdx.x * P, tid = threadIdx.x;
   // four neighbours along the input's inner dimension: pixels of a channel, or channels of a pixel
   const int per_row = nhwc ? CH / 4 : P / 4, step = BLK / per_row;   // quads of a row, rows of a pass
   const int quad = (tid % per_row) * 4, row = tid / per_row;
-  float xv[4][4];   // requested before the scale is known
+  float xv[U][4];   // requested before the scale is known
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < U; ++j) {
     const int r = row + j * step;
     const int c = nhwc ? c0 + quad : c0 + r, p = nhwc ? p0 + r : p0 + quad;
     const size_t at = nhwc ? ((size_t)n * HW + p) * C + c : ((size_t)n * C + c) * HW + p;
@@ -661,7 +661,7 @@ __global__ __launch_bounds__(BLK) void quantize_nhwc_sums_kernel(const float* __
   const SymCodes cd(s);
   const bool live = cd.live();
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < U; ++j) {
     const int r = row + j * step;
     int q[4];
 #pragma unroll
@@ -676,6 +676,7 @@ __global__ __launch_bounds__(BLK) void quantize_nhwc_sums_kernel(const float* __
   __syncthreads();
   constexpr int CHUNKS = CH / 16;   // lanes of a pixel
   const int px = tid / CHUNKS, ck = tid % CHUNKS, p = p0 + px;
+  if (px >= P) return;   // (whole pixels: their lanes leave together)
   const uint4 w = *reinterpret_cast<const uint4*>(&tile[px * ROW + ck * 16]);
   int sum = __builtin_amdgcn_sdot4((int)w.x, 0x01010101, 0, false);
   sum = __builtin_amdgcn_sdot4((int)w.y, 0x01010101, sum, false);
@@ -696,12 +697,16 @@ int launch_quantize_nhwc_sums(const float* x, int N, int C, int HW, int nhwc, fl
   if (C % 64 != 0) return PIPE_ESHAPE;
   // rows of whole 16-byte loads: pixels of a channel, or channels of a pixel, in a tensor that begins on 16 bytes
   const int vec = (reinterpret_cast<uintptr_t>(x) & 15) == 0 && (nhwc || HW % 4 == 0);
-  if (C % 128 == 0)
-    PIPE_KLAUNCH(quantize_nhwc_sums_kernel<128>, dim3(ceil_div(HW, 32), C / 128, N), dim3(BLK), 0, st, x, C, HW, nhwc, vec, s_static, amax, q8,
-                 csum, scale_out);
-  else
-    PIPE_KLAUNCH(quantize_nhwc_sums_kernel<64>, dim3(ceil_div(HW, 64), C / 64, N), dim3(BLK), 0, st, x, C, HW, nhwc, vec, s_static, amax, q8,
-                 csum, scale_out);
+  // One load a lane while that leaves four workgroups a compute unit at most, then two, four for the largest.  Kernels, us, with 1 / 2 / 4: 1 image of 128 x 28 x 28
+  // 3.5 / 4.0 / 4.9, 8 3.8 / 4.1 / 5.0, 16 4.6 / 4.5 / 5.2, 40 8.7 / 6.9 / 7.9; 128 of 64 x 56 x 56 34 / 22.8 / 22.9, 256 64 / 41.0 / 39.7.
+  const int64_t elements = (int64_t)N * C * HW;
+#define PIPE_NHWC(U)                                                                                                                      \
+  PIPE_KLAUNCH(quantize_nhwc_sums_kernel<U>, dim3(ceil_div(HW, 16 * U), C / 64, N), dim3(BLK), 0, st, x, C, HW, nhwc, vec, s_static, amax, q8, csum, \
+               scale_out)
+  if (elements <= 1 << 20) PIPE_NHWC(1);
+  else if (elements <= 16 << 20) PIPE_NHWC(2);
+  else PIPE_NHWC(4);
+#undef PIPE_NHWC
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
 }

@@ -85,10 +85,11 @@ def test_dynamic_scale_over_the_parts_of_the_reduction(pipe, T, I, shift):
     e.free()
 
 
-@pytest.mark.parametrize("C,H,W,N", [(64, 1, 3, 2), (64, 9, 7, 3), (128, 7, 7, 2), (192, 4, 17, 2), (256, 6, 6, 1)])
+@pytest.mark.parametrize("C,H,W,N", [(64, 1, 3, 2), (64, 9, 7, 3), (128, 7, 7, 2), (192, 4, 17, 2), (256, 6, 6, 1),
+                                       (64, 57, 59, 5), (128, 48, 44, 4), (64, 113, 115, 21)])   # two and four loads a lane
 @pytest.mark.parametrize("shift", [0, 1])
 def test_channels_last_codes_and_sums(pipe, C, H, W, N, shift):
-    """Codes and per-pixel sums of a convolution's input at the edges of its tiles of 4096 elements, both layouts, inputs that are not
+    """Codes and per-pixel sums of a convolution's input at the edges of its tiles of 1024 to 4096 elements, both layouts, inputs that are not
     16-byte aligned: a pointwise layer's accumulators and outputs (bit for bit) against the codes."""
     rng = np.random.default_rng(C + H + W)
     x = rng.standard_normal((N, C, H, W)).astype(f32)
@@ -96,7 +97,7 @@ def test_channels_last_codes_and_sums(pipe, C, H, W, N, shift):
     _, _, codes = e.order(1)
     s = f32(f32(np.abs(x).max()) / f32(127))
     q = _codes(x.reshape(-1), s).reshape(x.shape).astype(np.int64)
-    want = np.einsum("nchw,oc->nhwo", q, codes.astype(np.int64)).reshape(-1, 32)
+    want = q.transpose(0, 2, 3, 1).reshape(-1, C).astype(np.float64) @ codes.T.astype(np.float64)    # (whole numbers below 2^53)
     ys = []
     for nhwc in (False, True):
         xl = np.ascontiguousarray(x.transpose(0, 2, 3, 1)) if nhwc else x
