@@ -169,7 +169,12 @@ int pipe_expansion_order(const pipe_expansion* e, int k, int* n_groups_kept,
  *   reduce_members  1: y_dev [T, out] = sum over members (ascending);
  *                   0: y_dev [M, T, out], one slab per member.
  * Per member: y_m = s_x * sum_{k in member, ascending} s_k[o] * float(acc_k[t,o]) (+b),
- * acc_k the exact int32 contraction.                                           */
+ * acc_k the exact int32 contraction.
+ * The first call of a grouping of the orders (`split`) builds a tile schedule -- host work, an
+ * allocation and a synchronous copy -- above 128 tokens, and from 17 tokens on (an MLP or a chain:
+ * from 65) where the layer's sizes make the tiled kernels the faster ones.  pipe_prepare does it
+ * ahead of time.  Where a schedule cannot be had up to 128 tokens (no memory, an unprepared call
+ * under capture), kernels that need none serve the call, with the same bits.                   */
 int pipe_forward(const pipe_expansion* e, const float* x_dev, int T, float s_x,
                  const int* split, int M, const float* bias_dev, int reduce_members,
                  float* y_dev, void* stream);

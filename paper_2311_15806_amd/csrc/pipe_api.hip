@@ -282,8 +282,8 @@ static int build_schedule(pipe_expansion* e, hipStream_t st) {
   // Positions in the schedule-ordered buffers.  Bins of 4: fullest bins first and the stored row blocks
   // packed without gaps, so a bin's first position and item count follow from its index and the number of
   // bins with 4, 3 and 2 items (bin_thr): the kernel still addresses its codes from its block index alone,
-  // and the items a bin does not have are read from one all-zero position behind the last (zero_pos), which
-  // stays in cache, instead of from zeros of the bin's own in memory.  Wider bins (more than 4 orders):
+  // and reads nothing for the items a bin does not have.  Behind the last lies one all-zero position (zero_pos), for
+  // the items without an order in the tiled kernels' schedules.  Wider bins (more than 4 orders):
   // position = bin * cap + index, unused positions are zeros.
   if (cap == 4)
     std::stable_sort(packed.begin(), packed.end(), [](const BinRbs& a, const BinRbs& b) { return a.n_items > b.n_items; });

@@ -1,6 +1,7 @@
 // Device side of the activation codes, shared by the quantizers (pipe_quant.hip) and the depthwise layer
-// (pipe_depthwise.hip).  Q(x) = clamp(rint(x / s), ...) with the correctly rounded fp32 quotient, half to even; the including
-// files are compiled with floating-point contraction off.
+// (pipe_depthwise.hip).  Q(x) = clamp(rint(x / s), ...) with the correctly rounded fp32 quotient, half to even.  Written
+// in explicitly rounded operations, which a file compiled with contraction (pipe_gemv.hip) leaves apart as well: a rounded product is the factor or the addend of
+// a written fma, never a bare sum's.
 #pragma once
 #include "pipe_internal.h"
 

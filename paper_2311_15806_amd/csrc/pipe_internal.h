@@ -193,8 +193,9 @@ constexpr int PIPE_SLOT_WORDS = 64;   // 256 bytes: the lines lie on different c
 #if defined(__HIPCC__)
 // Requests every 64-byte line of the kernel's arguments at once.  An eagerly launched kernel's arguments lie in host memory
 // (the runtime's default): each line's first use costs a trip there, one after the other, and some are first used in
-// the epilogue (one token into 11008 to 32000 channels: 0 to 6 % of a call, 2 % on average, no more than the spread on 11008 x 4096 ternary).  Only for kernels that need nearly all of
-// them at once: a two-layer MLP at 35 tokens, whose launches use few of the lines, lost 5 of 30 us to the trips.
+// the epilogue (one token into 11008 to 32000 channels: 0 to 6 % of a call, 2 % on average, no more than the spread on 11008 x 4096 ternary).  Where a kernel begins with it and
+// uses few of the lines, the trips cost more than they save: a two-layer MLP at 35 tokens lost 5 of 30 us.  The streaming kernel asks behind its first loads, whose arguments are
+// in registers: where it does not quantize, that is within 3 % of asking line by line, either way (60 MLPs, chains and layers of 3 to 64 tokens, the same on average).
 template <int BYTES>
 __device__ __forceinline__ void request_arguments() {
   typedef const __attribute__((address_space(4))) int* cptr;

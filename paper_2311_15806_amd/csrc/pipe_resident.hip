@@ -227,7 +227,7 @@ __global__ __launch_bounds__(RES_THREADS, 1) void chain_resident_kernel(const Re
     // a valid address and drops the result), so the waits for them are exact counts: RD - 1 rounds of
     // codes (across layer boundaries) and a round of fragments stay in flight while a round is multiplied.
     constexpr int NXL = XM * STEPS;        // fragment loads of a round
-    constexpr int XR = 2;                  // rounds of fragments in flight (four: the same)
+    constexpr int XR = 2;                  // rounds of fragments in flight (four: 2 to 4 % slower, more loads that no one uses at the ends)
     const bool xlive = (lane & 15) < p.T;
     // (lanes of tokens beyond the batch: out of the resource's range, zeros)
     const unsigned xl = xlive ? lane * 16 : 0x80000000u;
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(RES_THREADS, 1) void chain_resident_kernel(const Re
       const float sx0 = s_scale[0], sx1 = s_scale[1];
       const int nu = ly.nu;
       const bool last = l == p.L - 1;
-      // the layer's description, read from the kernel arguments once (not once per use inside the units' epilogues)
+      // the layer's description in registers (ly comes from LDS)
       const int e_reduce = ly.reduce, e_xm = ly.xm, e_act = ly.act, e_pre = ly.res_pre_act, e_gated = ly.gated, e_outw = ly.out_w;
       const int e_resm = ly.res_members, e_resdev = ly.res_device, e_nsub = ly.nsub, e_stride = ly.stride, e_at = ly.at, e_M = p.M, e_T = p.T;
       const long long e_resms = ly.res_mstride;
