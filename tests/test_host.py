@@ -349,7 +349,7 @@ def failed_launches_are_reported(rt):
 
 
 def batches_take_the_kernel_of_their_size(rt):
-    """MLPs and chains of 17 to 128 tokens, on both sides of each line between the kernels: the last batch that is streamed and the first that is
+    """Layers, MLPs and chains of 17 to 128 tokens, on both sides of each line between the kernels: the last batch that is streamed and the first that is
     tiled.  Where a schedule of the tiled route cannot be built, or under capture, the whole call is streamed."""
     mlp, chain = rt.lib.pipe_mlp_forward, rt.lib.pipe_chain_forward
     mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 5
@@ -374,8 +374,13 @@ def batches_take_the_kernel_of_their_size(rt):
         layers, (arr, M) = (Layer * L)(*[Layer(e, None, 0, -1) for e in es]), members(split)
         return lambda T: chain(layers, L, 1 << 40, T, 0.0, arr, M, None, 1 << 44, None)
 
+    def a_layer(out, width, bits, K):
+        e = rt.expand(out, width, bits, K, 1.0, 16)
+        return lambda T: _linear(rt, e, T)
+
     GELU, GATED = 1, 2
-    lines = ((an_mlp, (GELU, 320, 1088, 4, 3, None), 64), (an_mlp, (GELU, 768, 3072, 4, 2, None), 96), (an_mlp, (GELU, 768, 3072, 4, 3, None), 80),
+    lines = ((a_layer, (1024, 5120, 4, 4), 112), (a_layer, (1024, 1024, 4, 4), 96), (a_layer, (1024, 1024, 2, 4), 96), (a_layer, (2048, 1024, 8, 2), 96), (a_layer, (768, 3072, 4, 4), 128),
+             (an_mlp, (GELU, 320, 1088, 4, 3, None), 64), (an_mlp, (GELU, 768, 3072, 4, 2, None), 96), (an_mlp, (GELU, 768, 3072, 4, 3, None), 80),
              (an_mlp, (GELU, 320, 1088, 4, 2, (1, 1)), 128), (an_mlp, (GELU, 320, 1088, 8, 2, None), 128),
              (an_mlp, (GATED, 320, 1088, 4, 3, None), 64), (an_mlp, (GATED, 320, 480, 4, 4, (2, 2)), 64), (an_mlp, (GATED, 320, 1088, 4, 4, (2, 2)), 128),
              (an_mlp, (GATED, 1024, 3072, 4, 4, (2, 2)), 96), (an_mlp, (GATED, 320, 1088, 2, 4, (2, 2)), 96), (an_mlp, (GATED, 320, 3072, 2, 4, (2, 2)), 64),
