@@ -356,28 +356,28 @@ def test_infinite_member_scale_leaves_pruned_row_blocks(pipe, bits, out, hidden,
 
 
 @pytest.mark.parametrize("kind,T", [("linear", 17), ("linear", 64), ("linear", 65), ("linear", 128), ("asymmetric", 40), ("gelu", 64), ("gelu", 65),
-                                    ("gated", 64), ("gated", 65), ("gated21", 113), ("chain", 65), ("chain", 128), ("chain8", 65)])
+                                    ("gated", 64), ("gated", 65), ("narrow", 65), ("gated21", 113), ("chain", 65), ("chain4", 128), ("chain8", 65), ("deep8", 65)])
 def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
-    """Calls that the tiled kernels serve by rule, against the streaming kernel, bit for bit; and captured where only the streaming kernel is
-    ready (its scratch, no tile schedules), replayed with other inputs."""
+    """Calls on either side of the lines between the tiled kernels and the streaming kernel, against the latter, bit for bit; and captured where only
+    the streaming kernel is ready (its scratch, no tile schedules), replayed with other inputs."""
     g = torch.Generator(device="cuda")
     g.manual_seed(T)
     mk = lambda o, i, bits, K, group=16: pipe.pipe_expand(torch.randn(o, i, generator=g, device="cuda") * (1.5 / i ** 0.5), bits, K, 0.5, group)
-    wide = 1552 if kind == "chain" else 320
+    wide = 1552 if kind in ("chain", "chain4") else 320
     xs = [torch.randn(T, wide, generator=g, device="cuda") * s for s in (1.0, 3.0)]
     x = xs[0].clone()
     if kind in ("linear", "asymmetric"):
         es = [mk(8192, 320, 4, 4)]          # 320 bins: 17 tokens are past the line
         call = (lambda: pipe.pipe_forward(es[0], x)) if kind == "linear" else (lambda: pipe.pipe_forward_asymmetric(es[0], x))
-    elif kind in ("gelu", "gated", "gated21"):
+    elif kind in ("gelu", "gated", "narrow", "gated21"):
         up = 2 if kind != "gelu" else 1
-        K, split = {"gelu": (3, None), "gated": (4, [2, 2]), "gated21": (3, [2, 1])}[kind]
-        hidden = 480 if kind == "gated" else 1088
+        K, split = {"gelu": (3, None), "gated": (4, [2, 2]), "narrow": (4, [2, 2]), "gated21": (3, [2, 1])}[kind]
+        hidden = 480 if kind == "narrow" else 1088
         es = [mk(up * hidden, 320, 4, K), mk(320, hidden, 4, K)]
         act = pipe.PIPE_ACT_GELU if kind == "gelu" else pipe.PIPE_ACT_SILU_GATED
         call = lambda: pipe.pipe_mlp_forward(es[0], es[1], act, x, split=split)
     else:
-        K, split, L = (4, None, 3) if kind == "chain" else (8, [4, 4], 4)
+        K, split, L = {"chain": (4, [2, 2], 3), "chain4": (4, None, 3), "chain8": (8, [4, 4], 3), "deep8": (8, [4, 4], 4)}[kind]
         es = [mk(wide, wide, 2, K) for _ in range(L)]
         layers = [(e, None, 0 if l == L - 1 else 3, 1 if l == 1 else -1, True) for l, e in enumerate(es)]
         call = lambda: pipe.pipe_chain_forward(layers, x, split=split)
