@@ -819,8 +819,8 @@ static int routed(bool tiled, Call call) {
 // Where 17 to 128 tokens are tiled: the streaming kernel runs a workgroup per bin and 16 tokens, each along the whole of k, the tiled one walks along k
 // once for up to 64.  A walk costs about what 400 such workgroups do, and a step of a long walk more beside them, at 8 and 2 bits above all.  Calls, us, streamed / tiled:
 //   11008 x 4096 4 bit, K = 4, half kept, 20 tokens 23.3 / 20.5, 64 32 / 22.4, 128 52 / 29; ternary 32 17.7 / 17.4, 64 22.8 / 18.7;
-//   4096 x 4096 4 bit 32 tokens 15.2 / 16.3, 64 17.9 / 16.7; ternary 64 14.7 / 17.1, 128 19.7 / 17.6; 8 bit, K = 2 64 18.8 / 20.4, 96 21.3 / 20.6;
-//   4096 x 11008 4 bit 32 tokens 22.9 / 27.2, 48 26.8 / 27.3, 96 37.1 / 30.5; 5632 x 5568, K = 2, a quarter kept, 50 16.8 / 19.0; 832 x 5056, all kept, 117 16.6 / 20.7; ternary 96 26.3 / 30.3, 128 29.7 / 30.7; 8 bit 96 38.9 / 39.2, 128 49.6 / 40.2;
+//   4096 x 4096 4 bit 32 tokens 15.2 / 16.3, 64 17.9 / 16.7; ternary 64 14.7 / 17.1, 128 19.7 / 17.6; 8 bit, K = 2 64 17.6 / 20.0, 96 20.2 / 20.3, 112 22.6 / 20.7;
+//   4096 x 11008 4 bit 32 tokens 22.9 / 27.2, 48 26.8 / 27.3, 96 37.1 / 30.5; 5632 x 5568, K = 2, a quarter kept, 50 16.8 / 19.0; 832 x 5056, all kept, 117 16.6 / 20.7; ternary 96 26.3 / 30.3, 128 29.7 / 30.7; 8 bit 96 37.8 / 39.0, 128 45.1 / 39.9;
 //   3072 x 768 4 bit 48 tokens 11.1 / 11.2, 96 15.9 / 14.0; 2048 x 2048 ternary 64 12.6 / 14.0, 128 14.2 / 13.9; 768 x 3072 never (4 bit, 96 14.0 / 15.7).
 static bool linear_tiled(const pipe_expansion* e, int T, int M, int reduce_members) {
   if (!e || g_kernel_choice != 0 || T <= STREAM_ONLY_T || T > PIPE_STREAM_MAX_T || e->bin_cap != 4 || (M > 1 && !reduce_members)) return false;

@@ -148,14 +148,16 @@ constexpr int QF_T = 16, QF_IN = 8192;   // tokens; codes of all tokens
 constexpr int QF_THREADS = 512;          // of a workgroup that quantizes, each up to QF_IN / 4 / QF_THREADS quads
 // What the first loads need comes as scalar arguments ahead of the struct, two to a word: they are in registers with the launch, while the struct has to be
 // read from memory first.
-template <int BITS, int NW, int XM, bool ACC_OUT, bool XMASK, bool QFUSE = false, class Params = StreamParams>
+// D = tiles an item that a wave asks for together: see two_tiles.
+template <int BITS, int NW, int XM, bool ACC_OUT, bool XMASK, bool QFUSE = false, class Params = StreamParams, int D = 1>
 __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)) <= 8) ? 4 : 2) void gemm_stream_kernel(
     const uint8_t* a_codes, const StreamBin* a_bins, const void* a_x, uint64_t a_nb_t0, uint64_t a_t1_t2, uint64_t a_in_mg, uint64_t a_sp_T,
     const Params p) {
   const int a_n_bins = (int)a_nb_t0, a_thr0 = (int)(a_nb_t0 >> 32), a_thr1 = (int)a_t1_t2, a_thr2 = (int)(a_t1_t2 >> 32);
   const int a_in = (int)a_in_mg, a_split = (int)a_sp_T, a_T = (int)(a_sp_T >> 32);
   const unsigned a_magic = (unsigned)(a_in_mg >> 32);
-  static_assert(!QFUSE || (XM == 1 && !ACC_OUT && NW * 64 == QF_THREADS), "the fused quantizer serves one shared input");
+  static_assert(!QFUSE || (XM == 1 && !ACC_OUT && NW * 64 == QF_THREADS && D == 1), "the fused quantizer serves one shared input");
+  static_assert(D == 1 || D == 2, "tiles asked for together");
   __shared__ __attribute__((aligned(16))) uint8_t s_qx[QFUSE ? QF_IN : 16];
   __shared__ float s_red[NW];
   __shared__ int s_rs[QF_T];
@@ -197,7 +199,8 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   // stored row blocks sit in the schedule-ordered buffers follows from the bin's index (below), so
   // the code stream (the HBM traffic that bounds this kernel) starts at once.  Wave w streams
   // tiles w, w+NW, ..., one tile per item in flight: with exact waits two, three and four were the slower the more (11008 x 4096 8 bit, 16 tokens,
-  // call 24.2 us / 27.1 / 29.8 / 30.3; 4 bit, one token 12.2 / 14.2; six ternary layers of 2048, two members, 50 tokens 77.8 / 89.6).
+  // call 24.2 us / 27.1 / 29.8 / 30.3; 4 bit, one token 12.2 / 14.2; six ternary layers of 2048, two members, 50 tokens 77.8 / 89.6).  At 8 bits two that are
+  // asked for and waited for together can be faster, see two_tiles.
   // All loads go through buffer resources that end with this workgroup's share of the k tiles: an item that the bin does not have, a tile beyond
   // the share and a token beyond the batch read as zero without any access, so no load is behind a branch and every wait is an exact count.
   const int tile_lo = ksplit > 1 ? (int)__umulhi(n_tiles * ksp, a_magic) : 0;
@@ -222,8 +225,8 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   for (int r = 0; r < R; ++r)
     l_w[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(a_codes) + (size_t)(pos0 + (r < n_here ? r : 0)) * n_tiles * 1024, 0,
                                                r < n_here ? (unsigned)tile_hi * 1024u : 0u, 0x00020000);
-  v4u w[R];
-  v4i x[NX];
+  v4u w[D][R];
+  v4i x[D][NX];
   auto load_w = [&](int tl, v4u (&w)[R]) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < R; ++r) w[r] = (v4u)__builtin_amdgcn_raw_buffer_load_b128(l_w[r], tl * 1024 + lane * 16, 0, 0);
@@ -255,8 +258,11 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
     }
   };
   int tl = tile_lo + wave;
-  load_w(tl, w);
-  if (!QFUSE) load_x(tl, x);
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    load_w(tl + d * NW, w[d]);
+    if (!QFUSE) load_x(tl + d * NW, x[d]);
+  }
   __builtin_amdgcn_sched_barrier(0);
   request_arguments<sizeof(Params) + STREAM_SCALARS>();
   if (XM == 1) d0 = load_d();
@@ -361,13 +367,26 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
       }
     }
   };
-  // The first tile stands apart: behind it are the epilogue's operands, of which the loop's waits know nothing.
-  if (QFUSE) load_x(tl, x);
-  mul_tile(w, x);
-  for (tl += NW; tl < tile_hi; tl += NW) {
-    load_w(tl, w);
-    load_x(tl, x);
-    mul_tile(w, x);
+  if constexpr (D == 1) {
+    // The first tile stands apart: behind it are the epilogue's operands, of which the loop's waits know nothing.
+    if (QFUSE) load_x(tl, x[0]);
+    mul_tile(w[0], x[0]);
+    for (tl += NW; tl < tile_hi; tl += NW) {
+      load_w(tl, w[0]);
+      load_x(tl, x[0]);
+      mul_tile(w[0], x[0]);
+    }
+  } else {
+    // The branches make the wait at the loop's head one for both tiles, and their loads leave back to back.  Without branches and with exact waits, so that one
+    // tile is on its way while the other is multiplied, or with the loads of both mixed, 16384 x 4096, K = 4, 123 tokens took 137 to 140 us: as with one tile, 136; so 125.
+    for (; tl < tile_hi; tl += 2 * NW) {
+      mul_tile(w[0], x[0]);
+      if (tl + 2 * NW < tile_hi) { load_w(tl + 2 * NW, w[0]); load_x(tl + 2 * NW, x[0]); }
+      if (tl + NW < tile_hi) {
+        mul_tile(w[D - 1], x[D - 1]);
+        if (tl + 3 * NW < tile_hi) { load_w(tl + 3 * NW, w[D - 1]); load_x(tl + 3 * NW, x[D - 1]); }
+      }
+    }
   }
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -751,6 +770,14 @@ inline uint64_t two_words(int lo, uint32_t hi) { return (uint64_t)(uint32_t)lo |
   p.codes, p.bins, (const void*)(x), two_words(p.n_bins, c.thr0), two_words(c.thr1, c.thr2),                             \
       two_words(c.in, 0xffffffffu / (unsigned)(p.ksplit * p.n_tb) + 1u), two_words(p.ksplit | p.n_tb << 8, p.T), params
 
+// At 8 bits a tile is one multiplication an item behind 5 KiB of loads, and a wave with one tile at a time does not keep the caches busy.  Two at a time against
+// one, calls of 1500 layers by tiles a wave, bins and token blocks: 17 to 128 tokens -1 to -12 % in the mean of every class (320 x 16384, K = 2, 107 tokens
+// 30.6 -> 25.9 us, 8192 x 8192, K = 4, 111 122.7 -> 113.9; at worst 11008 x 4096, K = 2, 32 24.8 -> 26.8).  Up to 16 tokens, where all codes come from HBM: 16 tiles a wave
+// and more from 768 bins on -6 % (28672 x 8192, K = 3, 5 tokens 129 -> 123), 8 from 1024 on -6 % (28672 x 4096, K = 3, 3 66.7 -> 61.4); elsewhere -2 to +3 %, single layers
+// +10 % (28672 x 4096, K = 2, 16 45.1 -> 49.6).  With an input for each member +6 to +16 % (chains of 1536 to 3072, 65 to 128 tokens: more registers, one workgroup
+// less a compute unit); at 4 bits -4 to +3 %, at 2 bits 0 to +5 % on walks of more than a tile a wave.
+inline bool two_tiles(const StreamParams& p) { return p.n_tb > 1 || (p.nks >= 64 && p.n_bins >= (p.nks >= 128 ? 768 : 1024)); }
+
 template <int BITS, int NW>
 int launch_nw(const StreamCall& c, int n_bins, int xm, bool acc_out, const GemmArgs& a, hipStream_t st) {
   const StreamParams& p = c.p;
@@ -767,8 +794,14 @@ int launch_nw(const StreamCall& c, int n_bins, int xm, bool acc_out, const GemmA
     PIPE_HIP(hipGetLastError());
     return PIPE_OK;
   }
-  const bool xmask = p.T % 16 != 0;
-#define PIPE_STREAM_LAUNCH(XMV, ACC, MASK) PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, XMV, ACC, MASK>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.qx, p))
+  const bool xmask = p.T % 16 != 0, two = BITS == 8 && xm == 1 && two_tiles(p);
+#define PIPE_STREAM_LAUNCH_D(XMV, ACC, MASK, D) \
+  PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, XMV, ACC, MASK, false, StreamParams, D>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.qx, p))
+#define PIPE_STREAM_LAUNCH(XMV, ACC, MASK)                                                              \
+  do {                                                                                                  \
+    if (two) PIPE_STREAM_LAUNCH_D(XMV, ACC, MASK, (BITS == 8 && (XMV) == 1 ? 2 : 1));                   \
+    else PIPE_STREAM_LAUNCH_D(XMV, ACC, MASK, 1);                                                       \
+  } while (0)
 #define PIPE_STREAM_PICK(XMV)                                                     \
   do {                                                                            \
     if (acc_out) { if (xmask) PIPE_STREAM_LAUNCH(XMV, true, true); else PIPE_STREAM_LAUNCH(XMV, true, false); }   \
@@ -779,6 +812,7 @@ int launch_nw(const StreamCall& c, int n_bins, int xm, bool acc_out, const GemmA
   else PIPE_STREAM_PICK(4);
 #undef PIPE_STREAM_PICK
 #undef PIPE_STREAM_LAUNCH
+#undef PIPE_STREAM_LAUNCH_D
   PIPE_HIP(hipGetLastError());
   return PIPE_OK;
 }

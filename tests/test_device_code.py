@@ -89,3 +89,13 @@ def test_streaming_kernel_raises_a_slot_once(kernels):
     plain = [name for name in counts if "StreamPlain" in name]       # the instance of few arguments takes no maxima
     assert len(plain) == 3 and not any(counts.pop(name) for name in plain)
     assert len(counts) >= 9 and all(0 < c <= 2 for c in counts.values()), counts
+
+
+def test_streaming_kernel_asks_for_two_tiles_at_8_bits(kernels):
+    """Its instances for two tiles at a time: both stand before the loop and in it, and the loop waits once for both."""
+    found = {name: code for name, code in kernels.items() if re.search(r"gemm_stream_kernelILi8E.*StreamParamsELi2EE", name)}
+    assert len(found) == 4
+    for name, code in found.items():
+        assert sum(ins.startswith("buffer_load_dwordx4") for ins in code) == 2 * 2 * 5, name
+        first = next(i for i, ins in enumerate(code) if ins.startswith("v_mfma"))
+        assert any("vmcnt(0)" in ins for ins in code[first - 4:first]), name

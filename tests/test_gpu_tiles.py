@@ -408,6 +408,32 @@ def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
         e.free()
 
 
+@pytest.mark.parametrize("T,n_in,out,K", [(17, 60, 48, 2), (33, 700, 336, 3), (128, 768, 1008, 4), (20, 1100, 64, 1), (64, 1536, 320, 2), (97, 1540, 176, 4),
+                                          (40, 2300, 96, 3), (100, 11008, 64, 2), (16, 4096, 16384, 4), (7, 8192, 12288, 4)])
+def test_streamed_8_bit_walks_by_two_tiles(pipe, T, n_in, out, K):
+    """8-bit layers whose waves walk no tile, one, an odd or an even number of them, by two at a time: outputs and accumulators bit for bit those of
+    the tiled kernels, accumulators the whole numbers of the codes."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + n_in)
+    e = pipe.pipe_expand(torch.randn(out, n_in, generator=g, device="cuda") / n_in ** 0.5, 8, K, 1.0, 16)
+    x = torch.randn(T, n_in, generator=g, device="cuda")
+    got = []
+    try:
+        for which in (2, 1):
+            pipe.pipe_set_kernel(which)
+            got.append((pipe.pipe_forward(e, x),) + tuple(pipe.pipe_forward_acc(e, x)))
+    finally:
+        pipe.pipe_set_kernel(0)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    acc, qx = got[0][1], got[0][2]
+    if n_in * out <= 1 << 20:
+        for k in range(K):
+            codes = np.asarray(e.order(k + 1)[2]).astype(np.float64)
+            assert np.array_equal(acc[k].cpu().numpy(), qx.cpu().numpy().astype(np.float64) @ codes.T)    # (whole numbers below 2^53)
+    e.free()
+
+
 @pytest.mark.parametrize("bits,T,n_in,scale,static", [(2, 1, 8192, 1.0, 0.0), (4, 1, 8188, 1.0, 0.0), (8, 1, 4, 1.0, 0.02), (4, 16, 252, 1.0, 0.0), (2, 3, 1028, 1.0, 0.0),
                                                       (8, 4, 1024, 1.0, 0.01), (4, 15, 20, 1.0, 0.0), (4, 2, 2048, 1e-30, 0.0), (2, 5, 516, 1e30, 0.0), (8, 16, 256, 0.0, 0.0)])
 def test_streaming_kernel_quantizes_its_tokens(pipe, bits, T, n_in, scale, static):

@@ -413,13 +413,36 @@ def batches_take_the_kernel_of_their_size(rt):
         rt.host.host_capture(0)
 
 
+def streamed_8_bit_walks_ask_for_two_tiles(rt):
+    """The instance of the streaming kernel that an 8-bit layer takes, on both sides of each line: token blocks, steps of k, bins; an input for
+    each member takes one tile at a time."""
+    mlp = rt.lib.pipe_mlp_forward
+    mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 5
+
+    def tiles():
+        return [int(m.group(1)) for m in (re.search(r"gemm_stream_kernelILi\d.*?StreamParamsELi(\d)E", n) for n in rt.names()) if m]
+
+    for out, width, bits, K, T, want in ((256, 256, 8, 2, 33, 2), (256, 4096, 8, 2, 16, 1), (256, 320, 4, 2, 33, 1), (256, 320, 2, 4, 33, 1),
+                                         (16384, 4096, 8, 4, 16, 2), (16368, 4096, 8, 4, 16, 1), (16384, 3840, 8, 4, 16, 1),     # 1024 bins, 64 steps
+                                         (12288, 8192, 8, 4, 16, 2), (12272, 8192, 8, 4, 16, 1), (12288, 7936, 8, 4, 16, 1)):    # 768 bins, 128 steps
+        e = rt.expand(out, width, bits, K, 1.0, 16)
+        rt.names()
+        assert _linear(rt, e, T) == 0
+        assert tiles() == [want], (out, width, bits, K, T)
+    l1, l2 = rt.expand(512, 320, 8, 4, 1.0, 16), rt.expand(320, 512, 8, 4, 1.0, 16)
+    two = (C.c_int * 2)(2, 2)
+    rt.names()
+    assert mlp(l1, l2, 1, 1 << 40, 40, 0.0, two, 2, None, None, None, 1 << 44, None) == 0
+    assert tiles() == [2, 1]
+
+
 @pytest.mark.parametrize("scenario", ["failed_allocation_is_reported_once", "control_words_start_at_zero",
                                       "failed_preparation_starts_over", "capture_builds_nothing",
                                       "any_number_of_images_is_served", "wide_layers_quantize_once",
                                       "single_pass_tables_hold_no_needless_items", "tiles_follow_the_units_they_leave",
                                       "a_sum_over_two_members_is_a_launch_each", "unprepared_batches_stream",
                                       "prepared_calls_allocate_nothing", "failed_launches_are_reported",
-                                      "batches_take_the_kernel_of_their_size"])
+                                      "batches_take_the_kernel_of_their_size", "streamed_8_bit_walks_ask_for_two_tiles"])
 def test_host(scenario, tmp_path):
     _host_hip.run(__file__, scenario, tmp_path)
 
