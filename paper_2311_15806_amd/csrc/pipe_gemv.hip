@@ -156,7 +156,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   const int a_n_bins = (int)a_nb_t0, a_thr0 = (int)(a_nb_t0 >> 32), a_thr1 = (int)a_t1_t2, a_thr2 = (int)(a_t1_t2 >> 32);
   const int a_in = (int)a_in_mg, a_split = (int)a_sp_T, a_T = (int)(a_sp_T >> 32);
   const unsigned a_magic = (unsigned)(a_in_mg >> 32);
-  static_assert(!QFUSE || (XM == 1 && !ACC_OUT && NW * 64 == QF_THREADS && D == 1), "the fused quantizer serves one shared input");
+  static_assert(!QFUSE || (XM == 1 && !ACC_OUT && NW * 64 == QF_THREADS), "the fused quantizer serves one shared input");
   static_assert(D == 1 || D == 2, "tiles asked for together");
   __shared__ __attribute__((aligned(16))) uint8_t s_qx[QFUSE ? QF_IN : 16];
   __shared__ float s_red[NW];
@@ -379,6 +379,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   } else {
     // The branches make the wait at the loop's head one for both tiles, and their loads leave back to back.  Without branches and with exact waits, so that one
     // tile is on its way while the other is multiplied, or with the loads of both mixed, 16384 x 4096, K = 4, 123 tokens took 137 to 140 us: as with one tile, 136; so 125.
+    if (QFUSE) { load_x(tl, x[0]); load_x(tl + NW, x[D - 1]); }
     for (; tl < tile_hi; tl += 2 * NW) {
       mul_tile(w[0], x[0]);
       if (tl + 2 * NW < tile_hi) { load_w(tl + 2 * NW, w[0]); load_x(tl + 2 * NW, x[0]); }
@@ -771,12 +772,19 @@ inline uint64_t two_words(int lo, uint32_t hi) { return (uint64_t)(uint32_t)lo |
       two_words(c.in, 0xffffffffu / (unsigned)(p.ksplit * p.n_tb) + 1u), two_words(p.ksplit | p.n_tb << 8, p.T), params
 
 // At 8 bits a tile is one multiplication an item behind 5 KiB of loads, and a wave with one tile at a time does not keep the caches busy.  Two at a time against
-// one, calls of 1500 layers by tiles a wave, bins and token blocks: 17 to 128 tokens -1 to -12 % in the mean of every class (320 x 16384, K = 2, 107 tokens
-// 30.6 -> 25.9 us, 8192 x 8192, K = 4, 111 122.7 -> 113.9; at worst 11008 x 4096, K = 2, 32 24.8 -> 26.8).  Up to 16 tokens, where all codes come from HBM: 16 tiles a wave
-// and more from 768 bins on -6 % (28672 x 8192, K = 3, 5 tokens 129 -> 123), 8 from 1024 on -6 % (28672 x 4096, K = 3, 3 66.7 -> 61.4); elsewhere -2 to +3 %, single layers
-// +10 % (28672 x 4096, K = 2, 16 45.1 -> 49.6).  With an input for each member +6 to +16 % (chains of 1536 to 3072, 65 to 128 tokens: more registers, one workgroup
-// less a compute unit); at 4 bits -4 to +3 %, at 2 bits 0 to +5 % on walks of more than a tile a wave.
-inline bool two_tiles(const StreamParams& p) { return p.n_tb > 1 || (p.nks >= 64 && p.n_bins >= (p.nks >= 128 ? 768 : 1024)); }
+// one, calls of 1700 layers:
+//   17 to 128 tokens -1 to -12 % in the mean of every class of bins, token blocks and steps of k (320 x 16384, K = 2, 107 tokens 30.6 -> 25.9 us, 8192 x 8192, K = 4, 111
+//   122.7 -> 113.9; at worst 11008 x 4096, K = 2, 32 24.8 -> 26.8);
+//   up to 16 tokens, where all codes come from HBM, from 1024 bins on -3 to -8 % (28672 x 3584, K = 3, 2 tokens 53.9 -> 49.6), from 768 on walks of 16 tiles a wave
+//   -6 % (28672 x 8192, K = 3, 5 129 -> 123); fewer -2 to +3 %, single layers +10 % (28672 x 4096, K = 2, 16 45.1 -> 49.6);
+//   one token that the launch quantizes itself, from 128 bins on walks of more than 8 tiles 0 to -16 % (28672 x 8192, K = 2 100 -> 84; 4096 x 8192 17.3 -> 15.4), above
+//   1280 bins -1 to -11 %; 20480 x 4096, K = 2 +13 %, shorter walks -9 to +9 %.
+// With an input for each member +6 to +16 % (chains of 1536 to 3072, 65 to 128 tokens: more registers, one workgroup less a compute unit); at 4 bits -4 to +3 %, at 2
+// bits 0 to +5 % on walks of more than a tile a wave.
+inline bool two_tiles(const StreamParams& p, bool fused) {
+  if (fused) return p.n_bins > 1280 || (p.n_bins >= 128 && p.nks > 64);
+  return p.n_tb > 1 || p.n_bins >= 1024 || (p.nks >= 128 && p.n_bins >= 768);
+}
 
 template <int BITS, int NW>
 int launch_nw(const StreamCall& c, int n_bins, int xm, bool acc_out, const GemmArgs& a, hipStream_t st) {
@@ -785,16 +793,23 @@ int launch_nw(const StreamCall& c, int n_bins, int xm, bool acc_out, const GemmA
   if (c.x_f32 != nullptr) {
     // no quantizer launch: the contraction quantizes its few tokens itself
     if (xm != 1 || acc_out || p.T > QF_T || p.T * p.nks * 64 > QF_IN || c.in % 4 != 0 || p.n_tb != 1) return PIPE_EINVAL;
+#define PIPE_STREAM_LAUNCH_Q(PARAMS, params, D) \
+  PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true, PARAMS, D>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(c.x_f32, params))
+    const bool two = BITS == 8 && two_tiles(p, true);
+    constexpr int D2 = BITS == 8 ? 2 : 1;
     if (p.M == 1 && p.act == PIPE_ACT_NONE && p.res == nullptr && p.amax_out == nullptr && p.zero_after == nullptr && p.zero_big == nullptr) {
       const StreamPlain q{p.scales, p.bias, p.y, p.ws_sum, p.ws_cnt, p.out, p.s_static, p.act_qmax};
-      PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true, StreamPlain>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(c.x_f32, q));
+      if (two) PIPE_STREAM_LAUNCH_Q(StreamPlain, q, D2);
+      else PIPE_STREAM_LAUNCH_Q(StreamPlain, q, 1);
     } else {
-      PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, 1, false, true, true>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(c.x_f32, p));
+      if (two) PIPE_STREAM_LAUNCH_Q(StreamParams, p, D2);
+      else PIPE_STREAM_LAUNCH_Q(StreamParams, p, 1);
     }
+#undef PIPE_STREAM_LAUNCH_Q
     PIPE_HIP(hipGetLastError());
     return PIPE_OK;
   }
-  const bool xmask = p.T % 16 != 0, two = BITS == 8 && xm == 1 && two_tiles(p);
+  const bool xmask = p.T % 16 != 0, two = BITS == 8 && xm == 1 && two_tiles(p, false);
 #define PIPE_STREAM_LAUNCH_D(XMV, ACC, MASK, D) \
   PIPE_LAUNCH((gemm_stream_kernel<BITS, NW, XMV, ACC, MASK, false, StreamParams, D>), grid, blk, st, a.ev_start, a.ev_stop, PIPE_STREAM_ARGS(p.qx, p))
 #define PIPE_STREAM_LAUNCH(XMV, ACC, MASK)                                                              \

@@ -87,13 +87,13 @@ def test_streaming_kernel_raises_a_slot_once(kernels):
     counts = {name: sum("atomic" in ins and "max" in ins for ins in code) for name, code in kernels.items()
               if re.search(r"gemm_stream_kernelILi\dELi\dELi\dELb0E", name)}
     plain = [name for name in counts if "StreamPlain" in name]       # the instance of few arguments takes no maxima
-    assert len(plain) == 3 and not any(counts.pop(name) for name in plain)
+    assert len(plain) == 4 and not any(counts.pop(name) for name in plain)
     assert len(counts) >= 9 and all(0 < c <= 2 for c in counts.values()), counts
 
 
 def test_streaming_kernel_asks_for_two_tiles_at_8_bits(kernels):
     """Its instances for two tiles at a time: both stand before the loop and in it, and the loop waits once for both."""
-    found = {name: code for name, code in kernels.items() if re.search(r"gemm_stream_kernelILi8E.*StreamParamsELi2EE", name)}
+    found = {name: code for name, code in kernels.items() if re.search(r"gemm_stream_kernelILi8E.*ELb0ENS_12StreamParamsELi2EE", name)}
     assert len(found) == 4
     for name, code in found.items():
         assert sum(ins.startswith("buffer_load_dwordx4") for ins in code) == 2 * 2 * 5, name

@@ -420,10 +420,12 @@ def streamed_8_bit_walks_ask_for_two_tiles(rt):
     mlp.argtypes = [C.c_void_p] * 2 + [C.c_int, C.c_void_p, C.c_int, C.c_float, C.c_void_p, C.c_int] + [C.c_void_p] * 5
 
     def tiles():
-        return [int(m.group(1)) for m in (re.search(r"gemm_stream_kernelILi\d.*?StreamParamsELi(\d)E", n) for n in rt.names()) if m]
+        return [int(m.group(1)) for m in (re.search(r"gemm_stream_kernelILi\d.*?Stream(?:Params|Plain)ELi(\d)E", n) for n in rt.names()) if m]
 
     for out, width, bits, K, T, want in ((256, 256, 8, 2, 33, 2), (256, 4096, 8, 2, 16, 1), (256, 320, 4, 2, 33, 1), (256, 320, 2, 4, 33, 1),
-                                         (16384, 4096, 8, 4, 16, 2), (16368, 4096, 8, 4, 16, 1), (16384, 3840, 8, 4, 16, 1),     # 1024 bins, 64 steps
+                                         (16384, 512, 8, 4, 16, 2), (16368, 512, 8, 4, 16, 1),                                   # 1024 bins
+                                         (2048, 4352, 8, 4, 1, 2), (2032, 4352, 8, 4, 1, 1), (2048, 4096, 8, 4, 1, 1),           # quantized by the launch: 128 bins, 68 steps
+                                         (20496, 256, 8, 4, 1, 2), (20480, 256, 8, 4, 1, 1),                                     # ... 1281 bins
                                          (12288, 8192, 8, 4, 16, 2), (12272, 8192, 8, 4, 16, 1), (12288, 7936, 8, 4, 16, 1)):    # 768 bins, 128 steps
         e = rt.expand(out, width, bits, K, 1.0, 16)
         rt.names()
