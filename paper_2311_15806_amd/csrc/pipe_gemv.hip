@@ -775,15 +775,15 @@ inline uint64_t two_words(int lo, uint32_t hi) { return (uint64_t)(uint32_t)lo |
 // one, calls of 1700 layers:
 //   17 to 128 tokens -1 to -12 % in the mean of every class of bins, token blocks and steps of k (320 x 16384, K = 2, 107 tokens 30.6 -> 25.9 us, 8192 x 8192, K = 4, 111
 //   122.7 -> 113.9; at worst 11008 x 4096, K = 2, 32 24.8 -> 26.8);
-//   up to 16 tokens, where all codes come from HBM, from 1024 bins on -3 to -8 % (28672 x 3584, K = 3, 2 tokens 53.9 -> 49.6), from 768 on walks of 16 tiles a wave
-//   -6 % (28672 x 8192, K = 3, 5 129 -> 123); fewer -2 to +3 %, single layers +10 % (28672 x 4096, K = 2, 16 45.1 -> 49.6);
+//   up to 16 tokens, where all codes come from HBM, from 1024 bins on -3 to -8 % (28672 x 3584, K = 3, 2 tokens 53.9 -> 49.6), from 512 on walks of 16 tiles a wave
+//   -3 to -9 % (16384 x 8192, K = 3, 2 83.7 -> 75.7); fewer -2 to +3 %, single layers +10 % (28672 x 4096, K = 2, 16 45.1 -> 49.6);
 //   one token that the launch quantizes itself, from 128 bins on walks of more than 8 tiles 0 to -16 % (28672 x 8192, K = 2 100 -> 84; 4096 x 8192 17.3 -> 15.4), above
 //   1280 bins -1 to -11 %; 20480 x 4096, K = 2 +13 %, shorter walks -9 to +9 %.
 // With an input for each member +6 to +16 % (chains of 1536 to 3072, 65 to 128 tokens: more registers, one workgroup less a compute unit); at 4 bits -4 to +3 %, at 2
 // bits 0 to +5 % on walks of more than a tile a wave.
 inline bool two_tiles(const StreamParams& p, bool fused) {
   if (fused) return p.n_bins > 1280 || (p.n_bins >= 128 && p.nks > 64);
-  return p.n_tb > 1 || p.n_bins >= 1024 || (p.nks >= 128 && p.n_bins >= 768);
+  return p.n_tb > 1 || p.n_bins >= 1024 || (p.nks >= 128 && p.n_bins >= 512);
 }
 
 template <int BITS, int NW>

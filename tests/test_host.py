@@ -426,7 +426,7 @@ def streamed_8_bit_walks_ask_for_two_tiles(rt):
                                          (16384, 512, 8, 4, 16, 2), (16368, 512, 8, 4, 16, 1),                                   # 1024 bins
                                          (2048, 4352, 8, 4, 1, 2), (2032, 4352, 8, 4, 1, 1), (2048, 4096, 8, 4, 1, 1),           # quantized by the launch: 128 bins, 68 steps
                                          (20496, 256, 8, 4, 1, 2), (20480, 256, 8, 4, 1, 1),                                     # ... 1281 bins
-                                         (12288, 8192, 8, 4, 16, 2), (12272, 8192, 8, 4, 16, 1), (12288, 7936, 8, 4, 16, 1)):    # 768 bins, 128 steps
+                                         (8192, 8192, 8, 4, 16, 2), (8176, 8192, 8, 4, 16, 1), (8192, 7936, 8, 4, 16, 1)):       # 512 bins, 128 steps
         e = rt.expand(out, width, bits, K, 1.0, 16)
         rt.names()
         assert _linear(rt, e, T) == 0
