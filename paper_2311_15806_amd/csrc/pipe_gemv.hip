@@ -514,7 +514,8 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
 
 // Bins of CAP = 4 * NCH items (expansions with 5 to 16 orders).  The workgroup streams the bin in
 // chunks of R = 4 items exactly as above (waves split k, one tile per item in flight; with two, and every wave raising the maxima itself, seven layers of 2048
-// ternary with two members of 4 orders took 138 us at 40 tokens instead of 92.7, 94.6 at 16 instead of 81.8), reduces
+// ternary with two members of 4 orders took 138 us at 40 tokens instead of 92.7, 94.6 at 16 instead of 81.8; at 8 bits two, 400 calls of 5 to 12 orders -5 % in the mean:
+// 1024 x 11008, K = 5, 69 tokens 37.3 us with one and 28.5 with two, 512 x 8192, 123 26.6 and 22.7, 4 layers of 3072, two members of 6, 49 167 and 178), reduces
 // each chunk's per-wave tiles into isum and runs one epilogue over all items: per output row
 // block and member the items are summed in ascending order k, the same fp32 order as everywhere.
 // XM = 1: all items read one activation tensor; XM = 4: one stream per item of the chunk (its
@@ -523,6 +524,7 @@ template <int BITS, int NW, int XM, int NCH>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const StreamParams p) {
   static_assert(XM == 1 || XM == R, "one stream, or one per item of a chunk");
   constexpr int CAP = R * NCH;
+  constexpr int D = BITS == 8 ? 2 : 1;   // tiles that a wave asks for together
   constexpr int OFF = BITS == 8 ? 0 : (BITS == 4 ? 8 : 1);
   constexpr int KSUP = 512 / BITS;
   constexpr int STEPS = KSUP / 64;
@@ -589,15 +591,19 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
       const uint8_t* wb[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) wb[r] = p.codes + (pos0 + r) * (size_t)n_tiles * 1024;
-      uint4 w0[R], x0[NX];
+      uint4 w[D][R], x[D][NX];
       auto load_w = [&](int tl, uint4 (&w)[R]) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < R; ++r) w[r] = reinterpret_cast<const uint4*>(wb[r] + (size_t)tl * 1024)[lane];
       };
 #pragma unroll
-      for (int r = 0; r < R; ++r) { w0[r] = make_uint4(0, 0, 0, 0); }
+      for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int r = 0; r < R; ++r) w[d][r] = make_uint4(0, 0, 0, 0);
       int tl = tile_lo + wk;
-      if (tl < tile_hi) load_w(tl, w0);
+#pragma unroll
+      for (int d = 0; d < D; ++d)
+        if (tl + d * wpc < tile_hi) load_w(tl + d * wpc, w[d]);
       const int n_items = word(0);
       const uint8_t* xb[XM];
 #pragma unroll
@@ -614,8 +620,12 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
           for (int j = 0; j < STEPS; ++j) x[s * STEPS + j] = reinterpret_cast<const uint4*>(xb[s] + (size_t)(tl * STEPS + j) * 1024)[lane];
       };
 #pragma unroll
-      for (int j = 0; j < NX; ++j) { x0[j] = make_uint4(0, 0, 0, 0); }
-      if (tl < tile_hi) load_x(tl, x0);
+      for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int j = 0; j < NX; ++j) x[d][j] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int d = 0; d < D; ++d)
+        if (tl + d * wpc < tile_hi) load_x(tl + d * wpc, x[d]);
       auto mul_tile = [&](uint4 (&w)[R], uint4 (&x)[NX]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < STEPS; ++j) {
@@ -629,11 +639,22 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_multi_kernel(const Str
           }
         }
       };
-      if (tl < tile_hi) mul_tile(w0, x0);
-      for (tl += wpc; tl < tile_hi; tl += wpc) {   // one tile in flight, as above
-        load_w(tl, w0);
-        load_x(tl, x0);
-        mul_tile(w0, x0);
+      if constexpr (D == 1) {
+        if (tl < tile_hi) mul_tile(w[0], x[0]);
+        for (tl += wpc; tl < tile_hi; tl += wpc) {
+          load_w(tl, w[0]);
+          load_x(tl, x[0]);
+          mul_tile(w[0], x[0]);
+        }
+      } else {
+        for (; tl < tile_hi; tl += 2 * wpc) {
+          mul_tile(w[0], x[0]);
+          if (tl + 2 * wpc < tile_hi) { load_w(tl + 2 * wpc, w[0]); load_x(tl + 2 * wpc, x[0]); }
+          if (tl + wpc < tile_hi) {
+            mul_tile(w[D - 1], x[D - 1]);
+            if (tl + 3 * wpc < tile_hi) { load_w(tl + 3 * wpc, w[D - 1]); load_x(tl + 3 * wpc, x[D - 1]); }
+          }
+        }
       }
     }
 #pragma unroll

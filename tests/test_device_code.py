@@ -99,3 +99,7 @@ def test_streaming_kernel_asks_for_two_tiles_at_8_bits(kernels):
         assert sum(ins.startswith("buffer_load_dwordx4") for ins in code) == 2 * 2 * 5, name
         first = next(i for i, ins in enumerate(code) if ins.startswith("v_mfma"))
         assert any("vmcnt(0)" in ins for ins in code[first - 4:first]), name
+    wide = {name: code for name, code in kernels.items() if re.search(r"gemm_stream_multi_kernelILi8ELi8ELi1E", name)}
+    assert len(wide) == 3
+    for name, code in wide.items():
+        assert sum(ins.startswith("global_load_dwordx4") for ins in code) >= 2 * 2 * 5, name

@@ -410,7 +410,7 @@ def test_batches_of_17_to_128_tokens_by_either_kernel(pipe, kind, T):
 
 @pytest.mark.parametrize("T,n_in,out,K", [(17, 60, 48, 2), (33, 700, 336, 3), (128, 768, 1008, 4), (20, 1100, 64, 1), (64, 1536, 320, 2), (97, 1540, 176, 4),
                                           (40, 2300, 96, 3), (100, 11008, 64, 2), (16, 520, 16384, 4), (7, 8192, 12288, 4), (1, 8192, 2048, 4), (1, 4100, 2064, 4),
-                                          (1, 252, 20512, 4), (1, 5000, 2064, 4)])
+                                          (1, 252, 20512, 4), (1, 5000, 2064, 4), (100, 2300, 96, 6), (3, 5000, 160, 12), (17, 60, 48, 16)])
 def test_streamed_8_bit_walks_by_two_tiles(pipe, T, n_in, out, K):
     """8-bit layers whose waves walk no tile, one, an odd or an even number of them, by two at a time: outputs and accumulators bit for bit those of
     the tiled kernels, accumulators the whole numbers of the codes."""
