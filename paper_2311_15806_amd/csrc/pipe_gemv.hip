@@ -202,7 +202,7 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
   // call 24.2 us / 27.1 / 29.8 / 30.3; 4 bit, one token 12.2 / 14.2; six ternary layers of 2048, two members, 50 tokens 77.8 / 89.6).  At 8 bits two that are
   // asked for and waited for together can be faster, see two_tiles.
   // All loads go through buffer resources that end with this workgroup's share of the k tiles: an item that the bin does not have, a tile beyond
-  // the share and a token beyond the batch read as zero without any access, so no load is behind a branch and every wait is an exact count.
+  // the share and a token beyond the batch read as zero without any access, so that with one tile at a time no load is behind a branch and every wait is an exact count.
   const int tile_lo = ksplit > 1 ? (int)__umulhi(n_tiles * ksp, a_magic) : 0;
   const int tile_hi = ksplit > 1 ? (int)__umulhi(n_tiles * (ksp + 1), a_magic) : n_tiles;
   // quantizing workgroups request their input before the codes: it is what they wait for first (results return in order)
@@ -378,7 +378,8 @@ __global__ __launch_bounds__(NW * 64, (XM * (BITS == 2 ? 4 : (BITS == 4 ? 2 : 1)
     }
   } else {
     // The branches make the wait at the loop's head one for both tiles, and their loads leave back to back.  Without branches and with exact waits, so that one
-    // tile is on its way while the other is multiplied, or with the loads of both mixed, 16384 x 4096, K = 4, 123 tokens took 137 to 140 us: as with one tile, 136; so 125.
+    // tile is on its way while the other is multiplied, or with the loads of both mixed, 16384 x 4096, K = 4, 123 tokens took 137 to 140 us,
+    // with one tile 136, in this form 125.
     if (QFUSE) { load_x(tl, x[0]); load_x(tl + NW, x[D - 1]); }
     for (; tl < tile_hi; tl += 2 * NW) {
       mul_tile(w[0], x[0]);
